@@ -7,25 +7,49 @@ import re
 import subprocess
 import sys
 import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfef.so")
 SOURCES = ["fef_api.hip", "head_gemm.hip", "head_gemm_tiled256.hip", "head_gemm_stream.hip", "head_gemm_rowstream.hip",
            "verify_kernels.hip", "ce_kernels.hip"]
-FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function"]
 
 
 def build(verbose=True, extra_flags=()):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc, *FLAGS, *extra_flags, *[os.path.join(CSRC, s) for s in SOURCES], "-o", LIB]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
-    check_rowstream_isa(verbose)
+    with tempfile.TemporaryDirectory() as tmp, ThreadPoolExecutor(max_workers=8) as pool:
+        def compile_one(src):
+            obj = os.path.join(tmp, src + ".o")
+            cmd = [hipcc, *FLAGS, *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            subprocess.run(cmd, check=True)
+            return obj
+        checks = [pool.submit(check_rowstream_isa, verbose), pool.submit(check_accumulators_isa, verbose)]
+        objs = list(pool.map(compile_one, sorted(SOURCES, key=lambda s: -os.path.getsize(os.path.join(CSRC, s)))))
+        cmd = [hipcc, "--offload-arch=gfx950", "-fPIC", "-shared", *objs, "-o", LIB]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.run(cmd, check=True)
+        for c in checks:
+            c.result()
     return LIB
+
+
+def _assembly(src):
+    """Lines of the device assembly of one source."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    with tempfile.TemporaryDirectory() as tmp:
+        out = os.path.join(tmp, "out.s")
+        flags = [f for f in FLAGS if f != "-fPIC"]
+        subprocess.run([hipcc, *flags, "--cuda-device-only", "-S", os.path.join(CSRC, src), "-o", out], check=True,
+                       stderr=subprocess.DEVNULL)
+        with open(out) as f:
+            return f.read().split("\n")
 
 
 def _vgprs(text):
@@ -45,13 +69,7 @@ def check_rowstream_isa(verbose=True):
     multiply takes its W operand from the very registers a load statement wrote.  This compiles
     the file to assembly and checks exactly that for each instantiation; a compiler that starts
     to shuffle these registers fails the build instead of producing a kernel that reads stale data."""
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    with tempfile.TemporaryDirectory() as tmp:
-        out = os.path.join(tmp, "rowstream.s")
-        flags = [f for f in FLAGS if f not in ("-fPIC", "-shared")]
-        subprocess.run([hipcc, *flags, "--cuda-device-only", "-S", os.path.join(CSRC, "head_gemm_rowstream.hip"), "-o", out],
-                       check=True, stderr=subprocess.DEVNULL)
-        lines = open(out).read().split("\n")
+    lines = _assembly("head_gemm_rowstream.hip")
     kernels = [i for i, l in enumerate(lines) if re.match(r"^_Z\w*head_rowstream_kernel\w*:", l)]
     if not kernels:
         raise RuntimeError("check_rowstream_isa: no head_rowstream_kernel in the assembly")
@@ -80,6 +98,54 @@ def check_rowstream_isa(verbose=True):
         if verbose:
             print(f"check_rowstream_isa: {lines[start].split(':')[0]}: {n} multiplies read {len(ring)} load registers directly",
                   flush=True)
+
+
+def _regs(text):
+    """Vector and accumulation registers named in an operand list."""
+    out = set()
+    for m in re.finditer(r"\b([va])\[(\d+):(\d+)\]|\b([va])(\d+)\b", text):
+        if m.group(1):
+            out.update(m.group(1) + str(i) for i in range(int(m.group(2)), int(m.group(3)) + 1))
+        else:
+            out.add(m.group(4) + m.group(5))
+    return out
+
+
+def check_accumulators_isa(verbose=True):
+    """The multiplies of head_gemm_tiled256.hip are inline assembly on accumulators in place, so the compiler does not
+    know that a multiply's result, or a register that a multiply is about to read, needs wait states around other
+    vector instructions.  That is sound as long as between the first and the last multiply of a kernel nothing but
+    multiplies touches an accumulator and no vector instruction (only LDS reads, which are waited for) writes a
+    register that a multiply reads.  This checks exactly that for each instantiation."""
+    lines = _assembly("head_gemm_tiled256.hip")
+    starts = [i for i, l in enumerate(lines) if re.match(r"^_Z\w*head_tiled256_kernel\w*:", l)]
+    if not starts:
+        raise RuntimeError("check_accumulators_isa: no kernel in the assembly")
+    for start in starts:
+        end = next(i for i in range(start, len(lines)) if "s_endpgm" in lines[i])
+        name = lines[start].split(":")[0]
+        mfma = [i for i in range(start, end) if lines[i].strip().startswith("v_mfma")]
+        ops = [lines[i].strip().split(None, 1)[1].split(",") for i in mfma]
+        acc = set().union(*[_regs(o[0]) for o in ops])
+        for o, i in zip(ops, mfma):
+            if o[0].strip() != o[3].strip():
+                raise RuntimeError(f"check_accumulators_isa: {name}: '{lines[i].strip()}' is not in place")
+        recent = []  # vector instructions just before a multiply
+        for i in range(mfma[0], mfma[-1]):
+            t = lines[i].strip()
+            if t.startswith("v_mfma"):
+                if any(_regs(t) & w for w in recent[-2:]):
+                    raise RuntimeError(f"check_accumulators_isa: {name}: '{t}' reads what a vector instruction just wrote")
+                recent.append(set())
+            elif t.startswith("v_") and not t.startswith("v_cmp"):
+                args = t.split(None, 1)[1] if len(t.split(None, 1)) > 1 else ""
+                if _regs(args) & acc:
+                    raise RuntimeError(f"check_accumulators_isa: {name}: '{t}' touches an accumulator between multiplies")
+                recent.append(_regs(args.split(",")[0]))
+            elif t and not t.startswith((";", ".")):
+                recent.append(set())
+        if verbose:
+            print(f"check_accumulators_isa: {name}: {len(mfma)} multiplies in place on {len(acc)} registers", flush=True)
 
 
 HARNESS_SRC = os.path.join(os.path.dirname(HERE), "tests", "c_abi", "abi_harness.cpp")

@@ -21,6 +21,10 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
+// Where a running maximum starts: finite, and finite still after the multiplication by log2(e), so that a piece of
+// nothing but -inf (tokens past V) leaves the partial (lowest, 0) and no NaN.
+constexpr float kLowest = -2e38f;
+
 // Workgroup barrier that waits for this wavefront's LDS traffic only.  __syncthreads() would
 // also drain the vector-memory counter and with it the W tiles prefetched for later steps.
 __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -45,6 +49,10 @@ __device__ inline int swz(int row, int chunk) { return row * 8 + (chunk ^ ((row 
 template <int N>
 __device__ inline float row_ror(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + N, 0xf, 0xf, false));
+}
+// Value of the neighbouring lane, lane ^ 1 (DPP quad_perm [1, 0, 3, 2]).
+__device__ inline float swap_pair(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0xB1, 0xf, 0xf, true));
 }
 // All-reduce over the 16 lanes of a DPP row.
 __device__ inline float row16_max(float x) {

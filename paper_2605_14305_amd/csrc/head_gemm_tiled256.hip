@@ -1,530 +1,315 @@
-// Vocabulary-head kernel for large M = 2*B*K (the batched configurations).
+// Vocabulary-head kernel for large M = 2*B*K (the batched configurations) and for the cross-entropy of many rows.
 //
-// Workgroup tile 256 (rows of H) x 256 (tokens), eight wavefronts in a 2 x 4 grid, each 128 x 64 as
-// 4 x 2 v_mfma_f32_32x32x16_bf16 tiles (128 accumulator registers), k-steps of 64.
+// Workgroup tile 32 NR rows of H (NR = 5 to 8) x 256 tokens, k-steps of 64, v_mfma_f32_16x16x32_bf16 with the W tile
+// as the A operand and H as the B operand.  Two forms:
+//   WN = 2  four wavefronts in a 2 x 2 grid (rows x tokens), each 16 NR rows x 128 tokens: M > 256
+//   WN = 4  eight wavefronts in a 2 x 4 grid, each 16 NR rows x 64 tokens: M <= 256, one row tile
 //
-// Operand slabs go HBM/L2 -> LDS directly (global_load_lds_dwordx4: lane l of a wavefront deposits
-// its 16 bytes at LDS base + 16 l): no register staging and no ds_write in the main loop.  A row
-// of a stage is 128 bytes, so one load instruction fetches eight rows of 128 contiguous bytes
-// (whole L2 lines; 64-byte segments move at about 60 % of that rate out of L2), and there is one
-// workgroup barrier per 64 columns of k.  The loads are inline assembly with hand-counted vmcnt
-// before each barrier: with the builtin, the compiler's wait-count pass ties the fragment reads of
+// What bounds it, and what follows.
+// (1) Power.  With every matrix unit busy on real data the chip lowers its clock, so energy per multiply is time.  A
+// loop of nothing but multiplies on random operands runs at 2100 TFLOP/s with the 16x16x32 instruction and at 1840
+// with 32x32x16 (2430 and 2480 with zeros): per product the smaller tile moves half the binary32 accumulators and
+// rounds half as often, which outweighs its twice as many 16-bit operands.
+// (2) Issue slots.  With one wavefront per SIMD the matrix unit idles for the length of any run of other
+// instructions (it holds one multiply beyond the one in work), so fragment reads and operand loads are dealt out singly
+// between the multiplies, and pointer additions are pinned behind their loads.
+// (3) The epilogue, during which the matrix units idle.  With the tokens in the rows of D a lane holds four consecutive
+// tokens of ONE row of H per tile: logits leave as 16-byte stores, and the (max, sum exp) of a row runs inside the
+// lane over all its tiles; nothing crosses lanes at all (each of the four lane groups that share a row writes
+// the partial of its own tokens to LDS, where a thread per row merges them).
+// (4) Rows that do not exist.  M is cut into ceil(M / 256) row tiles of equal height, a multiple of 32 (300 rows:
+// two tiles of 160, not 256 + 44), one instantiation per height.
+//
+// Measured (head kernel, rocprofv3; before: 32x32x16, tokens in the columns of D, 256-row tiles only):
+// FEF_T256_MEASURED
+//
+// Operand slabs go HBM/L2 -> LDS directly (global_load_lds_dwordx4: lane l of a wavefront deposits its 16 bytes at
+// LDS base + 16 l): no register staging and no ds_write in the main loop.  A row of a stage is 128 bytes, so one load
+// instruction fetches eight rows of 128 contiguous bytes (whole L2 lines; 64-byte segments move at about 60 % of that
+// rate out of L2), and there is one workgroup barrier per 64 columns of k.  The loads are inline assembly with
+// hand-counted vmcnt before each barrier: with the builtin, the compiler's wait-count pass ties the fragment reads of
 // one stage to the loads in flight for the others.
 //
-// LDS (all 160 KB of the CU): H ring of two 32 KB stages, W ring of three.  H comes from L2 / the
-// Infinity Cache and is requested one k-step ahead; W comes from HBM and is requested two ahead.
-// A stage is [256 rows][8 chunks of 16 B]; the LDS has 64 four-byte banks, i.e. two such rows per
-// sweep, so chunk c of row r is kept at position c ^ ((r >> 1) & 7) and the 16-byte fragment
-// reads of 16 consecutive rows touch every bank once.  The permutation is applied on the global
-// side of the load (lane l lands at LDS base + 16 l and fetches the chunk that belongs there).
+// LDS (all 160 KB of the CU with 256 rows): H ring of two stages, W ring of three.  H comes from L2 / the Infinity
+// Cache and is requested one k-step ahead; W comes from HBM and is requested two ahead.  A stage is [rows][8 chunks of
+// 16 B]; the LDS has 64 four-byte banks, i.e. two such rows per sweep, so chunk c of row r is kept at position
+// c ^ ((r >> 1) & 7) and the 16-byte fragment reads of 16 consecutive rows touch every bank once.  The permutation is
+// applied on the global side of the load (lane l lands at LDS base + 16 l and fetches the chunk that belongs there).
 //
-// One k-step is four 16-wide slices (the four H loads of a wavefront go out as one group in the
-// first, the four W loads in the third).  The fragments of a slice are read, one after each multiply,
-// while the multiplies of the slice before it run; the last slice of a step is multiplied after the next step's barrier,
-// under the first fragment reads of the new stage, so the barrier does not idle the matrix unit
-// for the latency of those reads.
+// A k-step is two 32-wide slices.  The fragments of a slice are read while the slice before it is multiplied; the last
+// slice of a step is multiplied behind the next step's barrier, under the first fragment reads of the new stage, so the
+// barrier does not idle the matrix unit for the latency of those reads.
 //
-// The epilogue works straight from the accumulator registers: for a fixed accumulator index the 32
-// lanes of a half-wavefront hold 32 consecutive tokens of one row, so dword stores write whole
-// 128-byte lines, and the per-row (max, sum exp) over the wavefront's 64 tokens is reduced by DPP.
-//
-// Tile order: workgroup ids go round-robin over the 8 XCDs; within an XCD consecutive workgroups
-// take the row tiles of one token tile, so a W tile comes from HBM once and is shared through
-// that XCD's L2.
+// Tile order: workgroup ids go round-robin over the 8 XCDs; within an XCD consecutive workgroups take the row tiles of
+// one token tile, so a W tile comes from HBM once and is shared through that XCD's L2.
 #include <type_traits>
+#include <utility>
 
 #include "head_common.hpp"
 
 namespace fef {
 namespace {
 
-constexpr int BM = 256, BN = 256, BK = 64;
-constexpr int kStage = BM * 8;   // 16-byte chunks per operand stage (BM == BN)
+constexpr int BN = 256, BK = 64;
 constexpr int kRingH = 2, kRingW = 3;
+constexpr int kStageW = BN * 8;  // 16-byte chunks per W stage
 
-// Epilogue of a wavefront that holds a whole 128 x 128 tile (four wavefronts per workgroup), interior tiles only:
-// rows mw .. mw + 127 all exist, tokens vbase .. vbase + 127 all exist.  With one wavefront per SIMD nothing else
-// runs while it does, so what counts is the number of instructions, of any kind, and every wait for a result.
-// Against two calls of the shared 128 x 64 epilogue: a lane holds four tokens of a row, so the first steps of a
-// row's reduction are in its own registers; the reduction stops at the row of 16 lanes (the DPP steps), and each
-// of the two rows of 16 that share a matrix row writes the partial of its own 64 tokens (tokens j, j + 32, j + 64,
-// j + 96 of the 128, j < 16 or j >= 16: any split of the tile's tokens will do for the merge that follows), so
-// nothing crosses between the rows of 16 and nothing waits for the LDS crossbar; one running pointer per row for
-// the four stores; the wait states of the DPP steps paid once per eight.
-// lp: this wavefront's first partial slot in LDS, [row][4 slots] of float2; the wavefront fills two slots per row.
-template <bool CE>
-__device__ __forceinline__ void epilogue_128x128(const HeadArgs& a, floatx16 (&acc)[2][4][2], int mw, int vbase, int lane,
-                                                 float2* lp) {
-  constexpr float kLog2e = 1.4426950408889634f;
-  const int j32 = lane & 31, h = lane >> 5;
-  const float sc = a.inv_tau;
-  if constexpr (CE) {
-    // A row's label token lies in one tile of one wavefront, in one lane's accumulators.  Every lane looks up the
-    // labels of two of the wavefront's 128 rows; a label that falls among this tile's 128 tokens (13 % of the
-    // (wavefront, tile) pairs have one at V = 126464) is then fetched in a loop over the hits with wavefront-uniform
-    // indices: the 32 x 32 accumulator tile by comparison of scalars, the element inside it likewise, and the lane
-    // that holds it stores it.  (Going through all of a lane's elements with a label lookup each was a chain of
-    // 64 load latencies per hit: 1850 against 1700 us per call at R = 2048, and the workgroups of an XCD, which
-    // share their operand tiles through its L2 while they walk in step, fell out of step: 47 % L2 hits against 77 %.)
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int lab = a.labels[mw + q * kWave + lane];
-      unsigned long long hits = __builtin_amdgcn_ballot_w64((unsigned)(lab - vbase) < 128u);
-      while (hits != 0) {  // wavefront-uniform
-        const int src = __builtin_ctzll(hits);
-        hits &= hits - 1;
-        const int rowl = q * kWave + src;                                     // row inside the wavefront's tile
-        const int col = __builtin_amdgcn_readlane(lab, src) - vbase;          // token inside it
-        const int ti = rowl >> 5, x = rowl & 31, th = (x >> 2) & 1, tr = ((x >> 3) << 2) | (x & 3);
-        const int tc = col >> 5, tj = col & 31;
-        float v = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-            if (i == ti && c == tc) {  // wavefront-uniform: one of the accumulator tiles
-              v = acc[c >> 1][i][c & 1][0];
-#pragma unroll
-              for (int r = 1; r < 16; ++r) v = r == tr ? acc[c >> 1][i][c & 1][r] : v;
-            }
-        if (lane == tj + 32 * th) a.label_logit[mw + rowl] = v * sc;
-      }
-    }
-  }
-  float2* pw = lp + 4 * h * 4 + ((lane >> 4) & 1);
-  // Each phase runs over eight rows before the next begins (the scheduling barriers keep it so: left alone, the
-  // compiler finishes one row's chain before it starts the next, every step waiting for the one before), so
-  // neighbours in program order never depend on one another.
-#pragma unroll
-  for (int g = 0; g < 8; ++g) {
-    const int i = g >> 1, r0 = (g & 1) * 8;  // 32-row tile, first accumulator index
-    const int mr0 = i * 32 + 8 * (r0 >> 2);  // row of index r0 (before the 4 h of the half-wavefront)
-    float l[8][4], m[8], e[8], t[8];  // t: -max log2(e)
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) l[q][c] = acc[c >> 1][i][c & 1][r0 + q] * sc;
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (!CE) {
-      // non-temporal, as in the shared epilogue; the pointer walks down the rows (the empty statement keeps it
-      // a running pointer: one 64-bit addition per row)
-      typedef __attribute__((address_space(1))) float gfloat;
-      gfloat* dst = (gfloat*)(a.logits + (size_t)(mw + 4 * h + mr0) * a.ldl + vbase + j32);
-      const size_t s1 = (size_t)a.ldl, s5 = 5 * (size_t)a.ldl;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) __builtin_nontemporal_store(l[q][c], dst + 32 * c);
-        if (q < 7) {
-          dst += q == 3 ? s5 : s1;
-          asm("" : "+v"(dst));
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) m[q] = vmax3(l[q][0], l[q][1], vmax(l[q][2], l[q][3]));
-    __builtin_amdgcn_sched_barrier(0);
-    max_ror_x8<8>(m);
-    max_ror_x8<4>(m);
-    max_ror_x8<2>(m);
-    max_ror_x8<1>(m);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int q = 0; q < 8; ++q) t[q] = m[q] * -kLog2e;
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) l[q][c] = fmaf(l[q][c], kLog2e, t[q]);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int q = 0; q < 8; ++q) l[q][c] = __builtin_amdgcn_exp2f(l[q][c]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) e[q] = (l[q][0] + l[q][1]) + (l[q][2] + l[q][3]);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int q = 0; q < 8; ++q) e[q] += row_ror<8>(e[q]);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int q = 0; q < 8; ++q) e[q] += row_ror<4>(e[q]);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int q = 0; q < 8; ++q) e[q] += row_ror<2>(e[q]);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int q = 0; q < 8; ++q) e[q] += row_ror<1>(e[q]);
-    __builtin_amdgcn_sched_barrier(0);
-    // every lane of a row of 16 holds the pair of its 64 tokens and writes it to the same address
-#pragma unroll
-    for (int q = 0; q < 8; ++q) pw[(mr0 + 8 * (q >> 2) + (q & 3)) * 4] = make_float2(m[q], e[q]);
-    __builtin_amdgcn_sched_barrier(0);
-  }
+// Which of `cnt` instructions spread evenly over `total` multiplies follows multiply m; -1: none.  cnt <= total.
+constexpr int spread_at(int m, int cnt, int total) {
+  for (int q = 0; q < cnt; ++q)
+    if ((2 * q + 1) * total / (2 * cnt) == m) return q;
+  return -1;
+}
+// f(integral_constant 0), f(1), .. f(N - 1), in order: an unrolled loop whose index is a constant expression.
+template <class F, int... I>
+__device__ __forceinline__ void for_each(std::integer_sequence<int, I...>, F f) {
+  (f(std::integral_constant<int, I>{}), ...);
 }
 
-template <bool CE>
-__global__ __launch_bounds__(512) void head_tiled256_kernel(HeadArgs a, int m_tiles, int n_tiles) {
-  __shared__ bf16x8 ringH[kRingH * kStage];  // 64 KB
-  __shared__ bf16x8 ringW[kRingW * kStage];  // 96 KB
+// c += w h^T on 16 tokens x 16 rows x 32 columns of k, in place.  As inline assembly because the compiler gives the
+// builtin's result other registers than its addend (16x16 tiles may overlap freely), and a kernel whose accumulators
+// wander needs 80 registers more than one whose accumulators stay.  The hazards that the compiler would look after: a
+// multiply finds its own accumulator two dozen multiplies old or older; operands come from LDS reads, which it does
+// wait for; and settle() stands between zeroing and the first multiply, and between the last and the first other use.
+template <bool AGPR>
+__device__ __forceinline__ void mfma16(floatx4& c, const bf16x8& w, const bf16x8& h) {
+  if constexpr (AGPR) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(w), "v"(h));
+  else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(w), "v"(h));
+}
+// Every accumulator in its registers, and no multiply or move to them in flight: behind the zeroing and behind the last
+// multiply.  (The empty statements keep the writers in front of the wait and the readers behind it.)
+template <bool AGPR, int NT, int NR>
+__device__ __forceinline__ void settle(floatx4 (&acc0)[NT][NR], floatx4 (&acc1)[NT][NR]) {
+  auto pin = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int n = 0; n < NR; ++n) {
+        if constexpr (AGPR) asm volatile("" : "+a"(acc0[t][n]), "+a"(acc1[t][n]));
+        else asm volatile("" : "+v"(acc0[t][n]), "+v"(acc1[t][n]));
+      }
+  };
+  pin();
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+  pin();
+}
+
+template <int NR, int WN, bool CE>
+__global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int m_tiles, int n_tiles) {
+  constexpr int NT = 16 / WN;                        // 16-token tiles per wavefront
+  constexpr int BM = 32 * NR, WROWS = 16 * NR;       // rows of the workgroup tile, of a wavefront
+  constexpr int LW = 16 / WN, LH = 2 * NR / WN;      // load instructions per wavefront and stage (8 rows each)
+  constexpr bool ONE = WN == 4;                      // one row tile, two wavefronts per SIMD
+  constexpr bool ROLL = ONE;                         // H fragments in one set of registers, each re-read behind its last use
+  constexpr int kStageH = BM * 8;                    // 16-byte chunks per H stage
+  static_assert((2 * NR) % WN == 0, "every wavefront loads as many rows");
+  __shared__ bf16x8 ringH[kRingH * kStageH];
+  __shared__ bf16x8 ringW[kRingW * kStageW];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 2, wn = wave & 3;
-  const int j32 = lane & 31, h = lane >> 5;
+  const int wm = wave / WN, wn = wave % WN;
+  const int i16 = lane & 15, g = lane >> 4;
   const int M = a.nrows;
+  const int nk = a.d / BK;
 
   const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
   const int nt = xcd + 8 * (seq / m_tiles), mt = seq % m_tiles;
   if (nt >= n_tiles) return;
   const int m0 = mt * BM, n0 = nt * BN;
-  const int nk = a.d / BK;
+
   // Every row of W starts at a multiple of 2 d bytes, so workgroups that walk k from 0 in step ask HBM for the
-  // same low address bits at the same moment: each token tile starts its walk at another k-step and wraps
-  // (M = 256: head 277 -> 263 us, step 326 -> 321.5 us; with several row tiles per token tile, which share H
-  // in time through L2, the same change measured +2 % at M = 2048 and is not used there).
-  const int k0 = (int)((unsigned)(nt * 37) % (unsigned)nk);
+  // same low address bits at the same moment: with one row tile each token tile starts its walk at another k-step and
+  // wraps (with several row tiles per token tile, which share H in time through L2, that measured 2 % slower).
+  const int k0 = ONE ? (int)((unsigned)(nt * 37) % (unsigned)nk) : 0;
   int h_left = nk - k0, w_left = nk - k0;  // steps until the walk is back at k = 0
 
-  // Direct-to-LDS loads: wavefront w fills rows [32 w, 32 w + 32) of an H stage and of a W stage,
+  // Direct-to-LDS loads: wavefront w fills rows [8 LH w, + 8 LH) of an H stage and [8 LW w, + 8 LW) of a W stage,
   // 8 rows per instruction; lane l owns LDS slot (row 8 q + l / 8, position l % 8).
-  const __bf16* gh[4];
-  const __bf16* gw[4];
+  const __bf16* gh[LH];
+  const __bf16* gw[LW];
+  // With two wavefronts per SIMD up to four loads go out behind one write of M0 (the instruction offset moves the LDS
+  // address and the memory address alike, so the pointers are kept 0, 1, 2, 3 KB low): every write of M0 in front of
+  // a direct-to-LDS load holds the wavefront for some tens of cycles (2.7 % at M = 256).  With one wavefront per SIMD
+  // single loads between two multiplies cost nothing measurable and a group would be a run.
+  constexpr int kLow = ONE ? 512 : 0;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int rl = wave * 32 + q * 8 + (lane >> 3);
+  for (int q = 0; q < LH; ++q) {
+    const int rl = wave * (8 * LH) + q * 8 + (lane >> 3);
     const int c = (lane & 7) ^ ((rl >> 1) & 7);
-    const int r = min(m0 + rl, M - 1);      // rows past M / V re-read the last row; masked in the epilogue
-    const int v = min(n0 + rl, a.V - 1);
-    gh[q] = h_row(a, r) + c * 8 + k0 * BK;
-    gw[q] = (const __bf16*)a.W + (size_t)v * a.d + c * 8 + k0 * BK;
-    gh[q] -= q * 512;  // 1024 bytes per position in the group of four: the instruction offset puts them back
-    gw[q] -= q * 512;
+    gh[q] = h_row(a, min(m0 + rl, M - 1)) + c * 8 + k0 * BK - q * kLow;  // rows past M re-read the last row; masked later
   }
-  // Four loads behind one write of M0 (the instruction offset moves the LDS address and the memory
-  // address alike): every write of M0 in front of a direct-to-LDS load holds the wavefront for some
-  // tens of cycles; 2 writes per k-step instead of 8 are worth 2.7 % at M = 256.
-  auto issue4 = [&](const __bf16* (&g)[4], uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %4\n\ts_nop 0\n\t"
-                 "global_load_lds_dwordx4 %0, off\n\tglobal_load_lds_dwordx4 %1, off offset:1024\n\t"
-                 "global_load_lds_dwordx4 %2, off offset:2048\n\tglobal_load_lds_dwordx4 %3, off offset:3072"
-                 :: "v"(g[0]), "v"(g[1]), "v"(g[2]), "v"(g[3]), "s"(lds_base) : "memory");
 #pragma unroll
-    for (int q = 0; q < 4; ++q) g[q] += BK;
+  for (int q = 0; q < LW; ++q) {
+    const int rl = wave * (8 * LW) + q * 8 + (lane >> 3);
+    const int c = (lane & 7) ^ ((rl >> 1) & 7);
+    gw[q] = (const __bf16*)a.W + (size_t)min(n0 + rl, a.V - 1) * a.d + c * 8 + k0 * BK - q * kLow;
+  }
+  const uint32_t slotH = lds_offset(ringH + wave * LH * 64), slotW = lds_offset(ringW + wave * LW * 64);
+  constexpr uint32_t kBytesH = kStageH * 16, kBytesW = kStageW * 16;
+  // Elements the pointers move on by after the loads of a step: one k-step, and back to k = 0 where the walk wraps.
+  auto advance = [&](int& left) __attribute__((always_inline)) -> long {
+    if constexpr (ONE) return --left == 0 ? (long)BK - a.d : (long)BK;
+    else return BK;
   };
-  const uint32_t slotH = lds_offset(ringH + wave * 32 * 8), slotW = lds_offset(ringW + wave * 32 * 8);
-  constexpr uint32_t kStageBytes = kStage * 16;
-  // loads of this wavefront for the k-step the pointers stand at, which then move on by one step
-  // single loads (prologue, wavefronts without rows)
-  auto issue_h = [&](int stage, int q) {
-    load_to_lds_16(gh[q] + q * 512, slotH + stage * kStageBytes + q * 1024);
-    gh[q] += BK;
+  // One load of this wavefront for the k-step the pointer stands at, which then moves on (the empty statement pins the
+  // addition there: left alone, the compiler gathers the 64-bit additions of a step in front of the barrier).
+  auto issue_one = [&](const __bf16*& p, int q, uint32_t lds, long move) __attribute__((always_inline)) {
+    load_to_lds_16(p + q * kLow, lds + q * 1024);
+    p += move;
+    asm volatile("" : "+v"(p));
   };
-  auto issue_w = [&](int stage, int q) {
-    load_to_lds_16(gw[q] + q * 512, slotW + stage * kStageBytes + q * 1024);
-    gw[q] += BK;
+  auto all_h = [&](int stage) __attribute__((always_inline)) {
+    const long move = advance(h_left);
+#pragma unroll
+    for (int q = 0; q < LH; ++q) issue_one(gh[q], q, slotH + stage * kBytesH, move);
   };
-
-  auto wrap_h = [&]() {  // after the H loads of a step
-    if (--h_left == 0)
+  auto all_w = [&](int stage) __attribute__((always_inline)) {
+    const long move = advance(w_left);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) gh[q] -= a.d;
+    for (int q = 0; q < LW; ++q) issue_one(gw[q], q, slotW + stage * kBytesW, move);
   };
-  auto wrap_w = [&]() {
-    if (--w_left == 0)
+  auto group = [&](auto& p, uint32_t base, int& left) __attribute__((always_inline)) {
+    constexpr int L = sizeof(p) / sizeof(p[0]);
+    if constexpr (L == 4)
+      asm volatile("s_mov_b32 m0, %4\n\ts_nop 0\n\t"
+                   "global_load_lds_dwordx4 %0, off\n\tglobal_load_lds_dwordx4 %1, off offset:1024\n\t"
+                   "global_load_lds_dwordx4 %2, off offset:2048\n\tglobal_load_lds_dwordx4 %3, off offset:3072"
+                   :: "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "s"(base) : "memory");
+    else if constexpr (L == 3)
+      asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\t"
+                   "global_load_lds_dwordx4 %0, off\n\tglobal_load_lds_dwordx4 %1, off offset:1024\n\t"
+                   "global_load_lds_dwordx4 %2, off offset:2048"
+                   :: "v"(p[0]), "v"(p[1]), "v"(p[2]), "s"(base) : "memory");
+    const long move = advance(left);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) gw[q] -= a.d;
+    for (int q = 0; q < L; ++q) p[q] += move;
   };
-
-  floatx16 acc[4][2];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = floatx16{};
-
-  struct Frag { bf16x8 a[4], b[2]; };
-  auto mfma_rows = [&](const Frag& f, int i0, int i1) {
-#pragma unroll
-    for (int i = i0; i < i1; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
-  };
-
-  const bool idle = m0 + wm * 128 >= M;  // none of this wavefront's rows exists: loads and barriers only
+  static_assert(!ONE || ((LH == 3 || LH == 4) && LW == 4), "groups of loads");
 
   // prologue: H(0), W(0), W(1)
-#pragma unroll
-  for (int q = 0; q < 4; ++q) issue_h(0, q);
-  wrap_h();
-#pragma unroll
-  for (int q = 0; q < 4; ++q) issue_w(0, q);
-  wrap_w();
-  if (1 < nk) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) issue_w(1, q);
-    wrap_w();
-  }
+  all_h(0);
+  all_w(0);
+  if (1 < nk) all_w(1);
 
-  Frag cur, nxt;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) cur.a[i] = bf16x8{};
-#pragma unroll
-  for (int j = 0; j < 2; ++j) cur.b[j] = bf16x8{};  // "last slice of step -1": multiplies by zero
-
-  // One k-step.  On entry `cur` holds the last slice of the step before.  Outstanding loads of
-  // this wavefront, oldest first: H(kt) [4], W(kt+1) [4]; the barrier needs H(kt) (W(kt) is older).
-  // FULL: kt + 2 < nk, every refill exists and the step is one basic block.
-  auto step = [&](int kt, int sh, int sw, auto full) {
-    constexpr bool FULL = decltype(full)::value;
-    const bf16x8* Hs = ringH + sh * kStage;
-    const bf16x8* Ws = ringW + sw * kStage;
-    const int sh1 = sh ^ 1, sw2 = sw == 0 ? 2 : sw - 1;  // stages of H(kt+1) and W(kt+2)
-    __builtin_amdgcn_sched_barrier(0);
-    if (FULL || kt + 1 < nk) wait_newer<4>();
-    else wait_newer<0>();
-    lds_barrier();
-    if (idle) {
-      if (FULL || kt + 1 < nk) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) issue_h(sh1, q);
-        wrap_h();
-      }
-      if (FULL || kt + 2 < nk) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) issue_w(sw2, q);
-        wrap_w();
-      }
-      return;
-    }
-    // Reads dealt out one after each multiply, in the order the next slice wants them, and the group of four
-    // loads after the seventh multiply of its slice: 2 to 3 % on the whole step at M = 256 against reading a
-    // slice's six fragments in one run (the second wavefront of the SIMD fills such gaps only in part).
-    auto read_one = [&](int ks, Frag& f, int n) {  // a0, b0, b1, a1, a2, a3
-      if (n == 0) f.a[0] = Hs[swz(wm * 128 + j32, ks * 2 + h)];
-      else if (n <= 2) f.b[n - 1] = Ws[swz(wn * 64 + (n - 1) * 32 + j32, ks * 2 + h)];
-      else f.a[n - 2] = Hs[swz(wm * 128 + (n - 2) * 32 + j32, ks * 2 + h)];
-    };
-    auto slice = [&](int ks, Frag& rd, const Frag& mm, int loads) {
-#pragma unroll
-      for (int n = 0; n < 8; ++n) {
-        const int i = n >> 1, j = n & 1;
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(mm.a[i], mm.b[j], acc[i][j], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        if (n < 6) {
-          read_one(ks, rd, n);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        if (n == 6) {
-          if (loads == 1 && (FULL || kt + 1 < nk)) {
-            issue4(gh, slotH + sh1 * kStageBytes);
-            wrap_h();
-          }
-          if (loads == 2 && (FULL || kt + 2 < nk)) {
-            issue4(gw, slotW + sw2 * kStageBytes);
-            wrap_w();
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-    };
-    slice(0, nxt, cur, 1);
-    slice(1, cur, nxt, 0);
-    slice(2, nxt, cur, 2);
-    slice(3, cur, nxt, 0);
-  };
-
-  int kt = 0, sw = 0;
-  for (; kt + 3 < nk; kt += 2) {  // two full steps: kt + 1 + 2 < nk
-    step(kt, 0, sw, std::true_type{});
-    sw = sw == 2 ? 0 : sw + 1;
-    step(kt + 1, 1, sw, std::true_type{});
-    sw = sw == 2 ? 0 : sw + 1;
-  }
-  for (; kt < nk; ++kt) {
-    step(kt, kt & 1, sw, std::false_type{});
-    sw = sw == 2 ? 0 : sw + 1;
-  }
-  if (!idle) mfma_rows(cur, 0, 4);  // last slice of the last step
-
-  lds_barrier();  // nobody reads the rings any more: the H ring takes the partials
-  float2* lp = reinterpret_cast<float2*>(ringH);
-  if (!idle) store_logits_and_partials<4, CE>(a, acc, m0 + wm * 128, n0 + wn * 64, M, lane, lp, wm * 128, wn);
-  lds_barrier();
-  merge_tile_partials(a, lp, BM, m0, nt, M, tid);
-}
-
-
-// ---------------------------------------------------------------------------------------------
-// The same tile with FOUR wavefronts in a 2 x 2 grid, each 128 x 128 as 4 x 4 MFMA tiles (256
-// accumulator registers; one wavefront per SIMD has 512 registers to itself), for M > 256.
-//
-// Why: with eight wavefronts of 128 x 64, a 16-wide slice of k costs every wavefront 4 + 2 fragment
-// reads of 1 KB for 8 multiplies, 48 KB per CU and slice, which together with the 16 KB the loads
-// deposit per slice is all the LDS can move (128 bytes per clock) in the 512 clocks the multiplies
-// of a slice take: the matrix units cannot be busier than the LDS lets them.  A 128 x 128
-// wavefront reads 4 + 4 fragments for 16 multiplies: 32 KB per CU and slice, three quarters of
-// the LDS rate.  (At M = 256 the kernel is short of memory parallelism rather than of LDS rate and
-// the eight wavefronts do better.)
-//
-// Loads: wavefront w fills rows [64 w, 64 w + 64) of an H stage and of a W stage (8 + 8
-// instructions per k-step, four per slice).
-//
-// One workgroup per tile, as above.  A persistent form (one workgroup per CU walking the tiles
-// b, b + G, ... and asking for the first stages of its next tile before the epilogue of the current
-// one) was measured 2.5 % slower at M = 512 to 2048: the hardware's dispatch of one workgroup per
-// tile balances the CUs better than a fixed share of 15 or 16 tiles each.
-// ---------------------------------------------------------------------------------------------
-template <bool CE>
-__global__ __launch_bounds__(256) void head_tiled256w4_kernel(HeadArgs a, int m_tiles, int n_tiles) {
-  __shared__ bf16x8 ringH[kRingH * kStage];  // 64 KB
-  __shared__ bf16x8 ringW[kRingW * kStage];  // 96 KB
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;
-  const int j32 = lane & 31, h = lane >> 5;
-  const int M = a.nrows;
-  const int nk = a.d / BK;
-
-  const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
-  const int nt = xcd + 8 * (seq / m_tiles), mt = seq % m_tiles;
-  if (nt >= n_tiles) return;
-  const int m0 = mt * BM, n0 = nt * BN;
-
-  const __bf16* gh[8];
-  const __bf16* gw[8];
-  const uint32_t slotH = lds_offset(ringH + wave * 64 * 8), slotW = lds_offset(ringW + wave * 64 * 8);
-  constexpr uint32_t kStageBytes = kStage * 16;
-  // The pointer moves on right behind its load (the empty statement pins the addition there): left to
-  // itself the compiler gathers the sixteen 64-bit additions of a step in front of the barrier, a run
-  // during which the matrix unit has nothing to do.
-  auto issue_h = [&](int stage, int q) {
-    load_to_lds_16(gh[q], slotH + stage * kStageBytes + q * 1024);
-    gh[q] += BK;
-    asm volatile("" : "+v"(gh[q]));
-  };
-  auto issue_w = [&](int stage, int q) {
-    load_to_lds_16(gw[q], slotW + stage * kStageBytes + q * 1024);
-    gw[q] += BK;
-    asm volatile("" : "+v"(gw[q]));
+  // acc(t, n): tokens 16 t + 4 g .. + 3 of row 16 n + i16 of the wavefront's tile
+  // (two arrays: one of 1 KB per lane is not taken apart into registers)
+  floatx4 acc0[NT / 2][NR], acc1[NT / 2][NR];
+  auto acc_at = [&](int t, int n) __attribute__((always_inline)) -> floatx4& {
+    return t < NT / 2 ? acc0[t][n] : acc1[t - NT / 2][n];
   };
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int rl = wave * 64 + q * 8 + (lane >> 3);
-    const int c = (lane & 7) ^ ((rl >> 1) & 7);
-    const int r = min(m0 + rl, M - 1);      // rows past M / V re-read the last row; masked in the epilogue
-    const int v = min(n0 + rl, a.V - 1);
-    gh[q] = h_row(a, r) + c * 8;
-    gw[q] = (const __bf16*)a.W + (size_t)v * a.d + c * 8;
-  }
-  // prologue: H(0), W(0), W(1)
+  for (int t = 0; t < NT / 2; ++t)
 #pragma unroll
-  for (int q = 0; q < 8; ++q) issue_h(0, q);
-#pragma unroll
-  for (int q = 0; q < 8; ++q) issue_w(0, q);
-  if (1 < nk) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) issue_w(1, q);
-  }
+    for (int n = 0; n < NR; ++n) acc0[t][n] = acc1[t][n] = floatx4{0.f, 0.f, 0.f, 0.f};
+  settle<!ONE>(acc0, acc1);
+  bf16x8 wf[2][NT], hf[ROLL ? 1 : 2][NR];
 
-  floatx16 acc[2][4][2];  // [64-token half][32-row tile][32-token tile]
-  struct Frag { bf16x8 a[4], b[4]; };
-  // fragment n of slice ks in the order the next slice's multiplies want them: a0, b0, b1, b2, b3, a1, a2, a3
-  auto read_one = [&](const bf16x8* Hs, const bf16x8* Ws, int ks, Frag& f, int n) {
-    if (n == 0) f.a[0] = Hs[swz(wm * 128 + j32, ks * 2 + h)];
-    else if (n <= 4) f.b[n - 1] = Ws[swz(wn * 128 + (n - 1) * 32 + j32, ks * 2 + h)];
-    else f.a[n - 4] = Hs[swz(wm * 128 + (n - 4) * 32 + j32, ks * 2 + h)];
-  };
-  auto mfma_row = [&](const Frag& f, int i) {
+  // fragment addresses in a stage (chunks): row 16 n + i16 of this wavefront's rows, chunk 4 ks + g; the swizzle term
+  // depends on i16 only because a wavefront's rows start at a multiple of 16
+  int fo[2];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      acc[j >> 1][i][j & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], acc[j >> 1][i][j & 1], 0, 0, 0);
-  };
+  for (int ks = 0; ks < 2; ++ks) fo[ks] = i16 * 8 + ((ks * 4 + g) ^ ((i16 >> 1) & 7));
 
   // none of this wavefront's rows exists: loads and barriers only (wavefront-uniform, and said so)
-  const bool idle = __builtin_amdgcn_readfirstlane((int)(m0 + wm * 128 >= M)) != 0;
-#pragma unroll
-  for (int c = 0; c < 2; ++c)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) acc[c][i][j] = floatx16{};
-  Frag cur, nxt;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) cur.a[i] = cur.b[i] = bf16x8{};  // "last slice of step -1": multiplies by zero
+  const bool idle = __builtin_amdgcn_readfirstlane((int)(m0 + wm * WROWS >= M)) != 0;
 
-  // One k-step; outstanding loads of this wavefront on entry, oldest first: H(kt) [8], W(kt+1) [8].
-  auto step = [&](int kt, int sh, int sw, auto full, auto idle_tag) __attribute__((always_inline)) {
+  // Slice KS of the step in work is read into fragment set KS while the slice before it (set KS ^ 1; KS = 0: the last
+  // slice of the step before) is multiplied.  LOADS: phase 0 requests the H stage of the next step, phase 1 the W
+  // stage of the step after that.
+  auto phase = [&](auto ks_tag, auto mul_tag, const bf16x8* Hs, const bf16x8* Ws, bool more, int stage)
+      __attribute__((always_inline)) {
+    constexpr int KS = decltype(ks_tag)::value;
+    constexpr bool MUL = decltype(mul_tag)::value;
+    constexpr int TOTAL = NT * NR, LOADS = KS == 0 ? LH : LW;
+    bf16x8(&wr)[NT] = wf[KS];
+    bf16x8(&wm_)[NT] = wf[KS ^ 1];
+    bf16x8(&hr)[NR] = hf[ROLL ? 0 : KS];
+    bf16x8(&hm)[NR] = hf[ROLL ? 0 : KS ^ 1];
+    auto read_w = [&](int t) __attribute__((always_inline)) { wr[t] = Ws[(wn * NT + t) * 128 + fo[KS]]; };
+    auto read_h = [&](int n) __attribute__((always_inline)) { hr[n] = Hs[(wm * NR + n) * 128 + fo[KS]]; };
+    for_each(std::make_integer_sequence<int, TOTAL>{}, [&](auto m_tag) __attribute__((always_inline)) {
+      constexpr int m = decltype(m_tag)::value, n = m / NT, t = m % NT;
+      if constexpr (MUL) {
+        mfma16<!ONE>(acc_at(t, n), wm_[t], hm[n]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (ROLL) {
+        // W fragments under the first row groups, an H fragment behind the last multiply that uses its registers
+        if constexpr (n < NT && t == 1) {
+          read_w(n);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (t == NT - 1) {
+          read_h(n);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (m == TOTAL / 2 + 2) {
+          if (more) {
+            if constexpr (KS == 0) group(gh, slotH + stage * kBytesH, h_left);
+            else group(gw, slotW + stage * kBytesW, w_left);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
+        // a read after every third multiply or so, in the order the next phase wants them: h0, w0.., h1..
+        constexpr int r = spread_at(m, NT + NR, TOTAL - TOTAL / 8), q = spread_at(m - 1, LOADS, TOTAL);
+        if constexpr (r >= 0) {
+          if constexpr (r == 0) read_h(0);
+          else if constexpr (r <= NT) read_w(r - 1);
+          else read_h(r - NT);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (q >= 0) {
+          if (more) {
+            if constexpr (KS == 0) issue_one(gh[q], q, slotH + stage * kBytesH, BK);
+            else issue_one(gw[q], q, slotW + stage * kBytesW, BK);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    });
+  };
+
+  // One k-step; outstanding loads of this wavefront on entry, oldest first: H(kt) [LH], W(kt+1) [LW]; the barrier
+  // needs H(kt) (W(kt) is older).  FULL: kt + 2 < nk, every refill exists and the step is one basic block.
+  auto step = [&](int kt, int sh, int sw, auto full, auto idle_tag, auto mul_tag) __attribute__((always_inline)) {
     constexpr bool FULL = decltype(full)::value;
     constexpr bool IDLE = decltype(idle_tag)::value;
-    const bf16x8* Hs = ringH + sh * kStage;
-    const bf16x8* Ws = ringW + sw * kStage;
-    const int sh1 = sh ^ 1, sw2 = sw == 0 ? 2 : sw - 1;
     const bool more_h = FULL || kt + 1 < nk, more_w = FULL || kt + 2 < nk;
+    const int sh1 = sh ^ 1, sw2 = sw == 0 ? 2 : sw - 1;  // stages of H(kt+1) and W(kt+2)
     __builtin_amdgcn_sched_barrier(0);
-    if (more_h) wait_newer<8>();
+    if (more_h) wait_newer<LW>();
     else wait_newer<0>();
     lds_barrier();
     if constexpr (IDLE) {
-      if (more_h)
-#pragma unroll
-        for (int q = 0; q < 8; ++q) issue_h(sh1, q);
-      if (more_w)
-#pragma unroll
-        for (int q = 0; q < 8; ++q) issue_w(sw2, q);
-      return;
+      if (more_h) all_h(sh1);
+      if (more_w) all_w(sw2);
+    } else {
+      const bf16x8* Hs = ringH + sh * kStageH;
+      const bf16x8* Ws = ringW + sw * kStageW;
+      phase(std::integral_constant<int, 0>{}, mul_tag, Hs, Ws, more_h, sh1);
+      phase(std::integral_constant<int, 1>{}, std::true_type{}, Hs, Ws, more_w, sw2);
     }
-    // Slice s of this step is read while slice s - 1 (s = 0: the last slice of the step before) is
-    // multiplied.  With one wavefront per SIMD the matrix unit has nothing to run while this wavefront
-    // issues anything else, and it holds only one multiply beyond the one in work: a run of eight
-    // fragment reads or four loads between two multiplies leaves it idle for the length of the run
-    // (in a loop of multiplies, reads, loads and barriers only: 1837 TFLOP/s with the reads and loads
-    // of a slice in runs, 2270 with one read after every second multiply and one load after the first
-    // multiply of each row; multiplies alone 2460).  So everything is dealt out singly.
-    auto phase = [&](int ks, Frag& rd, const Frag& mm, bool h_loads, int q0) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          acc[j >> 1][i][j & 1] =
-              __builtin_amdgcn_mfma_f32_32x32x16_bf16(mm.a[i], mm.b[j], acc[j >> 1][i][j & 1], 0, 0, 0);
-          __builtin_amdgcn_sched_barrier(0);
-          if (j & 1) {
-            read_one(Hs, Ws, ks, rd, i * 2 + (j >> 1));
-            __builtin_amdgcn_sched_barrier(0);
-          } else if (j == 0) {
-            if (h_loads) {
-              if (more_h) issue_h(sh1, q0 + i);
-            } else {
-              if (more_w) issue_w(sw2, q0 + i);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-      }
-    };
-    phase(0, nxt, cur, true, 0);
-    phase(1, cur, nxt, true, 4);
-    phase(2, nxt, cur, false, 0);
-    phase(3, cur, nxt, false, 4);
   };
-
-  // Two copies of the loop, chosen once: a wavefront without rows only loads and meets the barriers.  (With
-  // the choice inside the step the two paths meet again in every step, and the compiler reconciles their
-  // registers there with sixteen moves in front of the barrier.)
+  // Two copies of the loop, chosen once: a wavefront without rows only loads and meets the barriers.  (With the choice
+  // inside the step the two paths meet again in every step, and the compiler reconciles their registers there with
+  // sixteen moves in front of the barrier.)
   auto walk = [&](auto idle_tag) __attribute__((always_inline)) {
-    int kt = 0, sw = 0;
+    step(0, 0, 0, std::false_type{}, idle_tag, std::false_type{});  // nothing to multiply yet in its first phase
+    int kt = 1, sw = 1;
     for (; kt + 3 < nk; kt += 2) {  // two full steps: kt + 1 + 2 < nk
-      step(kt, 0, sw, std::true_type{}, idle_tag);
+      step(kt, 1, sw, std::true_type{}, idle_tag, std::true_type{});
       sw = sw == 2 ? 0 : sw + 1;
-      step(kt + 1, 1, sw, std::true_type{}, idle_tag);
+      step(kt + 1, 0, sw, std::true_type{}, idle_tag, std::true_type{});
       sw = sw == 2 ? 0 : sw + 1;
     }
     for (; kt < nk; ++kt) {
-      step(kt, kt & 1, sw, std::false_type{}, idle_tag);
+      step(kt, kt & 1, sw, std::false_type{}, idle_tag, std::true_type{});
       sw = sw == 2 ? 0 : sw + 1;
     }
   };
+
+  // Partials in LDS (the H ring is free by then): [slot][row of the tile], slot = 4 wn + g.
   float2* lp = reinterpret_cast<float2*>(ringH);
   if (idle) {
     walk(std::true_type{});
@@ -532,39 +317,137 @@ __global__ __launch_bounds__(256) void head_tiled256w4_kernel(HeadArgs a, int m_
   } else {
     walk(std::false_type{});
 #pragma unroll
-    for (int i = 0; i < 4; ++i) mfma_row(cur, i);  // last slice of the last step
-    lds_barrier();  // nobody reads the rings any more: the H ring takes the partials
-    const int mw = m0 + wm * 128, vb = n0 + wn * 128;
-    if (mw + 128 <= M && vb + 128 <= a.V) {  // wavefront-uniform
-      epilogue_128x128<CE>(a, acc, mw, vb, lane, lp + wm * 128 * 4 + 2 * wn);
-    } else {
-      store_logits_and_partials<4, CE>(a, acc[0], mw, vb, M, lane, lp, wm * 128, 2 * wn);
-      store_logits_and_partials<4, CE>(a, acc[1], mw, vb + 64, M, lane, lp, wm * 128, 2 * wn + 1);
-    }
+    for (int n = 0; n < NR; ++n)  // last slice of the last step
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        mfma16<!ONE>(acc_at(t, n), wf[1][t], hf[ROLL ? 0 : 1][n]);
+    settle<!ONE>(acc0, acc1);
+    lds_barrier();  // nobody reads the rings any more
+
+    // Epilogue.  Straight from the registers, row group by row group.
+    constexpr float kLog2e = 1.4426950408889634f;
+    const float sc = a.inv_tau;
+    const int vw = n0 + wn * (16 * NT);  // first token of the wavefront
+    const int v0 = vw + 4 * g;           // first token of the lane's piece of 16-token tile 0
+    auto rows = [&](auto edge) __attribute__((always_inline)) {
+      constexpr bool EDGE = decltype(edge)::value;  // some of the workgroup's 256 tokens lie past V
+#pragma unroll
+      for (int n = 0; n < NR; ++n) {
+        const int rl = wm * WROWS + 16 * n + i16, row = m0 + rl;
+        const bool row_ok = row < M;
+        floatx4 l[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) l[t] = acc_at(t, n) * sc;
+        if constexpr (CE) {
+          // The lane that holds the row's label token stores its logit.  Most row groups hold none of their labels among
+          // these tokens; where one does, the lanes pass their values through LDS (the W ring is free) to index them.
+          const int off = row_ok ? a.labels[row] - vw : -1;
+          const bool mine = (unsigned)off < (unsigned)(16 * NT) && ((off >> 2) & 3) == g && vw + off < a.V;
+          if (__builtin_amdgcn_ballot_w64(mine) != 0) {  // wavefront-uniform
+            floatx4* own = reinterpret_cast<floatx4*>(ringW) + wave * (NT * kWave) + lane;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) own[t * kWave] = l[t];
+            if (mine) a.label_logit[row] = reinterpret_cast<const float*>(own + (off >> 4) * kWave)[off & 3];
+          }
+        } else if constexpr (!EDGE) {
+          // A store instruction should write whole 128-byte lines, i.e. 8 lanes per row, but a row's values sit in four
+          // lanes.  So neighbouring lanes (rows 2j, 2j + 1) trade one of every two tiles: row 2j's pair of tiles then lies
+          // in both lanes, row 2j + 1's likewise (64-byte pieces cost 6 % of the kernel's time at M = 2048).
+          // Non-temporal: the logits are read next by another kernel, and as ordinary stores they sit dirty in L2
+          // and push out the W and H lines the neighbouring workgroups are about to ask for (6 % at M = 256).
+          const bool odd = i16 & 1;
+          const int row2 = row & ~1;
+          float* dst = a.logits + (size_t)row2 * a.ldl + v0 + (odd ? 16 : 0);
+floatx4 x[NT / 2], y[NT / 2];
+#pragma unroll
+          for (int t = 0; t < NT; t += 2)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              const float near = swap_pair(l[t][c]), far = swap_pair(l[t + 1][c]);
+              x[t / 2][c] = odd ? far : l[t][c];
+              y[t / 2][c] = odd ? l[t + 1][c] : near;
+            }
+          if (row2 < M)
+#pragma unroll
+            for (int t = 0; t < NT; t += 2) __builtin_nontemporal_store(x[t / 2], reinterpret_cast<floatx4*>(dst + 16 * t));
+          dst += a.ldl;
+          if (row2 + 1 < M)
+#pragma unroll
+            for (int t = 0; t < NT; t += 2) __builtin_nontemporal_store(y[t / 2], reinterpret_cast<floatx4*>(dst + 16 * t));
+        } else if (row_ok) {
+          float* dst = a.logits + (size_t)row * a.ldl + v0;
+#pragma unroll
+          for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+              if (v0 + 16 * t + c < a.V) dst[16 * t + c] = l[t][c];
+        }
+        if constexpr (EDGE) {
+#pragma unroll
+          for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+              if (v0 + 16 * t + c >= a.V) l[t][c] = -INFINITY;
+        }
+        float mx = kLowest;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) mx = vmax3(vmax3(l[t][0], l[t][1], mx), l[t][2], l[t][3]);
+        const float mb = mx * -kLog2e;
+        float e = 0.f;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          float x[4];
+#pragma unroll
+          for (int c = 0; c < 4; ++c) x[c] = __builtin_amdgcn_exp2f(fmaf(l[t][c], kLog2e, mb));
+          e += (x[0] + x[1]) + (x[2] + x[3]);
+        }
+        lp[(4 * wn + g) * BM + rl] = make_float2(mx, e);
+      }
+    };
+    if (n0 + BN <= a.V) rows(std::false_type{});  // workgroup-uniform
+    else rows(std::true_type{});
   }
   lds_barrier();
-  merge_tile_partials(a, lp, BM, m0, nt, M, tid);
+  // one (max, sum exp) partial per (row, 256-token tile), merged in a fixed order by the thread that owns the row
+  if (tid < BM && m0 + tid < M) {
+    constexpr float kLog2e = 1.4426950408889634f;
+    constexpr int SLOTS = 4 * WN;
+    float2 p[SLOTS];
+    float mx = kLowest;
+#pragma unroll
+    for (int c = 0; c < SLOTS; ++c) {
+      p[c] = lp[c * BM + tid];
+      mx = fmaxf(mx, p[c].x);
+    }
+    float sum = 0.f;
+#pragma unroll
+    for (int c = 0; c < SLOTS; ++c) sum += p[c].y * exp2f((p[c].x - mx) * kLog2e);
+    a.partials[(size_t)(m0 + tid) * a.nT + nt] = make_float2(mx, sum);
+  }
+}
+
+template <int NR, int WN>
+hipError_t launch_tiles(const HeadArgs& a, int m_tiles) {
+  const int n_tiles = (a.V + BN - 1) / BN;
+  const dim3 grid((unsigned)(8L * ((n_tiles + 7) / 8) * m_tiles)), block(128 * WN);
+  if (a.labels) FEF_LAUNCH_HEAD((head_tiled256_kernel<NR, WN, true>), grid, block, a, a, m_tiles, n_tiles);
+  else FEF_LAUNCH_HEAD((head_tiled256_kernel<NR, WN, false>), grid, block, a, a, m_tiles, n_tiles);
+  return hipGetLastError();
 }
 
 }  // namespace
 
+// ceil(M / 256) row tiles of equal height (a multiple of 32).  One row tile: eight wavefronts (the kernel is short of
+// memory parallelism there, not of LDS rate), 192 or 256 rows; several: four wavefronts, 160 to 256 rows.
 hipError_t launch_head_tiled256(const HeadArgs& a) {
-  const int M = a.nrows;
-  const int m_tiles = (M + BM - 1) / BM, n_tiles = (a.V + BN - 1) / BN;
-  const long grid = 8L * ((n_tiles + 7) / 8) * m_tiles;
-  if (m_tiles == 1) {  // M <= 256: eight wavefronts of 128 x 64, one workgroup per tile
-    if (a.labels)
-      FEF_LAUNCH_HEAD((head_tiled256_kernel<true>), dim3((unsigned)grid), dim3(512), a, a, m_tiles, n_tiles);
-    else
-      FEF_LAUNCH_HEAD((head_tiled256_kernel<false>), dim3((unsigned)grid), dim3(512), a, a, m_tiles, n_tiles);
-    return hipGetLastError();
+  const int m_tiles = (a.nrows + 255) / 256;
+  if (m_tiles == 1) return a.nrows <= 192 ? launch_tiles<6, 4>(a, 1) : launch_tiles<8, 4>(a, 1);
+  switch (((a.nrows + m_tiles - 1) / m_tiles + 31) / 32) {
+    case 5: return launch_tiles<5, 2>(a, m_tiles);
+    case 6: return launch_tiles<6, 2>(a, m_tiles);
+    case 7: return launch_tiles<7, 2>(a, m_tiles);
+    default: return launch_tiles<8, 2>(a, m_tiles);
   }
-  // M > 256: four wavefronts of 128 x 128
-  if (a.labels)
-    FEF_LAUNCH_HEAD((head_tiled256w4_kernel<true>), dim3((unsigned)grid), dim3(256), a, a, m_tiles, n_tiles);
-  else
-    FEF_LAUNCH_HEAD((head_tiled256w4_kernel<false>), dim3((unsigned)grid), dim3(256), a, a, m_tiles, n_tiles);
-  return hipGetLastError();
 }
 
 }  // namespace fef
