@@ -76,6 +76,18 @@ __device__ __forceinline__ void mfma16(floatx4& c, const bf16x8& w, const bf16x8
   if constexpr (AGPR) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(w), "v"(h));
   else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(w), "v"(h));
 }
+// The same with a direct-to-LDS load (lane l: 16 bytes from p to lds + 16 l) around it: the write of M0 in front, the load
+// behind, so that neither is a run of instructions between two multiplies and the multiply is the wait state that a
+// load needs after a write of M0.
+template <bool AGPR>
+__device__ __forceinline__ void mfma16_load(floatx4& c, const bf16x8& w, const bf16x8& h, const void* p, uint32_t lds) {
+  if constexpr (AGPR)
+    asm volatile("s_mov_b32 m0, %4\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\tglobal_load_lds_dwordx4 %3, off"
+                 : "+a"(c) : "v"(w), "v"(h), "v"(p), "s"(lds) : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %4\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\tglobal_load_lds_dwordx4 %3, off"
+                 : "+v"(c) : "v"(w), "v"(h), "v"(p), "s"(lds) : "memory");
+}
 // Every accumulator in its registers, and no multiply or move to them in flight: behind the zeroing and behind the last
 // multiply.  (The empty statements keep the writers in front of the wait and the readers behind it.)
 template <bool AGPR, int NT, int NR>
@@ -216,10 +228,10 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
   // Slice KS of the step in work is read into fragment set KS while the slice before it (set KS ^ 1; KS = 0: the last
   // slice of the step before) is multiplied.  LOADS: phase 0 requests the H stage of the next step, phase 1 the W
   // stage of the step after that.
-  auto phase = [&](auto ks_tag, auto mul_tag, const bf16x8* Hs, const bf16x8* Ws, bool more, int stage)
+  auto phase = [&](auto ks_tag, auto mul_tag, auto full, const bf16x8* Hs, const bf16x8* Ws, bool more, int stage)
       __attribute__((always_inline)) {
     constexpr int KS = decltype(ks_tag)::value;
-    constexpr bool MUL = decltype(mul_tag)::value;
+    constexpr bool MUL = decltype(mul_tag)::value, FULL = decltype(full)::value;
     constexpr int TOTAL = NT * NR, LOADS = KS == 0 ? LH : LW;
     bf16x8(&wr)[NT] = wf[KS];
     bf16x8(&wm_)[NT] = wf[KS ^ 1];
@@ -229,9 +241,19 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
     auto read_h = [&](int n) __attribute__((always_inline)) { hr[n] = Hs[(wm * NR + n) * 128 + fo[KS]]; };
     for_each(std::make_integer_sequence<int, TOTAL>{}, [&](auto m_tag) __attribute__((always_inline)) {
       constexpr int m = decltype(m_tag)::value, n = m / NT, t = m % NT;
+      // four wavefronts: the load that goes with this multiply, and the pointer that moved with the multiply before
+      constexpr int q = ROLL ? -1 : spread_at(m, LOADS, TOTAL), qb = ROLL ? -1 : spread_at(m - 1, LOADS, TOTAL);
       if constexpr (MUL) {
-        mfma16<!ONE>(acc_at(t, n), wm_[t], hm[n]);
+        if constexpr (q >= 0 && FULL)
+          mfma16_load<!ONE>(acc_at(t, n), wm_[t], hm[n], KS == 0 ? gh[q < LH ? q : 0] : gw[q < LW ? q : 0],
+                            (KS == 0 ? slotH + stage * kBytesH : slotW + stage * kBytesW) + q * 1024);
+        else
+          mfma16<!ONE>(acc_at(t, n), wm_[t], hm[n]);
         __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (q >= 0 && !(MUL && FULL)) {  // first and last steps: the load may not exist
+        if (more) load_to_lds_16(KS == 0 ? gh[q < LH ? q : 0] : gw[q < LW ? q : 0],
+                                 (KS == 0 ? slotH + stage * kBytesH : slotW + stage * kBytesW) + q * 1024);
       }
       if constexpr (ROLL) {
         // W fragments under the first row groups, an H fragment behind the last multiply that uses its registers
@@ -252,17 +274,18 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
         }
       } else {
         // a read after every third multiply or so, in the order the next phase wants them: h0, w0.., h1..
-        constexpr int r = spread_at(m, NT + NR, TOTAL - TOTAL / 8), q = spread_at(m - 1, LOADS, TOTAL);
+        constexpr int r = spread_at(m, NT + NR, TOTAL - TOTAL / 8);
         if constexpr (r >= 0) {
           if constexpr (r == 0) read_h(0);
           else if constexpr (r <= NT) read_w(r - 1);
           else read_h(r - NT);
           __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (q >= 0) {
+        if constexpr (qb >= 0) {
           if (more) {
-            if constexpr (KS == 0) issue_one(gh[q], q, slotH + stage * kBytesH, BK);
-            else issue_one(gw[q], q, slotW + stage * kBytesW, BK);
+            const __bf16*& p = KS == 0 ? gh[qb < LH ? qb : 0] : gw[qb < LW ? qb : 0];
+            p += BK;
+            asm volatile("" : "+v"(p));
           }
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -287,8 +310,8 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
     } else {
       const bf16x8* Hs = ringH + sh * kStageH;
       const bf16x8* Ws = ringW + sw * kStageW;
-      phase(std::integral_constant<int, 0>{}, mul_tag, Hs, Ws, more_h, sh1);
-      phase(std::integral_constant<int, 1>{}, std::true_type{}, Hs, Ws, more_w, sw2);
+      phase(std::integral_constant<int, 0>{}, mul_tag, full, Hs, Ws, more_h, sh1);
+      phase(std::integral_constant<int, 1>{}, std::true_type{}, full, Hs, Ws, more_w, sw2);
     }
   };
   // Two copies of the loop, chosen once: a wavefront without rows only loads and meets the barriers.  (With the choice
