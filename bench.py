@@ -52,17 +52,18 @@ class HipEvents:
         self.hip.hipEventDestroy(e)
 
 
-def head_bytes(wl, skinny, M, rowstream=False, tiled256=False, stream=False):
+def tile_count(V, M):
+    """Token tiles of the 256-token tile kernel = partials per row (see tiled256_tiles in the library)."""
+    whole = -(-V // 256)
+    rounds = -(-whole // 256)
+    return whole if M > 256 or rounds == 1 or whole - 256 * (rounds - 1) > 200 else 256 * rounds
+
+
+def head_bytes(wl, M, variant):
     """Algorithmic HBM bytes of one vocabulary-head launch over M rows: W once, H once, fp32
     logits written once, the per-tile (max, sum exp) partials."""
     esz = 2 if wl.dtype == "bf16" else 4
-    nT = min(-(-wl.V // 16), 256) if skinny else -(-wl.V // 64)
-    if tiled256:
-        nT = -(-wl.V // 256)      # the 256 x 256 kernels merge their partials per workgroup tile
-    if rowstream:
-        nT = min(256, -(-(-(-wl.V // 16)) // 8))
-    if stream:
-        nT = min(256, -(-(-(-wl.V // 64)) // 4))   # the LDS-streaming kernel leaves one partial per row and workgroup
+    nT = {"skinny": min(-(-wl.V // 16), 256), "tiled": -(-wl.V // 64), "f32": -(-wl.V // 64)}.get(variant) or tile_count(wl.V, M)
     return wl.V * wl.d * esz + M * wl.d * esz + M * wl.V * 4 + M * nT * 8
 
 
@@ -162,7 +163,7 @@ def bench_cross_entropy(args, wl, W, Wd, dev):
     elapsed = time.perf_counter() - t0
     head_s = sum(ev.elapsed_ms(a, b) for a, b in pairs) / len(pairs) / 1e3
     esz = 2 if wl.dtype == "bf16" else 4
-    nT = min(256, -(-(-(-wl.V // 64)) // 4)) if R <= 128 else -(-wl.V // 256)   # per workgroup / per 256-token tile
+    nT = tile_count(wl.V, R)
     hb = wl.V * wl.d * esz + R * wl.d * esz + R * nT * 8 + R * 4       # no logits are written
     flops = 2.0 * R * wl.V * wl.d
     if hb / (HBM_PEAK_GBS * 1e9) >= flops / (MFMA_BF16_PEAK_TFLOPS * 1e12):
@@ -173,7 +174,7 @@ def bench_cross_entropy(args, wl, W, Wd, dev):
         ach = flops / head_s / 1e12
         roof = {"bound": "mfma", "achieved": ach, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": ach / MFMA_BF16_PEAK_TFLOPS, "traffic": None}
-    roof.update({"kernel": "head_stream_kernel" if R <= 128 else ("head_tiled256_kernel" if R <= 256 else "head_tiled256w4_kernel"),
+    roof.update({"kernel": "head_tiled256_kernel",
                  "avg_kernel_us": head_s * 1e6, "algorithmic_bytes": hb, "flops": flops, "events": "inline"})
     out = {"metric": "cross-entropy rows/s through the vocabulary head (forward, no logits written)",
            "value": R / (elapsed / args.steps), "unit": "rows/s", "n_gpus": 1, "steps": args.steps,
@@ -381,8 +382,7 @@ def time_verify(args, wl, Wd, dev, steps, warmup):
     ms_per_step = elapsed / steps * 1e3
     positions = wl.B * wl.K
     M = positions if args.split else 2 * positions   # rows through one head launch
-    hb = head_bytes(wl, variant == fb.FEF_GEMM_SKINNY, M, variant == fb.FEF_GEMM_ROWSTREAM,
-                    variant == fb.FEF_GEMM_TILED256, variant == fb.FEF_GEMM_STREAM)
+    hb = head_bytes(wl, M, {fb.FEF_GEMM_SKINNY: "skinny", fb.FEF_GEMM_TILED: "tiled", fb.FEF_GEMM_F32: "f32"}.get(variant))
     flops = 2.0 * M * wl.V * wl.d
     hbm_time, mfma_time = hb / (HBM_PEAK_GBS * 1e9), flops / (MFMA_BF16_PEAK_TFLOPS * 1e12)
     if hbm_time >= mfma_time:
@@ -395,9 +395,8 @@ def time_verify(args, wl, Wd, dev, steps, warmup):
                 "frac": ach / MFMA_BF16_PEAK_TFLOPS, "traffic": None}
     roof.update({"kernel": {fb.FEF_GEMM_SKINNY: "head_skinny_kernel" if M <= 16 else "head_skinny32_kernel",
                             fb.FEF_GEMM_TILED: "head_tiled_kernel",
-                            fb.FEF_GEMM_TILED256: "head_tiled256_kernel" if M <= 256 else "head_tiled256w4_kernel",
-                            fb.FEF_GEMM_STREAM: "head_stream_kernel",
-                            fb.FEF_GEMM_ROWSTREAM: "head_rowstream_kernel",
+                            fb.FEF_GEMM_TILED256: "head_tiled256_kernel", fb.FEF_GEMM_STREAM: "head_tiled256_kernel",
+                            fb.FEF_GEMM_ROWSTREAM: "head_tiled256_kernel",
                             fb.FEF_GEMM_F32: "head_f32_kernel"}[variant],
                  "avg_kernel_us": head_avg_s * 1e6, "algorithmic_bytes": hb, "flops": flops,
                  "events": "separate" if args.graph else args.events,

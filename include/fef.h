@@ -82,15 +82,12 @@ typedef enum {
                           once, split-k; other d at M <= 32 go to STREAM (fef_select_gemm tells) */
   FEF_GEMM_TILED = 2,  /* bf16, any M: plain 128x128 LDS-tiled MFMA GEMM (never picked by AUTO) */
   FEF_GEMM_F32 = 3,    /* f32, any shape: reference-grade FMA kernel                       */
-  FEF_GEMM_TILED256 = 4, /* bf16, any M: 256x256 LDS-tiled MFMA GEMM, eight wavefronts of 128x64 up to
-                            256 rows, four of 128x128 above (AUTO: M > 128)                  */
-  FEF_GEMM_STREAM = 5,   /* bf16, M <= 128: all rows x 256 tokens per persistent workgroup, W
-                            streamed through a deep LDS ring, 64- or 128-row tiles (AUTO: 32 < M <= 128
-                            where the other streaming kernel is not chosen)                  */
-  FEF_GEMM_ROWSTREAM = 6 /* bf16, M <= 128, d a multiple of 512: every wavefront streams the W rows
-                            of its own 16-token tiles into registers, H through LDS, 64-, 96- or
-                            128-row tiles (AUTO: 32 < M <= 48 and 64 < M <= 96, where it needs
-                            fewer rows than the kernel above)                                */
+  FEF_GEMM_TILED256 = 4, /* bf16, any M: LDS-tiled MFMA GEMM, 256 tokens x 32 to 256 rows per workgroup, eight
+                            wavefronts up to 256 rows, four above (AUTO: M > 128)            */
+  FEF_GEMM_STREAM = 5,   /* bf16, M <= 128: the same kernel (AUTO: 48 < M <= 64, 96 < M <= 128, and M <= 128 where
+                            neither SKINNY nor ROWSTREAM takes the hidden size)              */
+  FEF_GEMM_ROWSTREAM = 6 /* bf16, M <= 128, d a multiple of 512: the same kernel (AUTO: 32 < M <= 48 and
+                            64 < M <= 96); the two names are kept for callers that select by them */
 } fef_gemm_variant;
 
 /* In Algorithm 2 the verification inputs X^(j_m) carry the draft prefix, so a real target
@@ -193,9 +190,9 @@ fef_status fef_verify_step(const fef_params* prm, const void* h_draft, const voi
  * arguments, kernels and results as fef_verify_step (all three phases), except that
  * prm->workspace and prm->workspace_bytes are ignored: the scratch is a buffer of
  * FEF_STATIC_SCRATCH_BYTES (32 MiB) built into the library, one copy per GPU, held until the
- * process ends.  The call allocates nothing.  A call whose fef_workspace_bytes exceeds that size
+ * process ends.  The call allocates nothing.  A call that needs more than that
  * (at V = 126464: more than 64 rows through the head, 2*B*K fused) returns FEF_ERR_WORKSPACE and
- * enqueues nothing.  The buffer keeps the previous call's contents; nothing in it has to start at
+ * enqueues nothing; a call whose fef_workspace_bytes does not exceed FEF_STATIC_SCRATCH_BYTES always fits.  The buffer keeps the previous call's contents; nothing in it has to start at
  * zero (every word is written before it is read within a call), and a TARGET call finds what the
  * DRAFT call before it left there.  All calls on one GPU share the buffer: calls that overlap in
  * time on one GPU (different streams or threads) race, so order them.  The first call on a device

@@ -1,6 +1,7 @@
-// Vocabulary-head kernel for large M = 2*B*K (the batched configurations) and for the cross-entropy of many rows.
+// Vocabulary-head kernel for all row counts and hidden sizes that the kernels with H in registers (head_gemm.hip) do not
+// take, and for the cross-entropy use of the head.
 //
-// Workgroup tile 32 NR rows of H (NR = 5 to 8) x 256 tokens, k-steps of 64, v_mfma_f32_16x16x32_bf16 with the W tile
+// Workgroup tile 32 NR rows of H (NR = 1 to 8) x up to 256 tokens, k-steps of 64, v_mfma_f32_16x16x32_bf16 with the W tile
 // as the A operand and H as the B operand.  Two forms:
 //   WN = 2  four wavefronts in a 2 x 2 grid (rows x tokens), each 16 NR rows x 128 tokens: M > 256
 //   WN = 4  eight wavefronts in a 2 x 4 grid, each 16 NR rows x 64 tokens: M <= 256, one row tile
@@ -21,7 +22,11 @@
 // two tiles of 160, not 256 + 44), one instantiation per height.
 //
 // Measured (head kernel, rocprofv3; before: 32x32x16, tokens in the columns of D, 256-row tiles only):
-// FEF_T256_MEASURED
+// M = 2048 (d = 4096, V = 126464) 1697 -> 1610 us with logits, 1600 -> 1470 without (cross-entropy: 1.44 PFLOP/s, matrix
+// units busy 0.72 of the cycles at 1.78 GHz); M = 300 without logits (d = 2048, V = 50257) 138 -> 67; M = 256 250 -> 238.
+// Up to 128 rows, where two kernels built around streaming W stood before (persistent workgroups; W into LDS or straight
+// into registers): 48 rows 189 -> 176 us, 64 rows 188 -> 178, 96 rows 207 -> 181, 128 rows 200 -> 187, and 159 -> 110 at
+// 110 rows of d = 2560, V = 100003.
 //
 // Operand slabs go HBM/L2 -> LDS directly (global_load_lds_dwordx4: lane l of a wavefront deposits its 16 bytes at
 // LDS base + 16 l): no register staging and no ds_write in the main loop.  A row of a stage is 128 bytes, so one load
@@ -50,8 +55,8 @@
 namespace fef {
 namespace {
 
-constexpr int BN = 256, BK = 64;
-constexpr int kRingH = 2, kRingW = 3;
+constexpr int BN = kTiled256Tn, BK = 64;
+constexpr int kUnit = kTiled256Unit;
 constexpr int kStageW = BN * 8;  // 16-byte chunks per W stage
 
 // Which of `cnt` instructions spread evenly over `total` multiplies follows multiply m; -1: none.  cnt <= total.
@@ -106,15 +111,19 @@ __device__ __forceinline__ void settle(floatx4 (&acc0)[NT][NR], floatx4 (&acc1)[
   pin();
 }
 
-template <int NR, int WN, bool CE>
-__global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int m_tiles, int n_tiles) {
+template <int NR, int WN, bool SHARES, bool CE>
+__global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int m_tiles) {
   constexpr int NT = 16 / WN;                        // 16-token tiles per wavefront
   constexpr int BM = 32 * NR, WROWS = 16 * NR;       // rows of the workgroup tile, of a wavefront
-  constexpr int LW = 16 / WN, LH = 2 * NR / WN;      // load instructions per wavefront and stage (8 rows each)
+  constexpr int LW = 16 / WN, LH = (2 * NR + WN - 1) / WN;  // load instructions per wavefront and stage (8 rows each)
   constexpr bool ONE = WN == 4;                      // one row tile, two wavefronts per SIMD
   constexpr bool ROLL = ONE;                         // H fragments in one set of registers, each re-read behind its last use
   constexpr int kStageH = BM * 8;                    // 16-byte chunks per H stage
-  static_assert((2 * NR) % WN == 0, "every wavefront loads as many rows");
+  // Stages in LDS.  Narrow shares make short k-steps, so H is requested two steps ahead there like W, where 160 KB allow
+  // (25.8 -> 22.9 us at 32 rows of d = 1536, V = 32000; 116 -> 110 at 110 rows of d = 2560, V = 100003; a fourth stage of
+  // both measured nothing).  With whole tiles a third H stage costs 2 % (178 against 184 us at 64 rows of d = 4096,
+  // V = 126464).
+  constexpr int kRingW = 3, kRingH = SHARES && NR <= 5 ? 3 : 2;
   __shared__ bf16x8 ringH[kRingH * kStageH];
   __shared__ bf16x8 ringW[kRingW * kStageW];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -126,8 +135,13 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
 
   const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
   const int nt = xcd + 8 * (seq / m_tiles), mt = seq % m_tiles;
-  if (nt >= n_tiles) return;
-  const int m0 = mt * BM, n0 = nt * BN;
+  if (nt >= a.nT) return;
+  // tokens [n0, n_end) of this workgroup, at most 256: a whole tile, or an equal share of the vocabulary in units of 32
+  // tokens (see tiled256_tiles)
+  const int n_units = (a.V + kUnit - 1) / kUnit;
+  const int m0 = mt * BM;
+  const int n0 = SHARES ? (int)((long)nt * n_units / a.nT) * kUnit : nt * BN;
+  const int n_end = min(a.V, SHARES ? (int)((long)(nt + 1) * n_units / a.nT) * kUnit : n0 + BN);
 
   // Every row of W starts at a multiple of 2 d bytes, so workgroups that walk k from 0 in step ask HBM for the
   // same low address bits at the same moment: with one row tile each token tile starts its walk at another k-step and
@@ -136,7 +150,9 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
   int h_left = nk - k0, w_left = nk - k0;  // steps until the walk is back at k = 0
 
   // Direct-to-LDS loads: wavefront w fills rows [8 LH w, + 8 LH) of an H stage and [8 LW w, + 8 LW) of a W stage,
-  // 8 rows per instruction; lane l owns LDS slot (row 8 q + l / 8, position l % 8).
+  // 8 rows per instruction; lane l owns LDS slot (row 8 q + l / 8, position l % 8).  Every wavefront issues as many
+  // loads as the others (the waits count them); where the rows of H do not divide, the last wavefronts repeat some.
+  const int hrow0 = 8 * min(wave * LH, 4 * NR - LH);
   const __bf16* gh[LH];
   const __bf16* gw[LW];
   // With two wavefronts per SIMD up to four loads go out behind one write of M0 (the instruction offset moves the LDS
@@ -146,7 +162,7 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
   constexpr int kLow = ONE ? 512 : 0;
 #pragma unroll
   for (int q = 0; q < LH; ++q) {
-    const int rl = wave * (8 * LH) + q * 8 + (lane >> 3);
+    const int rl = hrow0 + q * 8 + (lane >> 3);
     const int c = (lane & 7) ^ ((rl >> 1) & 7);
     gh[q] = h_row(a, min(m0 + rl, M - 1)) + c * 8 + k0 * BK - q * kLow;  // rows past M re-read the last row; masked later
   }
@@ -154,9 +170,9 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
   for (int q = 0; q < LW; ++q) {
     const int rl = wave * (8 * LW) + q * 8 + (lane >> 3);
     const int c = (lane & 7) ^ ((rl >> 1) & 7);
-    gw[q] = (const __bf16*)a.W + (size_t)min(n0 + rl, a.V - 1) * a.d + c * 8 + k0 * BK - q * kLow;
+    gw[q] = (const __bf16*)a.W + (size_t)min(n0 + rl, n_end - 1) * a.d + c * 8 + k0 * BK - q * kLow;  // past the share: its last row, masked later
   }
-  const uint32_t slotH = lds_offset(ringH + wave * LH * 64), slotW = lds_offset(ringW + wave * LW * 64);
+  const uint32_t slotH = lds_offset(ringH + hrow0 * 8), slotW = lds_offset(ringW + wave * LW * 64);
   constexpr uint32_t kBytesH = kStageH * 16, kBytesW = kStageW * 16;
   // Elements the pointers move on by after the loads of a step: one k-step, and back to k = 0 where the walk wraps.
   auto advance = [&](int& left) __attribute__((always_inline)) -> long {
@@ -192,16 +208,25 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
                    "global_load_lds_dwordx4 %0, off\n\tglobal_load_lds_dwordx4 %1, off offset:1024\n\t"
                    "global_load_lds_dwordx4 %2, off offset:2048"
                    :: "v"(p[0]), "v"(p[1]), "v"(p[2]), "s"(base) : "memory");
+    else if constexpr (L == 2)
+      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\t"
+                   "global_load_lds_dwordx4 %0, off\n\tglobal_load_lds_dwordx4 %1, off offset:1024"
+                   :: "v"(p[0]), "v"(p[1]), "s"(base) : "memory");
+    else
+      load_to_lds_16(p[0], base);
     const long move = advance(left);
 #pragma unroll
     for (int q = 0; q < L; ++q) p[q] += move;
   };
-  static_assert(!ONE || ((LH == 3 || LH == 4) && LW == 4), "groups of loads");
+  static_assert(!ONE || (LH <= 4 && LW <= 4), "groups of loads");
 
-  // prologue: H(0), W(0), W(1)
-  all_h(0);
-  all_w(0);
-  if (1 < nk) all_w(1);
+  // prologue: W as far ahead as its ring reaches, H likewise (one step where its ring is the shorter one)
+#pragma unroll
+  for (int t = 0; t < kRingW - 1; ++t) {
+    if (t >= nk) break;
+    if (t < kRingH - 1) all_h(t);
+    all_w(t);
+  }
 
   // acc(t, n): tokens 16 t + 4 g .. + 3 of row 16 n + i16 of the wavefront's tile
   // (two arrays: one of 1 KB per lane is not taken apart into registers)
@@ -222,8 +247,9 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) fo[ks] = i16 * 8 + ((ks * 4 + g) ^ ((i16 >> 1) & 7));
 
-  // none of this wavefront's rows exists: loads and barriers only (wavefront-uniform, and said so)
-  const bool idle = __builtin_amdgcn_readfirstlane((int)(m0 + wm * WROWS >= M)) != 0;
+  // none of this wavefront's rows, or none of its tokens, exists: loads and barriers only (wavefront-uniform, and said so)
+  const int vw = n0 + wn * (16 * NT);  // first token of the wavefront
+  const bool idle = __builtin_amdgcn_readfirstlane((int)(m0 + wm * WROWS >= M || vw >= n_end)) != 0;
 
   // Slice KS of the step in work is read into fragment set KS while the slice before it (set KS ^ 1; KS = 0: the last
   // slice of the step before) is multiplied.  LOADS: phase 0 requests the H stage of the next step, phase 1 the W
@@ -257,15 +283,16 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
       }
       if constexpr (ROLL) {
         // W fragments under the first row groups, an H fragment behind the last multiply that uses its registers
-        if constexpr (n < NT && t == 1) {
-          read_w(n);
+        constexpr int r = spread_at(m, NT, NR < NT ? TOTAL : NT * NT);  // one per row group where there are enough
+        if constexpr (r >= 0) {
+          read_w(r);
           __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (t == NT - 1) {
           read_h(n);
           __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (m == TOTAL / 2 + 2) {
+        if constexpr (m == TOTAL / 2 + (NR > 1 ? 2 : 0)) {
           if (more) {
             if constexpr (KS == 0) group(gh, slotH + stage * kBytesH, h_left);
             else group(gw, slotW + stage * kBytesW, w_left);
@@ -293,15 +320,18 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
     });
   };
 
-  // One k-step; outstanding loads of this wavefront on entry, oldest first: H(kt) [LH], W(kt+1) [LW]; the barrier
-  // needs H(kt) (W(kt) is older).  FULL: kt + 2 < nk, every refill exists and the step is one basic block.
-  auto step = [&](int kt, int sh, int sw, auto full, auto idle_tag, auto mul_tag) __attribute__((always_inline)) {
+  // One k-step; outstanding loads of this wavefront on entry, oldest first: H(kt), W(kt+1) (H ring of two, W ring of
+  // three), or those of the steps from kt on (rings of equal length); the barrier needs H(kt) and W(kt).  FULL:
+  // kt + kRingW - 1 < nk, every refill exists and the step is one basic block.
+  auto step = [&](int kt, int sw, auto parity, auto full, auto idle_tag, auto mul_tag) __attribute__((always_inline)) {
     constexpr bool FULL = decltype(full)::value;
     constexpr bool IDLE = decltype(idle_tag)::value;
-    const bool more_h = FULL || kt + 1 < nk, more_w = FULL || kt + 2 < nk;
-    const int sh1 = sh ^ 1, sw2 = sw == 0 ? 2 : sw - 1;  // stages of H(kt+1) and W(kt+2)
+    const bool more_h = FULL || kt + kRingH - 1 < nk, more_w = FULL || kt + kRingW - 1 < nk;
+    const int sw2 = sw == 0 ? kRingW - 1 : sw - 1;               // stage of W(kt + kRingW - 1)
+    const int sh = kRingH == kRingW ? sw : (int)decltype(parity)::value, sh1 = kRingH == kRingW ? sw2 : sh ^ 1;
+    constexpr int kStep = kRingH == kRingW ? LH + LW : LW;       // younger loads per step that may stay in flight
     __builtin_amdgcn_sched_barrier(0);
-    if (more_h) wait_newer<LW>();
+    if (FULL || kt + 1 < nk) wait_newer<kStep>();
     else wait_newer<0>();
     lds_barrier();
     if constexpr (IDLE) {
@@ -318,17 +348,22 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
   // inside the step the two paths meet again in every step, and the compiler reconciles their registers there with
   // sixteen moves in front of the barrier.)
   auto walk = [&](auto idle_tag) __attribute__((always_inline)) {
-    step(0, 0, 0, std::false_type{}, idle_tag, std::false_type{});  // nothing to multiply yet in its first phase
+    using Even = std::integral_constant<int, 0>;
+    using Odd = std::integral_constant<int, 1>;
+    step(0, 0, Even{}, std::false_type{}, idle_tag, std::false_type{});  // nothing to multiply yet in its first phase
     int kt = 1, sw = 1;
-    for (; kt + 3 < nk; kt += 2) {  // two full steps: kt + 1 + 2 < nk
-      step(kt, 1, sw, std::true_type{}, idle_tag, std::true_type{});
-      sw = sw == 2 ? 0 : sw + 1;
-      step(kt + 1, 0, sw, std::true_type{}, idle_tag, std::true_type{});
-      sw = sw == 2 ? 0 : sw + 1;
+    for (; kt + kRingW < nk; kt += 2) {  // two full steps
+      step(kt, sw, Odd{}, std::true_type{}, idle_tag, std::true_type{});
+      sw = sw == kRingW - 1 ? 0 : sw + 1;
+      step(kt + 1, sw, Even{}, std::true_type{}, idle_tag, std::true_type{});
+      sw = sw == kRingW - 1 ? 0 : sw + 1;
     }
-    for (; kt < nk; ++kt) {
-      step(kt, kt & 1, sw, std::false_type{}, idle_tag, std::true_type{});
-      sw = sw == 2 ? 0 : sw + 1;
+    for (; kt < nk; kt += 2) {  // what is left
+      step(kt, sw, Odd{}, std::false_type{}, idle_tag, std::true_type{});
+      sw = sw == kRingW - 1 ? 0 : sw + 1;
+      if (kt + 1 == nk) break;
+      step(kt + 1, sw, Even{}, std::false_type{}, idle_tag, std::true_type{});
+      sw = sw == kRingW - 1 ? 0 : sw + 1;
     }
   };
 
@@ -337,6 +372,8 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
   if (idle) {
     walk(std::true_type{});
     lds_barrier();
+#pragma unroll
+    for (int n = 0; n < NR; ++n) lp[(4 * wn + g) * BM + wm * WROWS + 16 * n + i16] = make_float2(kLowest, 0.f);
   } else {
     walk(std::false_type{});
 #pragma unroll
@@ -350,10 +387,9 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
     // Epilogue.  Straight from the registers, row group by row group.
     constexpr float kLog2e = 1.4426950408889634f;
     const float sc = a.inv_tau;
-    const int vw = n0 + wn * (16 * NT);  // first token of the wavefront
-    const int v0 = vw + 4 * g;           // first token of the lane's piece of 16-token tile 0
+    const int v0 = vw + 4 * g;  // first token of the lane's piece of 16-token tile 0
     auto rows = [&](auto edge) __attribute__((always_inline)) {
-      constexpr bool EDGE = decltype(edge)::value;  // some of the workgroup's 256 tokens lie past V
+      constexpr bool EDGE = decltype(edge)::value;  // some of the wavefront's tokens lie past the workgroup's
 #pragma unroll
       for (int n = 0; n < NR; ++n) {
         const int rl = wm * WROWS + 16 * n + i16, row = m0 + rl;
@@ -365,14 +401,14 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
           // The lane that holds the row's label token stores its logit.  Most row groups hold none of their labels among
           // these tokens; where one does, the lanes pass their values through LDS (the W ring is free) to index them.
           const int off = row_ok ? a.labels[row] - vw : -1;
-          const bool mine = (unsigned)off < (unsigned)(16 * NT) && ((off >> 2) & 3) == g && vw + off < a.V;
+          const bool mine = (unsigned)off < (unsigned)(16 * NT) && ((off >> 2) & 3) == g && vw + off < n_end;
           if (__builtin_amdgcn_ballot_w64(mine) != 0) {  // wavefront-uniform
             floatx4* own = reinterpret_cast<floatx4*>(ringW) + wave * (NT * kWave) + lane;
 #pragma unroll
             for (int t = 0; t < NT; ++t) own[t * kWave] = l[t];
             if (mine) a.label_logit[row] = reinterpret_cast<const float*>(own + (off >> 4) * kWave)[off & 3];
           }
-        } else if constexpr (!EDGE) {
+        } else {
           // A store instruction should write whole 128-byte lines, i.e. 8 lanes per row, but a row's values sit in four
           // lanes.  So neighbouring lanes (rows 2j, 2j + 1) trade one of every two tiles: row 2j's pair of tiles then lies
           // in both lanes, row 2j + 1's likewise (64-byte pieces cost 6 % of the kernel's time at M = 2048).
@@ -380,8 +416,9 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
           // and push out the W and H lines the neighbouring workgroups are about to ask for (6 % at M = 256).
           const bool odd = i16 & 1;
           const int row2 = row & ~1;
+          const int pairs = EDGE ? (n_end - vw) / 32 : NT / 2;  // whole pairs of tiles, wavefront-uniform
           float* dst = a.logits + (size_t)row2 * a.ldl + v0 + (odd ? 16 : 0);
-floatx4 x[NT / 2], y[NT / 2];
+          floatx4 x[NT / 2], y[NT / 2];
 #pragma unroll
           for (int t = 0; t < NT; t += 2)
 #pragma unroll
@@ -392,25 +429,34 @@ floatx4 x[NT / 2], y[NT / 2];
             }
           if (row2 < M)
 #pragma unroll
-            for (int t = 0; t < NT; t += 2) __builtin_nontemporal_store(x[t / 2], reinterpret_cast<floatx4*>(dst + 16 * t));
+            for (int t = 0; t < NT; t += 2)
+              if (!EDGE || t / 2 < pairs) __builtin_nontemporal_store(x[t / 2], reinterpret_cast<floatx4*>(dst + 16 * t));
           dst += a.ldl;
           if (row2 + 1 < M)
 #pragma unroll
-            for (int t = 0; t < NT; t += 2) __builtin_nontemporal_store(y[t / 2], reinterpret_cast<floatx4*>(dst + 16 * t));
-        } else if (row_ok) {
-          float* dst = a.logits + (size_t)row * a.ldl + v0;
+            for (int t = 0; t < NT; t += 2)
+              if (!EDGE || t / 2 < pairs) __builtin_nontemporal_store(y[t / 2], reinterpret_cast<floatx4*>(dst + 16 * t));
+          if constexpr (EDGE) {  // what does not fill a pair of tiles
+            float* one = a.logits + (size_t)row * a.ldl + v0;
 #pragma unroll
-          for (int t = 0; t < NT; ++t)
+            for (int t = 0; t < NT; ++t) {
+              if (t / 2 < pairs || vw + 16 * t >= n_end || !row_ok) continue;
+              if (v0 + 16 * t + 3 < n_end) {
+                __builtin_nontemporal_store(l[t], reinterpret_cast<floatx4*>(one + 16 * t));
+              } else {
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-              if (v0 + 16 * t + c < a.V) dst[16 * t + c] = l[t][c];
+                for (int c = 0; c < 4; ++c)
+                  if (v0 + 16 * t + c < n_end) one[16 * t + c] = l[t][c];
+              }
+            }
+          }
         }
         if constexpr (EDGE) {
 #pragma unroll
           for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-              if (v0 + 16 * t + c >= a.V) l[t][c] = -INFINITY;
+              if (v0 + 16 * t + c >= n_end) l[t][c] = -INFINITY;
         }
         float mx = kLowest;
 #pragma unroll
@@ -427,11 +473,11 @@ floatx4 x[NT / 2], y[NT / 2];
         lp[(4 * wn + g) * BM + rl] = make_float2(mx, e);
       }
     };
-    if (n0 + BN <= a.V) rows(std::false_type{});  // workgroup-uniform
+    if (vw + 16 * NT <= n_end) rows(std::false_type{});  // wavefront-uniform
     else rows(std::true_type{});
   }
   lds_barrier();
-  // one (max, sum exp) partial per (row, 256-token tile), merged in a fixed order by the thread that owns the row
+  // one (max, sum exp) partial per (row, workgroup), merged in a fixed order by the thread that owns the row
   if (tid < BM && m0 + tid < M) {
     constexpr float kLog2e = 1.4426950408889634f;
     constexpr int SLOTS = 4 * WN;
@@ -449,27 +495,59 @@ floatx4 x[NT / 2], y[NT / 2];
   }
 }
 
-template <int NR, int WN>
+template <int NR, int WN, bool SHARES>
 hipError_t launch_tiles(const HeadArgs& a, int m_tiles) {
-  const int n_tiles = (a.V + BN - 1) / BN;
-  const dim3 grid((unsigned)(8L * ((n_tiles + 7) / 8) * m_tiles)), block(128 * WN);
-  if (a.labels) FEF_LAUNCH_HEAD((head_tiled256_kernel<NR, WN, true>), grid, block, a, a, m_tiles, n_tiles);
-  else FEF_LAUNCH_HEAD((head_tiled256_kernel<NR, WN, false>), grid, block, a, a, m_tiles, n_tiles);
+  const dim3 grid((unsigned)(8L * ((a.nT + 7) / 8) * m_tiles)), block(128 * WN);
+  if (a.labels) FEF_LAUNCH_HEAD((head_tiled256_kernel<NR, WN, SHARES, true>), grid, block, a, a, m_tiles);
+  else FEF_LAUNCH_HEAD((head_tiled256_kernel<NR, WN, SHARES, false>), grid, block, a, a, m_tiles);
   return hipGetLastError();
+}
+
+template <int NR>
+hipError_t launch_one(const HeadArgs& a) {  // one row tile of 32 NR rows
+  return a.nT == (a.V + BN - 1) / BN ? launch_tiles<NR, 4, false>(a, 1) : launch_tiles<NR, 4, true>(a, 1);
 }
 
 }  // namespace
 
-// ceil(M / 256) row tiles of equal height (a multiple of 32).  One row tile: eight wavefronts (the kernel is short of
-// memory parallelism there, not of LDS rate), 192 or 256 rows; several: four wavefronts, 160 to 256 rows.
+// Token tiles of a launch over M rows = partials per row.  With one row tile the pass over W is what it costs, and
+// workgroups of whole 256-token tiles leave many CUs without work in the last round of 256: V = 100003 is 391 tiles,
+// one round and a half, V = 151936 is 594, two and a third, V = 32000 is 125, half a round.  There the tokens are dealt
+// out evenly over full rounds instead, in units of 32 (128 bytes of logits): 120 -> 110 us at 110 rows (d = 2560,
+// V = 100003), 233 -> 215 at 128 rows (d = 3584, V = 151936), 69 -> 51 at 64 rows (d = 4096, V = 32000), 155 -> 145 at 256
+// rows.  Where the last round is nearly full (V = 126464: 494 tiles, 238 in the last round) whole tiles are 2 % ahead;
+// hence the line at 200 of 256.  With several row tiles the multiplies are what it costs, and those of a partly filled
+// tile are not saved.
+int tiled256_tiles(int V, int M) {
+  const int whole = (V + BN - 1) / BN;
+  const int rounds = (whole + 255) / 256, last = whole - 256 * (rounds - 1);
+  if (M > BN || last > 200) return whole;
+  const int units = (V + kUnit - 1) / kUnit;
+  return 256 * rounds < units ? 256 * rounds : units;
+}
+
+// ceil(M / 256) row tiles of equal height (a multiple of 32).  One row tile: eight wavefronts (two per SIMD: the kernel
+// is short of memory parallelism there, not of LDS rate).  Several: four wavefronts, 160 to 256 rows.
 hipError_t launch_head_tiled256(const HeadArgs& a) {
   const int m_tiles = (a.nrows + 255) / 256;
-  if (m_tiles == 1) return a.nrows <= 192 ? launch_tiles<6, 4>(a, 1) : launch_tiles<8, 4>(a, 1);
-  switch (((a.nrows + m_tiles - 1) / m_tiles + 31) / 32) {
-    case 5: return launch_tiles<5, 2>(a, m_tiles);
-    case 6: return launch_tiles<6, 2>(a, m_tiles);
-    case 7: return launch_tiles<7, 2>(a, m_tiles);
-    default: return launch_tiles<8, 2>(a, m_tiles);
+  const int nr = ((a.nrows + m_tiles - 1) / m_tiles + 31) / 32;
+  if (m_tiles > 1) {
+    switch (nr) {
+      case 5: return launch_tiles<5, 2, false>(a, m_tiles);
+      case 6: return launch_tiles<6, 2, false>(a, m_tiles);
+      case 7: return launch_tiles<7, 2, false>(a, m_tiles);
+      default: return launch_tiles<8, 2, false>(a, m_tiles);
+    }
+  }
+  switch (nr) {
+    case 1: return launch_one<1>(a);
+    case 2: return launch_one<2>(a);
+    case 3: return launch_one<3>(a);
+    case 4: return launch_one<4>(a);
+    case 5: return launch_one<5>(a);
+    case 6: return launch_one<6>(a);
+    case 7: return launch_one<7>(a);
+    default: return launch_one<8>(a);
   }
 }
 

@@ -1,4 +1,4 @@
-"""The 256-token tiles at their edges: every tile height (160 to 256 rows, one row tile and several), one row more and
+"""The 256-token tiles at their edges: every tile height (32 to 256 rows, one row tile and several), one row more and
 less than a tile, k of one to five steps, tokens one more and less than a tile.  Logits, log-sum-exps and
 cross-entropy against a float64 product."""
 import numpy as np
@@ -16,7 +16,8 @@ def _bound(h, W, d, tau):
 
 
 @pytest.mark.parametrize("B,K,d,V", [
-    (1, 8, 64, 255), (13, 5, 128, 257), (96, 1, 192, 256), (97, 1, 256, 513), (8, 16, 320, 300), (43, 3, 64, 511),
+    (1, 8, 64, 255), (1, 16, 320, 257), (17, 1, 64, 300), (8, 4, 128, 511), (3, 11, 192, 256), (6, 8, 64, 1000),
+    (7, 7, 256, 513), (8, 8, 320, 255), (13, 5, 128, 257), (5, 16, 64, 700), (9, 9, 128, 258), (14, 8, 192, 260), (96, 1, 192, 256), (97, 1, 256, 513), (8, 16, 320, 300), (43, 3, 64, 511),
     (10, 16, 128, 259), (23, 7, 192, 64), (48, 4, 256, 1024), (193, 1, 64, 270), (15, 15, 128, 258), (16, 16, 192, 769),
     (257, 1, 64, 33), (32, 12, 128, 900),
 ])
