@@ -7,8 +7,9 @@
 //                            inverse CDF (tiles, then tokens inside the tile).
 //   accept_resid_kernel      per sequence: accept tests u <= min{1, pi(x~)/rho(x~)}, first
 //                            rejection by ballot; per 256-token chunk the residual mass
-//                            sum [pi - rho]_+ (and the overlap mass sum min{pi, rho}) of the
-//                            rejected slot.
+//                            sum [pi - rho]_+ of the rejected slot.
+//   slot_mass_kernel         in its place where the masses of every slot are wanted: residual and
+//                            overlap mass (sum min{pi, rho}) per slot and chunk.
 //   finalize_kernel          per sequence: inverse CDF over the residual chunks and inside
 //                            the selected chunk, commit of tokens and confidences, block-mask
 //                            update and LowConf.  (A separate launch on purpose: handing the
@@ -278,7 +279,16 @@ __global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
   const int b = s / a.K, m = s % a.K;
   const float2* P = a.partials + (size_t)r * a.nT;
 
-  // log-sum-exp of the row from the head kernel's per-tile partials
+  // log-sum-exp of the row from the head kernel's per-tile partials; the window slot and a given draft token are asked
+  // for in the same breath (each trip to memory that waits for another costs about 1 us)
+  int pos = -1, window = 0, given = -1;
+  auto window_and_token = [&]() {
+    if (!is_draft) return;
+    int unresolved;
+    if (a.draft_tokens_in) given = a.draft_tokens_in[s];
+    pos = window_slot(a, b, m, unresolved);
+    window = min(a.K, unresolved);
+  };
   float mass[PER > 0 ? PER : 1];  // exp-sums of this lane's tiles relative to the row maximum
   float mx = -INFINITY, sm = 0.f;
   if constexpr (PER > 0) {
@@ -294,8 +304,10 @@ __global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
     for (int j = 0; j < PER; ++j) {
       const int t = EXCHANGE ? j * kWave + lane : lane * PER + j;
       p[j] = t < a.nT ? P[t] : make_float2(-INFINITY, 0.f);
-      mx = fmaxf(mx, p[j].x);
     }
+    window_and_token();
+#pragma unroll
+    for (int j = 0; j < PER; ++j) mx = fmaxf(mx, p[j].x);
     mx = wave_max(mx);
 #pragma unroll
     for (int j = 0; j < PER; ++j) mass[j] = p[j].y > 0.f ? p[j].y * expf(p[j].x - mx) : 0.f;
@@ -313,6 +325,7 @@ __global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
 #pragma unroll
     for (int j = 0; j < PER; ++j) sm += mass[j];
   } else {
+    window_and_token();
     for (int t = lane; t < a.nT; t += kWave) mx = fmaxf(mx, P[t].x);
     mx = wave_max(mx);
     for (int t = lane; t < a.nT; t += kWave) {
@@ -334,9 +347,6 @@ __global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
     return;
   }
 
-  int unresolved;
-  const int pos = window_slot(a, b, m, unresolved);
-  const int window = min(a.K, unresolved);
   if (lane == 0) {
     a.slot_pos[s] = pos;
     if (m == 0) a.window[b] = window;
@@ -344,7 +354,7 @@ __global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
   int x = -1;
   if (m < window) {
     if (a.draft_tokens_in) {
-      x = min(max(a.draft_tokens_in[s], 0), a.V - 1);  // keep the gathers in bounds
+      x = min(max(given, 0), a.V - 1);  // keep the gathers in bounds
     } else if (a.greedy) {
       x = row_argmax(a, P, a.logits + (size_t)r * a.ldl, mx);  // point mass of the draft law
     } else {
@@ -391,28 +401,39 @@ __global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
 // ---------------------------------------------------------------------------------------------
 
 // rm_pre: (wavefront 0 only) the residual chunk masses of this sequence, 16 per lane, loaded by the
-// caller before the accept-phase results were known; valid if have_pre.
+// caller before the accept-phase results were known; valid if have_pre.  s_conf, s_mask, s_cand: the
+// block state before the round, my_pos: slot_pos of slot tid, pass: seq_pass of the sequence, likewise.
 __device__ void finalize_sequence(const VerifyArgs& a, int b, const SeqState& st, BlockTmp& tmp,
                                   float* s_conf, uint8_t* s_mask, uint8_t* s_cand, const float (&rm_pre)[16],
-                                  bool have_pre) {
+                                  bool have_pre, int my_pos, int pass) {
   const int tid = threadIdx.x;
   const int BK = a.B * a.K;
   const int window = st.window, acc_len = st.acc_len;
 
-  // diagnostics: overlap and residual mass of every slot
+  // diagnostics: overlap and residual mass of every slot, one wavefront per slot, eight loads of each in flight
+  // (27 -> 13 us at 64 sequences x 16 slots of 494 chunks against a workgroup sum per slot)
   if (a.all_slots) {
-    for (int m = 0; m < a.K; ++m) {
+    const int lane = tid & 63;
+    for (int m = tid >> 6; m < a.K; m += NW) {
       float al = 0.f, rm = 0.f;
       if (m < window) {
-        const size_t base = (size_t)(b * a.K + m) * a.nRC;
-        for (int c = tid; c < a.nRC; c += NT) {
-          al += a.amass[base + c];
-          rm += a.rmass[base + c];
+        const float* A = a.amass + (size_t)(b * a.K + m) * a.nRC;
+        const float* R = a.rmass + (size_t)(b * a.K + m) * a.nRC;
+        for (int c0 = lane; c0 < a.nRC; c0 += 8 * kWave) {
+          float x[8], y[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const int c = c0 + j * kWave;
+            x[j] = c < a.nRC ? A[c] : 0.f;
+            y[j] = c < a.nRC ? R[c] : 0.f;
+          }
+          al += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+          rm += ((y[0] + y[1]) + (y[2] + y[3])) + ((y[4] + y[5]) + (y[6] + y[7]));
         }
-        al = block_sum(al, tmp);
-        rm = block_sum(rm, tmp);
+        al = wave_sum(al);
+        rm = wave_sum(rm);
       }
-      if (tid == 0) {
+      if (lane == 0) {
         if (a.diag_alpha) a.diag_alpha[b * a.K + m] = al;
         if (a.diag_resid_mass) a.diag_resid_mass[b * a.K + m] = rm;
       }
@@ -539,24 +560,17 @@ __device__ void finalize_sequence(const VerifyArgs& a, int b, const SeqState& st
 
   // block state: mask, pass set, confidences
   const size_t row = (size_t)b * a.block;
-  for (int i = tid; i < a.block; i += NT) {
-    s_mask[i] = a.mask_in ? (a.mask_in[row + i] != 0) : 1;
-    s_cand[i] = a.pass_mask ? (a.pass_mask[row + i] != 0) : 0;
-    s_conf[i] = a.conf ? a.conf[row + i] : 0.f;
-  }
-  __syncthreads();
   if (tid < committed) {
-    const int pos = a.slot_pos[b * a.K + tid];
-    s_mask[pos] = 0;
-    s_cand[pos] = 1;
-    s_conf[pos] = (tid < acc_len) ? st.ptok[tid] : z_conf;
+    s_mask[my_pos] = 0;
+    s_cand[my_pos] = 1;
+    s_conf[my_pos] = (tid < acc_len) ? st.ptok[tid] : z_conf;
   }
   __syncthreads();
   int unresolved = 0;
   for (int i = tid; i < a.block; i += NT) unresolved |= s_mask[i];
   unresolved = block_max_int(unresolved, tmp);
 
-  const bool final = a.seq_pass ? a.seq_pass[b] >= a.n_pass - 1 : a.final_pass != 0;
+  const bool final = a.seq_pass ? pass >= a.n_pass - 1 : a.final_pass != 0;
   const bool fire = !unresolved && !final;
   int remasked = 0;
   if (fire) {
@@ -587,8 +601,8 @@ __device__ void finalize_sequence(const VerifyArgs& a, int b, const SeqState& st
     remasked = block_max_int(remasked, tmp);
   }
   if (a.tokens_state && tid < committed)
-    a.tokens_state[row + a.slot_pos[b * a.K + tid]] = tid < acc_len ? st.x[tid] : z;
-  __syncthreads();  // seq_pass was read above by every thread; the token writes precede the -1s
+    a.tokens_state[row + my_pos] = tid < acc_len ? st.x[tid] : z;
+  __syncthreads();  // the token writes precede the -1s
   for (int i = tid; i < a.block; i += NT) {
     a.out_remask[row + i] = s_mask[i];
     if (a.pass_mask) a.pass_mask[row + i] = fire ? 0 : s_cand[i];
@@ -597,7 +611,7 @@ __device__ void finalize_sequence(const VerifyArgs& a, int b, const SeqState& st
   }
   if (tid == 0) {
     if (a.seq_pass) {
-      if (fire && remasked) a.seq_pass[b] += 1;
+      if (fire && remasked) a.seq_pass[b] = pass + 1;
       else if (!unresolved) a.seq_pass[b] = a.n_pass;  // final pass resolved, or nothing left to redo
     }
     if (a.seq_rounds && window > 0) a.seq_rounds[b] += 1;
@@ -605,117 +619,200 @@ __device__ void finalize_sequence(const VerifyArgs& a, int b, const SeqState& st
 }
 
 // ---------------------------------------------------------------------------------------------
-// Kernel 2: accept tests, first rejection, residual / overlap mass per chunk.
-// grid = (nslots, ceil(nRC / NW)); nslots = B (rejected slot only) or B*K (every slot).
+// Accept tests and first rejection of sequence b, by one whole wavefront; results in st (LDS).
+// ---------------------------------------------------------------------------------------------
+__device__ inline void accept_tests(const VerifyArgs& a, int b, SeqState& st) {
+  const int lane = threadIdx.x & 63;
+  const int BK = a.B * a.K;
+  // everything whose address is known up front is requested together (slots beyond the window
+  // hold x = -1 and are not used); only the two gathers at x~ wait for a previous load
+  const int window = a.window[b];
+  const int sl = b * a.K + min(lane, a.K - 1);
+  const int x = a.xdraft[sl], pos = a.slot_pos[sl];
+  const float lse_q = a.lse[sl], lse_p = a.lse[BK + sl];
+  const int xt = a.greedy ? a.xtarget[sl] : -1;
+  bool rejected = false;
+  if (lane < window) {
+    const float lq = a.logits[(size_t)sl * a.ldl + x] - lse_q;
+    const float lp = a.logits[(size_t)(BK + sl) * a.ldl + x] - lse_p;
+    const float ratio = fminf(1.f, expf(lp - lq));
+    const float u = philox_uniform(a.seed, a.pos_base + (uint32_t)pos, a.step,
+                                   a.seq_base + (uint32_t)b, kStreamAccept);
+    // greedy: the ratio of the two point masses is 1 if the arg maxes agree, else 0
+    rejected = a.greedy ? x != xt : !(u <= ratio);
+    st.x[lane] = x;
+    st.ptok[lane] = expf(lp);
+  }
+  const unsigned long long rej = __ballot(rejected);
+  const int acc = rej ? __ffsll((long long)rej) - 1 : window;
+  if (lane == 0) {
+    st.window = window;
+    st.acc_len = acc;
+  }
+  if (lane == acc && acc < window) {  // the rejected slot's own values, for the final phase
+    st.rej_lse_q = lse_q;
+    st.rej_lse_p = lse_p;
+    st.rej_pos = pos;
+    st.rej_xtarget = xt;
+  }
+}
+
+// Four logits of each of the two rows of a slot, from token v on (zero past V).
+struct Quad {
+  float q[4], p[4];
+};
+__device__ inline Quad load_quad(const VerifyArgs& a, const float* Lq, const float* Lp, int v) {
+  Quad r;
+  if (v + 3 < a.V) {
+    const float4 q4 = *reinterpret_cast<const float4*>(Lq + v);
+    const float4 p4 = *reinterpret_cast<const float4*>(Lp + v);
+    r.q[0] = q4.x; r.q[1] = q4.y; r.q[2] = q4.z; r.q[3] = q4.w;
+    r.p[0] = p4.x; r.p[1] = p4.y; r.p[2] = p4.z; r.p[3] = p4.w;
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      r.q[j] = v + j < a.V ? Lq[v + j] : 0.f;
+      r.p[j] = v + j < a.V ? Lp[v + j] : 0.f;
+    }
+  }
+  return r;
+}
+// Residual mass (and, if asked for, overlap mass) of a chunk whose four tokens from v on this lane holds.
+__device__ inline float chunk_mass(const VerifyArgs& a, const Quad& x, int v, float lse_q, float lse_p, float* overlap) {
+  float rs = 0.f, as = 0.f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (v + j < a.V) {
+      const float q = expf(x.q[j] - lse_q), p = expf(x.p[j] - lse_p);
+      rs += fmaxf(p - q, 0.f);
+      as += fminf(p, q);
+    }
+  }
+  if (overlap) *overlap = wave_sum(as);
+  return wave_sum(rs);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Kernel 2: accept tests, first rejection, residual mass per chunk of the rejected slot.
+// grid = (B, ceil(nRC / NW)).
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(NT) void accept_resid_kernel(VerifyArgs a) {
   __shared__ SeqState st;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int BK = a.B * a.K;
-  const int y = blockIdx.x;   // slot (all_slots) or sequence index
+  const int b = blockIdx.x;   // sequence
   const int cg = blockIdx.y;  // chunk group
-  const int b = a.all_slots ? y / a.K : y;
-  const int window = a.window[b];
-
-  if (wave == 0) {
-    // everything whose address is known up front is requested together (slots beyond the window
-    // hold x = -1 and are not used); only the two gathers at x~ wait for a previous load
-    const int sl = b * a.K + min(lane, a.K - 1);
-    const int x = a.xdraft[sl], pos = a.slot_pos[sl];
-    const float lse_q = a.lse[sl], lse_p = a.lse[BK + sl];
-    const int xt = a.greedy ? a.xtarget[sl] : -1;
-    bool rejected = false;
-    if (lane < window) {
-      const float lq = a.logits[(size_t)sl * a.ldl + x] - lse_q;
-      const float lp = a.logits[(size_t)(BK + sl) * a.ldl + x] - lse_p;
-      const float ratio = fminf(1.f, expf(lp - lq));
-      const float u = philox_uniform(a.seed, a.pos_base + (uint32_t)pos, a.step,
-                                     a.seq_base + (uint32_t)b, kStreamAccept);
-      // greedy: the ratio of the two point masses is 1 if the arg maxes agree, else 0
-      rejected = a.greedy ? x != xt : !(u <= ratio);
-      st.x[lane] = x;
-      st.ptok[lane] = expf(lp);
-    }
-    const unsigned long long rej = __ballot(rejected);
-    const int acc = rej ? __ffsll((long long)rej) - 1 : window;
-    if (lane == 0) {
-      st.window = window;
-      st.acc_len = acc;
-    }
-    if (lane == acc && acc < window) {  // the rejected slot's own values, for the final phase
-      st.rej_lse_q = lse_q;
-      st.rej_lse_p = lse_p;
-      st.rej_pos = pos;
-      st.rej_xtarget = xt;
-    }
-  }
+  if (wave == 0) accept_tests(a, b, st);
   __syncthreads();
-  if (cg == 0 && (!a.all_slots || y % a.K == 0) && tid < (int)(sizeof(SeqState) / 4))
+  if (cg == 0 && tid < (int)(sizeof(SeqState) / 4))
     reinterpret_cast<int*>(a.seqstate + b)[tid] = reinterpret_cast<const int*>(&st)[tid];
-  const int acc_len = st.acc_len;
-  const int m = a.all_slots ? y % a.K : acc_len;
   const int c = cg * NW + wave;
-  // chunk masses: not needed when nothing was rejected, for slots beyond the window, or in the
-  // greedy variant (the corrected token is the target arg max) unless diagnostics want them
-  if (m < window && c < a.nRC && (!a.greedy || a.all_slots)) {
-    const int s = b * a.K + m;
-    const float* Lq = a.logits + (size_t)s * a.ldl;
-    const float* Lp = a.logits + (size_t)(BK + s) * a.ldl;
-    const float lse_q = a.lse[s], lse_p = a.lse[BK + s];
+  // not needed when nothing was rejected, or in the greedy variant (the corrected token is the target arg max)
+  if (st.acc_len < st.window && c < a.nRC && !a.greedy) {
+    const size_t s = (size_t)b * a.K + st.acc_len;
     const int v = c * kResidChunk + lane * 4;
-    float qv[4] = {0.f, 0.f, 0.f, 0.f}, pv[4] = {0.f, 0.f, 0.f, 0.f};
-    if (v + 3 < a.V) {
-      const float4 q4 = *reinterpret_cast<const float4*>(Lq + v);
-      const float4 p4 = *reinterpret_cast<const float4*>(Lp + v);
-      qv[0] = q4.x; qv[1] = q4.y; qv[2] = q4.z; qv[3] = q4.w;
-      pv[0] = p4.x; pv[1] = p4.y; pv[2] = p4.z; pv[3] = p4.w;
-    } else {
-      for (int j = 0; j < 4; ++j)
-        if (v + j < a.V) { qv[j] = Lq[v + j]; pv[j] = Lp[v + j]; }
-    }
-    float rs = 0.f, as = 0.f;
+    const Quad x = load_quad(a, a.logits + s * a.ldl, a.logits + (s + (size_t)a.B * a.K) * a.ldl, v);
+    const float rs = chunk_mass(a, x, v, st.rej_lse_q, st.rej_lse_p, nullptr);
+    if (lane == 0) a.rmass[(size_t)b * a.nRC + c] = rs;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Kernel 2 of a call that wants the masses of every slot: residual and overlap mass per chunk.
+// grid = (B*K, ceil(nRC / (NW * kMassPer))); a wavefront takes kMassPer neighbouring chunks and asks
+// for all of them before it uses the first.  Bound: the two passes' worth of exponentials and one read of all logits
+// (1.04 GB at 64 x 16 slots, V = 126464).  Which slot was rejected does not matter here, so nothing waits for the
+// accept tests (the final kernel does them); with them repeated in front of every chunk this took 260 us, now
+// 185 (5.6 TB/s).
+// ---------------------------------------------------------------------------------------------
+constexpr int kMassPer = 4;
+__global__ __launch_bounds__(NT) void slot_mass_kernel(VerifyArgs a) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int s = blockIdx.x, BK = a.B * a.K;
+  const int c0 = (blockIdx.y * NW + wave) * kMassPer;
+  if (c0 >= a.nRC) return;
+  const float* Lq = a.logits + (size_t)s * a.ldl;
+  const float* Lp = a.logits + (size_t)(BK + s) * a.ldl;
+  const int window = a.window[s / a.K];
+  const float lse_q = a.lse[s], lse_p = a.lse[BK + s];
+  Quad x[kMassPer];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (v + j < a.V) {
-        const float q = expf(qv[j] - lse_q), p = expf(pv[j] - lse_p);
-        rs += fmaxf(p - q, 0.f);
-        as += fminf(p, q);
-      }
-    }
-    rs = wave_sum(rs);
-    if (a.all_slots) as = wave_sum(as);
+  for (int j = 0; j < kMassPer; ++j) x[j] = load_quad(a, Lq, Lp, (c0 + j) * kResidChunk + lane * 4);
+  if (s % a.K >= window) return;
+#pragma unroll
+  for (int j = 0; j < kMassPer; ++j) {
+    if (c0 + j >= a.nRC) break;
+    float as;
+    const float rs = chunk_mass(a, x[j], (c0 + j) * kResidChunk + lane * 4, lse_q, lse_p, &as);
     if (lane == 0) {
-      a.rmass[(size_t)y * a.nRC + c] = rs;
-      if (a.all_slots) a.amass[(size_t)y * a.nRC + c] = as;
+      a.rmass[(size_t)s * a.nRC + c0 + j] = rs;
+      a.amass[(size_t)s * a.nRC + c0 + j] = as;
     }
   }
-
 }
 
 // ---------------------------------------------------------------------------------------------
 // Kernel 3: residual sample, commit, mask update, LowConf.  One workgroup per sequence.
+//   kHandoff  the accept tests and the chunk masses come from kernel 2
+//   kSlots    the chunk masses of every slot come from kernel 2, the accept tests are done here
+//   kAlone    both are done here: a vocabulary of at most kAloneChunks chunks is not worth a launch
+//             of its own (tiny vocabulary, 1 sequence: 2.6 + 5.2 us in two kernels, 5.5 in one)
 // ---------------------------------------------------------------------------------------------
+enum FinalMode { kHandoff, kSlots, kAlone };
+constexpr int kAloneChunks = 16;
+
+template <FinalMode MODE>
 __global__ __launch_bounds__(NT) void finalize_kernel(VerifyArgs a) {
   __shared__ BlockTmp tmp;
   __shared__ SeqState st;
   __shared__ float s_conf[kMaxBlock];
   __shared__ uint8_t s_mask[kMaxBlock], s_cand[kMaxBlock];
-  const int b = blockIdx.x, tid = threadIdx.x;
+  __shared__ float s_mass[MODE == kAlone ? kAloneChunks : 1];
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   int word = 0;
-  if (tid < (int)(sizeof(SeqState) / 4)) word = reinterpret_cast<const int*>(a.seqstate + b)[tid];
+  if (MODE == kHandoff && tid < (int)(sizeof(SeqState) / 4)) word = reinterpret_cast<const int*>(a.seqstate + b)[tid];
   // Without the diagnostics the chunk masses of a sequence sit at an address that does not depend
   // on which slot was rejected: wavefront 0 asks for them in the same breath as the accept-phase
-  // results (when nothing was rejected they are stale and unused).
+  // results (when nothing was rejected they are stale and unused).  So does everybody for the block state.
   float rm_pre[kChunkPer];
-  const bool have_pre = !a.all_slots && !a.greedy && a.nRC <= kWave * kChunkPer;
+  const bool have_pre = MODE == kAlone || (MODE == kHandoff && !a.greedy && a.nRC <= kWave * kChunkPer);
 #pragma unroll
   for (int j = 0; j < kChunkPer; ++j) {
     const int c = tid * kChunkPer + j;
-    rm_pre[j] = (have_pre && tid < kWave && c < a.nRC) ? a.rmass[(size_t)b * a.nRC + c] : 0.f;
+    rm_pre[j] = (MODE == kHandoff && have_pre && tid < kWave && c < a.nRC) ? a.rmass[(size_t)b * a.nRC + c] : 0.f;
   }
-  if (tid < (int)(sizeof(SeqState) / 4)) reinterpret_cast<int*>(&st)[tid] = word;
+  const int my_pos = tid < a.K ? a.slot_pos[b * a.K + tid] : 0;
+  const int pass = a.seq_pass ? a.seq_pass[b] : 0;
+  const size_t row = (size_t)b * a.block;
+  for (int i = tid; i < a.block; i += NT) {
+    const uint8_t mask = a.mask_in ? (a.mask_in[row + i] != 0) : 1;
+    const uint8_t cand = a.pass_mask ? (a.pass_mask[row + i] != 0) : 0;
+    const float conf = a.conf ? a.conf[row + i] : 0.f;
+    s_mask[i] = mask;
+    s_cand[i] = cand;
+    s_conf[i] = conf;
+  }
+  if (MODE == kHandoff) {
+    if (tid < (int)(sizeof(SeqState) / 4)) reinterpret_cast<int*>(&st)[tid] = word;
+  } else if (tid < kWave) {
+    accept_tests(a, b, st);
+  }
   __syncthreads();
-  finalize_sequence(a, b, st, tmp, s_conf, s_mask, s_cand, rm_pre, have_pre);
+  if (MODE == kAlone && st.acc_len < st.window && !a.greedy) {
+    const size_t s = (size_t)b * a.K + st.acc_len;
+    for (int c = tid >> 6; c < a.nRC; c += NW) {
+      const int v = c * kResidChunk + lane * 4;
+      const Quad x = load_quad(a, a.logits + s * a.ldl, a.logits + (s + (size_t)a.B * a.K) * a.ldl, v);
+      const float rs = chunk_mass(a, x, v, st.rej_lse_q, st.rej_lse_p, nullptr);
+      if (lane == 0) s_mass[c] = rs;
+    }
+    __syncthreads();  // uniform: st is the workgroup's
+#pragma unroll
+    for (int j = 0; j < kChunkPer; ++j) {
+      const int c = tid * kChunkPer + j;
+      if (c < a.nRC) rm_pre[j] = s_mass[c];
+    }
+  }
+  finalize_sequence(a, b, st, tmp, s_conf, s_mask, s_cand, rm_pre, have_pre, my_pos, pass);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -778,10 +875,16 @@ hipError_t launch_verify(const VerifyArgs& a) {
   if (a.phase == 3) {
     hipLaunchKernelGGL(topn_kernel, dim3(a.B), dim3(kWave), 0, a.stream, a);
   } else if (a.phase != 1) {  // everything after the draft sample needs the target laws
-    const int gx = (a.nRC + NW - 1) / NW;
-    const int nslots = a.all_slots ? a.B * a.K : a.B;
-    hipLaunchKernelGGL(accept_resid_kernel, dim3(nslots, gx), dim3(NT), 0, a.stream, a);
-    hipLaunchKernelGGL(finalize_kernel, dim3(a.B), dim3(NT), 0, a.stream, a);
+    if (a.all_slots) {
+      hipLaunchKernelGGL(slot_mass_kernel, dim3(a.B * a.K, (a.nRC + NW * kMassPer - 1) / (NW * kMassPer)), dim3(NT), 0,
+                         a.stream, a);
+      hipLaunchKernelGGL(finalize_kernel<kSlots>, dim3(a.B), dim3(NT), 0, a.stream, a);
+    } else if (a.nRC <= kAloneChunks) {
+      hipLaunchKernelGGL(finalize_kernel<kAlone>, dim3(a.B), dim3(NT), 0, a.stream, a);
+    } else {
+      hipLaunchKernelGGL(accept_resid_kernel, dim3(a.B, (a.nRC + NW - 1) / NW), dim3(NT), 0, a.stream, a);
+      hipLaunchKernelGGL(finalize_kernel<kHandoff>, dim3(a.B), dim3(NT), 0, a.stream, a);
+    }
   }
   if (a.diag_logits) {
     const long rows = a.nrows;
