@@ -259,6 +259,10 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
     constexpr int KS = decltype(ks_tag)::value;
     constexpr bool MUL = decltype(mul_tag)::value, FULL = decltype(full)::value;
     constexpr int TOTAL = NT * NR, LOADS = KS == 0 ? LH : LW;
+    // Eight wavefronts: the multiply behind which the group of loads goes out.  At once where the lead of a k-step is
+    // short for the load latency (many rows: 237 -> 224 us at M = 256, 207 -> 201 at 192; narrow shares: 216 -> 211 at 128
+    // rows of d = 3584, V = 151936); in mid-phase where the pass over W is all it costs (128 rows: 187 against 191 us).
+    constexpr int kLoadAt = SHARES || NR >= 5 ? 1 : TOTAL / 2 + (NR > 1 ? 2 : 0);
     bf16x8(&wr)[NT] = wf[KS];
     bf16x8(&wm_)[NT] = wf[KS ^ 1];
     bf16x8(&hr)[NR] = hf[ROLL ? 0 : KS];
@@ -292,7 +296,7 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
           read_h(n);
           __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (m == TOTAL / 2 + (NR > 1 ? 2 : 0)) {
+        if constexpr (m == kLoadAt) {
           if (more) {
             if constexpr (KS == 0) group(gh, slotH + stage * kBytesH, h_left);
             else group(gw, slotW + stage * kBytesW, w_left);
