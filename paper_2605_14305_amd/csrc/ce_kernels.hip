@@ -12,12 +12,6 @@ namespace {
 
 constexpr int NT = 256, NW = NT / kWave;
 
-// label logits start as NaN, so that a label no head kernel meets (>= V) shows in the result
-__global__ __launch_bounds__(NT) void ce_init_kernel(float* label_logit, int R) {
-  const int r = blockIdx.x * NT + threadIdx.x;
-  if (r < R) label_logit[r] = __builtin_nanf("");
-}
-
 // one wavefront per row
 __global__ __launch_bounds__(NT) void ce_row_kernel(CeArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -50,7 +44,8 @@ __global__ __launch_bounds__(NT) void ce_row_kernel(CeArgs a) {
     sm = sm > 0.f ? sm * expf(mx - wmx) : 0.f;
     mx = wmx;
     sm = wave_sum(sm);
-    ce = mx + logf(sm) - a.label_logit[r];
+    // a label past the vocabulary is met by no head kernel: its logit was never written
+    ce = lab < a.V ? mx + logf(sm) - a.label_logit[r] : __builtin_nanf("");
   }
   if (lane == 0) a.out_ce[r] = ce;
 }
@@ -71,11 +66,6 @@ __global__ __launch_bounds__(NT) void ce_sum_kernel(CeArgs a) {
 }
 
 }  // namespace
-
-hipError_t launch_ce_init(float* label_logit, int R, hipStream_t stream) {
-  hipLaunchKernelGGL(ce_init_kernel, dim3((R + NT - 1) / NT), dim3(NT), 0, stream, label_logit, R);
-  return hipGetLastError();
-}
 
 hipError_t launch_ce_finish(const CeArgs& a) {
   hipLaunchKernelGGL(ce_row_kernel, dim3((a.R + NW - 1) / NW), dim3(NT), 0, a.stream, a);

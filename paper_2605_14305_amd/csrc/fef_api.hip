@@ -481,8 +481,7 @@ fef_status fef_head_cross_entropy(const fef_params* prm, const void* h, const vo
   a.label_logit = (float*)(ws + align_up((size_t)R * (size_t)nT * sizeof(float2), 256));
   a.stream = (hipStream_t)prm->stream;
   a.ev_begin = (hipEvent_t)prm->ev_head_begin; a.ev_end = (hipEvent_t)prm->ev_head_end;
-  hipError_t e = fef::launch_ce_init(a.label_logit, R, a.stream);
-  if (e != hipSuccess) return fail(FEF_ERR_HIP, "cross-entropy kernel launch: %s", hipGetErrorString(e));
+  hipError_t e;
   switch (variant) {
     case FEF_GEMM_TILED256:
     case FEF_GEMM_STREAM: e = fef::launch_head_tiled256(a); break;
@@ -490,7 +489,7 @@ fef_status fef_head_cross_entropy(const fef_params* prm, const void* h, const vo
   }
   if (e != hipSuccess) return fail(FEF_ERR_HIP, "head kernel launch: %s", hipGetErrorString(e));
   fef::CeArgs c{};
-  c.R = R; c.nT = nT; c.partials = a.partials; c.labels = labels; c.label_logit = a.label_logit;
+  c.R = R; c.V = prm->V; c.nT = nT; c.partials = a.partials; c.labels = labels; c.label_logit = a.label_logit;
   c.out_ce = out_ce; c.out_loss = out_loss; c.stream = a.stream;
   e = fef::launch_ce_finish(c);
   if (e != hipSuccess) return fail(FEF_ERR_HIP, "cross-entropy kernel launch: %s", hipGetErrorString(e));

@@ -138,7 +138,7 @@ hipError_t launch_verify(const VerifyArgs& a);
 // Cross-entropy finish: per-row log-sum-exp from the partials, ce = lse - label logit, then the
 // sum over rows in a fixed order.
 struct CeArgs {
-  int R, nT;
+  int R, V, nT;
   const float2* partials;   // [R, nT]
   const int32_t* labels;    // [R]
   const float* label_logit; // [R]
@@ -146,7 +146,6 @@ struct CeArgs {
   float* out_loss;          // [1]
   hipStream_t stream;
 };
-hipError_t launch_ce_init(float* label_logit, int R, hipStream_t stream);
 hipError_t launch_ce_finish(const CeArgs& a);
 
 }  // namespace fef

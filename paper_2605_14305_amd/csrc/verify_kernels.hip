@@ -821,31 +821,34 @@ __global__ __launch_bounds__(NT) void finalize_kernel(VerifyArgs a) {
 // the n most confident slots (equal confidences: the lower position first).
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kWave) void topn_kernel(VerifyArgs a) {
+  // everything whose address is known up front is requested together; only the gather at x waits for a load
   const int b = blockIdx.x, lane = threadIdx.x;
+  const int s = b * a.K + lane, sl = b * a.K + min(lane, a.K - 1);
   const int window = a.window[b];
-  const int s = b * a.K + lane;
+  int x = a.xdraft[sl], pos = a.slot_pos[sl];
+  const float lse = a.lse[sl];
+  const size_t row = (size_t)b * a.block;
+  for (int i = lane; i < a.block; i += kWave) a.out_remask[row + i] = a.mask_in ? (a.mask_in[row + i] != 0) : 1;
   const bool live = lane < window;
-  int x = -1, pos = INT_MAX;
   float c = -1.f;
   if (live) {
-    x = a.xdraft[s];
-    pos = a.slot_pos[s];
-    c = expf(a.logits[(size_t)s * a.ldl + x] - a.lse[s]);
+    c = expf(a.logits[(size_t)s * a.ldl + x] - lse);
+  } else {
+    x = -1;
+    pos = INT_MAX;
   }
   int rank = 0;
-  for (int j = 0; j < window; ++j) {
-    const float cj = __shfl(c, j, 64);
-    const int pj = __shfl(pos, j, 64);
+  for (int j = 0; j < window; ++j) {  // j is the same in every lane: v_readlane, no trip through the LDS crossbar
+    const float cj = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, c), j));
+    const int pj = __builtin_amdgcn_readlane(pos, j);
     rank += (cj > c || (cj == c && pj < pos)) ? 1 : 0;
   }
   const bool commit = live && rank < a.n_transfer;
-  const size_t row = (size_t)b * a.block;
   if (lane < a.K) {
     a.out_tokens[s] = commit ? x : -1;
     if (a.diag_conf_tok) a.diag_conf_tok[s] = live ? c : 0.f;
   }
   if (lane == 0) a.out_accept_len[b] = min(a.n_transfer, window);
-  for (int i = lane; i < a.block; i += kWave) a.out_remask[row + i] = a.mask_in ? (a.mask_in[row + i] != 0) : 1;
   __syncthreads();  // one wavefront: orders the mask copy before the committed positions are cleared
   if (commit) {
     a.out_remask[row + pos] = 0;
