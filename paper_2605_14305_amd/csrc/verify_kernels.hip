@@ -22,6 +22,8 @@
 #include <limits.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include "fef_device.hpp"
 #include "wave_ops.hpp"
 
@@ -34,7 +36,7 @@ constexpr int NW = NT / kWave;   // wavefronts per workgroup
 struct BlockTmp {
   float f[NW];
   int i[NW];
-  float bcast_f;
+  float bcast_f, bcast_u;
   int bcast_i;
 };
 
@@ -259,7 +261,7 @@ __device__ inline int row_argmax(const VerifyArgs& a, const float2* P, const flo
 }
 
 constexpr int kChunkPer = 16;  // residual chunks per lane in the one-wavefront final phase
-constexpr int kTilePer = 10;  // tokens per lane inside one partial tile: tiles of up to 640 tokens (a 151936-token
+constexpr int kTilePer = 10;  // tokens per lane inside one partial tile: 4 up to 256 tokens, 10 up to 640 (a 151936-token
                               // vocabulary over 256 workgroups: 576 to 640 tokens each), longer ones are re-read
 
 // ---------------------------------------------------------------------------------------------
@@ -282,12 +284,20 @@ __global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
   // log-sum-exp of the row from the head kernel's per-tile partials; the window slot and a given draft token are asked
   // for in the same breath (each trip to memory that waits for another costs about 1 us)
   int pos = -1, window = 0, given = -1;
+  float u = 0.f;  // the slot's draft uniform
   auto window_and_token = [&]() {
     if (!is_draft) return;
     int unresolved;
     if (a.draft_tokens_in) given = a.draft_tokens_in[s];
+    // The generator's ten rounds are a chain of about 0.4 us.  In a block of up to 64 positions every lane draws for one
+    // position while the mask is on its way, and the slot's position picks the lane.
+    float u_lane = 0.f;
+    if (a.block <= kWave)
+      u_lane = philox_uniform(a.seed, a.pos_base + (uint32_t)lane, a.step, a.seq_base + (uint32_t)b, kStreamDraft);
     pos = window_slot(a, b, m, unresolved);
     window = min(a.K, unresolved);
+    u = a.block <= kWave ? __shfl(u_lane, max(pos, 0), kWave)
+                         : philox_uniform(a.seed, a.pos_base + (uint32_t)pos, a.step, a.seq_base + (uint32_t)b, kStreamDraft);
   };
   float mass[PER > 0 ? PER : 1];  // exp-sums of this lane's tiles relative to the row maximum
   float mx = -INFINITY, sm = 0.f;
@@ -359,8 +369,6 @@ __global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
       x = row_argmax(a, P, a.logits + (size_t)r * a.ldl, mx);  // point mass of the draft law
     } else {
       // x~ = min{v : sum_{w<=v} rho_w >= u}: first over vocabulary tiles, then inside the tile
-      const float u = philox_uniform(a.seed, a.pos_base + (uint32_t)pos, a.step,
-                                     a.seq_base + (uint32_t)b, kStreamDraft);
       Found tile;
       if constexpr (PER > 0) {
         const float inv = 1.f / sm;  // tile probability = exp-sum / row exp-sum
@@ -375,14 +383,20 @@ __global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
       const int v0 = tile_start(a, tile.idx);
       const int nv = min(tile_start(a, tile.idx + 1), a.V) - v0;
       Found in;
-      if (nv <= kWave * kTilePer) {
-        float q[kTilePer];
+      auto in_registers = [&](auto per) {
+        constexpr int N = decltype(per)::value;
+        float q[N];
 #pragma unroll
-        for (int j = 0; j < kTilePer; ++j) {
-          const int i = lane * kTilePer + j;
+        for (int j = 0; j < N; ++j) {
+          const int i = lane * N + j;
           q[j] = i < nv ? expf(L[v0 + i] - lse) : 0.f;
         }
         in = wave_find_first_reg(q, u - tile.before);
+      };
+      if (nv <= kWave * 4) {
+        in_registers(std::integral_constant<int, 4>{});
+      } else if (nv <= kWave * kTilePer) {
+        in_registers(std::integral_constant<int, kTilePer>{});
       } else {
         in = wave_find_first(nv, [&](int i) { return expf(L[v0 + i] - lse); }, u - tile.before);
       }
@@ -402,10 +416,11 @@ __global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
 
 // rm_pre: (wavefront 0 only) the residual chunk masses of this sequence, 16 per lane, loaded by the
 // caller before the accept-phase results were known; valid if have_pre.  s_conf, s_mask, s_cand: the
-// block state before the round, my_pos: slot_pos of slot tid, pass: seq_pass of the sequence, likewise.
+// block state before the round, my_pos: slot_pos of slot tid, pass: seq_pass of the sequence, likewise;
+// my_u: the residual uniform of slot tid (threads below K).
 __device__ void finalize_sequence(const VerifyArgs& a, int b, const SeqState& st, BlockTmp& tmp,
                                   float* s_conf, uint8_t* s_mask, uint8_t* s_cand, const float (&rm_pre)[16],
-                                  bool have_pre, int my_pos, int pass) {
+                                  bool have_pre, int my_pos, int pass, float my_u) {
   const int tid = threadIdx.x;
   const int BK = a.B * a.K;
   const int window = st.window, acc_len = st.acc_len;
@@ -451,8 +466,9 @@ __device__ void finalize_sequence(const VerifyArgs& a, int b, const SeqState& st
     // results, so nothing here waits for a load whose address depends on acc_len except the logits
     const float lse_q = st.rej_lse_q, lse_p = st.rej_lse_p;
     const float* rm = a.rmass + (size_t)(a.all_slots ? s : b) * a.nRC;
-    const float u = philox_uniform(a.seed, a.pos_base + (uint32_t)st.rej_pos, a.step,
-                                   a.seq_base + (uint32_t)b, kStreamResidual);
+    if (tid == acc_len) tmp.bcast_u = my_u;
+    __syncthreads();
+    const float u = tmp.bcast_u;
     if (a.greedy) {
       z = st.rej_xtarget;  // residual of two point masses: the target's
       z_conf = expf(Lp[z] - lse_p);
@@ -755,7 +771,8 @@ __global__ __launch_bounds__(NT) void slot_mass_kernel(VerifyArgs a) {
 //   kHandoff  the accept tests and the chunk masses come from kernel 2
 //   kSlots    the chunk masses of every slot come from kernel 2, the accept tests are done here
 //   kAlone    both are done here: a vocabulary of at most kAloneChunks chunks is not worth a launch
-//             of its own (tiny vocabulary, 1 sequence: 2.6 + 5.2 us in two kernels, 5.5 in one)
+//             of its own (tiny vocabulary, 1 sequence: 2.6 + 5.2 us in two kernels, 5.5 in one), and
+//             the greedy variant needs no masses at all
 // ---------------------------------------------------------------------------------------------
 enum FinalMode { kHandoff, kSlots, kAlone };
 constexpr int kAloneChunks = 16;
@@ -791,6 +808,10 @@ __global__ __launch_bounds__(NT) void finalize_kernel(VerifyArgs a) {
     s_cand[i] = cand;
     s_conf[i] = conf;
   }
+  // drawn for every slot while the loads above are on their way
+  const float my_u = tid < kWave ? philox_uniform(a.seed, a.pos_base + (uint32_t)my_pos, a.step, a.seq_base + (uint32_t)b,
+                                                  kStreamResidual)
+                                 : 0.f;
   if (MODE == kHandoff) {
     if (tid < (int)(sizeof(SeqState) / 4)) reinterpret_cast<int*>(&st)[tid] = word;
   } else if (tid < kWave) {
@@ -812,7 +833,7 @@ __global__ __launch_bounds__(NT) void finalize_kernel(VerifyArgs a) {
       if (c < a.nRC) rm_pre[j] = s_mass[c];
     }
   }
-  finalize_sequence(a, b, st, tmp, s_conf, s_mask, s_cand, rm_pre, have_pre, my_pos, pass);
+  finalize_sequence(a, b, st, tmp, s_conf, s_mask, s_cand, rm_pre, have_pre, my_pos, pass, my_u);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -882,7 +903,7 @@ hipError_t launch_verify(const VerifyArgs& a) {
       hipLaunchKernelGGL(slot_mass_kernel, dim3(a.B * a.K, (a.nRC + NW * kMassPer - 1) / (NW * kMassPer)), dim3(NT), 0,
                          a.stream, a);
       hipLaunchKernelGGL(finalize_kernel<kSlots>, dim3(a.B), dim3(NT), 0, a.stream, a);
-    } else if (a.nRC <= kAloneChunks) {
+    } else if (a.nRC <= kAloneChunks || a.greedy) {
       hipLaunchKernelGGL(finalize_kernel<kAlone>, dim3(a.B), dim3(NT), 0, a.stream, a);
     } else {
       hipLaunchKernelGGL(accept_resid_kernel, dim3(a.B, (a.nRC + NW - 1) / NW), dim3(NT), 0, a.stream, a);
