@@ -3,8 +3,8 @@
 //
 // Workgroup tile 32 NR rows of H (NR = 1 to 8) x up to 256 tokens, k-steps of 64, v_mfma_f32_16x16x32_bf16 with the W tile
 // as the A operand and H as the B operand.  Two forms:
-//   WN = 2  four wavefronts in a 2 x 2 grid (rows x tokens), each 16 NR rows x 128 tokens: M > 256
-//   WN = 4  eight wavefronts in a 2 x 4 grid, each 16 NR rows x 64 tokens: M <= 256, one row tile
+//   WN = 2  four wavefronts in a 2 x 2 grid (rows x tokens), each 16 NR rows x 128 tokens: M > 256, d >= 1024
+//   WN = 4  eight wavefronts in a 2 x 4 grid, each 16 NR rows x 64 tokens: M <= 256, and M > 256 with small d
 //
 // What bounds it, and what follows.
 // (1) Power.  With every matrix unit busy on real data the chip lowers its clock, so energy per multiply is time.  A
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
   constexpr int NT = 16 / WN;                        // 16-token tiles per wavefront
   constexpr int BM = 32 * NR, WROWS = 16 * NR;       // rows of the workgroup tile, of a wavefront
   constexpr int LW = 16 / WN, LH = (2 * NR + WN - 1) / WN;  // load instructions per wavefront and stage (8 rows each)
-  constexpr bool ONE = WN == 4;                      // one row tile, two wavefronts per SIMD
+  constexpr bool ONE = WN == 4;                      // two wavefronts per SIMD; as a rule one row tile
   constexpr bool ROLL = ONE;                         // H fragments in one set of registers, each re-read behind its last use
   constexpr int kStageH = BM * 8;                    // 16-byte chunks per H stage
   // Stages in LDS.  Narrow shares make short k-steps, so H is requested two steps ahead there like W, where 160 KB allow
@@ -144,8 +144,8 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
   const int n_end = min(a.V, SHARES ? (int)((long)(nt + 1) * n_units / a.nT) * kUnit : n0 + BN);
 
   // Every row of W starts at a multiple of 2 d bytes, so workgroups that walk k from 0 in step ask HBM for the
-  // same low address bits at the same moment: with one row tile each token tile starts its walk at another k-step and
-  // wraps (with several row tiles per token tile, which share H in time through L2, that measured 2 % slower).
+  // same low address bits at the same moment: with eight wavefronts each token tile starts its walk at another k-step and
+  // wraps (with four and several row tiles per token tile, which share H in time through L2, that measured 2 % slower).
   const int k0 = ONE ? (int)((unsigned)(nt * 37) % (unsigned)nk) : 0;
   int h_left = nk - k0, w_left = nk - k0;  // steps until the walk is back at k = 0
 
@@ -531,10 +531,21 @@ int tiled256_tiles(int V, int M) {
 }
 
 // ceil(M / 256) row tiles of equal height (a multiple of 32).  One row tile: eight wavefronts (two per SIMD: the kernel
-// is short of memory parallelism there, not of LDS rate).  Several: four wavefronts, 160 to 256 rows.
+// is short of memory parallelism there, not of LDS rate).  Several: four wavefronts, 160 to 256 rows; but eight where the
+// walk over k is so short that prologue and epilogue, which two wavefronts per SIMD overlap better, are what a tile costs:
+// 49.8 -> 46.0 us at 512 rows of d = 512, V = 50257, 95 -> 90 at 1024 rows; even at d = 1024 (68 -> 66 at 512 rows of
+// V = 50257, 271 -> 274 at 1024 of V = 126464), 4 % behind at d = 4096.
 hipError_t launch_head_tiled256(const HeadArgs& a) {
   const int m_tiles = (a.nrows + 255) / 256;
   const int nr = ((a.nrows + m_tiles - 1) / m_tiles + 31) / 32;
+  if (m_tiles > 1 && a.d < 1024) {
+    switch (nr) {
+      case 5: return launch_tiles<5, 4, false>(a, m_tiles);
+      case 6: return launch_tiles<6, 4, false>(a, m_tiles);
+      case 7: return launch_tiles<7, 4, false>(a, m_tiles);
+      default: return launch_tiles<8, 4, false>(a, m_tiles);
+    }
+  }
   if (m_tiles > 1) {
     switch (nr) {
       case 5: return launch_tiles<5, 2, false>(a, m_tiles);

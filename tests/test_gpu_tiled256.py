@@ -19,7 +19,8 @@ def _bound(h, W, d, tau):
     (1, 8, 64, 255), (1, 16, 320, 257), (17, 1, 64, 300), (8, 4, 128, 511), (3, 11, 192, 256), (6, 8, 64, 1000),
     (7, 7, 256, 513), (8, 8, 320, 255), (13, 5, 128, 257), (5, 16, 64, 700), (9, 9, 128, 258), (14, 8, 192, 260), (96, 1, 192, 256), (97, 1, 256, 513), (8, 16, 320, 300), (43, 3, 64, 511),
     (10, 16, 128, 259), (23, 7, 192, 64), (48, 4, 256, 1024), (193, 1, 64, 270), (15, 15, 128, 258), (16, 16, 192, 769),
-    (257, 1, 64, 33), (32, 12, 128, 900),
+    (257, 1, 64, 33), (32, 12, 128, 900), (43, 3, 1024, 511), (23, 7, 1088, 264), (193, 1, 1024, 300), (15, 15, 1152, 258),
+    (16, 16, 960, 257), (17, 16, 1024, 256), (32, 12, 1088, 513),
 ])
 def test_logits_and_lse(B, K, d, V):
     g = torch.Generator().manual_seed(B * 100 + K)
@@ -39,7 +40,7 @@ def test_logits_and_lse(B, K, d, V):
 
 
 @pytest.mark.parametrize("R,d,V", [(129, 64, 257), (193, 128, 255), (257, 64, 300), (320, 192, 512), (321, 64, 600),
-                                   (385, 128, 256), (449, 64, 1000), (513, 320, 31), (769, 64, 258)])
+                                   (385, 128, 256), (449, 64, 1000), (513, 320, 31), (769, 64, 258), (300, 1024, 259), (321, 1088, 300), (449, 1024, 513), (513, 1152, 255)])
 def test_cross_entropy(R, d, V):
     g = torch.Generator().manual_seed(R)
     W, h = (torch.randn(V, d, generator=g) * 0.1).bfloat16(), torch.randn(R, d, generator=g).bfloat16()
