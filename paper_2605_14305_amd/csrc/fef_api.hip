@@ -104,11 +104,11 @@ fef_status select_variant(const fef_params* p, int32_t K, int* variant) {
       break;
     case FEF_GEMM_STREAM:
       if (p->dtype != FEF_BF16 || !stream_supports(M, p->d))
-        return fail(FEF_ERR_UNSUPPORTED, "streaming head kernel needs bf16 and at most 128 rows through the head");
+        return fail(FEF_ERR_UNSUPPORTED, "the STREAM variant needs bf16 and at most 128 rows through the head");
       break;
     case FEF_GEMM_ROWSTREAM:
       if (p->dtype != FEF_BF16 || !rowstream_supports(M, p->d))
-        return fail(FEF_ERR_UNSUPPORTED, "row-streaming head kernel needs bf16, at most 128 rows through the head and d a multiple of 512");
+        return fail(FEF_ERR_UNSUPPORTED, "the ROWSTREAM variant needs bf16, at most 128 rows through the head and d a multiple of 512");
       break;
     case FEF_GEMM_F32:
       if (p->dtype != FEF_F32) return fail(FEF_ERR_UNSUPPORTED, "f32 head kernel needs dtype f32");
@@ -431,7 +431,7 @@ fef_status ce_check(const fef_params* p, int32_t R, int* variant, int* nT, size_
       break;
     case FEF_GEMM_STREAM:
       if (p->dtype != FEF_BF16 || !stream_supports(R, p->d))
-        return fail(FEF_ERR_UNSUPPORTED, "streaming head kernel needs bf16 and at most 128 rows");
+        return fail(FEF_ERR_UNSUPPORTED, "the STREAM variant needs bf16 and at most 128 rows");
       break;
     case FEF_GEMM_TILED256:
       if (p->dtype != FEF_BF16) return fail(FEF_ERR_UNSUPPORTED, "tiled head kernels are bf16 only");

@@ -488,14 +488,14 @@ __global__ __launch_bounds__(kTiledThreads) void head_tiled_kernel(HeadArgs a, i
 // Bound: the one pass over W (HBM), or the fp32 matrix rate once there are some tens of rows.
 // W and H go through LDS so that global reads are whole rows of 256 contiguous bytes and every W
 // element is fetched once per MR rows (the form before, one wavefront per row with a W row per lane,
-// fetched W once per row in 4-byte pieces 4 d bytes apart: 5500 us against 31 us at
+// fetched W once per row in 4-byte pieces 4 d bytes apart: 5500 us against 32 us at
 // 32 rows, d = 1024, V = 32000).  The next step's data waits in registers while the current one
 // is multiplied, two LDS buffers, one barrier per step.
 //
 // Operand layout of the 16x16x4 multiply (lane l, i = l % 16, g = l / 16): A[i][g], B[g][i], one
-// float each.  Which k a lane's element stands for is free as long as A and B agree, so a lane
-// reads four consecutive k (16 s + 4 g ..) as one 16-byte LDS read per operand and feeds them to four
-// multiplies.  A = W, B = H: D[4 g + r][i] puts four consecutive tokens of one row in a lane.
+// float each.  The sums run over k in ascending order, one rounding per product like a chain of FMAs: multiply q of a
+// group of 16 columns takes k = 16 s + 4 q + g from lane group g, and LDS rows hold those four columns (q = 0..3) next
+// to one another, so that a lane reads them as one 16-byte LDS read per operand for four multiplies.  A = W, B = H: D[4 g + r][i] puts four consecutive tokens of one row in a lane.
 // LDS rows are padded to 68 floats: the 16 rows of a 16-byte read fall on 64 different banks.
 //
 // VEC = 4: d is a multiple of 4, rows are 16-byte aligned and read as float4; VEC = 1: any d.
@@ -511,7 +511,7 @@ __global__ __launch_bounds__(256) void head_f32_kernel(HeadArgs a, int m_tiles, 
   constexpr int PW = kF32Tokens / RPP, PH = MR / RPP;
   __shared__ __attribute__((aligned(16))) float Ws[2][kF32Tokens * kF32Ld];
   __shared__ __attribute__((aligned(16))) float Hs[2][MR * kF32Ld];
-  __shared__ float2 part[MR][4];
+  __shared__ float tile_max[MR][4];
   typedef float vecf __attribute__((ext_vector_type(VEC == 1 ? 2 : VEC)));  // VEC == 1 uses element 0 only
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int i16 = lane & 15, g = lane >> 4;
@@ -560,19 +560,17 @@ __global__ __launch_bounds__(256) void head_f32_kernel(HeadArgs a, int m_tiles, 
         }
       }
     };
+    // column k = 16 s + 4 q + g of a row lies at 16 s + 4 g + q (see above)
     auto deposit = [&](int buf) {
+      const int at = (kq & ~15) + (VEC == 4 ? (kq >> 2) & 3 : 4 * (kq & 3) + ((kq >> 2) & 3));
 #pragma unroll
-      for (int j = 0; j < PW; ++j) {
-        float* p = &Ws[buf][(rq + RPP * j) * kF32Ld + kq];
-        if constexpr (VEC == 4) *reinterpret_cast<vecf*>(p) = rw[j];
-        else *p = rw[j][0];
-      }
+      for (int j = 0; j < PW; ++j)
 #pragma unroll
-      for (int j = 0; j < PH; ++j) {
-        float* p = &Hs[buf][(rq + RPP * j) * kF32Ld + kq];
-        if constexpr (VEC == 4) *reinterpret_cast<vecf*>(p) = rh[j];
-        else *p = rh[j][0];
-      }
+        for (int c = 0; c < VEC; ++c) Ws[buf][(rq + RPP * j) * kF32Ld + at + 4 * c] = rw[j][c];
+#pragma unroll
+      for (int j = 0; j < PH; ++j)
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) Hs[buf][(rq + RPP * j) * kF32Ld + at + 4 * c] = rh[j][c];
     };
 
     floatx4 acc[NR];
@@ -622,36 +620,42 @@ __global__ __launch_bounds__(256) void head_f32_kernel(HeadArgs a, int m_tiles, 
           }
         }
       }
-      float mx = -FLT_MAX;  // not -inf: sixteen tokens past V, or of logit -inf, leave (lowest, 0) and no NaN
+      acc[n] = l;
+      float mx = -FLT_MAX;  // not -inf: tokens past V, or of logit -inf, bring no NaN
 #pragma unroll
       for (int c = 0; c < 4; ++c)
         if (v + c < a.V) mx = fmaxf(mx, l[c]);
       mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      float e = 0.f;
+      if (g == 0) tile_max[rl][wave] = mx;
+    }
+    __syncthreads();  // also: the last reads of Ws are done
+    // exponentials to LDS, [wavefront][row][token % 16]; then a quad of threads per row adds them as a binary tree over
+    // the token number, highest bit first
+    floatx4* ex = reinterpret_cast<floatx4*>(Ws[0]);
+    static_assert(4 * MR * 16 <= 2 * kF32Tokens * kF32Ld, "the exponentials fit where W was");
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
-        if (v + c < a.V) e += expf(l[c] - mx);
-      e += __shfl_xor(e, 16, 64);
-      e += __shfl_xor(e, 32, 64);
-      if (g == 0) part[rl][wave] = make_float2(mx, e);
+    for (int n = 0; n < NR; ++n) {
+      const int rl = 16 * n + i16;
+      const float mx = fmaxf(fmaxf(tile_max[rl][0], tile_max[rl][1]), fmaxf(tile_max[rl][2], tile_max[rl][3]));
+      floatx4 e;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) e[c] = v + c < a.V ? expf(acc[n][c] - mx) : 0.f;
+      ex[(wave * MR + rl) * 4 + g] = e;
     }
     __syncthreads();
-    if (tid < MR && m0 + tid < M) {
-      float2 p[4];
-      float mx = -INFINITY;
+    if (tid < 4 * MR) {  // whole wavefronts
+      const int rl = tid >> 2, q = tid & 3;
+      floatx4 e = (ex[rl * 4 + q] + ex[(2 * MR + rl) * 4 + q]) + (ex[(MR + rl) * 4 + q] + ex[(3 * MR + rl) * 4 + q]);
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        p[w] = part[tid][w];
-        mx = fmaxf(mx, p[w].x);
-      }
-      float sum = 0.f;
+      for (int c = 0; c < 4; ++c) e[c] += __shfl_xor(e[c], 2, 64);
 #pragma unroll
-      for (int w = 0; w < 4; ++w) sum += p[w].y * expf(p[w].x - mx);
-      a.partials[(size_t)(m0 + tid) * a.nT + nt] = make_float2(mx, sum);
+      for (int c = 0; c < 4; ++c) e[c] += __shfl_xor(e[c], 1, 64);
+      const float sum = (e[0] + e[2]) + (e[1] + e[3]);
+      const float mx = fmaxf(fmaxf(tile_max[rl][0], tile_max[rl][1]), fmaxf(tile_max[rl][2], tile_max[rl][3]));
+      if (q == 0 && m0 + rl < M) a.partials[(size_t)(m0 + rl) * a.nT + nt] = make_float2(mx, sum);
     }
-    // the next tile's first deposit follows the last read of both buffers (barrier of the last k-step), and
-    // its partials are written behind the barriers of its own k loop
+    __syncthreads();  // the next tile's first deposit overwrites the exponentials
   }
 }
 
