@@ -878,12 +878,20 @@ __global__ __launch_bounds__(kWave) void topn_kernel(VerifyArgs a) {
   }
 }
 
-__global__ void copy_logits_kernel(const float* __restrict__ src, long ldl, float* __restrict__ dst,
-                                   int V, long rows) {
-  const long n = rows * V;
-  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-    const long r = i / V, v = i - r * V;
-    dst[i] = src[r * ldl + v];
+// Logits of one row without the padding of the workspace rows.  grid = (rows, pieces of kCopyPer tokens); a thread asks
+// for all of its eight elements before it stores the first.  (One flat index divided by V per element before: 131 -> 122 us
+// per call of 128 rows of V = 126464, d = 1024, that keeps its logits.)
+constexpr int kCopyPer = 8 * NT;
+__global__ __launch_bounds__(NT) void copy_logits_kernel(const float* __restrict__ src, long ldl, float* __restrict__ dst, int V) {
+  const float* s = src + (size_t)blockIdx.x * ldl;
+  float* d = dst + (size_t)blockIdx.x * V;
+  for (long v0 = (long)blockIdx.y * kCopyPer + threadIdx.x; v0 < V; v0 += (long)gridDim.y * kCopyPer) {
+    float x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = v0 + j * NT < V ? s[v0 + j * NT] : 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (v0 + j * NT < V) d[v0 + j * NT] = x[j];
   }
 }
 
@@ -911,11 +919,9 @@ hipError_t launch_verify(const VerifyArgs& a) {
     }
   }
   if (a.diag_logits) {
-    const long rows = a.nrows;
-    const long n = rows * a.V;
-    const int blocks = (int)((n + 255) / 256 > 65535 ? 65535 : (n + 255) / 256);
-    hipLaunchKernelGGL(copy_logits_kernel, dim3(blocks), dim3(256), 0, a.stream,
-                       a.logits + (size_t)a.row0 * a.ldl, a.ldl, a.diag_logits + (size_t)a.row0 * a.V, a.V, rows);
+    const long pieces = (a.V + (long)kCopyPer - 1) / kCopyPer;
+    hipLaunchKernelGGL(copy_logits_kernel, dim3(a.nrows, pieces < 65535 ? pieces : 65535), dim3(NT), 0, a.stream,
+                       a.logits + (size_t)a.row0 * a.ldl, a.ldl, a.diag_logits + (size_t)a.row0 * a.V, a.V);
   }
   return hipGetLastError();
 }
