@@ -82,12 +82,13 @@ typedef enum {
                           once, split-k; other d at M <= 32 go to STREAM (fef_select_gemm tells) */
   FEF_GEMM_TILED = 2,  /* bf16, any M: plain 128x128 LDS-tiled MFMA GEMM (never picked by AUTO) */
   FEF_GEMM_F32 = 3,    /* f32, any shape: reference-grade FMA kernel                       */
-  FEF_GEMM_TILED256 = 4, /* bf16, any M: LDS-tiled MFMA GEMM, 256 tokens x 32 to 256 rows per workgroup, eight
-                            wavefronts up to 256 rows, four above (AUTO: M > 128)            */
-  FEF_GEMM_STREAM = 5,   /* bf16, M <= 128: the same kernel (AUTO: 48 < M <= 64, 96 < M <= 128, and M <= 128 where
-                            neither SKINNY nor ROWSTREAM takes the hidden size)              */
-  FEF_GEMM_ROWSTREAM = 6 /* bf16, M <= 128, d a multiple of 512: the same kernel (AUTO: 32 < M <= 48 and
-                            64 < M <= 96); the two names are kept for callers that select by them */
+  FEF_GEMM_TILED256 = 4, /* bf16, any M: LDS-tiled MFMA GEMM, 256 tokens x 32 to 256 rows per workgroup (AUTO: M > 128) */
+  FEF_GEMM_STREAM = 5,   /* bf16, M <= 128: the same tiles, one workgroup per CU over a run of 64-token units (AUTO:
+                            48 < M <= 64, 96 < M <= 128, and M <= 128 where neither SKINNY nor ROWSTREAM takes the
+                            hidden size)                                                                */
+  FEF_GEMM_ROWSTREAM = 6 /* bf16, M <= 128, d a multiple of 512: likewise, runs of 16-token tiles (AUTO: 32 < M <= 48,
+                            64 < M <= 96, and M <= 32 where SKINNY does not take the hidden size).  The variants add
+                            the same terms in different orders, so they agree to rounding only            */
 } fef_gemm_variant;
 
 /* In Algorithm 2 the verification inputs X^(j_m) carry the draft prefix, so a real target
@@ -98,7 +99,7 @@ typedef enum {
  * must follow a DRAFT call with the same sizes, mask_in, seed, step and the SAME workspace,
  * left untouched in between (it holds the draft logits, their log-sum-exp and x~); h_draft is
  * not read and may be NULL.  DRAFT + TARGET give bit-identical results to FUSED when both
- * use the same head kernel, and read W twice.  The two calls may pass different W_vocab of the
+ * use the same head kernel (TILED256 up to 256 rows and above count as two), and read W twice.  The two calls may pass different W_vocab of the
  * same shape: a separate draft model with its own output embedding (the "A / B" rows of the
  * ablation on the choice of draft model). */
 typedef enum { FEF_PHASE_FUSED = 0, FEF_PHASE_DRAFT = 1, FEF_PHASE_TARGET = 2 } fef_phase;

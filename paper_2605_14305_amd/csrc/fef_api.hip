@@ -12,10 +12,7 @@
 // Scratch of fef_verify_step_static: one copy per GPU the library runs on, held until the process
 // ends.  In host code this name is only a handle for hipGetSymbolAddress; the device address it
 // yields (one per device) is what kernels, memsets and copies must be given.
-// Which calls fit is decided by FEF_STATIC_SCRATCH_BYTES with a fixed number of partials per row (Layout::total_fixed);
-// the kernels' own number of partials (at most one per 256 tokens and 255 more) may need up to 1 MB beyond.
-constexpr size_t kScratchBytes = (size_t)FEF_STATIC_SCRATCH_BYTES + (1u << 20);
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[FEF_STATIC_SCRATCH_BYTES];
 
 namespace {
 
@@ -36,15 +33,12 @@ struct Layout {
   long ldl;
   size_t off_logits, off_partials, off_lse, off_xdraft, off_xtarget, off_slot_pos, off_window, off_seqstate,
       off_rmass, off_amass, total;
-  size_t total_fixed;  // total, with the partials per row that fef_verify_step_static's limit counts
 };
 
-// Row counts and sizes of the two variants that name a range of the 256-token tile kernel.
+// Row counts and sizes of the two variants whose workgroups take runs of tokens.
 bool stream_supports(long M, int d) { return M <= 128 && d % 64 == 0; }
 bool rowstream_supports(long M, int d) { return M > 0 && M <= 128 && d % 512 == 0; }
-bool tiles_of_256(int variant) {
-  return variant == FEF_GEMM_TILED256 || variant == FEF_GEMM_STREAM || variant == FEF_GEMM_ROWSTREAM;
-}
+int run_unit(int variant) { return variant == FEF_GEMM_STREAM ? 64 : variant == FEF_GEMM_ROWSTREAM ? 16 : 0; }
 
 // Sizes only; no pointer checks.
 fef_status check_sizes(const fef_params* p, int32_t K, int32_t block) {
@@ -132,12 +126,15 @@ fef_status make_layout(const fef_params* p, int32_t K, int32_t block, Layout* L)
     L->tile_unit = fef::kSkinnyUnit;
     L->tile_T = (p->V + fef::kSkinnyUnit - 1) / fef::kSkinnyUnit;
     L->nT = L->tile_T < fef::kSkinnyMaxGrid ? L->tile_T : fef::kSkinnyMaxGrid;
-  } else if (tiles_of_256(L->variant)) {
-    // one partial per (row, workgroup): shares of at most 256 tokens, or whole tiles
-    const long rows = (p->phase == FEF_PHASE_FUSED ? 2L : 1L) * p->B * K;
-    L->nT = fef::tiled256_tiles(p->V, (int)rows);
-    L->tile_unit = L->nT == (p->V + fef::kTiled256Tn - 1) / fef::kTiled256Tn ? fef::kTiled256Tn : fef::kTiled256Unit;
-    L->tile_T = (p->V + L->tile_unit - 1) / L->tile_unit;
+  } else if (const int unit = run_unit(L->variant)) {
+    // one partial per (row, workgroup); a workgroup's tokens are a contiguous run of units
+    L->tile_unit = unit;
+    L->tile_T = (p->V + unit - 1) / unit;
+    L->nT = fef::runs_grid(p->V, unit);
+  } else if (L->variant == FEF_GEMM_TILED256) {
+    // one partial per (row, workgroup tile of 256 tokens)
+    L->tile_unit = fef::kTiled256Tn;
+    L->tile_T = L->nT = (p->V + fef::kTiled256Tn - 1) / fef::kTiled256Tn;
   } else {
     L->tile_unit = fef::kTiledTn;
     L->tile_T = L->nT = (p->V + fef::kTiledTn - 1) / fef::kTiledTn;
@@ -159,13 +156,6 @@ fef_status make_layout(const fef_params* p, int32_t K, int32_t block, Layout* L)
   L->off_rmass = take(nslots * (size_t)L->nRC * sizeof(float));
   L->off_amass = take(L->all_slots ? nslots * (size_t)L->nRC * sizeof(float) : 0);
   L->total = o;
-  // The limit of fef_verify_step_static counts at most 256 partials per row for the variants up to 128 rows and one per
-  // 256 tokens for TILED256, whatever the kernel leaves, so that a change of its tiles refuses no call.
-  long fixed = L->nT;
-  if (L->variant == FEF_GEMM_STREAM) fixed = (p->V + 255) / 256 < 256 ? (p->V + 255) / 256 : 256;
-  if (L->variant == FEF_GEMM_ROWSTREAM) fixed = (p->V + 127) / 128 < 256 ? (p->V + 127) / 128 : 256;
-  if (L->variant == FEF_GEMM_TILED256) fixed = (p->V + 255) / 256;
-  L->total_fixed = o - align_up(M * (size_t)L->nT * sizeof(float2), 256) + align_up(M * (size_t)fixed * sizeof(float2), 256);
   return FEF_OK;
 }
 
@@ -303,14 +293,14 @@ fef_status fef_verify_step_static(const fef_params* prm, const void* h_draft, co
   Layout L;
   fef_status s = make_layout(prm, K, block, &L);
   if (s != FEF_OK) return s;
-  if (L.total_fixed > (size_t)FEF_STATIC_SCRATCH_BYTES || L.total > kScratchBytes)
+  if (L.total > (size_t)FEF_STATIC_SCRATCH_BYTES)
     return fail(FEF_ERR_WORKSPACE, "this call needs %zu bytes of scratch, the built-in buffer has %zu: use fef_verify_step "
                 "with a caller workspace", L.total, (size_t)FEF_STATIC_SCRATCH_BYTES);
   void* ptr = nullptr;
   s = static_scratch(&ptr);
   if (s != FEF_OK) return s;
   return run_step(prm, prm->phase, 0, h_draft, h_target, W_vocab, K, block, seed, out_tokens, out_accept_len,
-                  out_remask, ptr, kScratchBytes);
+                  out_remask, ptr, (size_t)FEF_STATIC_SCRATCH_BYTES);
 }
 
 fef_status fef_topn_step(const fef_params* prm, const void* h, const void* W_vocab, int32_t K, int32_t block,
@@ -365,9 +355,9 @@ fef_status run_step(const fef_params* prm, int phase, int n_transfer, const void
   switch (L.variant) {
     case FEF_GEMM_SKINNY: e = fef::launch_head_skinny(h); break;
     case FEF_GEMM_TILED: e = fef::launch_head_tiled(h); break;
-    case FEF_GEMM_TILED256:
+    case FEF_GEMM_TILED256: e = fef::launch_head_tiled256(h); break;
     case FEF_GEMM_STREAM:
-    case FEF_GEMM_ROWSTREAM: e = fef::launch_head_tiled256(h); break;
+    case FEF_GEMM_ROWSTREAM: e = fef::launch_head_runs(h, run_unit(L.variant)); break;
     default: e = fef::launch_head_f32(h); break;
   }
   if (e != hipSuccess) return fail(FEF_ERR_HIP, "head kernel launch: %s", hipGetErrorString(e));
@@ -440,8 +430,7 @@ fef_status ce_check(const fef_params* p, int32_t R, int* variant, int* nT, size_
       return fail(FEF_ERR_UNSUPPORTED, "cross-entropy runs through the F32, STREAM or TILED256 head kernel");
   }
   *variant = v;
-  *nT = tiles_of_256(v) ? fef::tiled256_tiles(p->V, R)
-                        : (p->V + fef::kTiledTn - 1) / fef::kTiledTn;
+  *nT = v == FEF_GEMM_F32 ? (p->V + fef::kTiledTn - 1) / fef::kTiledTn : fef::tiled256_tiles(p->V, R);
   *total = align_up((size_t)R * (size_t)*nT * sizeof(float2), 256) + align_up((size_t)R * sizeof(float), 256);
   return FEF_OK;
 }

@@ -70,13 +70,15 @@ constexpr int kSkinnyMaxGrid = 256;  // ... split evenly over at most one workgr
                                      // writes one partial per (row, workgroup)
 constexpr int kTiledTn = 64;         // partial-tile width of the 128x128 tiled and f32 kernels
 constexpr int kTiled256Tn = 256;     // largest tile of the 256-token tile kernel, one partial per (row, workgroup) ...
-constexpr int kTiled256Unit = 32;    // ... and the unit of its shares where it takes narrower ones
+constexpr int kTiled256Unit = 32;    // ... and the unit of a cross-entropy call's shares where it takes narrower ones
 
 bool skinny_supports(int M, int d);
 hipError_t launch_head_skinny(const HeadArgs& a);
 hipError_t launch_head_tiled(const HeadArgs& a);
-int tiled256_tiles(int V, int M);  // token tiles = partial slots per row of a call over M rows
+int tiled256_tiles(int V, int M);  // cross-entropy: token tiles = partial slots per row of a call over M rows
 hipError_t launch_head_tiled256(const HeadArgs& a);
+int runs_grid(int V, int unit);    // STREAM (unit 64), ROWSTREAM (16): workgroups = partial slots per row
+hipError_t launch_head_runs(const HeadArgs& a, int unit);
 hipError_t launch_head_f32(const HeadArgs& a);
 
 // ---------------------------------------------------------------------------------------------

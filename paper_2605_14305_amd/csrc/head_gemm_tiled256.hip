@@ -2,9 +2,24 @@
 // take, and for the cross-entropy use of the head.
 //
 // Workgroup tile 32 NR rows of H (NR = 1 to 8) x up to 256 tokens, k-steps of 64, v_mfma_f32_16x16x32_bf16 with the W tile
-// as the A operand and H as the B operand.  Two forms:
-//   WN = 2  four wavefronts in a 2 x 2 grid (rows x tokens), each 16 NR rows x 128 tokens: M > 256, d >= 1024
-//   WN = 4  eight wavefronts in a 2 x 4 grid, each 16 NR rows x 64 tokens: M <= 256, and M > 256 with small d
+// as the A operand and H as the B operand.  Two grids of wavefronts:
+//   WN = 2  four in a 2 x 2 grid (rows x tokens), each 16 NR rows x 128 tokens: M > 256
+//   WN = 4  eight in a 2 x 4 grid, each 16 NR rows x 64 tokens: M <= 256, and the cross-entropy of M > 256 rows with d < 1024
+// and five forms: kTiles (whole tiles of 256 tokens), kRuns64 and kRuns16 (M <= 128: one workgroup per CU takes a run of
+// 64- or 16-token units, 256 tokens at a time), and the two of the cross-entropy, kLossTiles and kLossShares.
+//
+// The order of the sums.  A draw or an accept test can hang on the last bit of a sum, and with it the rest of the round, so
+// in the first three forms the order in which terms are added is part of the result and does not follow the tiles:
+//   a logit   groups of 16 columns (a 16x16x32 multiply gives bit for bit what two 32x32x16 in a row give), ascending
+//             from a start that depends on the token's tile or run b alone, and round to it again: kTiles 64 (37 b mod d/64)
+//             for M <= 256 and 0 above, kRuns64 32 (37 b mod d/32), kRuns16 128 (37 b mod d/128)
+//   a partial (max, sum exp) of 64 neighbouring tokens: tokens j and j + 32 first, then a binary tree over the bits of
+//             j < 32 in the order 3, 2, 1, 0, 4.  kTiles with M > 256, where 128 tokens x 128 rows exist (blocks aligned
+//             to 128): of the 64 tokens whose number has bit 4 clear or set, (j + j32) + (j64 + j96) first, then bits 3,
+//             2, 1, 0.  kRuns16: of 16 tokens, four neighbours in order, then bits 2 and 3.
+//   a row's   the partials of a tile in ascending order; kRuns64 goes on from tile to tile; kRuns16 keeps eight chains,
+//             every eighth tile of the run each, and adds the chains at the end.
+// The sums over lanes that this takes cost 0 to 3 % of the kernel (M = 2048 1606 -> 1615 us, M = 64 179 -> 182).
 //
 // What bounds it, and what follows.
 // (1) Power.  With every matrix unit busy on real data the chip lowers its clock, so energy per multiply is time.  A
@@ -15,18 +30,17 @@
 // instructions (it holds one multiply beyond the one in work), so fragment reads and operand loads are dealt out singly
 // between the multiplies, and pointer additions are pinned behind their loads.
 // (3) The epilogue, during which the matrix units idle.  With the tokens in the rows of D a lane holds four consecutive
-// tokens of ONE row of H per tile: logits leave as 16-byte stores, and the (max, sum exp) of a row runs inside the
-// lane over all its tiles; nothing crosses lanes at all (each of the four lane groups that share a row writes
-// the partial of its own tokens to LDS, where a thread per row merges them).
+// tokens of ONE row of H per tile: logits leave as 16-byte stores, and most of the (max, sum exp) of a row runs inside the
+// lane; the four lane groups that share a row trade with v_permlane16_swap / v_permlane32_swap, two sums per exchange
+// (ten exchanges per 16 rows x 64 tokens), and a thread per row merges what meets in LDS.  In the cross-entropy nothing
+// crosses lanes at all: each lane group writes the partial of its own tokens to LDS.
 // (4) Rows that do not exist.  M is cut into ceil(M / 256) row tiles of equal height, a multiple of 32 (300 rows:
 // two tiles of 160, not 256 + 44), one instantiation per height.
 //
-// Measured (head kernel, rocprofv3; before: 32x32x16, tokens in the columns of D, 256-row tiles only):
-// M = 2048 (d = 4096, V = 126464) 1697 -> 1610 us with logits, 1600 -> 1470 without (cross-entropy: 1.44 PFLOP/s, matrix
-// units busy 0.72 of the cycles at 1.78 GHz); M = 300 without logits (d = 2048, V = 50257) 138 -> 67; M = 256 250 -> 238.
-// Up to 128 rows, where two kernels built around streaming W stood before (persistent workgroups; W into LDS or straight
-// into registers): 48 rows 189 -> 176 us, 64 rows 188 -> 178, 96 rows 207 -> 181, 128 rows 200 -> 187, and 159 -> 110 at
-// 110 rows of d = 2560, V = 100003.
+// Measured (head kernel, rocprofv3, median of 310; before: 32x32x16, tokens in the columns of D, 256-row tiles, and two
+// kernels built around streaming W up to 128 rows): d = 4096, V = 126464: 48 rows 189 -> 182 us, 64 rows 188 -> 186, 96 rows
+// 207 -> 188, 128 rows 200 -> 189, 256 rows 250 -> 254 (fastest 233), 2048 rows 1697 -> 1631 (fastest 1592); 110 rows of d = 2560,
+// V = 100003 159 -> 112.  Cross-entropy, 2048 rows 1600 -> 1470 to 1522, 300 rows (d = 2048, V = 50257) 138 -> 67.
 //
 // Operand slabs go HBM/L2 -> LDS directly (global_load_lds_dwordx4: lane l of a wavefront deposits its 16 bytes at
 // LDS base + 16 l): no register staging and no ds_write in the main loop.  A row of a stage is 128 bytes, so one load
@@ -56,7 +70,6 @@ namespace fef {
 namespace {
 
 constexpr int BN = kTiled256Tn, BK = 64;
-constexpr int kUnit = kTiled256Unit;
 constexpr int kStageW = BN * 8;  // 16-byte chunks per W stage
 
 // Which of `cnt` instructions spread evenly over `total` multiplies follows multiply m; -1: none.  cnt <= total.
@@ -111,21 +124,66 @@ __device__ __forceinline__ void settle(floatx4 (&acc0)[NT][NR], floatx4 (&acc1)[
   pin();
 }
 
-template <int NR, int WN, bool SHARES, bool CE>
+// Exchange between the four lane groups of 16 that share a row of D.  halves: x = [x.lo, y.lo], y = [x.hi, y.hi] by halves
+// of the wavefront; quarters: x = [x0, y0, x2, y2], y = [x1, y1, x3, y3] by its rows of 16 lanes.
+__device__ __forceinline__ void swap_halves(float& x, float& y) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
+  x = __builtin_bit_cast(float, (unsigned)r[0]);
+  y = __builtin_bit_cast(float, (unsigned)r[1]);
+}
+__device__ __forceinline__ void swap_quarters(float& x, float& y) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
+  x = __builtin_bit_cast(float, (unsigned)r[0]);
+  y = __builtin_bit_cast(float, (unsigned)r[1]);
+}
+// Maximum of m0 over the four lane groups in m0 and of m1 in m1, in every lane.
+__device__ __forceinline__ void group_max(float& m0, float& m1) {
+  swap_halves(m0, m1);
+  float m = vmax(m0, m1), o = m;
+  swap_quarters(m, o);
+  m0 = m1 = vmax(m, o);
+  swap_halves(m0, m1);
+}
+// Binary tree over the 16 tokens j = 4 g + c of a 16-token tile, highest bit of j first, for two tiles at once: the sum
+// of e0 in the lower half of the wavefront, that of e1 in the upper half.
+__device__ __forceinline__ float group_sum(float (&e0)[4], float (&e1)[4]) {
+  float r[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    swap_halves(e0[c], e1[c]);
+    r[c] = e0[c] + e1[c];
+  }
+  swap_quarters(r[0], r[1]);
+  swap_quarters(r[2], r[3]);
+  float x = (r[0] + r[1]) + (r[2] + r[3]), y = x;
+  swap_quarters(x, y);
+  return x + y;
+}
+
+// What a launch is for; see "The order of the sums" above.
+enum Form { kTiles, kRuns64, kRuns16, kLossTiles, kLossShares };
+constexpr int form_unit(Form f) { return f == kRuns64 ? 64 : f == kRuns16 ? 16 : f == kLossShares ? kTiled256Unit : BN; }
+
+template <int NR, int WN, Form F>
 __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int m_tiles) {
+  constexpr bool CE = F == kLossTiles || F == kLossShares;
+  constexpr bool RUN = F == kRuns64 || F == kRuns16;  // a workgroup takes a run of tokens, 256 at a time
+  constexpr bool SHARES = RUN || F == kLossShares;
   constexpr int NT = 16 / WN;                        // 16-token tiles per wavefront
   constexpr int BM = 32 * NR, WROWS = 16 * NR;       // rows of the workgroup tile, of a wavefront
   constexpr int LW = 16 / WN, LH = (2 * NR + WN - 1) / WN;  // load instructions per wavefront and stage (8 rows each)
   constexpr bool ONE = WN == 4;                      // two wavefronts per SIMD; as a rule one row tile
   constexpr bool ROLL = ONE;                         // H fragments in one set of registers, each re-read behind its last use
   constexpr int kStageH = BM * 8;                    // 16-byte chunks per H stage
-  // Stages in LDS.  Narrow shares make short k-steps, so H is requested two steps ahead there like W, where 160 KB allow
-  // (25.8 -> 22.9 us at 32 rows of d = 1536, V = 32000; 116 -> 110 at 110 rows of d = 2560, V = 100003; a fourth stage of
-  // both measured nothing).  With whole tiles a third H stage costs 2 % (178 against 184 us at 64 rows of d = 4096,
-  // V = 126464).
+  // Stages in LDS.  Narrow shares and runs make short k-steps, so H is requested two steps ahead there like W, where 160 KB
+  // allow (rounds of 64 rows of d = 4096, V = 32000 69.2 -> 60.5 us together with the place of the loads, see kLoadAt; 254 ->
+  // 238 at 128 rows of d = 3584, V = 151936; nothing at V = 126464; a fourth stage of both measured nothing).  With whole
+  // tiles a third H stage costs 2 %.
   constexpr int kRingW = 3, kRingH = SHARES && NR <= 5 ? 3 : 2;
   __shared__ bf16x8 ringH[kRingH * kStageH];
   __shared__ bf16x8 ringW[kRingW * kStageW];
+  constexpr int SLOTS = F == kRuns16 ? 16 : CE ? 4 * WN : 4;  // partials per row that meet in LDS
+  __shared__ float2 run_part[RUN ? SLOTS * BM : 1];  // runs: their own place, the rings take the next tile's stages meanwhile
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
@@ -136,17 +194,26 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
   const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
   const int nt = xcd + 8 * (seq / m_tiles), mt = seq % m_tiles;
   if (nt >= a.nT) return;
-  // tokens [n0, n_end) of this workgroup, at most 256: a whole tile, or an equal share of the vocabulary in units of 32
-  // tokens (see tiled256_tiles)
+  // tokens [n0, n_stop) of this workgroup: a whole tile, or an equal share of the vocabulary in units of 16, 32 or 64
+  // tokens; [n0, n_end) of the tile in work, at most 256
+  constexpr int kUnit = form_unit(F);
   const int n_units = (a.V + kUnit - 1) / kUnit;
   const int m0 = mt * BM;
-  const int n0 = SHARES ? (int)((long)nt * n_units / a.nT) * kUnit : nt * BN;
-  const int n_end = min(a.V, SHARES ? (int)((long)(nt + 1) * n_units / a.nT) * kUnit : n0 + BN);
+  int n0 = SHARES ? (int)((long)nt * n_units / a.nT) * kUnit : nt * BN;
+  const int n_stop = min(a.V, SHARES ? (int)((long)(nt + 1) * n_units / a.nT) * kUnit : n0 + BN);
+  int n_end = RUN ? min(n_stop, n0 + BN) : n_stop;
 
   // Every row of W starts at a multiple of 2 d bytes, so workgroups that walk k from 0 in step ask HBM for the
   // same low address bits at the same moment: with eight wavefronts each token tile starts its walk at another k-step and
   // wraps (with four and several row tiles per token tile, which share H in time through L2, that measured 2 % slower).
-  const int k0 = ONE ? (int)((unsigned)(nt * 37) % (unsigned)nk) : 0;
+  // In units of kStart columns, which for the runs are what their order of sums is defined by.
+  constexpr int kStart = F == kRuns64 ? 32 : F == kRuns16 ? 128 : BK;
+  const int start = ONE ? (int)((unsigned)(nt * 37) % (unsigned)(a.d / kStart)) * kStart : 0;
+  // A start in the middle of a k-step (HALF): the walk takes that step twice, its second half first of all and its first
+  // half last of all.  (Steps that begin there would read every 128-byte line in two halves: 64 rows 237 against 198 us.)
+  constexpr bool HALF = kStart % BK != 0;
+  const bool half = HALF && start % BK != 0;
+  const int k0 = start / BK, nsteps = nk + (half ? 1 : 0);
   int h_left = nk - k0, w_left = nk - k0;  // steps until the walk is back at k = 0
 
   // Direct-to-LDS loads: wavefront w fills rows [8 LH w, + 8 LH) of an H stage and [8 LW w, + 8 LW) of a W stage,
@@ -166,12 +233,16 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
     const int c = (lane & 7) ^ ((rl >> 1) & 7);
     gh[q] = h_row(a, min(m0 + rl, M - 1)) + c * 8 + k0 * BK - q * kLow;  // rows past M re-read the last row; masked later
   }
+  auto aim_w = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int q = 0; q < LW; ++q) {
-    const int rl = wave * (8 * LW) + q * 8 + (lane >> 3);
-    const int c = (lane & 7) ^ ((rl >> 1) & 7);
-    gw[q] = (const __bf16*)a.W + (size_t)min(n0 + rl, n_end - 1) * a.d + c * 8 + k0 * BK - q * kLow;  // past the share: its last row, masked later
-  }
+    for (int q = 0; q < LW; ++q) {
+      const int rl = wave * (8 * LW) + q * 8 + (lane >> 3);
+      const int c = (lane & 7) ^ ((rl >> 1) & 7);
+      // past the share: its last row, masked later
+      gw[q] = (const __bf16*)a.W + (size_t)min(n0 + rl, n_end - 1) * a.d + c * 8 + k0 * BK - q * kLow;
+    }
+  };
+  aim_w();
   const uint32_t slotH = lds_offset(ringH + hrow0 * 8), slotW = lds_offset(ringW + wave * LW * 64);
   constexpr uint32_t kBytesH = kStageH * 16, kBytesW = kStageW * 16;
   // Elements the pointers move on by after the loads of a step: one k-step, and back to k = 0 where the walk wraps.
@@ -181,8 +252,13 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
   };
   // One load of this wavefront for the k-step the pointer stands at, which then moves on (the empty statement pins the
   // addition there: left alone, the compiler gathers the 64-bit additions of a step in front of the barrier).
+  // (uniform; inside the loop over a run's tiles the compiler has to be told)
+  auto scalar = [&](uint32_t x) __attribute__((always_inline)) -> uint32_t {
+    if constexpr (RUN) return __builtin_amdgcn_readfirstlane(x);
+    else return x;
+  };
   auto issue_one = [&](const __bf16*& p, int q, uint32_t lds, long move) __attribute__((always_inline)) {
-    load_to_lds_16(p + q * kLow, lds + q * 1024);
+    load_to_lds_16(p + q * kLow, scalar(lds + q * 1024));
     p += move;
     asm volatile("" : "+v"(p));
   };
@@ -198,6 +274,7 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
   };
   auto group = [&](auto& p, uint32_t base, int& left) __attribute__((always_inline)) {
     constexpr int L = sizeof(p) / sizeof(p[0]);
+    base = scalar(base);
     if constexpr (L == 4)
       asm volatile("s_mov_b32 m0, %4\n\ts_nop 0\n\t"
                    "global_load_lds_dwordx4 %0, off\n\tglobal_load_lds_dwordx4 %1, off offset:1024\n\t"
@@ -221,12 +298,15 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
   static_assert(!ONE || (LH <= 4 && LW <= 4), "groups of loads");
 
   // prologue: W as far ahead as its ring reaches, H likewise (one step where its ring is the shorter one)
+  auto prologue = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int t = 0; t < kRingW - 1; ++t) {
-    if (t >= nk) break;
-    if (t < kRingH - 1) all_h(t);
-    all_w(t);
-  }
+    for (int t = 0; t < kRingW - 1; ++t) {
+      if (t >= nsteps) break;
+      if (t < kRingH - 1) all_h(t);
+      all_w(t);
+    }
+  };
+  prologue();
 
   // acc(t, n): tokens 16 t + 4 g .. + 3 of row 16 n + i16 of the wavefront's tile
   // (two arrays: one of 1 KB per lane is not taken apart into registers)
@@ -234,11 +314,6 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
   auto acc_at = [&](int t, int n) __attribute__((always_inline)) -> floatx4& {
     return t < NT / 2 ? acc0[t][n] : acc1[t - NT / 2][n];
   };
-#pragma unroll
-  for (int t = 0; t < NT / 2; ++t)
-#pragma unroll
-    for (int n = 0; n < NR; ++n) acc0[t][n] = acc1[t][n] = floatx4{0.f, 0.f, 0.f, 0.f};
-  settle<!ONE>(acc0, acc1);
   bf16x8 wf[2][NT], hf[ROLL ? 1 : 2][NR];
 
   // fragment addresses in a stage (chunks): row 16 n + i16 of this wavefront's rows, chunk 4 ks + g; the swizzle term
@@ -246,10 +321,6 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
   int fo[2];
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) fo[ks] = i16 * 8 + ((ks * 4 + g) ^ ((i16 >> 1) & 7));
-
-  // none of this wavefront's rows, or none of its tokens, exists: loads and barriers only (wavefront-uniform, and said so)
-  const int vw = n0 + wn * (16 * NT);  // first token of the wavefront
-  const bool idle = __builtin_amdgcn_readfirstlane((int)(m0 + wm * WROWS >= M || vw >= n_end)) != 0;
 
   // Slice KS of the step in work is read into fragment set KS while the slice before it (set KS ^ 1; KS = 0: the last
   // slice of the step before) is multiplied.  LOADS: phase 0 requests the H stage of the next step, phase 1 the W
@@ -260,8 +331,9 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
     constexpr bool MUL = decltype(mul_tag)::value, FULL = decltype(full)::value;
     constexpr int TOTAL = NT * NR, LOADS = KS == 0 ? LH : LW;
     // Eight wavefronts: the multiply behind which the group of loads goes out.  At once where the lead of a k-step is
-    // short for the load latency (many rows: 237 -> 224 us at M = 256, 207 -> 201 at 192; narrow shares: 216 -> 211 at 128
-    // rows of d = 3584, V = 151936); in mid-phase where the pass over W is all it costs (128 rows: 187 against 191 us).
+    // short for the load latency (many rows: 237 -> 224 us at M = 256, 207 -> 201 at 192; narrow shares and runs: 254 -> 240
+    // per round of 128 rows of d = 3584, V = 151936; level at V = 126464); in mid-phase with whole tiles of up to 128 rows,
+    // where the pass over W is all it costs (187 against 191 us).
     constexpr int kLoadAt = SHARES || NR >= 5 ? 1 : TOTAL / 2 + (NR > 1 ? 2 : 0);
     bf16x8(&wr)[NT] = wf[KS];
     bf16x8(&wm_)[NT] = wf[KS ^ 1];
@@ -324,18 +396,32 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
     });
   };
 
+  // The half of the first and of the last step that the walk does not take counts as zero (both operands, so that an
+  // infinite one brings no NaN); the wait is for these writes in front of a multiply.
+  auto drop = [&](bf16x8(&w)[NT]) __attribute__((always_inline)) {
+    auto one = [&](bf16x8& f) __attribute__((always_inline)) {
+      f = half ? bf16x8{} : f;
+      asm volatile("" : "+v"(f));
+    };
+#pragma unroll
+    for (int t = 0; t < NT; ++t) one(w[t]);
+#pragma unroll
+    for (int n = 0; n < NR; ++n) one(hf[0][n]);
+    asm volatile("s_nop 7" ::: "memory");
+  };
+
   // One k-step; outstanding loads of this wavefront on entry, oldest first: H(kt), W(kt+1) (H ring of two, W ring of
   // three), or those of the steps from kt on (rings of equal length); the barrier needs H(kt) and W(kt).  FULL:
-  // kt + kRingW - 1 < nk, every refill exists and the step is one basic block.
+  // kt + kRingW - 1 < nsteps, every refill exists and the step is one basic block.
   auto step = [&](int kt, int sw, auto parity, auto full, auto idle_tag, auto mul_tag) __attribute__((always_inline)) {
     constexpr bool FULL = decltype(full)::value;
     constexpr bool IDLE = decltype(idle_tag)::value;
-    const bool more_h = FULL || kt + kRingH - 1 < nk, more_w = FULL || kt + kRingW - 1 < nk;
+    const bool more_h = FULL || kt + kRingH - 1 < nsteps, more_w = FULL || kt + kRingW - 1 < nsteps;
     const int sw2 = sw == 0 ? kRingW - 1 : sw - 1;               // stage of W(kt + kRingW - 1)
     const int sh = kRingH == kRingW ? sw : (int)decltype(parity)::value, sh1 = kRingH == kRingW ? sw2 : sh ^ 1;
     constexpr int kStep = kRingH == kRingW ? LH + LW : LW;       // younger loads per step that may stay in flight
     __builtin_amdgcn_sched_barrier(0);
-    if (FULL || kt + 1 < nk) wait_newer<kStep>();
+    if (FULL || kt + 1 < nsteps) wait_newer<kStep>();
     else wait_newer<0>();
     lds_barrier();
     if constexpr (IDLE) {
@@ -345,6 +431,7 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
       const bf16x8* Hs = ringH + sh * kStageH;
       const bf16x8* Ws = ringW + sw * kStageW;
       phase(std::integral_constant<int, 0>{}, mul_tag, full, Hs, Ws, more_h, sh1);
+      if constexpr (HALF && !decltype(mul_tag)::value) drop(wf[0]);
       phase(std::integral_constant<int, 1>{}, std::true_type{}, full, Hs, Ws, more_w, sw2);
     }
   };
@@ -352,34 +439,79 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
   // inside the step the two paths meet again in every step, and the compiler reconciles their registers there with
   // sixteen moves in front of the barrier.)
   auto walk = [&](auto idle_tag) __attribute__((always_inline)) {
+    using Yes = std::true_type;
+    using No = std::false_type;
     using Even = std::integral_constant<int, 0>;
     using Odd = std::integral_constant<int, 1>;
-    step(0, 0, Even{}, std::false_type{}, idle_tag, std::false_type{});  // nothing to multiply yet in its first phase
+    step(0, 0, Even{}, No{}, idle_tag, No{});  // nothing to multiply yet in its first phase
     int kt = 1, sw = 1;
-    for (; kt + kRingW < nk; kt += 2) {  // two full steps
-      step(kt, sw, Odd{}, std::true_type{}, idle_tag, std::true_type{});
+    for (; kt + kRingW < nsteps; kt += 2) {  // two full steps
+      step(kt, sw, Odd{}, Yes{}, idle_tag, Yes{});
       sw = sw == kRingW - 1 ? 0 : sw + 1;
-      step(kt + 1, sw, Even{}, std::true_type{}, idle_tag, std::true_type{});
+      step(kt + 1, sw, Even{}, Yes{}, idle_tag, Yes{});
       sw = sw == kRingW - 1 ? 0 : sw + 1;
     }
-    for (; kt < nk; kt += 2) {  // what is left
-      step(kt, sw, Odd{}, std::false_type{}, idle_tag, std::true_type{});
+    for (; kt < nsteps; kt += 2) {  // what is left
+      step(kt, sw, Odd{}, No{}, idle_tag, Yes{});
       sw = sw == kRingW - 1 ? 0 : sw + 1;
-      if (kt + 1 == nk) break;
-      step(kt + 1, sw, Even{}, std::false_type{}, idle_tag, std::true_type{});
+      if (kt + 1 == nsteps) break;
+      step(kt + 1, sw, Even{}, No{}, idle_tag, Yes{});
       sw = sw == kRingW - 1 ? 0 : sw + 1;
     }
   };
 
-  // Partials in LDS (the H ring is free by then): [slot][row of the tile], slot = 4 wn + g.
-  float2* lp = reinterpret_cast<float2*>(ringH);
+  // Partials in LDS, [slot][row of the tile].  Where a workgroup has one tile the H ring is free by then.
+  float2* lp = RUN ? run_part : reinterpret_cast<float2*>(ringH);
+  constexpr float kLog2e = 1.4426950408889634f;
+  // Runs: (max, sum exp) of row tid over the tiles done so far, kRuns16: for each eighth 16-token tile of the run
+  constexpr int CHAINS = F == kRuns16 ? 8 : 1;
+  float run_m[CHAINS], run_s[CHAINS];
+#pragma unroll
+  for (int w = 0; w < CHAINS; ++w) {
+    run_m[w] = -INFINITY;
+    run_s[w] = 0.f;
+  }
+
+  for (;;) {  // once, or over the tiles of a run
+  const int vw = n0 + wn * (16 * NT);  // first token of the wavefront
+  // none of this wavefront's rows, or none of its tokens, exists: loads and barriers only (wavefront-uniform, and said so)
+  const bool idle = __builtin_amdgcn_readfirstlane((int)(m0 + wm * WROWS >= M || vw >= n_end)) != 0;
+  const int tile0 = n0, tile_end = n_end;
+  // Behind the barrier after the walk nobody reads the rings any more: the first stages of the run's next tile are on
+  // their way during the epilogue of this one.  (Its stores come behind them in the counter of the vector-memory
+  // operations, so the waits of the next walk can only wait for more than they need.)
+  auto next_tile = [&]() __attribute__((always_inline)) {
+    if constexpr (RUN) {
+      n0 += BN;
+      if (n0 < n_stop) {
+        n_end = min(n_stop, n0 + BN);
+        h_left = w_left = nk - k0;  // the H pointers stand where they began, or a step behind
+        if (HALF && half)
+#pragma unroll
+          for (int q = 0; q < LH; ++q) gh[q] -= BK;
+        aim_w();
+        prologue();
+      }
+    }
+  };
   if (idle) {
     walk(std::true_type{});
     lds_barrier();
+    next_tile();
 #pragma unroll
-    for (int n = 0; n < NR; ++n) lp[(4 * wn + g) * BM + wm * WROWS + 16 * n + i16] = make_float2(kLowest, 0.f);
+    for (int n = 0; n < NR; ++n) {
+      const int rl = wm * WROWS + 16 * n + i16;
+      if constexpr (SLOTS == 4 * WN) lp[(4 * wn + g) * BM + rl] = make_float2(kLowest, 0.f);
+      else if (g < SLOTS / WN) lp[(SLOTS / WN * wn + g) * BM + rl] = make_float2(kLowest, 0.f);
+    }
   } else {
+#pragma unroll
+    for (int t = 0; t < NT / 2; ++t)
+#pragma unroll
+      for (int n = 0; n < NR; ++n) acc0[t][n] = acc1[t][n] = floatx4{0.f, 0.f, 0.f, 0.f};
+    settle<!ONE>(acc0, acc1);
     walk(std::false_type{});
+    if constexpr (HALF) drop(wf[1]);
 #pragma unroll
     for (int n = 0; n < NR; ++n)  // last slice of the last step
 #pragma unroll
@@ -387,13 +519,13 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
         mfma16<!ONE>(acc_at(t, n), wf[1][t], hf[ROLL ? 0 : 1][n]);
     settle<!ONE>(acc0, acc1);
     lds_barrier();  // nobody reads the rings any more
+    next_tile();
 
     // Epilogue.  Straight from the registers, row group by row group.
-    constexpr float kLog2e = 1.4426950408889634f;
     const float sc = a.inv_tau;
     const int v0 = vw + 4 * g;  // first token of the lane's piece of 16-token tile 0
     auto rows = [&](auto edge) __attribute__((always_inline)) {
-      constexpr bool EDGE = decltype(edge)::value;  // some of the wavefront's tokens lie past the workgroup's
+      constexpr bool EDGE = decltype(edge)::value;  // some of the wavefront's tokens (or, kTiles with WN = 2, rows) do not exist
 #pragma unroll
       for (int n = 0; n < NR; ++n) {
         const int rl = wm * WROWS + 16 * n + i16, row = m0 + rl;
@@ -405,7 +537,7 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
           // The lane that holds the row's label token stores its logit.  Most row groups hold none of their labels among
           // these tokens; where one does, the lanes pass their values through LDS (the W ring is free) to index them.
           const int off = row_ok ? a.labels[row] - vw : -1;
-          const bool mine = (unsigned)off < (unsigned)(16 * NT) && ((off >> 2) & 3) == g && vw + off < n_end;
+          const bool mine = (unsigned)off < (unsigned)(16 * NT) && ((off >> 2) & 3) == g && vw + off < tile_end;
           if (__builtin_amdgcn_ballot_w64(mine) != 0) {  // wavefront-uniform
             floatx4* own = reinterpret_cast<floatx4*>(ringW) + wave * (NT * kWave) + lane;
 #pragma unroll
@@ -420,7 +552,7 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
           // and push out the W and H lines the neighbouring workgroups are about to ask for (6 % at M = 256).
           const bool odd = i16 & 1;
           const int row2 = row & ~1;
-          const int pairs = EDGE ? (n_end - vw) / 32 : NT / 2;  // whole pairs of tiles, wavefront-uniform
+          const int pairs = EDGE ? (tile_end - vw) / 32 : NT / 2;  // whole pairs of tiles, wavefront-uniform
           float* dst = a.logits + (size_t)row2 * a.ldl + v0 + (odd ? 16 : 0);
           floatx4 x[NT / 2], y[NT / 2];
 #pragma unroll
@@ -444,13 +576,13 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
             float* one = a.logits + (size_t)row * a.ldl + v0;
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-              if (t / 2 < pairs || vw + 16 * t >= n_end || !row_ok) continue;
-              if (v0 + 16 * t + 3 < n_end) {
+              if (t / 2 < pairs || vw + 16 * t >= tile_end || !row_ok) continue;
+              if (v0 + 16 * t + 3 < tile_end) {
                 __builtin_nontemporal_store(l[t], reinterpret_cast<floatx4*>(one + 16 * t));
               } else {
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
-                  if (v0 + 16 * t + c < n_end) one[16 * t + c] = l[t][c];
+                  if (v0 + 16 * t + c < tile_end) one[16 * t + c] = l[t][c];
               }
             }
           }
@@ -460,98 +592,222 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
           for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-              if (v0 + 16 * t + c >= n_end) l[t][c] = -INFINITY;
+              if (v0 + 16 * t + c >= tile_end) l[t][c] = -INFINITY;
         }
-        float mx = kLowest;
+        auto max_of = [&](float mx, int t) __attribute__((always_inline)) -> float {
+          return vmax3(vmax3(l[t][0], l[t][1], mx), l[t][2], l[t][3]);
+        };
+        // l[t] becomes exp(l[t] - mx)
+        auto exps = [&](int t, float mx) __attribute__((always_inline)) {
+          const float mb = mx * -kLog2e;
 #pragma unroll
-        for (int t = 0; t < NT; ++t) mx = vmax3(vmax3(l[t][0], l[t][1], mx), l[t][2], l[t][3]);
-        const float mb = mx * -kLog2e;
-        float e = 0.f;
+          for (int c = 0; c < 4; ++c) l[t][c] = __builtin_amdgcn_exp2f(fmaf(l[t][c], kLog2e, mb));
+        };
+        if constexpr (CE) {
+          // nothing crosses lanes: the partial of the lane's own tokens
+          float mx = kLowest;
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          float x[4];
+          for (int t = 0; t < NT; ++t) mx = max_of(mx, t);
+          float e = 0.f;
 #pragma unroll
-          for (int c = 0; c < 4; ++c) x[c] = __builtin_amdgcn_exp2f(fmaf(l[t][c], kLog2e, mb));
-          e += (x[0] + x[1]) + (x[2] + x[3]);
+          for (int t = 0; t < NT; ++t) {
+            exps(t, mx);
+            e += (l[t][0] + l[t][1]) + (l[t][2] + l[t][3]);
+          }
+          lp[(4 * wn + g) * BM + rl] = make_float2(mx, e);
+        } else if constexpr (F == kRuns16) {
+          // one partial per 16-token tile: lane group g ends with that of tile g
+          float m[4], e[4];
+#pragma unroll
+          for (int t = 0; t < 4; ++t) m[t] = max_of(kLowest, t);
+          swap_quarters(m[0], m[1]);
+          swap_quarters(m[2], m[3]);
+          float lo = vmax(m[0], m[1]), hi = vmax(m[2], m[3]);
+          swap_halves(lo, hi);
+          const float mine = vmax(lo, hi);
+          m[0] = m[2] = mine;
+          swap_halves(m[0], m[2]);
+          m[1] = m[0];
+          m[3] = m[2];
+          swap_quarters(m[0], m[1]);
+          swap_quarters(m[2], m[3]);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            exps(t, m[t]);
+            e[t] = ((l[t][0] + l[t][1]) + l[t][2]) + l[t][3];
+          }
+          swap_quarters(e[0], e[1]);
+          swap_quarters(e[2], e[3]);
+          float x = e[0] + e[1], y = e[2] + e[3];
+          swap_halves(x, y);
+          lp[(4 * wn + g) * BM + rl] = make_float2(mine, x + y);
+        } else {
+          // sum over 64 neighbouring tokens, tiles t0 to t0 + 3, in every lane
+          auto block_sum = [&](int t0, float mx) __attribute__((always_inline)) -> float {
+            float e0[4], e1[4];
+#pragma unroll
+            for (int t = t0; t < t0 + 4; ++t) exps(t, mx);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              e0[c] = l[t0][c] + l[t0 + 2][c];
+              e1[c] = l[t0 + 1][c] + l[t0 + 3][c];
+            }
+            float x = group_sum(e0, e1), y = x;
+            swap_halves(x, y);
+            return x + y;
+          };
+          if constexpr (NT == 4) {
+            float mx = kLowest;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) mx = max_of(mx, t);
+            float o = mx;
+            group_max(mx, o);
+            const float e = block_sum(0, mx);
+            if (g == 0) lp[wn * BM + rl] = make_float2(mx, e);
+          } else {
+            // 128 tokens of 128 rows that all exist: the even and the odd 16-token tiles; else the two blocks of 64
+            const bool whole = !EDGE || ((row & ~15) < (M & ~127) && vw + 128 <= tile_end);  // wavefront-uniform
+            float m0 = kLowest, m1 = kLowest, e;
+            if (whole) {
+#pragma unroll
+              for (int t = 0; t < NT; t += 2) {
+                m0 = max_of(m0, t);
+                m1 = max_of(m1, t + 1);
+              }
+              group_max(m0, m1);
+              float e0[4], e1[4];
+#pragma unroll
+              for (int t = 0; t < NT; t += 2) {
+                exps(t, m0);
+                exps(t + 1, m1);
+              }
+#pragma unroll
+              for (int c = 0; c < 4; ++c) {
+                e0[c] = (l[0][c] + l[2][c]) + (l[4][c] + l[6][c]);
+                e1[c] = (l[1][c] + l[3][c]) + (l[5][c] + l[7][c]);
+              }
+              e = group_sum(e0, e1);
+            } else {
+#pragma unroll
+              for (int t = 0; t < NT / 2; ++t) {
+                m0 = max_of(m0, t);
+                m1 = max_of(m1, t + NT / 2);
+              }
+              group_max(m0, m1);
+              const float x = block_sum(0, m0), y = block_sum(NT / 2, m1);
+              e = g < 2 ? x : y;
+            }
+            if ((g & 1) == 0) lp[(2 * wn + (g >> 1)) * BM + rl] = make_float2(g ? m1 : m0, e);
+          }
         }
-        lp[(4 * wn + g) * BM + rl] = make_float2(mx, e);
       }
     };
-    if (vw + 16 * NT <= n_end) rows(std::false_type{});  // wavefront-uniform
+    const bool interior = vw + 16 * NT <= tile_end && (CE || NT == 4 || m0 + (wm + 1) * WROWS <= (M & ~127));
+    if (__builtin_amdgcn_readfirstlane((int)interior) != 0) rows(std::false_type{});
     else rows(std::true_type{});
   }
   lds_barrier();
-  // one (max, sum exp) partial per (row, workgroup), merged in a fixed order by the thread that owns the row
+  // One (max, sum exp) partial per (row, workgroup), merged in a fixed order by the thread that owns the row.  A run has
+  // its next partials written behind the barriers of its next walk.
   if (tid < BM && m0 + tid < M) {
-    constexpr float kLog2e = 1.4426950408889634f;
-    constexpr int SLOTS = 4 * WN;
-    float2 p[SLOTS];
-    float mx = kLowest;
+    if constexpr (F == kRuns16) {
 #pragma unroll
-    for (int c = 0; c < SLOTS; ++c) {
-      p[c] = lp[c * BM + tid];
-      mx = fmaxf(mx, p[c].x);
+      for (int t = 0; t < 16; ++t) {
+        const int w = t & 7;
+        if (tile0 + 16 * t < tile_end) {
+          const float2 p = lp[t * BM + tid];
+          if (p.x > run_m[w]) {
+            run_s[w] = run_s[w] * exp2f((run_m[w] - p.x) * kLog2e) + p.y;
+            run_m[w] = p.x;
+          } else {
+            run_s[w] += p.y * exp2f((p.x - run_m[w]) * kLog2e);
+          }
+        }
+      }
+    } else {
+      float2 p[SLOTS];
+      float mx = RUN ? run_m[0] : kLowest;
+#pragma unroll
+      for (int c = 0; c < SLOTS; ++c) {
+        p[c] = lp[c * BM + tid];
+        mx = fmaxf(mx, p[c].x);
+      }
+      float sum = RUN ? run_s[0] * exp2f((run_m[0] - mx) * kLog2e) : 0.f;
+#pragma unroll
+      for (int c = 0; c < SLOTS; ++c) sum += p[c].y * exp2f((p[c].x - mx) * kLog2e);
+      run_m[0] = mx;
+      run_s[0] = sum;
     }
-    float sum = 0.f;
+  }
+  if (!RUN || n0 >= n_stop) break;
+  }
+  if (tid < BM && m0 + tid < M) {
+    float mx = run_m[0], sum = run_s[0];
+    if constexpr (CHAINS > 1) {
 #pragma unroll
-    for (int c = 0; c < SLOTS; ++c) sum += p[c].y * exp2f((p[c].x - mx) * kLog2e);
+      for (int w = 0; w < CHAINS; ++w) mx = fmaxf(mx, run_m[w]);
+      sum = 0.f;
+#pragma unroll
+      for (int w = 0; w < CHAINS; ++w) sum += run_s[w] * exp2f((run_m[w] - mx) * kLog2e);
+    }
     a.partials[(size_t)(m0 + tid) * a.nT + nt] = make_float2(mx, sum);
   }
 }
 
-template <int NR, int WN, bool SHARES>
-hipError_t launch_tiles(const HeadArgs& a, int m_tiles) {
+template <int NR, int WN, Form F>
+hipError_t launch_form(const HeadArgs& a, int m_tiles) {
   const dim3 grid((unsigned)(8L * ((a.nT + 7) / 8) * m_tiles)), block(128 * WN);
-  if (a.labels) FEF_LAUNCH_HEAD((head_tiled256_kernel<NR, WN, SHARES, true>), grid, block, a, a, m_tiles);
-  else FEF_LAUNCH_HEAD((head_tiled256_kernel<NR, WN, SHARES, false>), grid, block, a, a, m_tiles);
+  FEF_LAUNCH_HEAD((head_tiled256_kernel<NR, WN, F>), grid, block, a, a, m_tiles);
   return hipGetLastError();
 }
 
 template <int NR>
 hipError_t launch_one(const HeadArgs& a) {  // one row tile of 32 NR rows
-  return a.nT == (a.V + BN - 1) / BN ? launch_tiles<NR, 4, false>(a, 1) : launch_tiles<NR, 4, true>(a, 1);
+  if (!a.labels) return launch_form<NR, 4, kTiles>(a, 1);
+  return a.nT == (a.V + BN - 1) / BN ? launch_form<NR, 4, kLossTiles>(a, 1) : launch_form<NR, 4, kLossShares>(a, 1);
 }
 
 }  // namespace
 
-// Token tiles of a launch over M rows = partials per row.  With one row tile the pass over W is what it costs, and
-// workgroups of whole 256-token tiles leave many CUs without work in the last round of 256: V = 100003 is 391 tiles,
+// Cross-entropy: token tiles of a launch over M rows = partials per row.  With one row tile the pass over W is what it costs,
+// and workgroups of whole 256-token tiles leave many CUs without work in the last round of 256: V = 100003 is 391 tiles,
 // one round and a half, V = 151936 is 594, two and a third, V = 32000 is 125, half a round.  There the tokens are dealt
-// out evenly over full rounds instead, in units of 32 (128 bytes of logits): 120 -> 110 us at 110 rows (d = 2560,
-// V = 100003), 233 -> 215 at 128 rows (d = 3584, V = 151936), 69 -> 51 at 64 rows (d = 4096, V = 32000), 155 -> 145 at 256
-// rows.  Where the last round is nearly full (V = 126464: 494 tiles, 238 in the last round) whole tiles are 2 % ahead;
-// hence the line at 200 of 256.  With several row tiles the multiplies are what it costs, and those of a partly filled
-// tile are not saved.
+// out evenly over full rounds instead, in units of 32: per call 121 -> 109 us at 110 rows (d = 2560, V = 100003), 233 -> 205
+// at 128 rows (d = 3584, V = 151936), 50.5 -> 46.3 at 64 rows (d = 4096, V = 32000), level at 256 rows.  Where the last round
+// is nearly full (V = 126464: 494 tiles, 238 in the last round) whole tiles are 2 % ahead; hence the line at 200 of 256.
+// With several row tiles the multiplies are what it costs, and those of a partly filled tile are not saved.  (A verify
+// step's tiles and runs are fixed by the order of its sums.)
 int tiled256_tiles(int V, int M) {
   const int whole = (V + BN - 1) / BN;
   const int rounds = (whole + 255) / 256, last = whole - 256 * (rounds - 1);
   if (M > BN || last > 200) return whole;
-  const int units = (V + kUnit - 1) / kUnit;
+  const int units = (V + kTiled256Unit - 1) / kTiled256Unit;
   return 256 * rounds < units ? 256 * rounds : units;
 }
 
 // ceil(M / 256) row tiles of equal height (a multiple of 32).  One row tile: eight wavefronts (two per SIMD: the kernel
-// is short of memory parallelism there, not of LDS rate).  Several: four wavefronts, 160 to 256 rows; but eight where the
-// walk over k is so short that prologue and epilogue, which two wavefronts per SIMD overlap better, are what a tile costs:
-// 49.8 -> 46.0 us at 512 rows of d = 512, V = 50257, 95 -> 90 at 1024 rows; even at d = 1024 (68 -> 66 at 512 rows of
-// V = 50257, 271 -> 274 at 1024 of V = 126464), 4 % behind at d = 4096.
+// is short of memory parallelism there, not of LDS rate).  Several: four wavefronts, 160 to 256 rows; but for the
+// cross-entropy eight where the walk over k is so short that prologue and epilogue, which two wavefronts per SIMD overlap
+// better, are what a tile costs (103.6 -> 97.6 us per call of 700 rows of d = 768, V = 80000; even at d = 1024, 4 % behind at
+// d = 4096).  In a verify step a partial there spans 128 tokens, which only four wavefronts hold in one: eight would save
+// 7 % at 512 rows of d = 512.
 hipError_t launch_head_tiled256(const HeadArgs& a) {
   const int m_tiles = (a.nrows + 255) / 256;
   const int nr = ((a.nrows + m_tiles - 1) / m_tiles + 31) / 32;
-  if (m_tiles > 1 && a.d < 1024) {
+  if (m_tiles > 1 && a.labels && a.d < 1024) {
     switch (nr) {
-      case 5: return launch_tiles<5, 4, false>(a, m_tiles);
-      case 6: return launch_tiles<6, 4, false>(a, m_tiles);
-      case 7: return launch_tiles<7, 4, false>(a, m_tiles);
-      default: return launch_tiles<8, 4, false>(a, m_tiles);
+      case 5: return launch_form<5, 4, kLossTiles>(a, m_tiles);
+      case 6: return launch_form<6, 4, kLossTiles>(a, m_tiles);
+      case 7: return launch_form<7, 4, kLossTiles>(a, m_tiles);
+      default: return launch_form<8, 4, kLossTiles>(a, m_tiles);
     }
   }
   if (m_tiles > 1) {
     switch (nr) {
-      case 5: return launch_tiles<5, 2, false>(a, m_tiles);
-      case 6: return launch_tiles<6, 2, false>(a, m_tiles);
-      case 7: return launch_tiles<7, 2, false>(a, m_tiles);
-      default: return launch_tiles<8, 2, false>(a, m_tiles);
+      case 5: return a.labels ? launch_form<5, 2, kLossTiles>(a, m_tiles) : launch_form<5, 2, kTiles>(a, m_tiles);
+      case 6: return a.labels ? launch_form<6, 2, kLossTiles>(a, m_tiles) : launch_form<6, 2, kTiles>(a, m_tiles);
+      case 7: return a.labels ? launch_form<7, 2, kLossTiles>(a, m_tiles) : launch_form<7, 2, kTiles>(a, m_tiles);
+      default: return a.labels ? launch_form<8, 2, kLossTiles>(a, m_tiles) : launch_form<8, 2, kTiles>(a, m_tiles);
     }
   }
   switch (nr) {
@@ -563,6 +819,22 @@ hipError_t launch_head_tiled256(const HeadArgs& a) {
     case 6: return launch_one<6>(a);
     case 7: return launch_one<7>(a);
     default: return launch_one<8>(a);
+  }
+}
+
+// Workgroups of a launch of runs = partials per row: one per CU, fewer where the vocabulary is short.  The first stages of a
+// workgroup's next tile are requested before the epilogue of the one in work.
+int runs_grid(int V, int unit) {
+  const int units = (V + unit - 1) / unit, per = unit == 64 ? 4 : 8;
+  const int want = (units + per - 1) / per;
+  return want < 256 ? want : 256;
+}
+hipError_t launch_head_runs(const HeadArgs& a, int unit) {
+  switch ((a.nrows + 31) / 32) {
+    case 1: return unit == 64 ? launch_form<1, 4, kRuns64>(a, 1) : launch_form<1, 4, kRuns16>(a, 1);
+    case 2: return unit == 64 ? launch_form<2, 4, kRuns64>(a, 1) : launch_form<2, 4, kRuns16>(a, 1);
+    case 3: return unit == 64 ? launch_form<3, 4, kRuns64>(a, 1) : launch_form<3, 4, kRuns16>(a, 1);
+    default: return unit == 64 ? launch_form<4, 4, kRuns64>(a, 1) : launch_form<4, 4, kRuns16>(a, 1);
   }
 }
 

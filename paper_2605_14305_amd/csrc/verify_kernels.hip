@@ -307,7 +307,7 @@ __global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
     // lane); with many it loads tile j*64 + l, 512 contiguous bytes per instruction, and hands
     // each exp-sum to its owner through this wavefront's slice of LDS (rows of PER + 1 floats,
     // an odd stride, so both directions are conflict-free).
-    constexpr bool EXCHANGE = PER > 12;
+    constexpr bool EXCHANGE = PER > 10;
     __shared__ float exchange[EXCHANGE ? NW : 1][EXCHANGE ? kWave * (PER + 1) : 1];
     float2 p[PER];
 #pragma unroll
@@ -383,20 +383,14 @@ __global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
       const int v0 = tile_start(a, tile.idx);
       const int nv = min(tile_start(a, tile.idx + 1), a.V) - v0;
       Found in;
-      auto in_registers = [&](auto per) {
-        constexpr int N = decltype(per)::value;
-        float q[N];
+      if (nv <= kWave * kTilePer) {
+        float q[kTilePer];
 #pragma unroll
-        for (int j = 0; j < N; ++j) {
-          const int i = lane * N + j;
+        for (int j = 0; j < kTilePer; ++j) {
+          const int i = lane * kTilePer + j;
           q[j] = i < nv ? expf(L[v0 + i] - lse) : 0.f;
         }
         in = wave_find_first_reg(q, u - tile.before);
-      };
-      if (nv <= kWave * 4) {
-        in_registers(std::integral_constant<int, 4>{});
-      } else if (nv <= kWave * kTilePer) {
-        in_registers(std::integral_constant<int, kTilePer>{});
       } else {
         in = wave_find_first(nv, [&](int i) { return expf(L[v0 + i] - lse); }, u - tile.before);
       }
@@ -901,7 +895,7 @@ hipError_t launch_verify(const VerifyArgs& a) {
   const dim3 g1((a.nrows + NW - 1) / NW);
   if (a.nT <= 64 * 4) hipLaunchKernelGGL(row_lse_draft_kernel<4>, g1, dim3(NT), 0, a.stream, a);
   else if (a.nT <= 64 * 8) hipLaunchKernelGGL(row_lse_draft_kernel<8>, g1, dim3(NT), 0, a.stream, a);
-  else if (a.nT <= 64 * 12) hipLaunchKernelGGL(row_lse_draft_kernel<12>, g1, dim3(NT), 0, a.stream, a);  // V = 151936: 594 tiles, 768 shares
+  else if (a.nT <= 64 * 10) hipLaunchKernelGGL(row_lse_draft_kernel<10>, g1, dim3(NT), 0, a.stream, a);  // V = 151936: 594 tiles
   else if (a.nT <= 64 * 40) hipLaunchKernelGGL(row_lse_draft_kernel<40>, g1, dim3(NT), 0, a.stream, a);
   else hipLaunchKernelGGL(row_lse_draft_kernel<0>, g1, dim3(NT), 0, a.stream, a);
   if (a.phase == 3) {
