@@ -419,8 +419,10 @@ __device__ void finalize_sequence(const VerifyArgs& a, int b, const SeqState& st
   const int BK = a.B * a.K;
   const int window = st.window, acc_len = st.acc_len;
 
-  // diagnostics: overlap and residual mass of every slot, one wavefront per slot, eight loads of each in flight
-  // (27 -> 13 us at 64 sequences x 16 slots of 494 chunks against a workgroup sum per slot)
+  // Diagnostics: overlap and residual mass of every slot, one wavefront per slot, eight loads of each in flight (27 -> 13 us
+  // at 64 sequences x 16 slots of 494 chunks against a workgroup sum per slot).  A residual mass that is the small difference
+  // of two laws shows the order of its terms: 256 chains over the chunks, 64 of them added at a time, four such sums in
+  // order, as a workgroup adds them.
   if (a.all_slots) {
     const int lane = tid & 63;
     for (int m = tid >> 6; m < a.K; m += NW) {
@@ -428,6 +430,7 @@ __device__ void finalize_sequence(const VerifyArgs& a, int b, const SeqState& st
       if (m < window) {
         const float* A = a.amass + (size_t)(b * a.K + m) * a.nRC;
         const float* R = a.rmass + (size_t)(b * a.K + m) * a.nRC;
+        float as[4] = {0.f, 0.f, 0.f, 0.f}, rs[4] = {0.f, 0.f, 0.f, 0.f};
         for (int c0 = lane; c0 < a.nRC; c0 += 8 * kWave) {
           float x[8], y[8];
 #pragma unroll
@@ -436,11 +439,17 @@ __device__ void finalize_sequence(const VerifyArgs& a, int b, const SeqState& st
             x[j] = c < a.nRC ? A[c] : 0.f;
             y[j] = c < a.nRC ? R[c] : 0.f;
           }
-          al += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
-          rm += ((y[0] + y[1]) + (y[2] + y[3])) + ((y[4] + y[5]) + (y[6] + y[7]));
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            as[j & 3] += x[j];
+            rs[j & 3] += y[j];
+          }
         }
-        al = wave_sum(al);
-        rm = wave_sum(rm);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          al += wave_sum(as[j]);
+          rm += wave_sum(rs[j]);
+        }
       }
       if (lane == 0) {
         if (a.diag_alpha) a.diag_alpha[b * a.K + m] = al;

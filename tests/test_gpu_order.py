@@ -15,7 +15,7 @@ from paper_2605_14305_amd import binding as fb
 pytestmark = pytest.mark.gpu
 
 GOLDEN = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "round_bits.txt")
-COLUMNS = ("logits", "lse", "draft_tokens", "tokens", "accepted", "conf")
+COLUMNS = ("logits", "lse", "draft_tokens", "tokens", "accepted", "conf", "alpha", "resid_mass")
 AUTO, TILED256, STREAM, ROWSTREAM = fb.FEF_GEMM_AUTO, fb.FEF_GEMM_TILED256, fb.FEF_GEMM_STREAM, fb.FEF_GEMM_ROWSTREAM
 
 # (kind, variant, B, K, d, V): the row counts and vocabularies at which another tile, share or epilogue begins
