@@ -65,7 +65,7 @@ typedef enum {
   FEF_OK = 0,
   FEF_ERR_INVALID_ARG = -1, /* NULL / misaligned pointer, size or parameter out of range   */
   FEF_ERR_UNSUPPORTED = -2, /* valid request that no kernel here serves                    */
-  FEF_ERR_WORKSPACE = -3,   /* workspace NULL or smaller than fef_workspace_bytes          */
+  FEF_ERR_WORKSPACE = -3,   /* workspace NULL, misaligned or smaller than the call needs   */
   FEF_ERR_HIP = -4          /* a HIP runtime call failed (see fef_last_error)              */
 } fef_status;
 
@@ -164,9 +164,10 @@ typedef struct {
                                   Confidences stay softmax(logits / tau)(token).  0: sample      */
 } fef_params;
 
-/* Bytes of device workspace a call with these sizes needs (depends on B, d, V, dtype,
- * gemm_variant, K, block and on whether diag_alpha / diag_resid_mass are requested).
- * Returns 0 if the arguments are invalid. */
+/* Bytes of device workspace that a call with these sizes is given: enough for a FUSED, a DRAFT and a
+ * TARGET call and for fef_topn_step, whatever prm->phase says (depends on B, d, V, dtype, gemm_variant,
+ * K, block and on whether diag_alpha / diag_resid_mass are requested).  Returns 0 if the arguments are
+ * invalid. */
 size_t fef_workspace_bytes(const fef_params* prm, int32_t K, int32_t block);
 
 /* One speculative round.  Argument order follows the statement of the problem:
@@ -213,7 +214,7 @@ fef_status fef_verify_step_static(const fef_params* prm, const void* h_draft, co
  *   out_committed [B]        min(n_transfer, window)
  *   out_remask    [B, block] unresolved positions after the step
  * Fields of prm that are read: as in a FEF_PHASE_DRAFT call (which fixes head kernel and workspace
- * size: fef_workspace_bytes with phase = DRAFT), plus greedy, conf and tokens_state (updated at
+ * size: fef_workspace_bytes), plus greedy, conf and tokens_state (updated at
  * the committed positions), diag_draft_tokens (the drawn token of every slot), diag_conf_tok
  * (its confidence), diag_lse (first B*K entries), diag_logits.  prm->phase must be FUSED (0);
  * draft_tokens, pass_mask, seq_pass and seq_rounds must be NULL. */

@@ -264,8 +264,6 @@ class VerifyStep:
         nbytes = fef_workspace_bytes(p, K, block)
         if nbytes == 0:
             raise FefError(FEF_ERR_INVALID_ARG, fef_last_error())
-        p.phase = FEF_PHASE_DRAFT          # split calls may pick another head kernel and layout
-        nbytes = max(nbytes, fef_workspace_bytes(p, K, block))
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
 
     def _params(self, **kw):

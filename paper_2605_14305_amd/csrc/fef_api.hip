@@ -238,7 +238,13 @@ fef_status fef_copy_probe(void* dst, const void* src, size_t nbytes, void* strea
 size_t fef_workspace_bytes(const fef_params* prm, int32_t K, int32_t block) {
   Layout L;
   if (make_layout(prm, K, block, &L) != FEF_OK) return 0;
-  return L.total;
+  // The halves of a split round share one workspace and may run another kernel than the whole round, with more partials
+  // per row: the size serves them all.
+  size_t need = L.total;
+  fef_params p = *prm;
+  for (p.phase = FEF_PHASE_FUSED; p.phase <= FEF_PHASE_TARGET; ++p.phase)
+    if (make_layout(&p, K, block, &L) == FEF_OK && L.total > need) need = L.total;
+  return need;
 }
 
 int32_t fef_select_gemm(const fef_params* prm, int32_t K) {
