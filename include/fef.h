@@ -194,7 +194,8 @@ fef_status fef_verify_step(const fef_params* prm, const void* h_draft, const voi
  * FEF_STATIC_SCRATCH_BYTES (32 MiB) built into the library, one copy per GPU, held until the
  * process ends.  The call allocates nothing.  A call that needs more than that
  * (at V = 126464: more than 64 rows through the head, 2*B*K fused) returns FEF_ERR_WORKSPACE and
- * enqueues nothing; a call whose fef_workspace_bytes does not exceed FEF_STATIC_SCRATCH_BYTES always fits.  The buffer keeps the previous call's contents; nothing in it has to start at
+ * enqueues nothing; a call whose fef_workspace_bytes does not exceed FEF_STATIC_SCRATCH_BYTES always
+ * fits.  The buffer keeps the previous call's contents; nothing in it has to start at
  * zero (every word is written before it is read within a call), and a TARGET call finds what the
  * DRAFT call before it left there.  All calls on one GPU share the buffer: calls that overlap in
  * time on one GPU (different streams or threads) race, so order them.  The first call on a device

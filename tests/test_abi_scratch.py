@@ -33,3 +33,22 @@ def test_limit_of_the_built_in_scratch(B, K, d):
         fits.append(s != fb.FEF_ERR_WORKSPACE)
         assert fits[-1] == (_total(B, K, V, variant) <= limit), (V, variant)
     assert any(fits) and not all(fits)
+
+
+@pytest.mark.parametrize("phase", [fb.FEF_PHASE_FUSED, fb.FEF_PHASE_DRAFT, fb.FEF_PHASE_TARGET])
+@pytest.mark.parametrize("B,K,d", [(1, 8, 4096), (3, 8, 4096), (5, 16, 4096), (5, 8, 4096), (7, 8, 1088), (13, 8, 512), (33, 8, 4096)])
+def test_a_workspace_of_that_size_always_fits(B, K, d, phase):
+    """What the header promises: fef_workspace_bytes <= FEF_STATIC_SCRATCH_BYTES is never refused for its size."""
+    lib, limit = fb.lib(), fb.FEF_STATIC_SCRATCH_BYTES
+    top = limit // (8 * B * K)
+    below = 0
+    for V in [*range(top - 900, top + 100, 4), 51872]:
+        p = fb.make_params(B, d, V)
+        p.phase = phase
+        if fb.fef_workspace_bytes(p, K, 32) > limit:
+            continue
+        below += 1
+        null = ctypes.c_void_p(0)
+        s = lib.fef_verify_step_static(ctypes.byref(p), null, null, null, K, 32, ctypes.c_uint64(0), null, null, null)
+        assert s == fb.FEF_ERR_INVALID_ARG, (V, fb.fef_last_error())
+    assert below
