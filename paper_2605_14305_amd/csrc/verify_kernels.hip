@@ -881,20 +881,22 @@ __global__ __launch_bounds__(kWave) void topn_kernel(VerifyArgs a) {
   }
 }
 
-// Logits of one row without the padding of the workspace rows.  grid = (rows, pieces of kCopyPer tokens); a thread asks
-// for all of its eight elements before it stores the first.  (One flat index divided by V per element before: 131 -> 122 us
+// Logits without the padding of the workspace rows.  grid = (rows, pieces of kCopyPer tokens), the rows capped (a launch
+// has less than 2^32 threads, a call up to 2^25 rows); a thread asks for all of its eight elements before it stores the first.  (One flat index divided by V per element before: 131 -> 122 us
 // per call of 128 rows of V = 126464, d = 1024, that keeps its logits.)
 constexpr int kCopyPer = 8 * NT;
-__global__ __launch_bounds__(NT) void copy_logits_kernel(const float* __restrict__ src, long ldl, float* __restrict__ dst, int V) {
-  const float* s = src + (size_t)blockIdx.x * ldl;
-  float* d = dst + (size_t)blockIdx.x * V;
-  for (long v0 = (long)blockIdx.y * kCopyPer + threadIdx.x; v0 < V; v0 += (long)gridDim.y * kCopyPer) {
-    float x[8];
+__global__ __launch_bounds__(NT) void copy_logits_kernel(const float* __restrict__ src, long ldl, float* __restrict__ dst, int V, int rows) {
+  for (int r = blockIdx.x; r < rows; r += gridDim.x) {
+    const float* s = src + (size_t)r * ldl;
+    float* d = dst + (size_t)r * V;
+    for (long v0 = (long)blockIdx.y * kCopyPer + threadIdx.x; v0 < V; v0 += (long)gridDim.y * kCopyPer) {
+      float x[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) x[j] = v0 + j * NT < V ? s[v0 + j * NT] : 0.f;
+      for (int j = 0; j < 8; ++j) x[j] = v0 + j * NT < V ? s[v0 + j * NT] : 0.f;
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (v0 + j * NT < V) d[v0 + j * NT] = x[j];
+      for (int j = 0; j < 8; ++j)
+        if (v0 + j * NT < V) d[v0 + j * NT] = x[j];
+    }
   }
 }
 
@@ -923,8 +925,8 @@ hipError_t launch_verify(const VerifyArgs& a) {
   }
   if (a.diag_logits) {
     const long pieces = (a.V + (long)kCopyPer - 1) / kCopyPer;
-    hipLaunchKernelGGL(copy_logits_kernel, dim3(a.nrows, pieces < 65535 ? pieces : 65535), dim3(NT), 0, a.stream,
-                       a.logits + (size_t)a.row0 * a.ldl, a.ldl, a.diag_logits + (size_t)a.row0 * a.V, a.V);
+    hipLaunchKernelGGL(copy_logits_kernel, dim3(a.nrows < 1 << 20 ? a.nrows : 1 << 20, pieces < 65535 ? pieces : 65535), dim3(NT), 0,
+                       a.stream, a.logits + (size_t)a.row0 * a.ldl, a.ldl, a.diag_logits + (size_t)a.row0 * a.V, a.V, a.nrows);
   }
   return hipGetLastError();
 }
