@@ -793,6 +793,28 @@ int tiled256_tiles(int V, int M) {
 // 7 % at 512 rows of d = 512.
 hipError_t launch_head_tiled256(const HeadArgs& a) {
   const int m_tiles = (a.nrows + 255) / 256;
+  // A launch of 2^32 threads or more runs only in part, without an error.  A cross-entropy call, whose logits need no
+  // memory, gets there within its documented rows (2^22 rows of V = 131072): several launches then.
+  const long most = ((1L << 32) - 1) / (8L * ((a.nT + 7) / 8) * 512);  // row tiles per launch
+  if (m_tiles > most && most > 0) {
+    const int rows = (int)most * 256;
+    for (int r = 0; r < a.nrows; r += rows) {
+      HeadArgs part = a;
+      part.row0 += r;
+      part.nrows = a.nrows - r < rows ? a.nrows - r : rows;
+      if (a.logits) part.logits += (size_t)r * a.ldl;
+      part.partials += (size_t)r * a.nT;
+      if (a.labels) {
+        part.labels += r;
+        part.label_logit += r;
+      }
+      part.ev_begin = r == 0 ? a.ev_begin : nullptr;
+      part.ev_end = r + rows >= a.nrows ? a.ev_end : nullptr;
+      const hipError_t e = launch_head_tiled256(part);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
   const int nr = ((a.nrows + m_tiles - 1) / m_tiles + 31) / 32;
   if (m_tiles > 1 && a.labels && a.d < 1024) {
     switch (nr) {

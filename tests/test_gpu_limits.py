@@ -22,3 +22,19 @@ def test_diagnostic_logits_of_2_to_24_rows():
             assert bool(((x - want).abs() <= 66 * 2.0 ** -24 * 512).all())
     del vs
     torch.cuda.empty_cache()
+
+
+def test_cross_entropy_of_2_to_22_rows_with_a_small_hidden_size():
+    R, d, V = (1 << 22) + 5, 64, 131072
+    W = torch.randn(V, d, device="cuda").mul_(0.3).bfloat16()
+    h = torch.randn(R, d, device="cuda", dtype=torch.bfloat16)
+    labels = torch.randint(0, V, (R,), device="cuda", dtype=torch.int32)
+    ce, _ = fb.HeadCrossEntropy(R, d, V)(h, W, labels)
+    torch.cuda.synchronize()
+    rows = torch.tensor([0, 1, 255, 256, 12345, R // 2, R - 257, R - 2, R - 1], device="cuda")
+    L = h[rows].double() @ W.double().t().contiguous()
+    want = torch.logsumexp(L, 1) - L.gather(1, labels[rows].long()[:, None])[:, 0]
+    # two terms of 66 half-ulps of products of magnitude below 64 together, and 1e-5 for exp, log and their sums
+    assert bool(((ce[rows].double() - want).abs() <= 2 * 66 * 2.0 ** -24 * 64 + 1e-5).all())
+    assert bool(torch.isfinite(ce).all())
+    torch.cuda.empty_cache()
