@@ -28,23 +28,29 @@ def build(verbose=True, extra_flags=()):
                 print(" ".join(cmd), flush=True)
             subprocess.run(cmd, check=True)
             return obj
-        check = pool.submit(check_accumulators_isa, verbose)
+        check = pool.submit(check_accumulators_isa, verbose, extra_flags)
         objs = list(pool.map(compile_one, sorted(SOURCES, key=lambda s: -os.path.getsize(os.path.join(CSRC, s)))))
-        cmd = [hipcc, "--offload-arch=gfx950", "-fPIC", "-shared", *objs, "-o", LIB]
+        fresh = LIB + ".new"  # takes the library's place only when the check has passed
+        cmd = [hipcc, "--offload-arch=gfx950", "-fPIC", "-shared", *objs, "-o", fresh]
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.run(cmd, check=True)
-        check.result()
+        try:
+            check.result()
+        except BaseException:
+            os.remove(fresh)
+            raise
+        os.replace(fresh, LIB)
     return LIB
 
 
-def _assembly(src):
+def _assembly(src, extra_flags=()):
     """Lines of the device assembly of one source."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     with tempfile.TemporaryDirectory() as tmp:
         out = os.path.join(tmp, "out.s")
         flags = [f for f in FLAGS if f != "-fPIC"]
-        subprocess.run([hipcc, *flags, "--cuda-device-only", "-S", os.path.join(CSRC, src), "-o", out], check=True,
+        subprocess.run([hipcc, *flags, *extra_flags, "--cuda-device-only", "-S", os.path.join(CSRC, src), "-o", out], check=True,
                        stderr=subprocess.DEVNULL)
         with open(out) as f:
             return f.read().split("\n")
@@ -61,27 +67,37 @@ def _regs(text):
     return out
 
 
-def check_accumulators_isa(verbose=True):
+def check_accumulators_isa(verbose=True, extra_flags=()):
     """The multiplies of head_gemm_tiled256.hip are inline assembly on accumulators in place, so the compiler does not
     know that a multiply's result, or a register that a multiply is about to read, needs wait states around other
     vector instructions.  That is sound as long as between the first and the last multiply of a kernel nothing but
-    multiplies touches an accumulator and no vector instruction (only LDS reads, which are waited for) writes a
-    register that a multiply reads.  This checks exactly that for each instantiation."""
-    lines = _assembly("head_gemm_tiled256.hip")
+    multiplies touches an accumulator, a multiply finds its own accumulator at least four multiplies old (it would need
+    no wait states behind the very multiply that wrote it: the same instruction on the same registers is forwarded, and
+    the compiler issues such chains back to back; four is what the smallest tile gives), and no vector instruction
+    writes a register within two wait states of a multiply that reads it (most come from LDS reads, which are waited
+    for).  This checks exactly that for each instantiation."""
+    check_accumulators(_assembly("head_gemm_tiled256.hip", extra_flags), verbose)
+
+
+def check_accumulators(lines, verbose=True):
     starts = [i for i, l in enumerate(lines) if re.match(r"^_Z\w*head_tiled256_kernel\w*:", l)]
     if not starts:
         raise RuntimeError("check_accumulators_isa: no kernel in the assembly")
     for start in starts:
-        end = next(i for i in range(start, len(lines)) if "s_endpgm" in lines[i])
+        end = next(i for i in range(start, len(lines)) if lines[i].startswith(".Lfunc_end"))
         name = lines[start].split(":")[0]
         mfma = [i for i in range(start, end) if lines[i].strip().startswith("v_mfma")]
         ops = [lines[i].strip().split(None, 1)[1].split(",") for i in mfma]
+        if not ops:
+            raise RuntimeError(f"check_accumulators_isa: {name}: no multiply")
         acc = set().union(*[_regs(o[0]) for o in ops])
-        for o, i in zip(ops, mfma):
+        for n, (o, i) in enumerate(zip(ops, mfma)):
             if o[0].strip() != o[3].strip():
                 raise RuntimeError(f"check_accumulators_isa: {name}: '{lines[i].strip()}' is not in place")
+            if any(_regs(o[0]) & _regs(p[0]) for p in ops[max(0, n - 3):n]):
+                raise RuntimeError(f"check_accumulators_isa: {name}: '{lines[i].strip()}' is less than four behind the last on its registers")
         recent = []  # vector instructions just before a multiply
-        for i in range(mfma[0], mfma[-1]):
+        for i in range(mfma[0], mfma[-1] + 1):
             t = lines[i].strip()
             if t.startswith("v_mfma"):
                 if any(_regs(t) & w for w in recent[-2:]):
@@ -93,7 +109,7 @@ def check_accumulators_isa(verbose=True):
                     raise RuntimeError(f"check_accumulators_isa: {name}: '{t}' touches an accumulator between multiplies")
                 recent.append(_regs(args.split(",")[0]))
             elif t and not t.startswith((";", ".")):
-                recent.append(set())
+                recent += [set()] * (int(t.split()[1]) + 1 if t.startswith("s_nop") else 1)
         if verbose:
             print(f"check_accumulators_isa: {name}: {len(mfma)} multiplies in place on {len(acc)} registers", flush=True)
 

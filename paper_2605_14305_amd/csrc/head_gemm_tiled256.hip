@@ -87,8 +87,11 @@ __device__ __forceinline__ void for_each(std::integer_sequence<int, I...>, F f) 
 // c += w h^T on 16 tokens x 16 rows x 32 columns of k, in place.  As inline assembly because the compiler gives the
 // builtin's result other registers than its addend (16x16 tiles may overlap freely), and a kernel whose accumulators
 // wander needs 80 registers more than one whose accumulators stay.  The hazards that the compiler would look after: a
-// multiply finds its own accumulator two dozen multiplies old or older; operands come from LDS reads, which it does
-// wait for; and settle() stands between zeroing and the first multiply, and between the last and the first other use.
+// multiply finds its own accumulator NT NR multiplies old, 4 at the least, and would need no wait states even right behind
+// the multiply that wrote it (the same instruction on the same registers is forwarded: the compiler issues such chains
+// back to back); operands come from LDS reads, which it does wait for, or from drop(), which waits itself; and settle()
+// stands between zeroing and the first multiply, and between the last and the first other use.  The build checks the
+// assembly for it (check_accumulators_isa in build.py).
 template <bool AGPR>
 __device__ __forceinline__ void mfma16(floatx4& c, const bf16x8& w, const bf16x8& h) {
   if constexpr (AGPR) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(w), "v"(h));
