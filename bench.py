@@ -52,18 +52,25 @@ class HipEvents:
         self.hip.hipEventDestroy(e)
 
 
-def tile_count(V, M):
-    """Token tiles of the 256-token tile kernel = partials per row (see tiled256_tiles in the library)."""
+def ce_tiles(V, R):
+    """Partials per row of a bf16 cross-entropy call (tiled256_tiles in the library): whole tiles of 256 tokens, or equal
+    shares over full rounds of the 256 CUs in units of 32 tokens."""
     whole = -(-V // 256)
     rounds = -(-whole // 256)
-    return whole if M > 256 or rounds == 1 or whole - 256 * (rounds - 1) > 200 else 256 * rounds
+    return whole if R > 256 or whole - 256 * (rounds - 1) > 200 else min(256 * rounds, -(-V // 32))
+
+
+def head_partials(V, variant):
+    """Partials per row that a head kernel leaves: one per workgroup for the kernels whose workgroups take a run of tokens."""
+    return {"skinny": min(-(-V // 16), 256), "rowstream": min(-(-V // 128), 256), "stream": min(-(-V // 256), 256),
+            "tiled256": -(-V // 256), "tiled": -(-V // 64), "f32": -(-V // 64)}[variant]
 
 
 def head_bytes(wl, M, variant):
     """Algorithmic HBM bytes of one vocabulary-head launch over M rows: W once, H once, fp32
     logits written once, the per-tile (max, sum exp) partials."""
     esz = 2 if wl.dtype == "bf16" else 4
-    nT = {"skinny": min(-(-wl.V // 16), 256), "tiled": -(-wl.V // 64), "f32": -(-wl.V // 64)}.get(variant) or tile_count(wl.V, M)
+    nT = head_partials(wl.V, variant)
     return wl.V * wl.d * esz + M * wl.d * esz + M * wl.V * 4 + M * nT * 8
 
 
@@ -163,7 +170,7 @@ def bench_cross_entropy(args, wl, W, Wd, dev):
     elapsed = time.perf_counter() - t0
     head_s = sum(ev.elapsed_ms(a, b) for a, b in pairs) / len(pairs) / 1e3
     esz = 2 if wl.dtype == "bf16" else 4
-    nT = tile_count(wl.V, R)
+    nT = ce_tiles(wl.V, R)
     hb = wl.V * wl.d * esz + R * wl.d * esz + R * nT * 8 + R * 4       # no logits are written
     flops = 2.0 * R * wl.V * wl.d
     if hb / (HBM_PEAK_GBS * 1e9) >= flops / (MFMA_BF16_PEAK_TFLOPS * 1e12):
@@ -382,7 +389,9 @@ def time_verify(args, wl, Wd, dev, steps, warmup):
     ms_per_step = elapsed / steps * 1e3
     positions = wl.B * wl.K
     M = positions if args.split else 2 * positions   # rows through one head launch
-    hb = head_bytes(wl, M, {fb.FEF_GEMM_SKINNY: "skinny", fb.FEF_GEMM_TILED: "tiled", fb.FEF_GEMM_F32: "f32"}.get(variant))
+    hb = head_bytes(wl, M, {fb.FEF_GEMM_SKINNY: "skinny", fb.FEF_GEMM_TILED: "tiled", fb.FEF_GEMM_F32: "f32",
+                            fb.FEF_GEMM_TILED256: "tiled256", fb.FEF_GEMM_STREAM: "stream",
+                            fb.FEF_GEMM_ROWSTREAM: "rowstream"}[variant])
     flops = 2.0 * M * wl.V * wl.d
     hbm_time, mfma_time = hb / (HBM_PEAK_GBS * 1e9), flops / (MFMA_BF16_PEAK_TFLOPS * 1e12)
     if hbm_time >= mfma_time:
