@@ -1,0 +1,64 @@
+"""The 256-token tile kernel where a workgroup's tokens are not one whole tile: runs of 16- and 64-token units over several
+tiles, equal shares of 32 to 256 tokens in the cross-entropy, and whole tiles beside partly filled ones, at every tile
+height (32 to 256 rows) and one row to either side of it.  Logits, log-sum-exps, cross-entropy against a float64 product."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_14305_amd import binding as fb
+
+pytestmark = pytest.mark.gpu
+
+# shares of one to eight units of 32 tokens (8200: 1 and 2; 16500: 2 and 3; 33001: 4 and 5; 50257: 6 and 7; 65536: 8), a
+# second round (66000, 100003); for the runs one tile per workgroup, one and a part, two and a part
+VOCABULARIES = [8200, 16500, 33001, 50257, 65535, 66000, 100003, 135000]
+
+
+def _bound(h, W, d, tau):
+    """bf16 products are exact in binary32; d sums in any order and one multiplication by 1/tau."""
+    return (d + 2) * 2.0 ** -24 * (h.abs() @ W.abs().t().contiguous()) * tau + 1e-30
+
+
+def _check_round(variant, M, d, V):
+    g = torch.Generator(device="cuda").manual_seed(M * 7 + V)
+    B, K = (M // 2, 1)
+    W = (torch.randn(V, d, generator=g, device="cuda") * 0.1).bfloat16()
+    hd, ht = (torch.randn(B, K, d, generator=g, device="cuda").bfloat16() for _ in range(2))
+    vs = fb.VerifyStep(B, K, 4, d, V, diag=True, diag_logits=True, gemm_variant=variant)
+    vs(hd, ht, W, 5, temperature=0.7)
+    h, W64 = torch.cat([hd.reshape(-1, d), ht.reshape(-1, d)]).double(), W.double()
+    tau = float(np.float32(1.0) / np.float32(0.7))
+    want, bound = (h @ W64.t().contiguous()) * tau, _bound(h, W64, d, tau)
+    assert bool(((vs.diag["logits"].view(-1, V) - want).abs() <= bound).all())
+    # 2e-5: exp, log and sums of at most 135000 terms (two levels of at most 640) at magnitudes below 64
+    assert bool(((vs.diag["lse"].view(-1) - torch.logsumexp(want, 1)).abs() <= bound.max(1).values + 2e-5).all())
+
+
+@pytest.mark.parametrize("V", VOCABULARIES)
+@pytest.mark.parametrize("variant,d", [(fb.FEF_GEMM_STREAM, 64), (fb.FEF_GEMM_STREAM, 192), (fb.FEF_GEMM_ROWSTREAM, 512)])
+def test_runs(variant, d, V):
+    for M in (2, 32, 34, 64, 66, 96, 98, 126, 128):
+        _check_round(variant, M, d, V)
+
+
+@pytest.mark.parametrize("V", [8200, 33001, 65535, 100003])
+def test_whole_tiles_of_one_row_tile(V):
+    for M in (32, 34, 96, 128, 130, 160, 162, 190, 194, 224, 226, 254, 256):
+        _check_round(fb.FEF_GEMM_TILED256, M, 128, V)
+
+
+@pytest.mark.parametrize("V", VOCABULARIES)
+def test_shares_of_a_cross_entropy_call(V):
+    for R in (1, 31, 33, 64, 65, 95, 97, 128, 129, 160, 161, 191, 193, 224, 225, 255, 256):
+        d = 64 + 64 * (R % 3)
+        g = torch.Generator(device="cuda").manual_seed(R + V)
+        W = (torch.randn(V, d, generator=g, device="cuda") * 0.1).bfloat16()
+        h = torch.randn(R, d, generator=g, device="cuda").bfloat16()
+        labels = torch.randint(0, V, (R,), generator=g, device="cuda", dtype=torch.int32)
+        labels[::5] = V - 1
+        ce, loss = fb.HeadCrossEntropy(R, d, V)(h, W, labels)
+        L = h.double() @ W.double().t().contiguous()
+        want = torch.logsumexp(L, 1) - L.gather(1, labels.long()[:, None])[:, 0]
+        bound = 2 * _bound(h.double(), W.double(), d, 1.0).max(1).values + 2e-5
+        assert bool(((ce - want).abs() <= bound).all()), R
+        assert abs(float(loss) - float(want.sum())) <= float(bound.sum())
