@@ -71,7 +71,7 @@ typedef enum {
 
 typedef enum {
   FEF_BF16 = 0, /* h_draft, h_target, W_vocab are bfloat16; MFMA path                      */
-  FEF_F32 = 1   /* all three are float32; plain FMA path for tiny instances                */
+  FEF_F32 = 1   /* all three are float32; fp32 matrix path, sums like a chain of FMAs       */
 } fef_dtype;
 
 /* Which vocabulary-head kernel to run.  AUTO picks by (dtype, M, d), M = rows through the head
@@ -79,9 +79,10 @@ typedef enum {
 typedef enum {
   FEF_GEMM_AUTO = 0,
   FEF_GEMM_SKINNY = 1, /* bf16, M <= 32, d in {512, 1024, 2048, 2560, 3072, 3584, 4096}: W streamed
-                          once, split-k; other d at M <= 32 go to STREAM (fef_select_gemm tells) */
+                          once, split-k; other d at M <= 32 go to ROWSTREAM or STREAM
+                          (fef_select_gemm tells)                                             */
   FEF_GEMM_TILED = 2,  /* bf16, any M: plain 128x128 LDS-tiled MFMA GEMM (never picked by AUTO) */
-  FEF_GEMM_F32 = 3,    /* f32, any shape: reference-grade FMA kernel                       */
+  FEF_GEMM_F32 = 3,    /* f32, any shape: reference-grade kernel, k in ascending order     */
   FEF_GEMM_TILED256 = 4, /* bf16, any M: LDS-tiled MFMA GEMM, 256 tokens x 32 to 256 rows per workgroup (AUTO: M > 128) */
   FEF_GEMM_STREAM = 5,   /* bf16, M <= 128: the same tiles, one workgroup per CU over a run of 64-token units (AUTO:
                             48 < M <= 64, 96 < M <= 128, and M <= 128 where neither SKINNY nor ROWSTREAM takes the

@@ -19,7 +19,8 @@
 //             2, 1, 0.  kRuns16: of 16 tokens, four neighbours in order, then bits 2 and 3.
 //   a row's   the partials of a tile in ascending order; kRuns64 goes on from tile to tile; kRuns16 keeps eight chains,
 //             every eighth tile of the run each, and adds the chains at the end.
-// The sums over lanes that this takes cost 0 to 3 % of the kernel (M = 2048 1606 -> 1615 us, M = 64 179 -> 182).
+// The sums over lanes and the runs that this takes cost nothing measurable at M = 2048 and 2 to 5 % up to 128 rows (64 rows of
+// d = 4096, V = 126464: 179 -> 182 to 187 us by trace).
 //
 // What bounds it, and what follows.
 // (1) Power.  With every matrix unit busy on real data the chip lowers its clock, so energy per multiply is time.  A
@@ -37,10 +38,11 @@
 // (4) Rows that do not exist.  M is cut into ceil(M / 256) row tiles of equal height, a multiple of 32 (300 rows:
 // two tiles of 160, not 256 + 44), one instantiation per height.
 //
-// Measured (head kernel, rocprofv3, median of 310; before: 32x32x16, tokens in the columns of D, 256-row tiles, and two
-// kernels built around streaming W up to 128 rows): d = 4096, V = 126464: 48 rows 189 -> 182 us, 64 rows 188 -> 186, 96 rows
-// 207 -> 188, 128 rows 200 -> 189, 256 rows 250 -> 254 (fastest 233), 2048 rows 1697 -> 1631 (fastest 1592); 110 rows of d = 2560,
-// V = 100003 159 -> 112.  Cross-entropy, 2048 rows 1600 -> 1470 to 1522, 300 rows (d = 2048, V = 50257) 138 -> 67.
+// Measured (head kernel by HIP events, unless marked t: by trace; before: 32x32x16, tokens in the columns of D, 256-row tiles,
+// and two kernels built around streaming W up to 128 rows): d = 4096, V = 126464: 48 rows 189 -> 182 us, 64 rows 188 -> 188, 96
+// rows 207 -> 187, 128 rows 200 -> 197, 256 rows 250 -> 240, 2048 rows 1697 -> 1590; 110 rows of d = 2560, V = 100003 159 -> 112 t;
+// 512 rows of d = 512, V = 50257 57.5 -> 50.1 t.  Cross-entropy, 2048 rows 1600 -> 1470 (1.44 PFLOP/s, matrix units busy 0.74 of
+// the cycles at 1.78 GHz), 300 rows (d = 2048, V = 50257) 138 -> 67 t.
 //
 // Operand slabs go HBM/L2 -> LDS directly (global_load_lds_dwordx4: lane l of a wavefront deposits its 16 bytes at
 // LDS base + 16 l): no register staging and no ds_write in the main loop.  A row of a stage is 128 bytes, so one load
