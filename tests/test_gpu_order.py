@@ -2,7 +2,7 @@
 bit; a draw from the tail of a law, or an accept test, that lies on the margin then falls the other way, and the committed
 tokens of that sequence with it (about one draft token in a thousand at a vocabulary of 1e5).  A program that records
 seeds and inputs to replay a decode relies on getting the same tokens from the same call, whatever tiles the kernels take.
-tests/golden/round_bits.txt holds checksums of the outputs of the calls below as the library gave them before its
+tests/golden/step_bits.txt holds checksums of the outputs of the calls below as the library gave them before its
 head kernels were rearranged around 16x16x32 multiplies; inputs are made from integers, so they are the same everywhere."""
 import os
 import zlib
@@ -14,26 +14,26 @@ from paper_2605_14305_amd import binding as fb
 
 pytestmark = pytest.mark.gpu
 
-GOLDEN = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "round_bits.txt")
+GOLDEN = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "step_bits.txt")
 COLUMNS = ("logits", "lse", "draft_tokens", "tokens", "accepted", "conf", "alpha", "resid_mass")
 AUTO, TILED256, STREAM, ROWSTREAM = fb.FEF_GEMM_AUTO, fb.FEF_GEMM_TILED256, fb.FEF_GEMM_STREAM, fb.FEF_GEMM_ROWSTREAM
 
 # (kind, variant, B, K, d, V): the row counts and vocabularies at which another tile, share or epilogue begins
 CASES = [
-    ("round", AUTO, 1, 8, 2048, 50257), ("topn", AUTO, 2, 16, 1024, 20001), ("f32", AUTO, 2, 9, 333, 5003),
+    ("fused", AUTO, 1, 8, 2048, 50257), ("topn", AUTO, 2, 16, 1024, 20001), ("f32", AUTO, 2, 9, 333, 5003),
     # runs of 16-token tiles: short vocabularies, several tiles of 256 tokens per workgroup, 32 to 128 rows
-    ("greedy", AUTO, 2, 8, 1536, 32000), ("round", AUTO, 3, 8, 512, 66000), ("round", AUTO, 5, 9, 512, 131500),
-    ("round", ROWSTREAM, 4, 16, 1024, 33001), ("round", ROWSTREAM, 1, 8, 512, 200), ("split", AUTO, 11, 8, 512, 50257),
+    ("greedy", AUTO, 2, 8, 1536, 32000), ("fused", AUTO, 3, 8, 512, 66000), ("fused", AUTO, 5, 9, 512, 131500),
+    ("fused", ROWSTREAM, 4, 16, 1024, 33001), ("fused", ROWSTREAM, 1, 8, 512, 200), ("split", AUTO, 11, 8, 512, 50257),
     # runs of 64-token units
-    ("round", AUTO, 1, 7, 64, 70001), ("round", AUTO, 4, 8, 320, 32000), ("round", AUTO, 7, 8, 960, 66000),
-    ("round", AUTO, 5, 11, 1088, 100003), ("round", AUTO, 8, 8, 512, 151936), ("split", AUTO, 8, 8, 576, 30011),
-    ("topn", AUTO, 3, 30, 1216, 65537), ("round", STREAM, 3, 8, 128, 130),
+    ("fused", AUTO, 1, 7, 64, 70001), ("fused", AUTO, 4, 8, 320, 32000), ("fused", AUTO, 7, 8, 960, 66000),
+    ("fused", AUTO, 5, 11, 1088, 100003), ("fused", AUTO, 8, 8, 512, 151936), ("split", AUTO, 8, 8, 576, 30011),
+    ("topn", AUTO, 3, 30, 1216, 65537), ("fused", STREAM, 3, 8, 128, 130),
     # whole tiles of 256 tokens, one row tile of any height
-    ("round", TILED256, 3, 6, 192, 20011), ("round", TILED256, 7, 9, 512, 33001), ("round", AUTO, 9, 8, 320, 66000),
-    ("round", AUTO, 11, 10, 512, 32000), ("round", AUTO, 16, 8, 960, 50257), ("split", AUTO, 10, 16, 192, 151936),
+    ("fused", TILED256, 3, 6, 192, 20011), ("fused", TILED256, 7, 9, 512, 33001), ("fused", AUTO, 9, 8, 320, 66000),
+    ("fused", AUTO, 11, 10, 512, 32000), ("fused", AUTO, 16, 8, 960, 50257), ("split", AUTO, 10, 16, 192, 151936),
     # several row tiles: hidden sizes below and above 1024, rows and tokens that do and do not fill blocks of 128
-    ("round", AUTO, 17, 8, 512, 60000), ("round", AUTO, 22, 16, 768, 33024), ("round", AUTO, 31, 9, 960, 40100),
-    ("round", AUTO, 16, 16, 1024, 30011), ("greedy", AUTO, 37, 9, 1088, 20001), ("split", AUTO, 33, 8, 640, 151936),
+    ("fused", AUTO, 17, 8, 512, 60000), ("fused", AUTO, 22, 16, 768, 33024), ("fused", AUTO, 31, 9, 960, 40100),
+    ("fused", AUTO, 16, 16, 1024, 30011), ("greedy", AUTO, 37, 9, 1088, 20001), ("split", AUTO, 33, 8, 640, 151936),
 ]
 
 
