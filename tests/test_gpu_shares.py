@@ -62,3 +62,28 @@ def test_shares_of_a_cross_entropy_call(V):
         bound = 2 * _bound(h.double(), W.double(), d, 1.0).max(1).values + 2e-5
         assert bool(((ce - want).abs() <= bound).all()), R
         assert abs(float(loss) - float(want.sum())) <= float(bound.sum())
+
+
+@pytest.mark.parametrize("variant,M", [(fb.FEF_GEMM_TILED256, 40), (fb.FEF_GEMM_STREAM, 40), (fb.FEF_GEMM_ROWSTREAM, 40),
+                                       (fb.FEF_GEMM_TILED256, 200), (fb.FEF_GEMM_TILED256, 300)])
+@pytest.mark.parametrize("first,last", [(640, 704), (512, 768), (16, 32), (1000, 3000)])
+def test_tokens_of_logit_minus_infinity(variant, M, first, last):
+    """Tokens banned by an overflowing column of W: a piece of a tile, or all of it, that holds nothing else brings no mass
+    and no NaN, and its neighbours keep theirs."""
+    d, V = 512, 9001
+    g = torch.Generator(device="cuda").manual_seed(first)
+    W = torch.randn(V, d, generator=g, device="cuda") * 0.1
+    W[first:last, 0] = -3e38
+    h = torch.randn(M, d, generator=g, device="cuda")
+    h[:, 0] = 8.0
+    W, h = W.bfloat16(), h.bfloat16()
+    vs = fb.VerifyStep(M // 2, 1, 4, d, V, diag=True, diag_logits=True, gemm_variant=variant)
+    vs(h[:M // 2].view(M // 2, 1, d), h[M // 2:].view(M // 2, 1, d), W, 1)
+    L = h.double() @ W.double().t().contiguous()
+    keep = torch.ones(V, dtype=torch.bool, device="cuda")
+    keep[first:last] = False
+    want, bound = torch.logsumexp(L[:, keep], 1), _bound(h.double(), W.double()[keep], d, 1.0).max(1).values + 2e-5
+    assert bool((vs.diag["lse"].view(-1) - want).abs().le(bound).all())
+    assert bool((vs.diag["logits"].view(M, V)[:, first:last] == -float("inf")).all())
+    drafts = vs.diag["draft_tokens"]
+    assert bool(((drafts < first) | (drafts >= last)).all())
