@@ -169,7 +169,8 @@ __device__ __forceinline__ float group_sum(float (&e0)[4], float (&e1)[4]) {
 enum Form { kTiles, kRuns64, kRuns16, kLossTiles, kLossShares };
 constexpr int form_unit(Form f) { return f == kRuns64 ? 64 : f == kRuns16 ? 16 : f == kLossShares ? kTiled256Unit : BN; }
 
-template <int NR, int WN, Form F>
+// STREAM_W: the refills of the W ring are non-temporal loads (see streams_w).
+template <int NR, int WN, Form F, bool STREAM_W>
 __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int m_tiles) {
   constexpr bool CE = F == kLossTiles || F == kLossShares;
   constexpr bool RUN = F == kRuns64 || F == kRuns16;  // a workgroup takes a run of tokens, 256 at a time
@@ -277,10 +278,16 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
 #pragma unroll
     for (int q = 0; q < LW; ++q) issue_one(gw[q], q, slotW + stage * kBytesW, move);
   };
-  auto group = [&](auto& p, uint32_t base, int& left) __attribute__((always_inline)) {
+  auto group = [&](auto& p, uint32_t base, int& left, auto stream) __attribute__((always_inline)) {
     constexpr int L = sizeof(p) / sizeof(p[0]);
+    static_assert(!decltype(stream)::value || L == 4, "W is streamed in groups of four");
     base = scalar(base);
-    if constexpr (L == 4)
+    if constexpr (decltype(stream)::value)
+      asm volatile("s_mov_b32 m0, %4\n\ts_nop 0\n\t"
+                   "global_load_lds_dwordx4 %0, off nt\n\tglobal_load_lds_dwordx4 %1, off offset:1024 nt\n\t"
+                   "global_load_lds_dwordx4 %2, off offset:2048 nt\n\tglobal_load_lds_dwordx4 %3, off offset:3072 nt"
+                   :: "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "s"(base) : "memory");
+    else if constexpr (L == 4)
       asm volatile("s_mov_b32 m0, %4\n\ts_nop 0\n\t"
                    "global_load_lds_dwordx4 %0, off\n\tglobal_load_lds_dwordx4 %1, off offset:1024\n\t"
                    "global_load_lds_dwordx4 %2, off offset:2048\n\tglobal_load_lds_dwordx4 %3, off offset:3072"
@@ -375,8 +382,8 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
         }
         if constexpr (m == kLoadAt) {
           if (more) {
-            if constexpr (KS == 0) group(gh, slotH + stage * kBytesH, h_left);
-            else group(gw, slotW + stage * kBytesW, w_left);
+            if constexpr (KS == 0) group(gh, slotH + stage * kBytesH, h_left, std::false_type{});
+            else group(gw, slotW + stage * kBytesW, w_left, std::bool_constant<STREAM_W>{});
           }
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -759,10 +766,23 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
   }
 }
 
+// With one row tile W is read once, and as ordinary loads it pushes H, which all workgroups read over and over, out of L2.
+// Non-temporal loads leave it there: per round of 64 rows of d = 4096, V = 126464 203 -> 179 us, of 128 rows 214 -> 188, of 256
+// rows 266 -> 258; 110 rows of d = 2560, V = 100003 127 -> 117.  But they pass by the Infinity Cache (256 MB) too, in which a
+// shorter W stays from one call to the next: 37 -> 45 us at 98 MB, 62 -> 66 at 257 MB, 63.4 -> 64.5 at 262 MB, 71.2 -> 70.1 and
+// (224 rows) 94.9 -> 91.4 at 309 MB.  Hence the line at 9/8 of its size.  The first stages of a tile stay ordinary loads (non-temporal
+// ones there cost 1 to 4 us per call), and so does W shared by several row tiles, which is read again out of L2 (300 rows of V = 50257
+// 68 -> 78 us, level at 512 and 2048 rows of 1 GB).
+bool streams_w(const HeadArgs& a) { return (size_t)a.V * a.d * 2 > (size_t)288 << 20; }
+
 template <int NR, int WN, Form F>
 hipError_t launch_form(const HeadArgs& a, int m_tiles) {
   const dim3 grid((unsigned)(8L * ((a.nT + 7) / 8) * m_tiles)), block(128 * WN);
-  FEF_LAUNCH_HEAD((head_tiled256_kernel<NR, WN, F>), grid, block, a, a, m_tiles);
+  if (WN == 4 && m_tiles == 1 && streams_w(a)) {
+    FEF_LAUNCH_HEAD((head_tiled256_kernel<NR, WN, F, WN == 4>), grid, block, a, a, m_tiles);
+  } else {
+    FEF_LAUNCH_HEAD((head_tiled256_kernel<NR, WN, F, false>), grid, block, a, a, m_tiles);
+  }
   return hipGetLastError();
 }
 

@@ -64,6 +64,28 @@ def test_shares_of_a_cross_entropy_call(V):
         assert abs(float(loss) - float(want.sum())) <= float(bound.sum())
 
 
+@pytest.mark.parametrize("variant,M", [(fb.FEF_GEMM_STREAM, 34), (fb.FEF_GEMM_STREAM, 128), (fb.FEF_GEMM_ROWSTREAM, 50),
+                                       (fb.FEF_GEMM_ROWSTREAM, 96), (fb.FEF_GEMM_TILED256, 32), (fb.FEF_GEMM_TILED256, 160),
+                                       (fb.FEF_GEMM_TILED256, 256)])
+@pytest.mark.parametrize("V", [36864, 36865])  # 288 MiB of W and a row more: ordinary and non-temporal loads
+def test_w_to_either_side_of_the_infinity_cache(variant, M, V):
+    _check_round(variant, M, 4096, V)
+
+
+@pytest.mark.parametrize("R", [30, 120, 250])
+@pytest.mark.parametrize("V", [36864, 36865])
+def test_cross_entropy_with_w_to_either_side_of_the_infinity_cache(R, V):
+    g = torch.Generator(device="cuda").manual_seed(R + V)
+    W = (torch.randn(V, 4096, generator=g, device="cuda") * 0.1).bfloat16()
+    h = torch.randn(R, 4096, generator=g, device="cuda").bfloat16()
+    labels = torch.randint(0, V, (R,), generator=g, device="cuda", dtype=torch.int32)
+    ce, _ = fb.HeadCrossEntropy(R, 4096, V)(h, W, labels)
+    L = h.double() @ W.double().t().contiguous()
+    want = torch.logsumexp(L, 1) - L.gather(1, labels.long()[:, None])[:, 0]
+    bound = 2 * _bound(h.double(), W.double(), 4096, 1.0).max(1).values + 2e-5
+    assert bool(((ce - want).abs() <= bound).all())
+
+
 @pytest.mark.parametrize("variant,M", [(fb.FEF_GEMM_TILED256, 40), (fb.FEF_GEMM_STREAM, 40), (fb.FEF_GEMM_ROWSTREAM, 40),
                                        (fb.FEF_GEMM_TILED256, 200), (fb.FEF_GEMM_TILED256, 300)])
 @pytest.mark.parametrize("first,last", [(640, 704), (512, 768), (16, 32), (1000, 3000)])
