@@ -67,14 +67,14 @@ def test_shares_of_a_cross_entropy_call(V):
 @pytest.mark.parametrize("variant,M", [(fb.FEF_GEMM_STREAM, 34), (fb.FEF_GEMM_STREAM, 128), (fb.FEF_GEMM_ROWSTREAM, 50),
                                        (fb.FEF_GEMM_ROWSTREAM, 96), (fb.FEF_GEMM_TILED256, 32), (fb.FEF_GEMM_TILED256, 160),
                                        (fb.FEF_GEMM_TILED256, 256)])
-@pytest.mark.parametrize("V", [36864, 36865])  # 288 MiB of W and a row more: ordinary and non-temporal loads
-def test_w_to_either_side_of_the_infinity_cache(variant, M, V):
+@pytest.mark.parametrize("V", [10240, 10241])  # 80 MiB of W and a row more: ordinary and non-temporal loads
+def test_w_to_either_side_of_the_line_for_non_temporal_loads(variant, M, V):
     _check_round(variant, M, 4096, V)
 
 
 @pytest.mark.parametrize("R", [30, 120, 250])
-@pytest.mark.parametrize("V", [36864, 36865])
-def test_cross_entropy_with_w_to_either_side_of_the_infinity_cache(R, V):
+@pytest.mark.parametrize("V", [10240, 10241])
+def test_cross_entropy_to_either_side_of_that_line(R, V):
     g = torch.Generator(device="cuda").manual_seed(R + V)
     W = (torch.randn(V, 4096, generator=g, device="cuda") * 0.1).bfloat16()
     h = torch.randn(R, 4096, generator=g, device="cuda").bfloat16()
