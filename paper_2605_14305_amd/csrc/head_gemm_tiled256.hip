@@ -766,20 +766,10 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
   }
 }
 
-// With one row tile W is read once, and as ordinary loads it pushes H, which all workgroups read over and over, out of L2.
-// Non-temporal loads leave it there: per round of 64 rows of d = 4096, V = 126464 203 -> 179 us, of 128 rows 214 -> 188, of 256
-// rows 267 -> 254; 110 rows of d = 2560, V = 100003 128 -> 122; 80 rows of V = 50257 59 -> 54 (d = 2048) and 39 -> 36 (d = 1024); a
-// cross-entropy of 27 rows of d = 3072, V = 16746 34 -> 31 (W not in the Infinity Cache at the start of a call, as behind a model's
-// forward pass).  They pass by the Infinity Cache (256 MB) too, where a short W may stay from one call to the next: in calls that
-// follow one another on three heads in turn 30.7 -> 33.1 us at 65 MB of W.  Hence the line below a third of its size.  The
-// first stages of a tile stay ordinary loads (non-temporal ones there cost 1 to 4 us per call), and so does W shared by several row tiles,
-// which is read again out of L2 (300 rows of V = 50257 68 -> 78 us, level at 512 and 2048 rows of 1 GB).
-bool streams_w(const HeadArgs& a) { return (size_t)a.V * a.d * 2 > (size_t)80 << 20; }
-
 template <int NR, int WN, Form F>
 hipError_t launch_form(const HeadArgs& a, int m_tiles) {
   const dim3 grid((unsigned)(8L * ((a.nT + 7) / 8) * m_tiles)), block(128 * WN);
-  if (WN == 4 && m_tiles == 1 && streams_w(a)) {
+  if (WN == 4 && m_tiles == 1 && streams_w(a, 2)) {
     FEF_LAUNCH_HEAD((head_tiled256_kernel<NR, WN, F, WN == 4>), grid, block, a, a, m_tiles);
   } else {
     FEF_LAUNCH_HEAD((head_tiled256_kernel<NR, WN, F, false>), grid, block, a, a, m_tiles);

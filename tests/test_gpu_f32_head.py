@@ -44,3 +44,44 @@ def test_f32_cross_entropy(R, d, V):
     bound = 2 * (d + 2) * 2.0 ** -24 * (h.double().abs() @ W.double().abs().t()).max(1).values + 1e-5
     assert bool(((ce.double().cpu() - want).abs() <= bound).all())
     assert abs(float(loss) - float(want.sum())) <= float(bound.sum())
+
+
+def _check_rows(M, d, V):
+    g = torch.Generator(device="cuda").manual_seed(M * 1000 + d)
+    W, h = torch.randn(V, d, generator=g, device="cuda"), torch.randn(M, d, generator=g, device="cuda")
+    vs = fb.VerifyStep(M // 2, 1, 4, d, V, dtype="f32", diag=True, diag_logits=True)
+    vs(h[:M // 2].view(M // 2, 1, d), h[M // 2:].clone().view(M // 2, 1, d), W, 5)
+    want = h.double() @ W.double().t().contiguous()
+    bound = (d + 2) * 2.0 ** -24 * (h.double().abs() @ W.double().abs().t().contiguous()) + 1e-30  # as above
+    assert bool(((vs.diag["logits"].view(M, V) - want).abs() <= bound).all())
+    assert bool(((vs.diag["lse"].view(M) - torch.logsumexp(want, 1)).abs() <= bound.max(1).values + 1e-5).all())
+
+
+@pytest.mark.parametrize("d", [1, 4, 28, 31, 32, 33, 60, 64, 68, 95, 97, 128, 131])  # one to five steps of 32 columns
+def test_f32_edges_of_steps(d):
+    for M in (2, 16, 18, 34, 50):
+        _check_rows(M, d, 257)
+
+
+@pytest.mark.parametrize("V", [15297, 15360, 15361])  # up to 64 rows per workgroup from 240 token tiles on
+def test_f32_row_tiles(V):
+    for M in (14, 16, 18, 32, 34, 48, 50, 64, 66, 96, 130):
+        _check_rows(M, 37, V)
+
+
+@pytest.mark.parametrize("d,V", [(1024, 20480), (1024, 20481), (1023, 20500), (1023, 20501)])  # 80 MiB of W and more
+def test_f32_to_either_side_of_the_line_for_non_temporal_loads(d, V):
+    for M in (16, 32, 48, 64):
+        _check_rows(M, d, V)
+
+
+@pytest.mark.parametrize("d", [(1 << 24) - 1, 1 << 24, (1 << 24) + 1])
+def test_f32_rows_of_two_to_the_24(d):
+    at = torch.tensor([0, 5, d // 2, d - 2, d - 1], device="cuda")  # few terms, so that the bound means something
+    W = torch.zeros(5, d, device="cuda").normal_()
+    h = torch.zeros(4, d, device="cuda")
+    h[:, at] = torch.randn(4, 5, device="cuda")
+    vs = fb.VerifyStep(2, 1, 4, d, 5, dtype="f32", diag=True, diag_logits=True)
+    vs(h[:2].view(2, 1, d), h[2:].clone().view(2, 1, d), W, 5)
+    terms = h[:, None, at].double() * W[None][:, :, at].double()
+    assert bool(((vs.diag["logits"].view(4, 5) - terms.sum(2)).abs() <= 7 * 2.0 ** -24 * terms.abs().sum(2)).all())
