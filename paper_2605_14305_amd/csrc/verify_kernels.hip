@@ -771,9 +771,12 @@ __global__ __launch_bounds__(NT) void accept_resid_kernel(VerifyArgs a) {
 // for all of them before it uses the first.  Bound: the two passes' worth of exponentials and one read of all logits
 // (1.04 GB at 64 x 16 slots, V = 126464).  Which slot was rejected does not matter here, so nothing waits for the
 // accept tests (the final kernel does them); with them repeated in front of every chunk this took 260 us, now
-// 185 (5.6 TB/s).
+// 185 (5.6 TB/s).  COPY: a call that wants the logits too gets them from here, where they are in registers: 122 -> 112 us per
+// call of 128 rows of d = 1024, V = 126464 against a kernel that reads them once more, 106 -> 101 at V = 100003, and a launch less
+// (51.2 -> 50.0 at 32 fp32 rows of V = 32000).
 // ---------------------------------------------------------------------------------------------
 constexpr int kMassPer = 4;
+template <bool COPY>
 __global__ __launch_bounds__(NT) void slot_mass_kernel(VerifyArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int s = blockIdx.x, BK = a.B * a.K;
@@ -786,6 +789,38 @@ __global__ __launch_bounds__(NT) void slot_mass_kernel(VerifyArgs a) {
   Quad x[kMassPer];
 #pragma unroll
   for (int j = 0; j < kMassPer; ++j) x[j] = load_quad(a, Lq, Lp, (c0 + j) * kResidChunk + lane * 4);
+  if constexpr (COPY) {
+    // diagnostic logits: these rows without the padding, while they are in registers; of the target half of a split round
+    // its own rows only
+    float* Dq = a.diag_logits + (size_t)s * a.V;
+    float* Dp = a.diag_logits + (size_t)(BK + s) * a.V;
+    const bool quads = a.V % 4 == 0 && (reinterpret_cast<uintptr_t>(a.diag_logits) & 15) == 0, draft = a.row0 == 0;
+#pragma unroll
+    for (int j = 0; j < kMassPer; ++j) {
+      const int v = (c0 + j) * kResidChunk + lane * 4;
+      if (quads) {
+        if (v < a.V) {
+          if (draft) *reinterpret_cast<float4*>(Dq + v) = make_float4(x[j].q[0], x[j].q[1], x[j].q[2], x[j].q[3]);
+          *reinterpret_cast<float4*>(Dp + v) = make_float4(x[j].p[0], x[j].p[1], x[j].p[2], x[j].p[3]);
+        }
+      } else {  // 256 neighbouring bytes per store instruction, through this wavefront's slice of LDS
+        __shared__ __attribute__((aligned(16))) float turn[COPY ? NW : 1][2][kResidChunk];
+        float(&t)[2][kResidChunk] = turn[wave];
+        *reinterpret_cast<float4*>(&t[0][lane * 4]) = make_float4(x[j].q[0], x[j].q[1], x[j].q[2], x[j].q[3]);
+        *reinterpret_cast<float4*>(&t[1][lane * 4]) = make_float4(x[j].p[0], x[j].p[1], x[j].p[2], x[j].p[3]);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // same wavefront on both sides: order only
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int w = (c0 + j) * kResidChunk + i * kWave + lane;
+          if (w < a.V) {
+            if (draft) Dq[w] = t[0][i * kWave + lane];
+            Dp[w] = t[1][i * kWave + lane];
+          }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+      }
+    }
+  }
   if (s % a.K >= window) return;
 #pragma unroll
   for (int j = 0; j < kMassPer; ++j) {
@@ -911,7 +946,7 @@ __global__ __launch_bounds__(kWave) void topn_kernel(VerifyArgs a) {
   }
 }
 
-// Logits without the padding of the workspace rows.  grid = (rows, pieces of kCopyPer tokens), the rows capped (a launch
+// Logits without the padding of the workspace rows, for calls without slot_mass_kernel.  grid = (rows, pieces of kCopyPer tokens), the rows capped (a launch
 // has less than 2^32 threads, a call up to 2^25 rows); a thread asks for all of its eight elements before it stores the first.  (One flat index divided by V per element before: 131 -> 122 us
 // per call of 128 rows of V = 126464, d = 1024, that keeps its logits.)
 constexpr int kCopyPer = 8 * NT;
@@ -943,8 +978,9 @@ hipError_t launch_verify(const VerifyArgs& a) {
     hipLaunchKernelGGL(topn_kernel, dim3(a.B), dim3(kWave), 0, a.stream, a);
   } else if (a.phase != 1) {  // everything after the draft sample needs the target laws
     if (a.all_slots) {
-      hipLaunchKernelGGL(slot_mass_kernel, dim3(a.B * a.K, (a.nRC + NW * kMassPer - 1) / (NW * kMassPer)), dim3(NT), 0,
-                         a.stream, a);
+      const dim3 grid(a.B * a.K, (a.nRC + NW * kMassPer - 1) / (NW * kMassPer));
+      if (a.diag_logits) hipLaunchKernelGGL(slot_mass_kernel<true>, grid, dim3(NT), 0, a.stream, a);
+      else hipLaunchKernelGGL(slot_mass_kernel<false>, grid, dim3(NT), 0, a.stream, a);
       hipLaunchKernelGGL(finalize_kernel<kSlots>, dim3(a.B), dim3(NT), 0, a.stream, a);
     } else if (a.nRC <= kAloneChunks || a.greedy) {
       hipLaunchKernelGGL(finalize_kernel<kAlone>, dim3(a.B), dim3(NT), 0, a.stream, a);
@@ -953,7 +989,7 @@ hipError_t launch_verify(const VerifyArgs& a) {
       hipLaunchKernelGGL(finalize_kernel<kHandoff>, dim3(a.B), dim3(NT), 0, a.stream, a);
     }
   }
-  if (a.diag_logits) {
+  if (a.diag_logits && (!a.all_slots || a.phase == 1 || a.phase == 3)) {  // else slot_mass_kernel has written them
     const long pieces = (a.V + (long)kCopyPer - 1) / kCopyPer;
     hipLaunchKernelGGL(copy_logits_kernel, dim3(a.nrows < 1 << 20 ? a.nrows : 1 << 20, pieces < 65535 ? pieces : 65535), dim3(NT), 0,
                        a.stream, a.logits + (size_t)a.row0 * a.ldl, a.ldl, a.diag_logits + (size_t)a.row0 * a.V, a.V, a.nrows);
