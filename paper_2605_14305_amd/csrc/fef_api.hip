@@ -357,17 +357,6 @@ fef_status run_step(const fef_params* prm, int phase, int n_transfer, const void
   h.partials = (float2*)(ws + L.off_partials) + (size_t)h.row0 * L.nT; h.nT = L.nT;
   h.stream = stream;
   h.ev_begin = (hipEvent_t)prm->ev_head_begin; h.ev_end = (hipEvent_t)prm->ev_head_end;
-  hipError_t e;
-  switch (L.variant) {
-    case FEF_GEMM_SKINNY: e = fef::launch_head_skinny(h); break;
-    case FEF_GEMM_TILED: e = fef::launch_head_tiled(h); break;
-    case FEF_GEMM_TILED256: e = fef::launch_head_tiled256(h); break;
-    case FEF_GEMM_STREAM:
-    case FEF_GEMM_ROWSTREAM: e = fef::launch_head_runs(h, run_unit(L.variant)); break;
-    default: e = fef::launch_head_f32(h); break;
-  }
-  if (e != hipSuccess) return fail(FEF_ERR_HIP, "head kernel launch: %s", hipGetErrorString(e));
-
   fef::VerifyArgs v;
   memset(&v, 0, sizeof v);
   v.B = prm->B; v.K = K; v.block = block; v.V = prm->V;
@@ -397,6 +386,22 @@ fef_status run_step(const fef_params* prm, int phase, int n_transfer, const void
   v.diag_logits = prm->diag_logits; v.diag_conf_tok = prm->diag_conf_tok;
   v.stream = stream;
   v.n_transfer = n_transfer;
+  // (events mark the head kernel alone; the masses of every slot and the logits come from kernels of their own)
+  if (L.variant == FEF_GEMM_F32 && phase == FEF_PHASE_FUSED && !h.ev_begin && !v.all_slots && !v.diag_logits && fef::toy_round_serves(v.B, K, h.d, h.V)) {
+    const hipError_t e = fef::launch_toy_round(h, v);
+    if (e != hipSuccess) return fail(FEF_ERR_HIP, "round kernel launch: %s", hipGetErrorString(e));
+    return FEF_OK;
+  }
+  hipError_t e;
+  switch (L.variant) {
+    case FEF_GEMM_SKINNY: e = fef::launch_head_skinny(h); break;
+    case FEF_GEMM_TILED: e = fef::launch_head_tiled(h); break;
+    case FEF_GEMM_TILED256: e = fef::launch_head_tiled256(h); break;
+    case FEF_GEMM_STREAM:
+    case FEF_GEMM_ROWSTREAM: e = fef::launch_head_runs(h, run_unit(L.variant)); break;
+    default: e = fef::launch_head_f32(h); break;
+  }
+  if (e != hipSuccess) return fail(FEF_ERR_HIP, "head kernel launch: %s", hipGetErrorString(e));
   e = fef::launch_verify(v);
   if (e != hipSuccess) return fail(FEF_ERR_HIP, "verify kernel launch: %s", hipGetErrorString(e));
   return FEF_OK;

@@ -136,6 +136,8 @@ struct VerifyArgs {
 };
 
 hipError_t launch_verify(const VerifyArgs& a);
+bool toy_round_serves(int B, int K, int d, int V);
+hipError_t launch_toy_round(const HeadArgs& h, const VerifyArgs& a);  // head and verify step in one launch
 
 // Cross-entropy finish: per-row log-sum-exp from the partials, ce = lse - label logit, then the
 // sum over rows in a fixed order.

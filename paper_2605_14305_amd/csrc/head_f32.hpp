@@ -1,0 +1,257 @@
+// The fp32 vocabulary head, one tile at a time: shared by the head kernel for fp32 inputs (head_gemm.hip) and the kernel that does the
+// whole round of a toy vocabulary (verify_kernels.hip).
+#pragma once
+#include <float.h>
+
+#include <type_traits>
+
+#include "head_common.hpp"
+
+namespace fef {
+namespace {
+
+// ---------------------------------------------------------------------------------------------
+// fp32 kernel: workgroup tile of 64 tokens x MR rows of H (16 to 64), k in steps of 32, four wavefronts of
+// 16 tokens x MR rows each on v_mfma_f32_16x16x4_f32 (products and sums in binary32, like FMA).
+//
+// Bound: the one pass over W (HBM), or the fp32 matrix rate once there are some tens of rows (32 rows of 131 MB: 21 and 14 us).
+// W and H go straight from memory to LDS, two steps ahead in a ring of three stages: rows of 128 contiguous bytes, every W element
+// once per MR rows, one barrier per step, and 31 to 51 KB per workgroup, so that three to five share a CU.  The fragments of
+// a step are read while the step before is multiplied.  What it measured, per call with diagnostics and logits, against the form before
+// (one step ahead through registers, 32 or 64 rows): 16 rows of d = 1024, V = 32000 50 -> 42 us, 32 rows 55 -> 52; 48 rows of d = 599,
+// V = 18136 58 -> 48; 4 rows of d = 475, V = 17778 36 -> 31; 16 rows of V = 151936 (round) 165 -> 136.  Four or six stages, steps of 64
+// columns and eight wavefronts: equal or slower.
+//
+// Operand layout of the 16x16x4 multiply (lane l, i = l % 16, g = l / 16): A[i][g], B[g][i], one
+// float each.  The sums run over k in ascending order, one rounding per product like a chain of FMAs: multiply c of a step takes
+// columns 4 c .. 4 c + 3, one from each lane group.  A = W, B = H: D[4 g + r][i] puts four consecutive tokens of one row in a lane.
+// A stage is [rows][8 chunks of 16 bytes], chunk c of row r at c ^ ((r >> 1) & 7): two rows cover the 64 banks, so the 64 reads of
+// a fragment (16 rows, the four columns of a chunk) fall on different ones.  The permutation is applied on the global side of the load.
+//
+// VEC = 4: d is a multiple of 4, rows are 16-byte aligned and come in pieces of 16 bytes; VEC = 1: any d, 4 bytes per lane.
+// STREAM_W: W in non-temporal loads (see streams_w).  WIDE: rows so long that 64 of them pass 4 GB (d > 2^24): W by 64-bit addresses.
+// ---------------------------------------------------------------------------------------------
+constexpr int kF32Tokens = kTiledTn, kF32Tk = 32, kF32Stages = 3;
+
+// Direct-to-LDS loads of VEC floats per lane, to LDS offset lds_off + 4 VEC l: from an address, or from an offset in bytes to a
+// uniform one.
+template <int VEC>
+__device__ inline void load_to_lds(const float* p, uint32_t lds_off) {
+  if constexpr (VEC == 4)
+    load_to_lds_16(p, lds_off);
+  else
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" :: "v"(p), "s"(lds_off) : "memory");
+}
+template <int VEC, bool STREAM>
+__device__ inline void load_to_lds(const float* base, uint32_t offset, uint32_t lds_off) {
+  if constexpr (VEC == 4 && STREAM)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" :: "v"(offset), "s"(base), "s"(lds_off) : "memory");
+  else if constexpr (VEC == 4)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" :: "v"(offset), "s"(base), "s"(lds_off) : "memory");
+  else if constexpr (STREAM)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1 nt" :: "v"(offset), "s"(base), "s"(lds_off) : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" :: "v"(offset), "s"(base), "s"(lds_off) : "memory");
+}
+// Wait until all loads but those of the last `stages` (at most MAX) stages of PER loads are done.
+template <int MAX, int PER>
+__device__ inline void wait_stages(int stages) {
+  if constexpr (MAX == 0) wait_newer<0>();
+  else if (stages >= MAX) wait_newer<MAX * PER>();
+  else wait_stages<MAX - 1, PER>(stages);
+}
+
+// One tile: 16 TW tokens from token n0 on (64-token partial n0 / 64 first) x rows m0 .. m0 + rows - 1 of the launch, by TW wavefronts of
+// 16 tokens each.  h_of(m): row m.  logits, partials: of row 0, rows ldl and a.nT apart.  ring: f32_ring_floats<TW, MR>() floats, free
+// when the function is entered; everybody leaves it behind a barrier.
+template <int TW, int MR>
+constexpr int f32_ring_floats() { return kF32Stages * (16 * TW + MR) * kF32Tk; }
+
+template <int TW, int MR, int VEC, bool STREAM_W, bool WIDE, class RowPtr>
+__device__ __forceinline__ void f32_tile(const HeadArgs& a, long n0, int m0, int rows, RowPtr h_of, float* logits, long ldl, float2* partials,
+                                         float* ring, float (*tile_max)[TW]) {
+  constexpr int NR = MR / 16;                 // 16-row groups of H
+  constexpr int TK = kF32Tk, ST = kF32Stages, TOKENS = 16 * TW;
+  constexpr int LW = TK / (4 * VEC);                                                      // load instructions per wavefront and stage
+  constexpr int kLoadsH = MR * TK / (64 * VEC), LH = (kLoadsH + TW - 1) / TW;
+  constexpr int kStage = (TOKENS + MR) * TK;  // floats: the rows of W, then MR rows of H
+  static_assert(TW % 4 == 0 && MR % 16 == 0 && kLoadsH >= LH, "whole 64-token partials");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i16 = lane & 15, g = lane >> 4;
+  const int d = a.d;
+  const int nk = (d + TK - 1) / TK;
+  // 16-byte chunk c of row r of a stage lies at chunk c ^ twist(r)
+  auto twist = [](int r) { return (r >> 1) & 7; };
+  // Load instruction j of a wavefront fills 64 VEC floats of a stage, lane l the VEC of them from float l VEC on.
+  uint32_t wo[LW];        // offset in bytes to the tile's first row
+  const float* wp[WIDE ? LW : 1];
+  const float* hp[LH];
+  int wc[LW], hc[LH];     // the lane's first column within a step
+  auto aim = [&](int f, int& col) __attribute__((always_inline)) -> int {
+    const int r = f / TK, at = f % TK;
+    col = (((at >> 2) ^ twist(r)) << 2) | (at & 3);
+    return r;
+  };
+  const int last_v = (int)min((long)TOKENS - 1, a.V - 1 - n0);
+#pragma unroll
+  for (int j = 0; j < LW; ++j) {
+    const int r = min(aim((wave * LW + j) * 64 * VEC + lane * VEC, wc[j]), last_v);
+    wo[j] = ((uint32_t)r * (uint32_t)d + (uint32_t)wc[j]) * 4u;
+    if constexpr (WIDE) wp[j] = (const float*)a.W + (size_t)(n0 + r) * d + wc[j];
+  }
+  const float* wbase = (const float*)a.W + (size_t)n0 * d;
+  const int hfirst = min(wave * LH, kLoadsH - LH);  // where the rows do not divide, the last wavefronts repeat some
+#pragma unroll
+  for (int j = 0; j < LH; ++j) {
+    const int r = min(aim((hfirst + j) * 64 * VEC + lane * VEC, hc[j]), rows - 1);
+    hp[j] = h_of(m0 + r) + hc[j];
+  }
+  const uint32_t slot = lds_offset(ring);
+  auto fetch = [&](int k0, int stage) __attribute__((always_inline)) {
+    const uint32_t at = slot + stage * (kStage * 4);
+    const uint32_t at_w = at + wave * (LW * 256 * VEC), at_h = at + TOKENS * TK * 4 + hfirst * (256 * VEC);
+    auto all = [&](auto whole) __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < LW; ++j) {
+        const int back = whole || k0 + wc[j] < d ? 0 : wc[j];
+        if constexpr (WIDE) load_to_lds<VEC>(wp[j] + k0 - back, at_w + j * 256 * VEC);
+        else load_to_lds<VEC, STREAM_W>(wbase + k0, wo[j] - back * 4u, at_w + j * 256 * VEC);
+      }
+#pragma unroll
+      for (int j = 0; j < LH; ++j)
+        load_to_lds<VEC>(hp[j] + k0 - (whole || k0 + hc[j] < d ? 0 : hc[j]), at_h + j * 256 * VEC);
+    };
+    if (k0 + TK <= d) all(std::true_type{});
+    else all(std::false_type{});  // columns past the row: the step's first instead, which exist; the multiplies leave them out
+  };
+
+  floatx4 acc[NR];
+#pragma unroll
+  for (int n = 0; n < NR; ++n) acc[n] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < ST - 1 && t < nk; ++t) fetch(t * TK, t);
+  int stage = 0;
+  // The fragments of a step are read while the step before is multiplied.
+  float wv[2][TK / 4], hv[2][NR][TK / 4];
+  int at[TK / 4];
+#pragma unroll
+  for (int c = 0; c < TK / 4; ++c) at[c] = (c ^ twist(i16)) * 4;
+  auto read = [&](int kt, auto set_tag) __attribute__((always_inline)) {
+    constexpr int S = decltype(set_tag)::value;
+    wait_stages<ST - 2, LW + LH>(nk - 1 - kt);
+    lds_barrier();  // the step has arrived, and everybody is done with the one before
+    if (kt + ST - 1 < nk) fetch((kt + ST - 1) * TK, stage == 0 ? ST - 1 : stage - 1);
+    const float* ws = ring + stage * kStage + (wave * 16 + i16) * TK + g;
+    const float* hs = ring + stage * kStage + (TOKENS + i16) * TK + g;
+#pragma unroll
+    for (int c = 0; c < TK / 4; ++c) {
+      wv[S][c] = ws[at[c]];
+#pragma unroll
+      for (int n = 0; n < NR; ++n) hv[S][n][c] = hs[n * 16 * TK + at[c]];
+    }
+    stage = stage == ST - 1 ? 0 : stage + 1;
+  };
+  auto multiply = [&](auto set_tag) __attribute__((always_inline)) {
+    constexpr int S = decltype(set_tag)::value;
+#pragma unroll
+    for (int c = 0; c < TK / 4; ++c)
+#pragma unroll
+      for (int n = 0; n < NR; ++n) acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[S][c], hv[S][n][c], acc[n], 0, 0, 0);
+  };
+  auto mask = [&](auto set_tag) __attribute__((always_inline)) {  // last step: columns at and past d count as zero
+    constexpr int S = decltype(set_tag)::value;
+#pragma unroll
+    for (int c = 0; c < TK / 4; ++c) {
+      const bool in = (nk - 1) * TK + 4 * c + g < d;
+      wv[S][c] = in ? wv[S][c] : 0.f;
+#pragma unroll
+      for (int n = 0; n < NR; ++n) hv[S][n][c] = in ? hv[S][n][c] : 0.f;
+    }
+  };
+  using Even = std::integral_constant<int, 0>;
+  using Odd = std::integral_constant<int, 1>;
+  read(0, Even{});
+  int kt = 1;
+  for (; kt + 1 < nk; kt += 2) {
+    read(kt, Odd{});
+    multiply(Even{});
+    read(kt + 1, Even{});
+    multiply(Odd{});
+  }
+  if (kt < nk) {
+    read(kt, Odd{});
+    multiply(Even{});
+    if (d % TK != 0) mask(Odd{});
+    multiply(Odd{});
+  } else {
+    if (d % TK != 0) mask(Even{});
+    multiply(Even{});
+  }
+
+  // epilogue: lane holds tokens v .. v + 3 of row m0 + 16 n + i16
+  const long v = n0 + wave * 16 + 4 * g;
+#pragma unroll
+  for (int n = 0; n < NR; ++n) {
+    const int rl = 16 * n + i16;
+    const floatx4 l = acc[n] * a.inv_tau;
+    if (rl < rows) {
+      const int m = m0 + rl;
+      if (a.labels) {  // cross-entropy use: keep only the label token's logit
+        const long c = (long)a.labels[m] - v;
+        if (c >= 0 && c < 4 && v + c < a.V) a.label_logit[m] = c == 0 ? l[0] : c == 1 ? l[1] : c == 2 ? l[2] : l[3];
+      } else {
+        float* dst = logits + (size_t)m * ldl + v;
+        if (v + 3 < a.V) {
+          *reinterpret_cast<floatx4*>(dst) = l;
+        } else {
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            if (v + c < a.V) dst[c] = l[c];
+        }
+      }
+    }
+    acc[n] = l;
+    float mx = -FLT_MAX;  // not -inf: tokens past V, or of logit -inf, bring no NaN
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (v + c < a.V) mx = fmaxf(mx, l[c]);
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    if (g == 0) tile_max[rl][wave] = mx;
+  }
+  __syncthreads();  // also: the last reads of the ring are done
+  // exponentials to LDS, [wavefront][row][token % 16]; then a quad of threads per row adds them as a binary tree over
+  // the token number, highest bit first
+  auto max_of = [&](int rl, int part) __attribute__((always_inline)) -> float {
+    const float* m = &tile_max[rl][4 * part];
+    return fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]));
+  };
+  floatx4* ex = reinterpret_cast<floatx4*>(ring);
+  static_assert(TW * MR * 16 <= ST * kStage, "the exponentials fit where the stages were");
+#pragma unroll
+  for (int n = 0; n < NR; ++n) {
+    const int rl = 16 * n + i16;
+    const float mx = max_of(rl, wave >> 2);
+    floatx4 e;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) e[c] = v + c < a.V ? expf(acc[n][c] - mx) : 0.f;
+    ex[(wave * MR + rl) * 4 + g] = e;
+  }
+  __syncthreads();
+  if (tid < TW * MR) {  // whole wavefronts
+    const int part = tid / (4 * MR), rl = tid / 4 % MR, q = tid & 3;
+    const floatx4* p = ex + (size_t)(4 * part * MR + rl) * 4 + q;
+    floatx4 e = (p[0] + p[2 * MR * 4]) + (p[MR * 4] + p[3 * MR * 4]);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) e[c] += __shfl_xor(e[c], 2, 64);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) e[c] += __shfl_xor(e[c], 1, 64);
+    const float sum = (e[0] + e[2]) + (e[1] + e[3]);
+    if (q == 0 && rl < rows && n0 + 64 * part < a.V)
+      partials[(size_t)(m0 + rl) * a.nT + n0 / 64 + part] = make_float2(max_of(rl, part), sum);
+  }
+  __syncthreads();  // the next tile's first stages overwrite the exponentials
+}
+
+}  // namespace
+}  // namespace fef

@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "head_common.hpp"
+#include "head_f32.hpp"
 
 namespace fef {
 namespace {
@@ -481,246 +482,27 @@ __global__ __launch_bounds__(kTiledThreads) void head_tiled_kernel(HeadArgs a, i
   }
 }
 
-// ---------------------------------------------------------------------------------------------
-// fp32 kernel: workgroup tile of 64 tokens x MR rows of H (16 to 64), k in steps of 32, four wavefronts of
-// 16 tokens x MR rows each on v_mfma_f32_16x16x4_f32 (products and sums in binary32, like FMA).
-//
-// Bound: the one pass over W (HBM), or the fp32 matrix rate once there are some tens of rows (32 rows of 131 MB: 21 and 14 us).
-// W and H go straight from memory to LDS, two steps ahead in a ring of three stages: rows of 128 contiguous bytes, every W element
-// once per MR rows, one barrier per step, and 31 to 51 KB per workgroup, so that three to five share a CU.  The fragments of
-// a step are read while the step before is multiplied.  What it measured, per call with diagnostics and logits, against the form before
-// (one step ahead through registers, 32 or 64 rows): 16 rows of d = 1024, V = 32000 50 -> 42 us, 32 rows 55 -> 52; 48 rows of d = 599,
-// V = 18136 58 -> 48; 4 rows of d = 475, V = 17778 36 -> 31; 16 rows of V = 151936 (round) 165 -> 136.  Four or six stages, steps of 64
-// columns and eight wavefronts: equal or slower.
-//
-// Operand layout of the 16x16x4 multiply (lane l, i = l % 16, g = l / 16): A[i][g], B[g][i], one
-// float each.  The sums run over k in ascending order, one rounding per product like a chain of FMAs: multiply c of a step takes
-// columns 4 c .. 4 c + 3, one from each lane group.  A = W, B = H: D[4 g + r][i] puts four consecutive tokens of one row in a lane.
-// A stage is [rows][8 chunks of 16 bytes], chunk c of row r at c ^ ((r >> 1) & 7): two rows cover the 64 banks, so the 64 reads of
-// a fragment (16 rows, the four columns of a chunk) fall on different ones.  The permutation is applied on the global side of the load.
-//
-// VEC = 4: d is a multiple of 4, rows are 16-byte aligned and come in pieces of 16 bytes; VEC = 1: any d, 4 bytes per lane.
-// STREAM_W: W in non-temporal loads (see streams_w).  WIDE: rows so long that 64 of them pass 4 GB (d > 2^24): W by 64-bit addresses.
-// ---------------------------------------------------------------------------------------------
-constexpr int kF32Tokens = kTiledTn, kF32Tk = 32, kF32Stages = 3;
+// Below this many token tiles they are dealt out one by one instead of by XCD: 2048 sequences x 16 rows of V = 256 80 -> 53 us per call.
+constexpr int kF32FewTiles = 64;
 
-// Direct-to-LDS loads of VEC floats per lane, to LDS offset lds_off + 4 VEC l: from an address, or from an offset in bytes to a
-// uniform one.
-template <int VEC>
-__device__ inline void load_to_lds(const float* p, uint32_t lds_off) {
-  if constexpr (VEC == 4)
-    load_to_lds_16(p, lds_off);
-  else
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" :: "v"(p), "s"(lds_off) : "memory");
-}
-template <int VEC, bool STREAM>
-__device__ inline void load_to_lds(const float* base, uint32_t offset, uint32_t lds_off) {
-  if constexpr (VEC == 4 && STREAM)
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" :: "v"(offset), "s"(base), "s"(lds_off) : "memory");
-  else if constexpr (VEC == 4)
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" :: "v"(offset), "s"(base), "s"(lds_off) : "memory");
-  else if constexpr (STREAM)
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1 nt" :: "v"(offset), "s"(base), "s"(lds_off) : "memory");
-  else
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" :: "v"(offset), "s"(base), "s"(lds_off) : "memory");
-}
-// Wait until all loads but those of the last `stages` (at most MAX) stages of PER loads are done.
-template <int MAX, int PER>
-__device__ inline void wait_stages(int stages) {
-  if constexpr (MAX == 0) wait_newer<0>();
-  else if (stages >= MAX) wait_newer<MAX * PER>();
-  else wait_stages<MAX - 1, PER>(stages);
-}
-
+// fp32 inputs: tiles of 64 tokens x MR rows (head_f32.hpp).
 template <int MR, int VEC, bool STREAM_W, bool WIDE = false>
 __global__ __launch_bounds__(256) void head_f32_kernel(HeadArgs a, int m_tiles, int n_tiles, long tiles) {
-  static_assert(kF32Tokens == 64 && MR % 16 == 0, "four wavefronts of 16 tokens");
-  constexpr int NR = MR / 16;                 // 16-row groups of H
-  constexpr int TK = kF32Tk, ST = kF32Stages;
-  constexpr int LW = kF32Tokens * TK / (256 * VEC);                           // load instructions per wavefront and stage
-  constexpr int kLoadsH = MR * TK / (64 * VEC), LH = (kLoadsH + 3) / 4;
-  constexpr int kStage = (kF32Tokens + MR) * TK;  // floats: 64 rows of W, then MR rows of H
-  __shared__ __attribute__((aligned(16))) float ring[ST * kStage];
+  __shared__ __attribute__((aligned(16))) float ring[f32_ring_floats<4, MR>()];
   __shared__ float tile_max[MR][4];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int i16 = lane & 15, g = lane >> 4;
-  const int M = a.nrows, d = a.d;
-  const int nk = (d + TK - 1) / TK;
-  // 16-byte chunk c of row r of a stage lies at chunk c ^ twist(r)
-  auto twist = [](int r) { return (r >> 1) & 7; };
-
   // row tiles of one token tile follow one another on one XCD (workgroup ids go round-robin over
   // the eight), so a W tile is shared through that L2; the grid is capped, hence the loop
   for (long tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
     const long seq = tile >> 3;
-    const int nt = (int)(seq / m_tiles) * 8 + (int)(tile & 7), mt = (int)(seq % m_tiles);
+    const bool few = n_tiles < kF32FewTiles;
+    const int nt = few ? (int)(tile % n_tiles) : (int)(seq / m_tiles) * 8 + (int)(tile & 7);
+    const int mt = few ? (int)(tile / n_tiles) : (int)(seq % m_tiles);
     if (nt >= n_tiles) continue;
-    const int m0 = mt * MR;
-    const long n0 = (long)nt * kF32Tokens;
-    // Load instruction j of a wavefront fills 64 VEC floats of a stage, lane l the VEC of them from float l VEC on.
-    uint32_t wo[LW];        // offset in bytes to the tile's first row
-    const float* wp[WIDE ? LW : 1];
-    const float* hp[LH];
-    int wc[LW], hc[LH];     // the lane's first column within a step
-    auto aim = [&](int f, int& col) __attribute__((always_inline)) -> int {
-      const int r = f / TK, at = f % TK;
-      col = (((at >> 2) ^ twist(r)) << 2) | (at & 3);
-      return r;
+    const auto h_of = [&](int m) {
+      const int r = a.row0 + m;
+      return r < a.BK ? (const float*)a.h_draft + (size_t)r * a.d : (const float*)a.h_target + (size_t)(r - a.BK) * a.d;
     };
-    const int last_v = (int)min((long)kF32Tokens - 1, a.V - 1 - n0);
-#pragma unroll
-    for (int j = 0; j < LW; ++j) {
-      const int r = min(aim((wave * LW + j) * 64 * VEC + lane * VEC, wc[j]), last_v);
-      wo[j] = ((uint32_t)r * (uint32_t)d + (uint32_t)wc[j]) * 4u;
-      if constexpr (WIDE) wp[j] = (const float*)a.W + (size_t)(n0 + r) * d + wc[j];
-    }
-    const float* wbase = (const float*)a.W + (size_t)n0 * d;
-    const int hfirst = min(wave * LH, kLoadsH - LH);  // where the rows do not divide, the last wavefronts repeat some
-#pragma unroll
-    for (int j = 0; j < LH; ++j) {
-      const int r = min(m0 + aim((hfirst + j) * 64 * VEC + lane * VEC, hc[j]), M - 1), gr = a.row0 + r;
-      hp[j] = (gr < a.BK ? (const float*)a.h_draft + (size_t)gr * d
-                         : (const float*)a.h_target + (size_t)(gr - a.BK) * d) + hc[j];
-    }
-    const uint32_t slot = lds_offset(ring);
-    auto fetch = [&](int k0, int stage) __attribute__((always_inline)) {
-      const uint32_t at = slot + stage * (kStage * 4);
-      const uint32_t at_w = at + wave * (LW * 256 * VEC), at_h = at + kF32Tokens * TK * 4 + hfirst * (256 * VEC);
-      auto all = [&](auto whole) __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < LW; ++j) {
-          const int back = whole || k0 + wc[j] < d ? 0 : wc[j];
-          if constexpr (WIDE) load_to_lds<VEC>(wp[j] + k0 - back, at_w + j * 256 * VEC);
-          else load_to_lds<VEC, STREAM_W>(wbase + k0, wo[j] - back * 4u, at_w + j * 256 * VEC);
-        }
-#pragma unroll
-        for (int j = 0; j < LH; ++j)
-          load_to_lds<VEC>(hp[j] + k0 - (whole || k0 + hc[j] < d ? 0 : hc[j]), at_h + j * 256 * VEC);
-      };
-      if (k0 + TK <= d) all(std::true_type{});
-      else all(std::false_type{});  // columns past the row: the step's first instead, which exist; the multiplies leave them out
-    };
-
-    floatx4 acc[NR];
-#pragma unroll
-    for (int n = 0; n < NR; ++n) acc[n] = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int t = 0; t < ST - 1 && t < nk; ++t) fetch(t * TK, t);
-    int stage = 0;
-    // The fragments of a step are read while the step before is multiplied.
-    float wv[2][TK / 4], hv[2][NR][TK / 4];
-    int at[TK / 4];
-#pragma unroll
-    for (int c = 0; c < TK / 4; ++c) at[c] = (c ^ twist(i16)) * 4;
-    auto read = [&](int kt, auto set_tag) __attribute__((always_inline)) {
-      constexpr int S = decltype(set_tag)::value;
-      wait_stages<ST - 2, LW + LH>(nk - 1 - kt);
-      lds_barrier();  // the step has arrived, and everybody is done with the one before
-      if (kt + ST - 1 < nk) fetch((kt + ST - 1) * TK, stage == 0 ? ST - 1 : stage - 1);
-      const float* ws = ring + stage * kStage + (wave * 16 + i16) * TK + g;
-      const float* hs = ring + stage * kStage + (kF32Tokens + i16) * TK + g;
-#pragma unroll
-      for (int c = 0; c < TK / 4; ++c) {
-        wv[S][c] = ws[at[c]];
-#pragma unroll
-        for (int n = 0; n < NR; ++n) hv[S][n][c] = hs[n * 16 * TK + at[c]];
-      }
-      stage = stage == ST - 1 ? 0 : stage + 1;
-    };
-    auto multiply = [&](auto set_tag) __attribute__((always_inline)) {
-      constexpr int S = decltype(set_tag)::value;
-#pragma unroll
-      for (int c = 0; c < TK / 4; ++c)
-#pragma unroll
-        for (int n = 0; n < NR; ++n) acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[S][c], hv[S][n][c], acc[n], 0, 0, 0);
-    };
-    auto mask = [&](auto set_tag) __attribute__((always_inline)) {  // last step: columns at and past d count as zero
-      constexpr int S = decltype(set_tag)::value;
-#pragma unroll
-      for (int c = 0; c < TK / 4; ++c) {
-        const bool in = (nk - 1) * TK + 4 * c + g < d;
-        wv[S][c] = in ? wv[S][c] : 0.f;
-#pragma unroll
-        for (int n = 0; n < NR; ++n) hv[S][n][c] = in ? hv[S][n][c] : 0.f;
-      }
-    };
-    using Even = std::integral_constant<int, 0>;
-    using Odd = std::integral_constant<int, 1>;
-    read(0, Even{});
-    int kt = 1;
-    for (; kt + 1 < nk; kt += 2) {
-      read(kt, Odd{});
-      multiply(Even{});
-      read(kt + 1, Even{});
-      multiply(Odd{});
-    }
-    if (kt < nk) {
-      read(kt, Odd{});
-      multiply(Even{});
-      if (d % TK != 0) mask(Odd{});
-      multiply(Odd{});
-    } else {
-      if (d % TK != 0) mask(Even{});
-      multiply(Even{});
-    }
-
-    // epilogue: lane holds tokens v .. v + 3 of row m0 + 16 n + i16
-    const long v = n0 + wave * 16 + 4 * g;
-#pragma unroll
-    for (int n = 0; n < NR; ++n) {
-      const int rl = 16 * n + i16, m = m0 + rl;
-      const floatx4 l = acc[n] * a.inv_tau;
-      if (m < M) {
-        if (a.labels) {  // cross-entropy use: keep only the label token's logit
-          const long c = (long)a.labels[m] - v;
-          if (c >= 0 && c < 4 && v + c < a.V) a.label_logit[m] = c == 0 ? l[0] : c == 1 ? l[1] : c == 2 ? l[2] : l[3];
-        } else {
-          float* dst = a.logits + (size_t)m * a.ldl + v;
-          if (v + 3 < a.V) {
-            *reinterpret_cast<floatx4*>(dst) = l;
-          } else {
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-              if (v + c < a.V) dst[c] = l[c];
-          }
-        }
-      }
-      acc[n] = l;
-      float mx = -FLT_MAX;  // not -inf: tokens past V, or of logit -inf, bring no NaN
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-        if (v + c < a.V) mx = fmaxf(mx, l[c]);
-      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      if (g == 0) tile_max[rl][wave] = mx;
-    }
-    __syncthreads();  // also: the last reads of the ring are done
-    // exponentials to LDS, [wavefront][row][token % 16]; then a quad of threads per row adds them as a binary tree over
-    // the token number, highest bit first
-    floatx4* ex = reinterpret_cast<floatx4*>(ring);
-    static_assert(4 * MR * 16 <= ST * kStage, "the exponentials fit where the stages were");
-#pragma unroll
-    for (int n = 0; n < NR; ++n) {
-      const int rl = 16 * n + i16;
-      const float mx = fmaxf(fmaxf(tile_max[rl][0], tile_max[rl][1]), fmaxf(tile_max[rl][2], tile_max[rl][3]));
-      floatx4 e;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) e[c] = v + c < a.V ? expf(acc[n][c] - mx) : 0.f;
-      ex[(wave * MR + rl) * 4 + g] = e;
-    }
-    __syncthreads();
-    if (tid < 4 * MR) {  // whole wavefronts
-      const int rl = tid >> 2, q = tid & 3;
-      floatx4 e = (ex[rl * 4 + q] + ex[(2 * MR + rl) * 4 + q]) + (ex[(MR + rl) * 4 + q] + ex[(3 * MR + rl) * 4 + q]);
-#pragma unroll
-      for (int c = 0; c < 4; ++c) e[c] += __shfl_xor(e[c], 2, 64);
-#pragma unroll
-      for (int c = 0; c < 4; ++c) e[c] += __shfl_xor(e[c], 1, 64);
-      const float sum = (e[0] + e[2]) + (e[1] + e[3]);
-      const float mx = fmaxf(fmaxf(tile_max[rl][0], tile_max[rl][1]), fmaxf(tile_max[rl][2], tile_max[rl][3]));
-      if (q == 0 && m0 + rl < M) a.partials[(size_t)(m0 + rl) * a.nT + nt] = make_float2(mx, sum);
-    }
-    __syncthreads();  // the next tile's first stages overwrite the exponentials
+    f32_tile<4, MR, VEC, STREAM_W, WIDE>(a, (long)nt * kTiledTn, mt * MR, min(MR, a.nrows - mt * MR), h_of, a.logits, a.ldl, a.partials, ring, tile_max);
   }
 }
 
@@ -771,7 +553,7 @@ hipError_t launch_head_tiled(const HeadArgs& a) {
 template <int MR>
 hipError_t launch_f32(const HeadArgs& a) {
   const int m_tiles = (a.nrows + MR - 1) / MR, n_tiles = a.nT;
-  const long tiles = 8L * ((n_tiles + 7) / 8) * m_tiles;
+  const long tiles = (n_tiles < kF32FewTiles ? n_tiles : 8L * ((n_tiles + 7) / 8)) * m_tiles;
   const dim3 grid((unsigned)(tiles < (1L << 20) ? tiles : 1L << 20)), block(256);
   const bool stream = m_tiles == 1 && streams_w(a, 4);
   if (a.d > 1 << 24) {

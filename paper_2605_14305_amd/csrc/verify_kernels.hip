@@ -23,6 +23,7 @@
 #include <math.h>
 
 #include "fef_device.hpp"
+#include "head_f32.hpp"
 #include "wave_ops.hpp"
 
 namespace fef {
@@ -268,13 +269,13 @@ constexpr int kTilePer = 10;  // tokens per lane inside one partial tile: up to 
 // registers, so every global value is loaded once and every exponential evaluated once.
 // PER == 0: any number of partials, re-read from memory.
 // ---------------------------------------------------------------------------------------------
+constexpr int exchange_floats(int per) { return per > 10 ? kWave * (per + 1) : 0; }
+
+// One row by one wavefront; ex: its slice of LDS for the tokens of a tile, exchange: for the partials (PER > 10).
 template <int PER>
-__global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
-  __shared__ __attribute__((aligned(16))) float tile_mass[NW][4 * kWave];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+__device__ __forceinline__ void row_lse_draft(const VerifyArgs& a, int r, float* ex, float* exchange) {
+  const int lane = threadIdx.x & 63;
   const int BK = a.B * a.K;
-  const int r = a.row0 + blockIdx.x * NW + wave;
-  if (r >= a.row0 + a.nrows) return;
   const bool is_draft = r < BK;
   const int s = is_draft ? r : r - BK;
   const int b = s / a.K, m = s % a.K;
@@ -306,8 +307,7 @@ __global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
     // lane); with many it loads tile j*64 + l, 512 contiguous bytes per instruction, and hands
     // each exp-sum to its owner through this wavefront's slice of LDS (rows of PER + 1 floats,
     // an odd stride, so both directions are conflict-free).
-    constexpr bool EXCHANGE = PER > 10;
-    __shared__ float exchange[EXCHANGE ? NW : 1][EXCHANGE ? kWave * (PER + 1) : 1];
+    constexpr bool EXCHANGE = exchange_floats(PER) > 0;
     float2 p[PER];
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
@@ -321,15 +321,14 @@ __global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
 #pragma unroll
     for (int j = 0; j < PER; ++j) mass[j] = p[j].y > 0.f ? p[j].y * expf(p[j].x - mx) : 0.f;
     if constexpr (EXCHANGE) {
-      float* ex = exchange[wave];
 #pragma unroll
       for (int j = 0; j < PER; ++j) {
         const int t = j * kWave + lane;
-        ex[(t / PER) * (PER + 1) + t % PER] = mass[j];
+        exchange[(t / PER) * (PER + 1) + t % PER] = mass[j];
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // same wavefront on both sides: order only
 #pragma unroll
-      for (int j = 0; j < PER; ++j) mass[j] = ex[lane * (PER + 1) + j];
+      for (int j = 0; j < PER; ++j) mass[j] = exchange[lane * (PER + 1) + j];
     }
 #pragma unroll
     for (int j = 0; j < PER; ++j) sm += mass[j];
@@ -397,7 +396,6 @@ __global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
             q[j] = i < kWave ? ei : 0.f;
           }
         } else if (nv <= 4 * kWave) {
-          float* ex = tile_mass[wave];  // this wavefront's slice of LDS
           const int i0 = 4 * lane;
           float4 e;
           e.x = i0 < nv ? expf(L[v0 + i0] - lse) : 0.f;
@@ -432,6 +430,15 @@ __global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
     if (a.diag_draft_tokens) a.diag_draft_tokens[s] = x;
     if (a.phase == 1) a.out_tokens[s] = x;  // draft-only call: the caller gets the draft tokens
   }
+}
+
+template <int PER>
+__global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
+  __shared__ __attribute__((aligned(16))) float tile_mass[NW][4 * kWave];
+  __shared__ float exchange[NW][exchange_floats(PER) + 1];
+  const int wave = threadIdx.x >> 6;
+  const int r = a.row0 + blockIdx.x * NW + wave;
+  if (r < a.row0 + a.nrows) row_lse_draft<PER>(a, r, tile_mass[wave], exchange[wave]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -846,13 +853,13 @@ enum FinalMode { kHandoff, kSlots, kAlone };
 constexpr int kAloneChunks = 16;
 
 template <FinalMode MODE>
-__global__ __launch_bounds__(NT) void finalize_kernel(VerifyArgs a) {
+__device__ __forceinline__ void finalize_round(const VerifyArgs& a, int b) {
   __shared__ BlockTmp tmp;
   __shared__ SeqState st;
   __shared__ float s_conf[kMaxBlock];
   __shared__ uint8_t s_mask[kMaxBlock], s_cand[kMaxBlock];
   __shared__ float s_mass[MODE == kAlone ? kAloneChunks : 1];
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63;
   int word = 0;
   if (MODE == kHandoff && tid < (int)(sizeof(SeqState) / 4)) word = reinterpret_cast<const int*>(a.seqstate + b)[tid];
   // Without the diagnostics the chunk masses of a sequence sit at an address that does not depend
@@ -902,6 +909,72 @@ __global__ __launch_bounds__(NT) void finalize_kernel(VerifyArgs a) {
     }
   }
   finalize_sequence(a, b, st, tmp, s_conf, s_mask, s_cand, rm_pre, have_pre, my_pos, pass, my_u);
+}
+
+template <FinalMode MODE>
+__global__ __launch_bounds__(NT) void finalize_kernel(VerifyArgs a) {
+  finalize_round<MODE>(a, blockIdx.x);
+}
+
+// ---------------------------------------------------------------------------------------------
+// A whole round of a toy model in one launch: one workgroup per sequence takes its 2 K <= 16 rows through the fp32 head, a wavefront
+// per row, and the final phase.  Bound: start-up, code that arrives from a cold instruction cache, and trips to memory that wait for one
+// another; with three kernels each has its own, and what they hand on goes through memory.  Here logits, partials, log-sum-exps and
+// draft tokens stay in LDS: the sequence is a batch of one whose workspace is this workgroup's LDS.  4 tokens of a toy model (d = 64,
+// V = 32) 16.0 -> 10.8 us per call, 8 tokens of d = 128, V = 256 16.0 -> 12.7, 64 sequences of d = 64, V = 256 16.7 -> 13.3.  Four or eight
+// wavefronts are slower (12.4, 12.8 at V = 32, still through memory), and so is handing on through memory (11.7).
+// ---------------------------------------------------------------------------------------------
+constexpr int kToyWaves = 16, kToyTokens = 16 * kToyWaves;
+
+template <int VEC>
+__global__ __launch_bounds__(kToyWaves * kWave) void toy_round_kernel(HeadArgs h, VerifyArgs a) {
+  __shared__ __attribute__((aligned(16))) float ring[f32_ring_floats<kToyWaves, 16>()];
+  __shared__ __attribute__((aligned(16))) float logits[16][kToyTokens];
+  __shared__ float tile_max[16][kToyWaves];
+  __shared__ float2 partials[16 * (kToyTokens / kTiledTn)];
+  __shared__ float lse[16];
+  __shared__ int32_t xdraft[8], xtarget[8], slot_pos[8], window;
+  const int b = blockIdx.x, K = a.K, wave = threadIdx.x >> 6;
+  const size_t slot = (size_t)b * K, position = (size_t)b * a.block;
+
+  const float* hd = (const float*)h.h_draft + slot * h.d;
+  const float* ht = (const float*)h.h_target + slot * h.d - (size_t)K * h.d;
+  const auto h_of = [=](int m) { return (m < K ? hd : ht) + (size_t)m * h.d; };
+  f32_tile<kToyWaves, 16, VEC, false, false>(h, 0, 0, 2 * K, h_of, &logits[0][0], kToyTokens, partials, ring, tile_max);
+
+  float* diag_lse = a.diag_lse;
+  const int BK = a.B * K;
+  auto move = [](auto*& p, size_t by) __attribute__((always_inline)) { if (p) p += by; };
+  a.B = 1;
+  a.nrows = 2 * K;
+  a.seq_base += (uint32_t)b;
+  a.logits = &logits[0][0];
+  a.ldl = kToyTokens;
+  a.partials = partials;
+  a.lse = lse;
+  a.xdraft = xdraft;
+  a.xtarget = xtarget;
+  a.slot_pos = slot_pos;
+  a.window = &window;
+  a.diag_lse = nullptr;
+  move(a.mask_in, position);
+  move(a.pass_mask, position);
+  move(a.conf, position);
+  move(a.tokens_state, position);
+  a.out_remask += position;
+  move(a.draft_tokens_in, slot);
+  a.out_tokens += slot;
+  move(a.diag_draft_tokens, slot);
+  move(a.diag_conf_tok, slot);
+  a.out_accept_len += b;
+  move(a.seq_pass, b);
+  move(a.seq_rounds, b);
+  if (wave < 2 * K) {
+    row_lse_draft<4>(a, wave, ring + wave * (4 * kWave), nullptr);
+    if (diag_lse && (threadIdx.x & 63) == 0) diag_lse[wave < K ? slot + wave : BK + slot + wave - K] = lse[wave];
+  }
+  __syncthreads();
+  if (wave < NW) finalize_round<kAlone>(a, 0);  // the other wavefronts end; barriers count the ones that are left
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -965,7 +1038,28 @@ __global__ __launch_bounds__(NT) void copy_logits_kernel(const float* __restrict
   }
 }
 
+// Diagnostic logits of a call without slot_mass_kernel.
+hipError_t launch_copy(const VerifyArgs& a) {
+  if (a.diag_logits && (!a.all_slots || a.phase == 1 || a.phase == 3)) {
+    const long pieces = (a.V + (long)kCopyPer - 1) / kCopyPer;
+    hipLaunchKernelGGL(copy_logits_kernel, dim3(a.nrows < 1 << 20 ? a.nrows : 1 << 20, pieces < 65535 ? pieces : 65535), dim3(NT), 0,
+                       a.stream, a.logits + (size_t)a.row0 * a.ldl, a.ldl, a.diag_logits + (size_t)a.row0 * a.V, a.V, a.nrows);
+  }
+  return hipGetLastError();
+}
+
 }  // namespace
+
+// Up to 16 rows per sequence and 256 tokens, which is one pass of the workgroup's wavefronts; up to one sequence per CU (at 512 sequences of
+// d = 64, V = 128 18 us in three kernels, 24 in one); and hidden sizes up to which one CU's matrix units are not what it costs (V = 256:
+// 16.0 against 14.5 us at d = 192, 16.1 against 16.3 at d = 256).
+bool toy_round_serves(int B, int K, int d, int V) { return B <= 256 && 2 * K <= 16 && V <= kToyTokens && d <= 192; }
+
+hipError_t launch_toy_round(const HeadArgs& h, const VerifyArgs& a) {
+  if (h.d % 4 == 0) hipLaunchKernelGGL(toy_round_kernel<4>, dim3(a.B), dim3(kToyWaves * kWave), 0, a.stream, h, a);
+  else hipLaunchKernelGGL(toy_round_kernel<1>, dim3(a.B), dim3(kToyWaves * kWave), 0, a.stream, h, a);
+  return hipGetLastError();
+}
 
 hipError_t launch_verify(const VerifyArgs& a) {
   const dim3 g1((a.nrows + NW - 1) / NW);
@@ -989,12 +1083,7 @@ hipError_t launch_verify(const VerifyArgs& a) {
       hipLaunchKernelGGL(finalize_kernel<kHandoff>, dim3(a.B), dim3(NT), 0, a.stream, a);
     }
   }
-  if (a.diag_logits && (!a.all_slots || a.phase == 1 || a.phase == 3)) {  // else slot_mass_kernel has written them
-    const long pieces = (a.V + (long)kCopyPer - 1) / kCopyPer;
-    hipLaunchKernelGGL(copy_logits_kernel, dim3(a.nrows < 1 << 20 ? a.nrows : 1 << 20, pieces < 65535 ? pieces : 65535), dim3(NT), 0,
-                       a.stream, a.logits + (size_t)a.row0 * a.ldl, a.ldl, a.diag_logits + (size_t)a.row0 * a.V, a.V, a.nrows);
-  }
-  return hipGetLastError();
+  return launch_copy(a);
 }
 
 }  // namespace fef
