@@ -4,7 +4,7 @@
 // Workgroup tile 32 NR rows of H (NR = 1 to 8) x up to 256 tokens, k-steps of 64, v_mfma_f32_16x16x32_bf16 with the W tile
 // as the A operand and H as the B operand.  Two grids of wavefronts:
 //   WN = 2  four in a 2 x 2 grid (rows x tokens), each 16 NR rows x 128 tokens: M > 256
-//   WN = 4  eight in a 2 x 4 grid, each 16 NR rows x 64 tokens: M <= 256, and the cross-entropy of M > 256 rows with d < 1024
+//   WN = 4  eight in a 2 x 4 grid, each 16 NR rows x 64 tokens: M <= 256, and the cross-entropy of some more (launch_head_tiled256)
 // and five forms: kTiles (whole tiles of 256 tokens), kRuns64 and kRuns16 (M <= 128: one workgroup per CU takes a run of
 // 64- or 16-token units, 256 tokens at a time), and the two of the cross-entropy, kLossTiles and kLossShares.
 //
@@ -35,8 +35,8 @@
 // lane; the four lane groups that share a row trade with v_permlane16_swap / v_permlane32_swap, two sums per exchange
 // (ten exchanges per 16 rows x 64 tokens), and a thread per row merges what meets in LDS.  In the cross-entropy nothing
 // crosses lanes at all: each lane group writes the partial of its own tokens to LDS.
-// (4) Rows that do not exist.  M is cut into ceil(M / 256) row tiles of equal height, a multiple of 32 (300 rows:
-// two tiles of 160, not 256 + 44), one instantiation per height.
+// (4) Rows that do not exist, and CUs without a workgroup.  M is cut into row tiles of equal height, a multiple of 32 (300 rows:
+// two tiles of 160, not 256 + 44), more of them where the vocabulary is short (row_tiles), one instantiation per height.
 //
 // Measured (head kernel by HIP events, unless marked t: by trace; before: 32x32x16, tokens in the columns of D, 256-row tiles,
 // and two kernels built around streaming W up to 128 rows): d = 4096, V = 126464: 48 rows 189 -> 182 us, 64 rows 188 -> 188, 96
@@ -342,6 +342,7 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
     constexpr int KS = decltype(ks_tag)::value;
     constexpr bool MUL = decltype(mul_tag)::value, FULL = decltype(full)::value;
     constexpr int TOTAL = NT * NR, LOADS = KS == 0 ? LH : LW;
+    static_assert(ROLL || spread_at(TOTAL - 1, LOADS, TOTAL) < 0, "a load's pointer moves on behind the next multiply");
     // Eight wavefronts: the multiply behind which the group of loads goes out.  At once where the lead of a k-step is
     // short for the load latency (many rows: 237 -> 224 us at M = 256, 207 -> 201 at 192; narrow shares and runs: 254 -> 240
     // per round of 128 rows of d = 3584, V = 151936; level at V = 126464); in mid-phase with whole tiles of up to 128 rows,
@@ -769,7 +770,7 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
 template <int NR, int WN, Form F>
 hipError_t launch_form(const HeadArgs& a, int m_tiles) {
   const dim3 grid((unsigned)(8L * ((a.nT + 7) / 8) * m_tiles)), block(128 * WN);
-  if (WN == 4 && m_tiles == 1 && streams_w(a, 2)) {
+  if (WN == 4 && m_tiles <= 2 && streams_w(a, 2)) {
     FEF_LAUNCH_HEAD((head_tiled256_kernel<NR, WN, F, WN == 4>), grid, block, a, a, m_tiles);
   } else {
     FEF_LAUNCH_HEAD((head_tiled256_kernel<NR, WN, F, false>), grid, block, a, a, m_tiles);
@@ -777,10 +778,48 @@ hipError_t launch_form(const HeadArgs& a, int m_tiles) {
   return hipGetLastError();
 }
 
-template <int NR>
-hipError_t launch_one(const HeadArgs& a) {  // one row tile of 32 NR rows
-  if (!a.labels) return launch_form<NR, 4, kTiles>(a, 1);
-  return a.nT == (a.V + BN - 1) / BN ? launch_form<NR, 4, kLossTiles>(a, 1) : launch_form<NR, 4, kLossShares>(a, 1);
+// Row tiles of a launch over M rows in nT token tiles or runs: equal heights, a multiple of 32, at most `most` rows, and more of them than
+// that takes only of `least` rows or more.  ceil(M / most) of them multiply the fewest rows that do not exist and read W the fewest times; but a short vocabulary
+// leaves CUs idle then (V = 8437: 33 tiles), or fills a last round of 256 workgroups badly (V = 20000: 79 tiles x 4 row tiles).  So the number is
+// taken that makes rounds x (height + 64) smallest; 64 stands for what a k-step and a tile cost whatever their height: fits to
+// measured times give 40 to 140.  Where it differs from ceil(M / most): 256 rows of d = 1024, V = 8437 41 -> 28 us per round, 528 rows of
+// d = 3072 64 -> 48, 320 rows of d = 1024, V = 16000 40 -> 32, 352 rows of d = 512, V = 46900 54 -> 48, 128 rows of d = 4096, V = 32000 81 -> 73;
+// cross-entropy 500 rows of d = 2048, V = 12000 45 -> 31, 1000 rows of d = 1024, V = 20000 59 -> 48.  (Tiles of 32 rows: 80 rows of
+// V = 16000 32 us in three, 26 in two.)
+int row_tiles(int M, int nT, int least, int most) {
+  int best = (M + most - 1) / most;
+  if ((long)nT * best > 8 * 256) return best;  // many rounds: the last one matters little
+  long best_cost = 0;
+  for (int m = best; m == best || (long)nT * m <= 16 * 256; ++m) {
+    const int height = ((M + m - 1) / m + 31) / 32 * 32;
+    if (best_cost != 0 && height < least) break;
+    const long cost = (((long)nT * m + 255) / 256) * (height + 64);
+    if (best_cost == 0 || cost < best_cost) {
+      best = m;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
+// Heights from `least` rows of up to `most` come in one instantiation each.
+template <int WN, Form F>
+hipError_t launch_rows(const HeadArgs& a, int m_tiles) {
+  constexpr int most = F == kRuns64 || F == kRuns16 ? 4 : 8;
+  const int nr = ((a.nrows + m_tiles - 1) / m_tiles + 31) / 32;
+  if constexpr (WN == 4) {
+    if (nr == 1) return launch_form<1, WN, F>(a, m_tiles);
+    if (nr == 2) return launch_form<2, WN, F>(a, m_tiles);
+  }
+  if (nr == 3) return launch_form<3, WN, F>(a, m_tiles);
+  if (nr == 4) return launch_form<4, WN, F>(a, m_tiles);
+  if constexpr (most == 8) {
+    if (nr == 5) return launch_form<5, WN, F>(a, m_tiles);
+    if (nr == 6) return launch_form<6, WN, F>(a, m_tiles);
+    if (nr == 7) return launch_form<7, WN, F>(a, m_tiles);
+    if (nr == 8) return launch_form<8, WN, F>(a, m_tiles);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -801,11 +840,11 @@ int tiled256_tiles(int V, int M) {
   return 256 * rounds < units ? 256 * rounds : units;
 }
 
-// ceil(M / 256) row tiles of equal height (a multiple of 32).  One row tile: eight wavefronts (two per SIMD: the kernel
-// is short of memory parallelism there, not of LDS rate).  Several: four wavefronts, 160 to 256 rows; but for the
-// cross-entropy eight where the walk over k is so short that prologue and epilogue, which two wavefronts per SIMD overlap
-// better, are what a tile costs (103.6 -> 97.6 us per call of 700 rows of d = 768, V = 80000; even at d = 1024, 4 % behind at
-// d = 4096).  In a verify step a partial there spans 128 tokens, which only four wavefronts hold in one: eight would save
+// Up to 256 rows: eight wavefronts (two per SIMD: the kernel is short of memory parallelism there, not of LDS rate).  More: four; but for
+// the cross-entropy eight where prologue and epilogue, which two wavefronts per SIMD overlap better, are much of what a tile costs: up to
+// d = 1024 (126 -> 121 us at 500 rows of V = 126464, 47.5 -> 46.0 at 1000 rows of V = 20000), and two row tiles of any d (300 rows of V = 50257:
+// 84 -> 77 us at d = 2048, 150 -> 142 at d = 4096; 313 -> 302 at d = 4096, V = 126464; level at 700 rows of d = 2048, and at 2048 rows of
+// d = 4096 4 % behind).  In a verify step a partial there spans 128 tokens, which only four wavefronts hold in one: eight would save
 // 7 % at 512 rows of d = 512.
 hipError_t launch_head_tiled256(const HeadArgs& a) {
   const int m_tiles = (a.nrows + 255) / 256;
@@ -831,33 +870,14 @@ hipError_t launch_head_tiled256(const HeadArgs& a) {
     }
     return hipSuccess;
   }
-  const int nr = ((a.nrows + m_tiles - 1) / m_tiles + 31) / 32;
-  if (m_tiles > 1 && a.labels && a.d < 1024) {
-    switch (nr) {
-      case 5: return launch_form<5, 4, kLossTiles>(a, m_tiles);
-      case 6: return launch_form<6, 4, kLossTiles>(a, m_tiles);
-      case 7: return launch_form<7, 4, kLossTiles>(a, m_tiles);
-      default: return launch_form<8, 4, kLossTiles>(a, m_tiles);
-    }
+  if (a.labels && m_tiles == 1 && a.nT != (a.V + BN - 1) / BN) return launch_rows<4, kLossShares>(a, 1);
+  if (m_tiles == 1) {
+    const int m = row_tiles(a.nrows, a.nT, 64, 256);
+    return a.labels ? launch_rows<4, kLossTiles>(a, m) : launch_rows<4, kTiles>(a, m);
   }
-  if (m_tiles > 1) {
-    switch (nr) {
-      case 5: return a.labels ? launch_form<5, 2, kLossTiles>(a, m_tiles) : launch_form<5, 2, kTiles>(a, m_tiles);
-      case 6: return a.labels ? launch_form<6, 2, kLossTiles>(a, m_tiles) : launch_form<6, 2, kTiles>(a, m_tiles);
-      case 7: return a.labels ? launch_form<7, 2, kLossTiles>(a, m_tiles) : launch_form<7, 2, kTiles>(a, m_tiles);
-      default: return a.labels ? launch_form<8, 2, kLossTiles>(a, m_tiles) : launch_form<8, 2, kTiles>(a, m_tiles);
-    }
-  }
-  switch (nr) {
-    case 1: return launch_one<1>(a);
-    case 2: return launch_one<2>(a);
-    case 3: return launch_one<3>(a);
-    case 4: return launch_one<4>(a);
-    case 5: return launch_one<5>(a);
-    case 6: return launch_one<6>(a);
-    case 7: return launch_one<7>(a);
-    default: return launch_one<8>(a);
-  }
+  const int m = row_tiles(a.nrows, a.nT, 96, 256);
+  if (!a.labels) return launch_rows<2, kTiles>(a, m);
+  return a.d <= 1024 || m == 2 ? launch_rows<4, kLossTiles>(a, m) : launch_rows<2, kLossTiles>(a, m);
 }
 
 // Workgroups of a launch of runs = partials per row: one per CU, fewer where the vocabulary is short.  The first stages of a
@@ -868,12 +888,8 @@ int runs_grid(int V, int unit) {
   return want < 256 ? want : 256;
 }
 hipError_t launch_head_runs(const HeadArgs& a, int unit) {
-  switch ((a.nrows + 31) / 32) {
-    case 1: return unit == 64 ? launch_form<1, 4, kRuns64>(a, 1) : launch_form<1, 4, kRuns16>(a, 1);
-    case 2: return unit == 64 ? launch_form<2, 4, kRuns64>(a, 1) : launch_form<2, 4, kRuns16>(a, 1);
-    case 3: return unit == 64 ? launch_form<3, 4, kRuns64>(a, 1) : launch_form<3, 4, kRuns16>(a, 1);
-    default: return unit == 64 ? launch_form<4, 4, kRuns64>(a, 1) : launch_form<4, 4, kRuns16>(a, 1);
-  }
+  const int m = row_tiles(a.nrows, a.nT, 64, 128);
+  return unit == 64 ? launch_rows<4, kRuns64>(a, m) : launch_rows<4, kRuns16>(a, m);
 }
 
 }  // namespace fef

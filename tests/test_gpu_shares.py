@@ -64,6 +64,29 @@ def test_shares_of_a_cross_entropy_call(V):
         assert abs(float(loss) - float(want.sum())) <= float(bound.sum())
 
 
+@pytest.mark.parametrize("V", [257, 2000, 8437, 16384, 32700])  # 2 to 128 token tiles: more row tiles than the rows take
+@pytest.mark.parametrize("variant,d,rows", [(fb.FEF_GEMM_STREAM, 192, (66, 96, 126, 128)), (fb.FEF_GEMM_ROWSTREAM, 512, (66, 100, 128)),
+                                            (fb.FEF_GEMM_TILED256, 128, (66, 130, 190, 200, 256, 258, 300, 450, 528, 770, 1000))])
+def test_more_row_tiles_where_the_vocabulary_is_short(variant, d, rows, V):
+    for M in rows:
+        _check_round(variant, M, d, V)
+
+
+@pytest.mark.parametrize("V", [257, 8437, 16384, 40000])
+@pytest.mark.parametrize("R", [200, 257, 300, 512, 513, 1000])
+@pytest.mark.parametrize("d", [128, 1024, 1088])  # eight and four wavefronts
+def test_row_tiles_of_a_cross_entropy_call(V, R, d):
+    g = torch.Generator(device="cuda").manual_seed(R + V)
+    W = (torch.randn(V, d, generator=g, device="cuda") * 0.1).bfloat16()
+    h = torch.randn(R, d, generator=g, device="cuda").bfloat16()
+    labels = torch.randint(0, V, (R,), generator=g, device="cuda", dtype=torch.int32)
+    ce, _ = fb.HeadCrossEntropy(R, d, V)(h, W, labels)
+    L = h.double() @ W.double().t().contiguous()
+    want = torch.logsumexp(L, 1) - L.gather(1, labels.long()[:, None])[:, 0]
+    bound = 2 * _bound(h.double(), W.double(), d, 1.0).max(1).values + 2e-5
+    assert bool(((ce - want).abs() <= bound).all())
+
+
 @pytest.mark.parametrize("variant,M", [(fb.FEF_GEMM_STREAM, 34), (fb.FEF_GEMM_STREAM, 128), (fb.FEF_GEMM_ROWSTREAM, 50),
                                        (fb.FEF_GEMM_ROWSTREAM, 96), (fb.FEF_GEMM_TILED256, 32), (fb.FEF_GEMM_TILED256, 160),
                                        (fb.FEF_GEMM_TILED256, 256)])
