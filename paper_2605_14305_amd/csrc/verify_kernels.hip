@@ -713,17 +713,24 @@ __device__ inline void accept_tests(const VerifyArgs& a, int b, SeqState& st) {
   }
 }
 
-// Four logits of each of the two rows of a slot, from token v on (zero past V).
+// Four logits of each of the two rows of a slot, from token v on (zero past V).  ONCE: in non-temporal loads.
 struct Quad {
   float q[4], p[4];
 };
+template <bool ONCE = false>
 __device__ inline Quad load_quad(const VerifyArgs& a, const float* Lq, const float* Lp, int v) {
   Quad r;
   if (v + 3 < a.V) {
-    const float4 q4 = *reinterpret_cast<const float4*>(Lq + v);
-    const float4 p4 = *reinterpret_cast<const float4*>(Lp + v);
-    r.q[0] = q4.x; r.q[1] = q4.y; r.q[2] = q4.z; r.q[3] = q4.w;
-    r.p[0] = p4.x; r.p[1] = p4.y; r.p[2] = p4.z; r.p[3] = p4.w;
+    const auto load = [](const float* p) {
+      const floatx4* at = reinterpret_cast<const floatx4*>(p);
+      return ONCE ? __builtin_nontemporal_load(at) : *at;
+    };
+    const floatx4 q4 = load(Lq + v), p4 = load(Lp + v);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      r.q[j] = q4[j];
+      r.p[j] = p4[j];
+    }
   } else {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -777,12 +784,14 @@ __global__ __launch_bounds__(NT) void accept_resid_kernel(VerifyArgs a) {
 // grid = (B*K, ceil(nRC / (NW * kMassPer))); a wavefront takes kMassPer neighbouring chunks and asks
 // for all of them before it uses the first.  Bound: the two passes' worth of exponentials and one read of all logits
 // (1.04 GB at 64 x 16 slots, V = 126464).  Which slot was rejected does not matter here, so nothing waits for the
-// accept tests (the final kernel does them); with them repeated in front of every chunk this took 260 us, now
-// 185 (5.6 TB/s).  COPY: a call that wants the logits too gets them from here, where they are in registers: 122 -> 112 us per
+// accept tests (the final kernel does them); with them repeated in front of every chunk this took 260 us, without them 185, and
+// 165 (6.3 TB/s) with non-temporal loads: the logits are read once (per call 411 -> 393 us at 540 slots of V = 151936, 148 -> 134 at 512 of
+// V = 50257).  Two chunks per wavefront; four leave a small call short of wavefronts (50.4 -> 49.1 us at 32 slots of V = 100003), one
+// or two per mille behind at the large ones.  COPY: a call that wants the logits too gets them from here, where they are in registers: 122 -> 112 us per
 // call of 128 rows of d = 1024, V = 126464 against a kernel that reads them once more, 106 -> 101 at V = 100003, and a launch less
 // (51.2 -> 50.0 at 32 fp32 rows of V = 32000).
 // ---------------------------------------------------------------------------------------------
-constexpr int kMassPer = 4;
+constexpr int kMassPer = 2;
 template <bool COPY>
 __global__ __launch_bounds__(NT) void slot_mass_kernel(VerifyArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -795,7 +804,7 @@ __global__ __launch_bounds__(NT) void slot_mass_kernel(VerifyArgs a) {
   const float lse_q = a.lse[s], lse_p = a.lse[BK + s];
   Quad x[kMassPer];
 #pragma unroll
-  for (int j = 0; j < kMassPer; ++j) x[j] = load_quad(a, Lq, Lp, (c0 + j) * kResidChunk + lane * 4);
+  for (int j = 0; j < kMassPer; ++j) x[j] = load_quad<true>(a, Lq, Lp, (c0 + j) * kResidChunk + lane * 4);
   if constexpr (COPY) {
     // diagnostic logits: these rows without the padding, while they are in registers; of the target half of a split round
     // its own rows only
