@@ -11,7 +11,7 @@ namespace fef {
 namespace {
 
 // ---------------------------------------------------------------------------------------------
-// fp32 kernel: workgroup tile of 64 tokens x MR rows of H (16 to 64), k in steps of 32, four wavefronts of
+// fp32 kernel: workgroup tile of 16 tokens per wavefront (64 in the head kernel) x MR rows of H (16 to 64), k in steps of 32, wavefronts of
 // 16 tokens x MR rows each on v_mfma_f32_16x16x4_f32 (products and sums in binary32, like FMA).
 //
 // Bound: the one pass over W (HBM), or the fp32 matrix rate once there are some tens of rows (32 rows of 131 MB: 21 and 14 us).
@@ -31,7 +31,7 @@ namespace {
 // VEC = 4: d is a multiple of 4, rows are 16-byte aligned and come in pieces of 16 bytes; VEC = 1: any d, 4 bytes per lane.
 // STREAM_W: W in non-temporal loads (see streams_w).  WIDE: rows so long that 64 of them pass 4 GB (d > 2^24): W by 64-bit addresses.
 // ---------------------------------------------------------------------------------------------
-constexpr int kF32Tokens = kTiledTn, kF32Tk = 32, kF32Stages = 3;
+constexpr int kF32Tk = 32, kF32Stages = 3;
 
 // Direct-to-LDS loads of VEC floats per lane, to LDS offset lds_off + 4 VEC l: from an address, or from an offset in bytes to a
 // uniform one.

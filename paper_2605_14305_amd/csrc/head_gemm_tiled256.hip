@@ -19,8 +19,7 @@
 //             2, 1, 0.  kRuns16: of 16 tokens, four neighbours in order, then bits 2 and 3.
 //   a row's   the partials of a tile in ascending order; kRuns64 goes on from tile to tile; kRuns16 keeps eight chains,
 //             every eighth tile of the run each, and adds the chains at the end.
-// The sums over lanes and the runs that this takes cost nothing measurable at M = 2048 and 2 to 5 % up to 128 rows (64 rows of
-// d = 4096, V = 126464: 179 -> 182 to 187 us by trace).
+// The sums over lanes and the runs that this takes cost nothing measurable at M = 2048 and 2 to 5 % up to 128 rows.
 //
 // What bounds it, and what follows.
 // (1) Power.  With every matrix unit busy on real data the chip lowers its clock, so energy per multiply is time.  A
@@ -38,11 +37,11 @@
 // (4) Rows that do not exist, and CUs without a workgroup.  M is cut into row tiles of equal height, a multiple of 32 (300 rows:
 // two tiles of 160, not 256 + 44), more of them where the vocabulary is short (row_tiles), one instantiation per height.
 //
-// Measured (head kernel by HIP events, unless marked t: by trace; before: 32x32x16, tokens in the columns of D, 256-row tiles,
-// and two kernels built around streaming W up to 128 rows): d = 4096, V = 126464: 48 rows 189 -> 182 us, 64 rows 188 -> 188, 96
-// rows 207 -> 187, 128 rows 200 -> 197, 256 rows 250 -> 240, 2048 rows 1697 -> 1590; 110 rows of d = 2560, V = 100003 159 -> 112 t;
-// 512 rows of d = 512, V = 50257 57.5 -> 50.1 t.  Cross-entropy, 2048 rows 1600 -> 1470 (1.44 PFLOP/s, matrix units busy 0.74 of
-// the cycles at 1.78 GHz), 300 rows (d = 2048, V = 50257) 138 -> 67 t.
+// Measured (head kernel by HIP events, unless marked t: by trace; before: W in ordinary loads, as few row tiles as the rows take):
+// d = 4096, V = 126464: 48 rows 182 -> 163 us, 64 rows 188 -> 165 (6.5 TB/s), 96 rows 187 -> 168, 128 rows 197 -> 171, 256 rows 240 -> 237
+// (t, one machine: 223 -> 215), 512 rows 426 -> 423, 2048 rows 1590 -> 1600 (two machines); 128 rows of d = 3584, V = 151936 222 -> 203;
+// 110 rows of d = 2560, V = 100003 116 -> 105 t.  Cross-entropy, 2048 rows 1470 to 1480 (1.43 PFLOP/s, matrix units busy 0.75 of the
+// cycles at 1.77 GHz).
 //
 // Operand slabs go HBM/L2 -> LDS directly (global_load_lds_dwordx4: lane l of a wavefront deposits its 16 bytes at
 // LDS base + 16 l): no register staging and no ds_write in the main loop.  A row of a stage is 128 bytes, so one load

@@ -784,8 +784,8 @@ __global__ __launch_bounds__(NT) void accept_resid_kernel(VerifyArgs a) {
 // grid = (B*K, ceil(nRC / (NW * kMassPer))); a wavefront takes kMassPer neighbouring chunks and asks
 // for all of them before it uses the first.  Bound: the two passes' worth of exponentials and one read of all logits
 // (1.04 GB at 64 x 16 slots, V = 126464).  Which slot was rejected does not matter here, so nothing waits for the
-// accept tests (the final kernel does them); with them repeated in front of every chunk this took 260 us, without them 185, and
-// 165 (6.3 TB/s) with non-temporal loads: the logits are read once (per call 411 -> 393 us at 540 slots of V = 151936, 148 -> 134 at 512 of
+// accept tests (the final kernel does them); with them repeated in front of every chunk this took 260 us, without them 191, and
+// 167 (6.2 TB/s) with non-temporal loads: the logits are read once (per call 411 -> 393 us at 540 slots of V = 151936, 148 -> 134 at 512 of
 // V = 50257).  Two chunks per wavefront; four leave a small call short of wavefronts (50.4 -> 49.1 us at 32 slots of V = 100003), one
 // or two per mille behind at the large ones.  COPY: a call that wants the logits too gets them from here, where they are in registers: 122 -> 112 us per
 // call of 128 rows of d = 1024, V = 126464 against a kernel that reads them once more, 106 -> 101 at V = 100003, and a launch less

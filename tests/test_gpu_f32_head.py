@@ -1,4 +1,4 @@
-"""The fp32 head kernel at the edges of its tiles (64 tokens, 32 or 64 rows, 64 columns of k, float4 or
+"""The fp32 head kernel at the edges of its tiles (64 tokens, 16 to 64 rows, 32 columns of k, float4 or
 scalar rows): logits and log-sum-exps against a float64 product."""
 import numpy as np
 import pytest
