@@ -4,6 +4,7 @@
 #include <math.h>
 
 #include "fef_device.hpp"
+#include "head_rules.hpp"
 
 // Launch a head kernel; the dispatch-timestamp events need the extended launch call, every other
 // launch uses the plain one (which a capturing stream records like any kernel node).
@@ -16,17 +17,6 @@
   } while (0)
 
 namespace fef {
-
-// W past the caches.  With one or two row tiles W is read once or nearly so, and as ordinary loads it pushes H, which all workgroups
-// read over and over, out of L2.  Non-temporal loads leave it there: per round of 64 rows of d = 4096, V = 126464 203 -> 179 us, of 128 rows
-// 214 -> 188, of 256 rows 267 -> 254; 110 rows of d = 2560, V = 100003 128 -> 122; 80 rows of V = 50257 59 -> 54 (d = 2048) and 39 -> 36
-// (d = 1024); 128 rows of d = 4096, V = 32000 in two row tiles 76 -> 73; 16 fp32 rows of d = 1024, V = 32000 49 -> 43; cross-entropy of 27
-// rows of d = 3072, V = 16746 34 -> 31, of 300 rows of V = 50257 78 -> 75.  That is with W not in the Infinity Cache (256 MB) at the start of a
-// call, as a model's forward pass leaves it; a program that does nothing between calls on one W of 85 to 256 MB would find it there, which
-// non-temporal loads pass by (300 rows of V = 50257 65 -> 75 us).  Below a third of that cache W survives more (three heads of 65 MB in turn
-// 30.7 -> 33.1 us): hence the line.  The first stages of a tile stay ordinary loads (non-temporal ones there cost 1 to 4 us per call), and
-// so does W shared by many row tiles or by four wavefronts, which is read again out of L2 (level at 512 and 2048 rows of 1 GB).
-inline bool streams_w(const HeadArgs& a, int element_bytes) { return (size_t)a.V * a.d * element_bytes > (size_t)80 << 20; }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));

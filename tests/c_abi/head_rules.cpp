@@ -1,0 +1,23 @@
+// Prints what csrc/head_rules.hpp decides: one line per line of input, "rule argument ...".
+#include "../../paper_2605_14305_amd/csrc/head_rules.hpp"
+
+#include <iostream>
+#include <sstream>
+#include <string>
+
+int main() {
+  for (std::string line; std::getline(std::cin, line);) {
+    std::istringstream in(line);
+    std::string rule;
+    in >> rule;
+    if (rule == "streams_w") {
+      size_t V, d, element_bytes;
+      in >> V >> d >> element_bytes;
+      std::cout << fef::streams_w(V, d, element_bytes) << "\n";
+    } else {
+      return 1;
+    }
+    if (!in) return 1;
+  }
+  return 0;
+}
