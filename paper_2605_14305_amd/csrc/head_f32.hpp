@@ -44,12 +44,11 @@ __device__ inline void load_to_lds(const float* p, uint32_t lds_off) {
 }
 template <int VEC, bool STREAM>
 __device__ inline void load_to_lds(const float* base, uint32_t offset, uint32_t lds_off) {
-  if constexpr (VEC == 4 && STREAM)
+  static_assert(!STREAM || VEC == 4, "streams_w asks for rows of whole lines");
+  if constexpr (STREAM)
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" :: "v"(offset), "s"(base), "s"(lds_off) : "memory");
   else if constexpr (VEC == 4)
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" :: "v"(offset), "s"(base), "s"(lds_off) : "memory");
-  else if constexpr (STREAM)
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1 nt" :: "v"(offset), "s"(base), "s"(lds_off) : "memory");
   else
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" :: "v"(offset), "s"(base), "s"(lds_off) : "memory");
 }

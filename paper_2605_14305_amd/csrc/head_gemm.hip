@@ -562,8 +562,7 @@ hipError_t launch_f32(const HeadArgs& a) {
     if (stream) FEF_LAUNCH_HEAD((head_f32_kernel<MR, 4, true>), grid, block, a, a, m_tiles, n_tiles, tiles);
     else FEF_LAUNCH_HEAD((head_f32_kernel<MR, 4, false>), grid, block, a, a, m_tiles, n_tiles, tiles);
   } else {
-    if (stream) FEF_LAUNCH_HEAD((head_f32_kernel<MR, 1, true>), grid, block, a, a, m_tiles, n_tiles, tiles);
-    else FEF_LAUNCH_HEAD((head_f32_kernel<MR, 1, false>), grid, block, a, a, m_tiles, n_tiles, tiles);
+    FEF_LAUNCH_HEAD((head_f32_kernel<MR, 1, false>), grid, block, a, a, m_tiles, n_tiles, tiles);
   }
   return hipGetLastError();
 }

@@ -14,6 +14,10 @@ namespace fef {
 // runs between the calls ordinary loads are up to 1.5 times as fast (16 rows of d = 4864, V = 17354 44.5 against 62.6 us, 190 rows of
 // d = 2560, V = 40000 60 against 77), and so is the second half of a split round (8 rows of d = 5056, V = 10577 111 against 129 us
 // per round); where the cache is swept in between, non-temporal ones are 0 to 4 % ahead.  Hence the line.
-inline bool streams_w(size_t V, size_t d, size_t element_bytes) { return V * d * element_bytes > (size_t)256 << 20; }
+// Rows of W that are not whole 128-byte lines (fp32, d not a multiple of 32): the two k-steps that share a line then fetch it twice, at
+// any size of W (16 fp32 rows of d = 1046, V = 150369 164 -> 191 us with non-temporal loads, 30 of d = 2548, V = 47390 129 -> 152).
+inline bool streams_w(size_t V, size_t d, size_t element_bytes) {
+  return d * element_bytes % 128 == 0 && V * d * element_bytes > (size_t)256 << 20;
+}
 
 }  // namespace fef
