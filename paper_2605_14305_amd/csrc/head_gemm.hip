@@ -555,7 +555,7 @@ hipError_t launch_f32(const HeadArgs& a) {
   const int m_tiles = (a.nrows + MR - 1) / MR, n_tiles = a.nT;
   const long tiles = (n_tiles < kF32FewTiles ? n_tiles : 8L * ((n_tiles + 7) / 8)) * m_tiles;
   const dim3 grid((unsigned)(tiles < (1L << 20) ? tiles : 1L << 20)), block(256);
-  const bool stream = m_tiles == 1 && streams_w(a.V, a.d, 4);
+  const bool stream = streams_w(a.V, a.d, 4, m_tiles, false);
   if (a.d > 1 << 24) {
     FEF_LAUNCH_HEAD((head_f32_kernel<MR, 1, false, MR == 16>), grid, block, a, a, m_tiles, n_tiles, tiles);
   } else if (a.d % 4 == 0) {

@@ -769,7 +769,7 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
 template <int NR, int WN, Form F>
 hipError_t launch_form(const HeadArgs& a, int m_tiles) {
   const dim3 grid((unsigned)(8L * ((a.nT + 7) / 8) * m_tiles)), block(128 * WN);
-  if (WN == 4 && m_tiles <= 2 && streams_w(a.V, a.d, 2)) {
+  if (WN == 4 && streams_w(a.V, a.d, 2, m_tiles, F == kLossTiles)) {
     FEF_LAUNCH_HEAD((head_tiled256_kernel<NR, WN, F, WN == 4>), grid, block, a, a, m_tiles);
   } else {
     FEF_LAUNCH_HEAD((head_tiled256_kernel<NR, WN, F, false>), grid, block, a, a, m_tiles);

@@ -16,8 +16,12 @@ namespace fef {
 // per round); where the cache is swept in between, non-temporal ones are 0 to 4 % ahead.  Hence the line.
 // Rows of W that are not whole 128-byte lines (fp32, d not a multiple of 32): the two k-steps that share a line then fetch it twice, at
 // any size of W (16 fp32 rows of d = 1046, V = 150369 164 -> 191 us with non-temporal loads, 30 of d = 2548, V = 47390 129 -> 152).
-inline bool streams_w(size_t V, size_t d, size_t element_bytes) {
-  return d * element_bytes % 128 == 0 && V * d * element_bytes > (size_t)256 << 20;
+// Two row tiles share W through L2 as far as they keep in step, and non-temporal loads cost a round that (144 rows of d = 7168, V = 22000
+// 124 -> 144 us where nothing runs between the calls and 127 -> 150 where the cache is swept, 160 of d = 4608, V = 30000 95 -> 102
+// and level, 256 of d = 5120 to 8192 level to 4 % ahead); a cross-entropy call, which writes no logits, gains 0 to 5 % (300 rows of d = 4096,
+// V = 126464 315 -> 303, of d = 1024, V = 151936 120 -> 114).
+inline bool streams_w(size_t V, size_t d, size_t element_bytes, int row_tiles, bool loss) {
+  return row_tiles <= (loss ? 2 : 1) && d * element_bytes % 128 == 0 && V * d * element_bytes > (size_t)256 << 20;
 }
 
 }  // namespace fef

@@ -12,8 +12,10 @@ int main() {
     in >> rule;
     if (rule == "streams_w") {
       size_t V, d, element_bytes;
-      in >> V >> d >> element_bytes;
-      std::cout << fef::streams_w(V, d, element_bytes) << "\n";
+      int row_tiles;
+      bool loss;
+      in >> V >> d >> element_bytes >> row_tiles >> loss;
+      std::cout << fef::streams_w(V, d, element_bytes, row_tiles, loss) << "\n";
     } else {
       return 1;
     }
