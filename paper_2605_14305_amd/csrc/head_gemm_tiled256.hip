@@ -777,31 +777,7 @@ hipError_t launch_form(const HeadArgs& a, int m_tiles) {
   return hipGetLastError();
 }
 
-// Row tiles of a launch over M rows in nT token tiles or runs: equal heights, a multiple of 32, at most `most` rows, and more of them than
-// that takes only of `least` rows or more.  ceil(M / most) of them multiply the fewest rows that do not exist and read W the fewest times; but a short vocabulary
-// leaves CUs idle then (V = 8437: 33 tiles), or fills a last round of 256 workgroups badly (V = 20000: 79 tiles x 4 row tiles).  So the number is
-// taken that makes rounds x (height + 64) smallest; 64 stands for what a k-step and a tile cost whatever their height: fits to
-// measured times give 40 to 140.  Where it differs from ceil(M / most): 256 rows of d = 1024, V = 8437 41 -> 28 us per round, 528 rows of
-// d = 3072 64 -> 48, 320 rows of d = 1024, V = 16000 40 -> 32, 352 rows of d = 512, V = 46900 54 -> 48, 128 rows of d = 4096, V = 32000 81 -> 73;
-// cross-entropy 500 rows of d = 2048, V = 12000 45 -> 31, 1000 rows of d = 1024, V = 20000 59 -> 48.  (Tiles of 32 rows: 80 rows of
-// V = 16000 32 us in three, 26 in two.)
-int row_tiles(int M, int nT, int least, int most) {
-  int best = (M + most - 1) / most;
-  if ((long)nT * best > 8 * 256) return best;  // many rounds: the last one matters little
-  long best_cost = 0;
-  for (int m = best; m == best || (long)nT * m <= 16 * 256; ++m) {
-    const int height = ((M + m - 1) / m + 31) / 32 * 32;
-    if (best_cost != 0 && height < least) break;
-    const long cost = (((long)nT * m + 255) / 256) * (height + 64);
-    if (best_cost == 0 || cost < best_cost) {
-      best = m;
-      best_cost = cost;
-    }
-  }
-  return best;
-}
-
-// Heights from `least` rows of up to `most` come in one instantiation each.
+// One instantiation per height: 32 to 256 rows with eight wavefronts (runs: to 128), 96 to 256 with four.
 template <int WN, Form F>
 hipError_t launch_rows(const HeadArgs& a, int m_tiles) {
   constexpr int most = F == kRuns64 || F == kRuns16 ? 4 : 8;
@@ -871,10 +847,10 @@ hipError_t launch_head_tiled256(const HeadArgs& a) {
   }
   if (a.labels && m_tiles == 1 && a.nT != (a.V + BN - 1) / BN) return launch_rows<4, kLossShares>(a, 1);
   if (m_tiles == 1) {
-    const int m = row_tiles(a.nrows, a.nT, 64, 256);
+    const int m = row_tiles(a.nrows, a.nT, a.d, 64, 256);
     return a.labels ? launch_rows<4, kLossTiles>(a, m) : launch_rows<4, kTiles>(a, m);
   }
-  const int m = row_tiles(a.nrows, a.nT, 96, 256);
+  const int m = row_tiles(a.nrows, a.nT, a.d, 96, 256);
   if (!a.labels) return launch_rows<2, kTiles>(a, m);
   return a.d <= 1024 || m == 2 ? launch_rows<4, kLossTiles>(a, m) : launch_rows<2, kLossTiles>(a, m);
 }
@@ -887,7 +863,7 @@ int runs_grid(int V, int unit) {
   return want < 256 ? want : 256;
 }
 hipError_t launch_head_runs(const HeadArgs& a, int unit) {
-  const int m = row_tiles(a.nrows, a.nT, 64, 128);
+  const int m = row_tiles(a.nrows, a.nT, a.d, 64, 128);
   return unit == 64 ? launch_rows<4, kRuns64>(a, m) : launch_rows<4, kRuns16>(a, m);
 }
 

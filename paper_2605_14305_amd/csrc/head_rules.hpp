@@ -24,4 +24,39 @@ inline bool streams_w(size_t V, size_t d, size_t element_bytes, int row_tiles, b
   return row_tiles <= (loss ? 2 : 1) && d * element_bytes % 128 == 0 && V * d * element_bytes > (size_t)256 << 20;
 }
 
+constexpr int kXcds = 8, kCusPerXcd = 32;
+
+// Rounds of one workgroup per CU that a launch of row_tiles x n_tiles workgroups takes.  Workgroups go to the XCDs in turn and the row tiles of a
+// token tile stay on one XCD, so the XCD with the most token tiles decides: 18 token tiles x 14 row tiles are 252 workgroups, but
+// 42 on two XCDs and 28 on the others.
+inline long tile_rounds(long n_tiles, long row_tiles) {
+  return ((n_tiles + kXcds - 1) / kXcds * row_tiles + kCusPerXcd - 1) / kCusPerXcd;
+}
+
+// Row tiles of a launch over M rows in n_tiles token tiles or runs: equal heights, a multiple of 32, at most `most` rows, and more of them
+// than that takes only of `least` rows or more.  ceil(M / most) of them multiply the fewest rows that do not exist and read W the fewest
+// times; but a short vocabulary leaves CUs idle then (V = 8437: 33 tiles), or fills a last round badly (V = 20000: 79 tiles x 4
+// row tiles).  So the number is taken that makes rounds x (height + 64) smallest; 64 stands for what a k-step and a tile cost whatever
+// their height.  More of them read W more often, so where a row is long the gain has to be more than 10 % of that, and up to 256 rows
+// (one row tile, whose W comes at the rate of the caches) the height has to fall below 0.6 of that of one.
+// Fitted to the times of 640 calls in every number of row tiles that they allow, with W still in the Infinity Cache and with that cache
+// swept: against ceil(M / most) 0.84 and 0.87 of the time in the mean, none slower but for one (4 % with the cache swept, 4 % faster
+// without).  Rounds counted over the whole chip instead: 32 of the 640 slower by more than 3 %, up to 1.45 times (2310 rows of d = 4608,
+// V = 4491 113 us in 10 row tiles, 152 in 14).  Without the 10 %: 384 rows of d = 3584, V = 44081 142 us in two, 166 in four; with it also at
+// short rows: 450 of d = 896, V = 71400 18 % slower.  Without the 0.6: 144 rows of d = 3968, V = 29869 64 us in one tile of 160, 83 in two of 96.
+inline int row_tiles(int M, int n_tiles, int d, int least, int most) {
+  const int fewest = (M + most - 1) / most;
+  if ((long)n_tiles * fewest > 8 * 256) return fewest;  // many rounds: the last one matters little
+  const auto height_of = [=](int m) { return ((M + m - 1) / m + 31) / 32 * 32; };
+  const auto cost_of = [=](int m) { return tile_rounds(n_tiles, m) * (height_of(m) + 64); };
+  const bool runs = most == 128;
+  const long enough = cost_of(fewest) * (runs || d <= 1024 ? 100 : 90);
+  int best = fewest;
+  for (int m = fewest + 1; (long)n_tiles * m <= 16 * 256 && height_of(m) >= least; ++m) {
+    if (!runs && fewest == 1 && 5 * height_of(m) >= 3 * height_of(1)) continue;
+    if (100 * cost_of(m) < enough && cost_of(m) < cost_of(best)) best = m;
+  }
+  return best;
+}
+
 }  // namespace fef

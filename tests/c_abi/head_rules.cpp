@@ -16,6 +16,10 @@ int main() {
       bool loss;
       in >> V >> d >> element_bytes >> row_tiles >> loss;
       std::cout << fef::streams_w(V, d, element_bytes, row_tiles, loss) << "\n";
+    } else if (rule == "row_tiles") {
+      int M, n_tiles, d, least, most;
+      in >> M >> n_tiles >> d >> least >> most;
+      std::cout << fef::row_tiles(M, n_tiles, d, least, most) << "\n";
     } else {
       return 1;
     }

@@ -33,3 +33,41 @@ def test_rows_that_share_lines_are_read_by_ordinary_loads(ask):
 
 def test_a_w_that_row_tiles_share_is_read_by_ordinary_loads(ask):
     assert ask([("streams_w", 126464, 4096, 2, tiles, loss) for loss in (0, 1) for tiles in (1, 2, 3, 8)]) == [1, 0, 0, 0, 1, 1, 0, 0]
+
+
+LAUNCHES = [(33, 128, 64, 128), (33, 256, 64, 256), (257, 4096, 96, 256)]  # rows from, to, least, most
+
+
+def _rounds(n_tiles, row_tiles):
+    """Rounds of the busiest XCD: token tile t and all its row tiles run on XCD t % 8, one workgroup on each of 32 CUs."""
+    per_xcd = [0] * 8
+    for t in range(n_tiles):
+        per_xcd[t % 8] += row_tiles
+    return -(-max(per_xcd) // 32)
+
+
+def _height(M, m):
+    return -(-(-(-M // m)) // 32) * 32
+
+
+@pytest.mark.parametrize("d", [512, 1024, 1088, 4096])
+def test_more_row_tiles_only_where_the_busiest_xcd_gains(ask, d):
+    for first, last, least, most in LAUNCHES:
+        sizes = [(M, n) for M in range(first, last + 1, 1 if last <= 256 else 37) for n in [*range(1, 70, 3), 97, 128, 187, 250, 256, 301, 391]]
+        picked = ask([("row_tiles", M, n, d, least, most) for M, n in sizes])
+        for (M, n), m in zip(sizes, picked):
+            fewest = -(-M // most)
+            assert m >= fewest and _height(M, m) <= most and (m - 1) * _height(M, m) < M  # no row tile without rows
+            if m > fewest:
+                assert _height(M, m) >= least
+                assert _rounds(n, m) * (_height(M, m) + 64) < _rounds(n, fewest) * (_height(M, fewest) + 64)
+
+
+def test_row_tiles_of_calls_that_were_measured(ask):
+    # rows, token tiles, d, least, most; what more row tiles (10 -> 14 and so on) made slower
+    slower = [(2310, 18, 4608, 96, 256), (432, 50, 6016, 96, 256), (7676, 2, 576, 96, 256), (484, 187, 3712, 96, 256),
+              (144, 117, 3968, 64, 256), (384, 173, 3584, 96, 256)]
+    assert ask([("row_tiles", *r) for r in slower]) == [10, 4, 30, 2, 1, 2]
+    faster = [(256, 33, 1024, 64, 256), (528, 63, 3072, 96, 256), (256, 63, 1024, 64, 256), (128, 125, 4096, 64, 128)]
+    assert ask([("row_tiles", *r) for r in faster]) == [4, 4, 4, 2]
+    assert ask([("row_tiles", 300, 197, 2048, 96, 256), ("row_tiles", 2048, 494, 4096, 96, 256)]) == [2, 8]
