@@ -482,9 +482,6 @@ __global__ __launch_bounds__(kTiledThreads) void head_tiled_kernel(HeadArgs a, i
   }
 }
 
-// Below this many token tiles they are dealt out one by one instead of by XCD: 2048 sequences x 16 rows of V = 256 80 -> 53 us per call.
-constexpr int kF32FewTiles = 64;
-
 // fp32 inputs: tiles of 64 tokens x MR rows (head_f32.hpp).
 template <int MR, int VEC, bool STREAM_W, bool WIDE = false>
 __global__ __launch_bounds__(256) void head_f32_kernel(HeadArgs a, int m_tiles, int n_tiles, long tiles) {
@@ -567,13 +564,8 @@ hipError_t launch_f32(const HeadArgs& a) {
   return hipGetLastError();
 }
 
-// Equal row tiles of at most 64 rows: as few as possible, for every one reads W again, but more where that leaves CUs without a
-// workgroup (32 rows of d = 777, V = 5000, 79 token tiles: 36.5 us per call as one row tile, 33.0 as two; 64 rows of d = 300, V = 8000
-// 33.5 and 28.9; 48 rows of V = 18136, 284 token tiles: 48.5 as one, 54 and 51.5 as two and three).
 hipError_t launch_head_f32(const HeadArgs& a) {
-  long m_tiles = (a.nrows + 63) / 64;
-  while (m_tiles * a.nT < 240 && m_tiles * 16 < a.nrows) ++m_tiles;
-  if (a.d > 1 << 24) m_tiles = a.nrows;
+  const int m_tiles = a.d > 1 << 24 ? a.nrows : f32_row_tiles(a.nrows, a.nT);
   switch (((a.nrows + m_tiles - 1) / m_tiles + 15) / 16) {
     case 1: return launch_f32<16>(a);
     case 2: return launch_f32<32>(a);

@@ -59,4 +59,28 @@ inline int row_tiles(int M, int n_tiles, int d, int least, int most) {
   return best;
 }
 
+// Token tiles of an fp32 launch below which they are dealt out one by one instead of by XCD: 2048 sequences x 16 rows of V = 256 80 -> 53 us
+// per call.
+constexpr int kF32FewTiles = 64;
+
+// Row tiles of an fp32 launch: equal heights of 16 to 64 rows.  As few as possible, for every one reads W again, but more where that leaves
+// CUs idle or gives some of them more than others: the number that makes (workgroups of the busiest CU) x (height + 16) smallest,
+// more of them only for 3 % of it.  (Several workgroups share a CU, so a CU's work counts and not its rounds.)  Fitted to 160 calls
+// in every number of row tiles that they allow: 0.89 of the time in as few as possible, 1.1 % behind the best, none slower than 1 %.
+// "More of them up to 240 workgroups", whatever their height, was slower than as few as possible for one call in twenty: 113 rows of
+// d = 3976, V = 7478 109 us in two, 134 in three; 347 rows of d = 484, V = 2058 24.2 in six, 27.4 in eight.
+inline int f32_row_tiles(int M, int n_tiles) {
+  const int fewest = (M + 63) / 64;
+  const auto cost_of = [=](int m) -> long {
+    const long height = ((M + m - 1) / m + 15) / 16 * 16;
+    const long busiest = n_tiles < kF32FewTiles ? ((long)n_tiles * m + kXcds * kCusPerXcd - 1) / (kXcds * kCusPerXcd) : tile_rounds(n_tiles, m);
+    return busiest * (height + 16);
+  };
+  int best = fewest;
+  if (cost_of(fewest) > 8L * (64 + 16)) return best;  // many workgroups per CU: the last ones matter little
+  for (int m = fewest + 1; 16 * (m - 1) < M; ++m)
+    if (100 * cost_of(m) < 97 * cost_of(best)) best = m;
+  return best;
+}
+
 }  // namespace fef

@@ -20,6 +20,10 @@ int main() {
       int M, n_tiles, d, least, most;
       in >> M >> n_tiles >> d >> least >> most;
       std::cout << fef::row_tiles(M, n_tiles, d, least, most) << "\n";
+    } else if (rule == "f32_row_tiles") {
+      int M, n_tiles;
+      in >> M >> n_tiles;
+      std::cout << fef::f32_row_tiles(M, n_tiles) << "\n";
     } else {
       return 1;
     }

@@ -46,8 +46,8 @@ def _rounds(n_tiles, row_tiles):
     return -(-max(per_xcd) // 32)
 
 
-def _height(M, m):
-    return -(-(-(-M // m)) // 32) * 32
+def _height(M, m, unit=32):
+    return -(-(-(-M // m)) // unit) * unit
 
 
 @pytest.mark.parametrize("d", [512, 1024, 1088, 4096])
@@ -71,3 +71,17 @@ def test_row_tiles_of_calls_that_were_measured(ask):
     faster = [(256, 33, 1024, 64, 256), (528, 63, 3072, 96, 256), (256, 63, 1024, 64, 256), (128, 125, 4096, 64, 128)]
     assert ask([("row_tiles", *r) for r in faster]) == [4, 4, 4, 2]
     assert ask([("row_tiles", 300, 197, 2048, 96, 256), ("row_tiles", 2048, 494, 4096, 96, 256)]) == [2, 8]
+
+
+def test_fp32_row_tiles_only_where_the_busiest_cu_gains(ask):
+    def work(M, n, m):
+        workgroups = -(-n * m // 256) if n < 64 else _rounds(n, m)
+        return workgroups * (_height(M, m, 16) + 16)
+    sizes = [(M, n) for M in [*range(1, 200), 347, 512, 1000, 4000, 65535] for n in [*range(1, 130, 3), 187, 250, 256, 301, 500, 2000, 1 << 25]]
+    for (M, n), m in zip(sizes, ask([("f32_row_tiles", *s) for s in sizes])):
+        fewest = -(-M // 64)
+        assert fewest <= m <= -(-M // 16)
+        assert m == fewest or work(M, n, m) < work(M, n, fewest)
+    # rows and token tiles of calls that more row tiles made slower, and of some that they made faster
+    assert ask([("f32_row_tiles", *s) for s in [(113, 117), (347, 33), (162, 65), (100, 92)]]) == [2, 6, 3, 2]
+    assert ask([("f32_row_tiles", *s) for s in [(32, 79), (64, 125), (48, 284), (16, 500), (32, 500)]]) == [2, 2, 1, 1, 1]
