@@ -31,7 +31,12 @@ namespace {
 // VEC = 4: d is a multiple of 4, rows are 16-byte aligned and come in pieces of 16 bytes; VEC = 1: any d, 4 bytes per lane.
 // STREAM_W: W in non-temporal loads (see streams_w).  WIDE: rows so long that 64 of them pass 4 GB (d > 2^24): W by 64-bit addresses.
 // ---------------------------------------------------------------------------------------------
-constexpr int kF32Tk = 32, kF32Stages = 3;
+constexpr int kF32Tk = 32;
+
+// Stages of the ring.  In pieces of 4 bytes and with 48 or 64 rows a step is 14 or 16 loads per wavefront: two stages (1078 rows of d = 106,
+// V = 52940 306 -> 290 us) and the loads in groups behind one write of M0 (of d = 183, V = 60000 425 -> 411) are what it takes to stay
+// level with a form that loads through registers (287 and 418).  With fewer rows three stages are up to 20 % ahead, and single loads 5 %.
+constexpr int f32_stages(int mr, int vec) { return vec == 1 && mr >= 48 ? 2 : 3; }
 
 // Direct-to-LDS loads of VEC floats per lane, to LDS offset lds_off + 4 VEC l: from an address, or from an offset in bytes to a
 // uniform one.
@@ -52,6 +57,18 @@ __device__ inline void load_to_lds(const float* base, uint32_t offset, uint32_t 
   else
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" :: "v"(offset), "s"(base), "s"(lds_off) : "memory");
 }
+// VEC = 1: four or two loads behind one write of M0, which holds a wavefront for some tens of cycles.  The instruction's offset moves the
+// LDS address and the memory address alike, 256 bytes per load, so offset (or address) j is 256 j bytes low.
+__device__ inline void load_singles_to_lds(const float* base, const uint32_t (&o)[4], uint32_t lds_off) {
+  asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\t"
+               "global_load_lds_dword %0, %4\n\tglobal_load_lds_dword %1, %4 offset:256\n\t"
+               "global_load_lds_dword %2, %4 offset:512\n\tglobal_load_lds_dword %3, %4 offset:768"
+               :: "v"(o[0]), "v"(o[1]), "v"(o[2]), "v"(o[3]), "s"(base), "s"(lds_off) : "memory");
+}
+__device__ inline void load_singles_to_lds(const float* p0, const float* p1, uint32_t lds_off) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, off\n\tglobal_load_lds_dword %1, off offset:256"
+               :: "v"(p0), "v"(p1), "s"(lds_off) : "memory");
+}
 // Wait until all loads but those of the last `stages` (at most MAX) stages of PER loads are done.
 template <int MAX, int PER>
 __device__ inline void wait_stages(int stages) {
@@ -61,20 +78,22 @@ __device__ inline void wait_stages(int stages) {
 }
 
 // One tile: 16 TW tokens from token n0 on (64-token partial n0 / 64 first) x rows m0 .. m0 + rows - 1 of the launch, by TW wavefronts of
-// 16 tokens each.  h_of(m): row m.  logits, partials: of row 0, rows ldl and a.nT apart.  ring: f32_ring_floats<TW, MR>() floats, free
-// when the function is entered; everybody leaves it behind a barrier.
-template <int TW, int MR>
-constexpr int f32_ring_floats() { return kF32Stages * (16 * TW + MR) * kF32Tk; }
+// 16 tokens each.  h_of(m): row m.  logits, partials: of row 0, rows ldl and a.nT apart.  ring: f32_ring_floats<TW, MR, VEC>() floats,
+// free when the function is entered; everybody leaves it behind a barrier.
+template <int TW, int MR, int VEC>
+constexpr int f32_ring_floats() { return f32_stages(MR, VEC) * (16 * TW + MR) * kF32Tk; }
 
 template <int TW, int MR, int VEC, bool STREAM_W, bool WIDE, class RowPtr>
 __device__ __forceinline__ void f32_tile(const HeadArgs& a, long n0, int m0, int rows, RowPtr h_of, float* logits, long ldl, float2* partials,
                                          float* ring, float (*tile_max)[TW]) {
   constexpr int NR = MR / 16;                 // 16-row groups of H
-  constexpr int TK = kF32Tk, ST = kF32Stages, TOKENS = 16 * TW;
+  constexpr int TK = kF32Tk, ST = f32_stages(MR, VEC), TOKENS = 16 * TW;
   constexpr int LW = TK / (4 * VEC);                                                      // load instructions per wavefront and stage
   constexpr int kLoadsH = MR * TK / (64 * VEC), LH = (kLoadsH + TW - 1) / TW;
   constexpr int kStage = (TOKENS + MR) * TK;  // floats: the rows of W, then MR rows of H
+  constexpr bool MANY = VEC == 1 && MR >= 48;  // see f32_stages
   static_assert(TW % 4 == 0 && MR % 16 == 0 && kLoadsH >= LH, "whole 64-token partials");
+  static_assert(!MANY || (!WIDE && LW % 4 == 0 && LH % 2 == 0), "loads in groups of four and two");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i16 = lane & 15, g = lane >> 4;
@@ -111,15 +130,27 @@ __device__ __forceinline__ void f32_tile(const HeadArgs& a, long n0, int m0, int
     const uint32_t at = slot + stage * (kStage * 4);
     const uint32_t at_w = at + wave * (LW * 256 * VEC), at_h = at + TOKENS * TK * 4 + hfirst * (256 * VEC);
     auto all = [&](auto whole) __attribute__((always_inline)) {
+      const auto back = [&](int col) __attribute__((always_inline)) { return whole || k0 + col < d ? 0 : col; };
+      if constexpr (MANY) {
 #pragma unroll
-      for (int j = 0; j < LW; ++j) {
-        const int back = whole || k0 + wc[j] < d ? 0 : wc[j];
-        if constexpr (WIDE) load_to_lds<VEC>(wp[j] + k0 - back, at_w + j * 256 * VEC);
-        else load_to_lds<VEC, STREAM_W>(wbase + k0, wo[j] - back * 4u, at_w + j * 256 * VEC);
+        for (int j = 0; j < LW; j += 4) {  // the offsets low by 256 bytes each, from a base that is 768 bytes low: none passes zero
+          uint32_t o[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[i] = wo[j + i] - back(wc[j + i]) * 4u + (3 - i) * 256u;
+          load_singles_to_lds(wbase + k0 - 3 * 64, o, at_w + j * 256);
+        }
+#pragma unroll
+        for (int j = 0; j < LH; j += 2)
+          load_singles_to_lds(hp[j] + k0 - back(hc[j]), hp[j + 1] + k0 - back(hc[j + 1]) - 64, at_h + j * 256);
+      } else {
+#pragma unroll
+        for (int j = 0; j < LW; ++j) {
+          if constexpr (WIDE) load_to_lds<VEC>(wp[j] + k0 - back(wc[j]), at_w + j * 256 * VEC);
+          else load_to_lds<VEC, STREAM_W>(wbase + k0, wo[j] - back(wc[j]) * 4u, at_w + j * 256 * VEC);
+        }
+#pragma unroll
+        for (int j = 0; j < LH; ++j) load_to_lds<VEC>(hp[j] + k0 - back(hc[j]), at_h + j * 256 * VEC);
       }
-#pragma unroll
-      for (int j = 0; j < LH; ++j)
-        load_to_lds<VEC>(hp[j] + k0 - (whole || k0 + hc[j] < d ? 0 : hc[j]), at_h + j * 256 * VEC);
     };
     if (k0 + TK <= d) all(std::true_type{});
     else all(std::false_type{});  // columns past the row: the step's first instead, which exist; the multiplies leave them out

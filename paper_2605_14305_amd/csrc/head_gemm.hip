@@ -485,7 +485,7 @@ __global__ __launch_bounds__(kTiledThreads) void head_tiled_kernel(HeadArgs a, i
 // fp32 inputs: tiles of 64 tokens x MR rows (head_f32.hpp).
 template <int MR, int VEC, bool STREAM_W, bool WIDE = false>
 __global__ __launch_bounds__(256) void head_f32_kernel(HeadArgs a, int m_tiles, int n_tiles, long tiles) {
-  __shared__ __attribute__((aligned(16))) float ring[f32_ring_floats<4, MR>()];
+  __shared__ __attribute__((aligned(16))) float ring[f32_ring_floats<4, MR, VEC>()];
   __shared__ float tile_max[MR][4];
   // row tiles of one token tile follow one another on one XCD (workgroup ids go round-robin over
   // the eight), so a W tile is shared through that L2; the grid is capped, hence the loop

@@ -937,7 +937,7 @@ constexpr int kToyWaves = 16, kToyTokens = 16 * kToyWaves;
 
 template <int VEC>
 __global__ __launch_bounds__(kToyWaves * kWave) void toy_round_kernel(HeadArgs h, VerifyArgs a) {
-  __shared__ __attribute__((aligned(16))) float ring[f32_ring_floats<kToyWaves, 16>()];
+  __shared__ __attribute__((aligned(16))) float ring[f32_ring_floats<kToyWaves, 16, VEC>()];
   __shared__ __attribute__((aligned(16))) float logits[16][kToyTokens];
   __shared__ float tile_max[16][kToyWaves];
   __shared__ float2 partials[16 * (kToyTokens / kTiledTn)];

@@ -69,6 +69,12 @@ def test_f32_row_tiles(V):
         _check_rows(M, 37, V)
 
 
+@pytest.mark.parametrize("d", [1, 2, 31, 33, 63, 65, 95, 97, 127, 129, 1027])  # 4-byte pieces, 48 and 64 rows: two stages, one to 33 steps
+def test_f32_steps_of_many_rows_in_single_pieces(d):
+    for M in (34, 48, 50, 64, 98, 130):
+        _check_rows(M, d, 16321)
+
+
 @pytest.mark.parametrize("d,V", [(1024, 20480), (1024, 20481), (1023, 20500), (1023, 20501)])  # 80 MiB of W and more
 def test_f32_to_either_side_of_the_line_for_non_temporal_loads(d, V):
     for M in (16, 32, 48, 64):
