@@ -28,15 +28,19 @@ namespace {
 // A stage is [rows][8 chunks of 16 bytes], chunk c of row r at c ^ ((r >> 1) & 7): two rows cover the 64 banks, so the 64 reads of
 // a fragment (16 rows, the four columns of a chunk) fall on different ones.  The permutation is applied on the global side of the load.
 //
+// TK = 64: steps of 64 columns in two stages, for rows of W that are not whole 128-byte lines.  Where a step is 128 bytes of every row it
+// touches two lines per row then, and neighbouring steps ask for each line twice; of 256 bytes it touches three.  That pays with
+// tiles of 32 rows and long rows: 32 rows of d = 2548, V = 47390 133 -> 120 us per round, of d = 1028, V = 90000 114 -> 107, of d = 1644,
+// V = 60000 114 -> 106 (through registers, with such steps, 121, 106 and 109); with 16 rows up to 20 % behind, with 64 rows, of which
+// two workgroups share a CU and not three, 4 to 12.  [rows][16 chunks], chunk c of row r at c ^ (r & 15).
+//
 // VEC = 4: d is a multiple of 4, rows are 16-byte aligned and come in pieces of 16 bytes; VEC = 1: any d, 4 bytes per lane.
 // STREAM_W: W in non-temporal loads (see streams_w).  WIDE: rows so long that 64 of them pass 4 GB (d > 2^24): W by 64-bit addresses.
 // ---------------------------------------------------------------------------------------------
-constexpr int kF32Tk = 32;
-
 // Stages of the ring.  In pieces of 4 bytes and with 48 or 64 rows a step is 14 or 16 loads per wavefront: two stages (1078 rows of d = 106,
 // V = 52940 306 -> 290 us) and the loads in groups behind one write of M0 (of d = 183, V = 60000 425 -> 411) are what it takes to stay
 // level with a form that loads through registers (287 and 418).  With fewer rows three stages are up to 20 % ahead, and single loads 5 %.
-constexpr int f32_stages(int mr, int vec) { return vec == 1 && mr >= 48 ? 2 : 3; }
+constexpr int f32_stages(int mr, int vec, int tk) { return tk == 64 || (vec == 1 && mr >= 48) ? 2 : 3; }
 
 // Direct-to-LDS loads of VEC floats per lane, to LDS offset lds_off + 4 VEC l: from an address, or from an offset in bytes to a
 // uniform one.
@@ -78,16 +82,16 @@ __device__ inline void wait_stages(int stages) {
 }
 
 // One tile: 16 TW tokens from token n0 on (64-token partial n0 / 64 first) x rows m0 .. m0 + rows - 1 of the launch, by TW wavefronts of
-// 16 tokens each.  h_of(m): row m.  logits, partials: of row 0, rows ldl and a.nT apart.  ring: f32_ring_floats<TW, MR, VEC>() floats,
+// 16 tokens each.  h_of(m): row m.  logits, partials: of row 0, rows ldl and a.nT apart.  ring: f32_ring_floats<TW, MR, VEC, TK>() floats,
 // free when the function is entered; everybody leaves it behind a barrier.
-template <int TW, int MR, int VEC>
-constexpr int f32_ring_floats() { return f32_stages(MR, VEC) * (16 * TW + MR) * kF32Tk; }
+template <int TW, int MR, int VEC, int TK>
+constexpr int f32_ring_floats() { return f32_stages(MR, VEC, TK) * (16 * TW + MR) * TK; }
 
-template <int TW, int MR, int VEC, bool STREAM_W, bool WIDE, class RowPtr>
+template <int TW, int MR, int VEC, int TK, bool STREAM_W, bool WIDE, class RowPtr>
 __device__ __forceinline__ void f32_tile(const HeadArgs& a, long n0, int m0, int rows, RowPtr h_of, float* logits, long ldl, float2* partials,
                                          float* ring, float (*tile_max)[TW]) {
   constexpr int NR = MR / 16;                 // 16-row groups of H
-  constexpr int TK = kF32Tk, ST = f32_stages(MR, VEC), TOKENS = 16 * TW;
+  constexpr int ST = f32_stages(MR, VEC, TK), HALVES = TK / 32, TOKENS = 16 * TW;
   constexpr int LW = TK / (4 * VEC);                                                      // load instructions per wavefront and stage
   constexpr int kLoadsH = MR * TK / (64 * VEC), LH = (kLoadsH + TW - 1) / TW;
   constexpr int kStage = (TOKENS + MR) * TK;  // floats: the rows of W, then MR rows of H
@@ -98,9 +102,9 @@ __device__ __forceinline__ void f32_tile(const HeadArgs& a, long n0, int m0, int
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i16 = lane & 15, g = lane >> 4;
   const int d = a.d;
-  const int nk = (d + TK - 1) / TK;
+  const int nk = (d + 31) / 32, nsteps = (d + TK - 1) / TK;
   // 16-byte chunk c of row r of a stage lies at chunk c ^ twist(r)
-  auto twist = [](int r) { return (r >> 1) & 7; };
+  auto twist = [](int r) { return TK == 32 ? (r >> 1) & 7 : r & 15; };
   // Load instruction j of a wavefront fills 64 VEC floats of a stage, lane l the VEC of them from float l VEC on.
   uint32_t wo[LW];        // offset in bytes to the tile's first row
   const float* wp[WIDE ? LW : 1];
@@ -129,6 +133,13 @@ __device__ __forceinline__ void f32_tile(const HeadArgs& a, long n0, int m0, int
   auto fetch = [&](int k0, int stage) __attribute__((always_inline)) {
     const uint32_t at = slot + stage * (kStage * 4);
     const uint32_t at_w = at + wave * (LW * 256 * VEC), at_h = at + TOKENS * TK * 4 + hfirst * (256 * VEC);
+    // (uniform; with steps of 64 the compiler has to be told)
+    const float* wk = wbase + k0;
+    if constexpr (TK != 32) {
+      const uint64_t x = (uint64_t)(uintptr_t)wk;
+      wk = (const float*)(uintptr_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x) |
+                                     (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32);
+    }
     auto all = [&](auto whole) __attribute__((always_inline)) {
       const auto back = [&](int col) __attribute__((always_inline)) { return whole || k0 + col < d ? 0 : col; };
       if constexpr (MANY) {
@@ -137,7 +148,7 @@ __device__ __forceinline__ void f32_tile(const HeadArgs& a, long n0, int m0, int
           uint32_t o[4];
 #pragma unroll
           for (int i = 0; i < 4; ++i) o[i] = wo[j + i] - back(wc[j + i]) * 4u + (3 - i) * 256u;
-          load_singles_to_lds(wbase + k0 - 3 * 64, o, at_w + j * 256);
+          load_singles_to_lds(wk - 3 * 64, o, at_w + j * 256);
         }
 #pragma unroll
         for (int j = 0; j < LH; j += 2)
@@ -146,7 +157,7 @@ __device__ __forceinline__ void f32_tile(const HeadArgs& a, long n0, int m0, int
 #pragma unroll
         for (int j = 0; j < LW; ++j) {
           if constexpr (WIDE) load_to_lds<VEC>(wp[j] + k0 - back(wc[j]), at_w + j * 256 * VEC);
-          else load_to_lds<VEC, STREAM_W>(wbase + k0, wo[j] - back(wc[j]) * 4u, at_w + j * 256 * VEC);
+          else load_to_lds<VEC, STREAM_W>(wk, wo[j] - back(wc[j]) * 4u, at_w + j * 256 * VEC);
         }
 #pragma unroll
         for (int j = 0; j < LH; ++j) load_to_lds<VEC>(hp[j] + k0 - back(hc[j]), at_h + j * 256 * VEC);
@@ -159,40 +170,45 @@ __device__ __forceinline__ void f32_tile(const HeadArgs& a, long n0, int m0, int
   floatx4 acc[NR];
 #pragma unroll
   for (int n = 0; n < NR; ++n) acc[n] = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int t = 0; t < ST - 1 && t < nk; ++t) fetch(t * TK, t);
+  for (int t = 0; t < ST - 1 && t < nsteps; ++t) fetch(t * TK, t);
   int stage = 0;
-  // The fragments of a step are read while the step before is multiplied.
-  float wv[2][TK / 4], hv[2][NR][TK / 4];
-  int at[TK / 4];
+  // The fragments of 32 columns are read while the 32 before are multiplied: a step, or half of one (the parity says which).
+  float wv[2][8], hv[2][NR][8];
+  int at[8];
 #pragma unroll
-  for (int c = 0; c < TK / 4; ++c) at[c] = (c ^ twist(i16)) * 4;
+  for (int c = 0; c < 8; ++c) at[c] = (c ^ (twist(i16) & 7)) * 4;
+  const int half0 = TK == 32 ? 0 : (i16 & 8) * 4;
   auto read = [&](int kt, auto set_tag) __attribute__((always_inline)) {
     constexpr int S = decltype(set_tag)::value;
-    wait_stages<ST - 2, LW + LH>(nk - 1 - kt);
-    lds_barrier();  // the step has arrived, and everybody is done with the one before
-    if (kt + ST - 1 < nk) fetch((kt + ST - 1) * TK, stage == 0 ? ST - 1 : stage - 1);
-    const float* ws = ring + stage * kStage + (wave * 16 + i16) * TK + g;
-    const float* hs = ring + stage * kStage + (TOKENS + i16) * TK + g;
+    if constexpr (HALVES == 1 || S == 0) {
+      const int step = kt / HALVES;
+      wait_stages<ST - 2, LW + LH>(nsteps - 1 - step);
+      lds_barrier();  // the step has arrived, and everybody is done with the one before
+      if (step + ST - 1 < nsteps) fetch((step + ST - 1) * TK, stage == 0 ? ST - 1 : stage - 1);
+    }
+    const int half = HALVES == 1 ? 0 : S == 0 ? half0 : 32 - half0;
+    const float* ws = ring + stage * kStage + (wave * 16 + i16) * TK + half + g;
+    const float* hs = ring + stage * kStage + (TOKENS + i16) * TK + half + g;
 #pragma unroll
-    for (int c = 0; c < TK / 4; ++c) {
+    for (int c = 0; c < 8; ++c) {
       wv[S][c] = ws[at[c]];
 #pragma unroll
       for (int n = 0; n < NR; ++n) hv[S][n][c] = hs[n * 16 * TK + at[c]];
     }
-    stage = stage == ST - 1 ? 0 : stage + 1;
+    if constexpr (HALVES == 1 || S == 1) stage = stage == ST - 1 ? 0 : stage + 1;
   };
   auto multiply = [&](auto set_tag) __attribute__((always_inline)) {
     constexpr int S = decltype(set_tag)::value;
 #pragma unroll
-    for (int c = 0; c < TK / 4; ++c)
+    for (int c = 0; c < 8; ++c)
 #pragma unroll
       for (int n = 0; n < NR; ++n) acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[S][c], hv[S][n][c], acc[n], 0, 0, 0);
   };
   auto mask = [&](auto set_tag) __attribute__((always_inline)) {  // last step: columns at and past d count as zero
     constexpr int S = decltype(set_tag)::value;
 #pragma unroll
-    for (int c = 0; c < TK / 4; ++c) {
-      const bool in = (nk - 1) * TK + 4 * c + g < d;
+    for (int c = 0; c < 8; ++c) {
+      const bool in = (nk - 1) * 32 + 4 * c + g < d;
       wv[S][c] = in ? wv[S][c] : 0.f;
 #pragma unroll
       for (int n = 0; n < NR; ++n) hv[S][n][c] = in ? hv[S][n][c] : 0.f;
@@ -211,10 +227,10 @@ __device__ __forceinline__ void f32_tile(const HeadArgs& a, long n0, int m0, int
   if (kt < nk) {
     read(kt, Odd{});
     multiply(Even{});
-    if (d % TK != 0) mask(Odd{});
+    if (d % 32 != 0) mask(Odd{});
     multiply(Odd{});
   } else {
-    if (d % TK != 0) mask(Even{});
+    if (d % 32 != 0) mask(Even{});
     multiply(Even{});
   }
 

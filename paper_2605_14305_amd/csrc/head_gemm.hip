@@ -483,9 +483,9 @@ __global__ __launch_bounds__(kTiledThreads) void head_tiled_kernel(HeadArgs a, i
 }
 
 // fp32 inputs: tiles of 64 tokens x MR rows (head_f32.hpp).
-template <int MR, int VEC, bool STREAM_W, bool WIDE = false>
+template <int MR, int VEC, int TK, bool STREAM_W, bool WIDE = false>
 __global__ __launch_bounds__(256) void head_f32_kernel(HeadArgs a, int m_tiles, int n_tiles, long tiles) {
-  __shared__ __attribute__((aligned(16))) float ring[f32_ring_floats<4, MR, VEC>()];
+  __shared__ __attribute__((aligned(16))) float ring[f32_ring_floats<4, MR, VEC, TK>()];
   __shared__ float tile_max[MR][4];
   // row tiles of one token tile follow one another on one XCD (workgroup ids go round-robin over
   // the eight), so a W tile is shared through that L2; the grid is capped, hence the loop
@@ -499,7 +499,7 @@ __global__ __launch_bounds__(256) void head_f32_kernel(HeadArgs a, int m_tiles, 
       const int r = a.row0 + m;
       return r < a.BK ? (const float*)a.h_draft + (size_t)r * a.d : (const float*)a.h_target + (size_t)(r - a.BK) * a.d;
     };
-    f32_tile<4, MR, VEC, STREAM_W, WIDE>(a, (long)nt * kTiledTn, mt * MR, min(MR, a.nrows - mt * MR), h_of, a.logits, a.ldl, a.partials, ring, tile_max);
+    f32_tile<4, MR, VEC, TK, STREAM_W, WIDE>(a, (long)nt * kTiledTn, mt * MR, min(MR, a.nrows - mt * MR), h_of, a.logits, a.ldl, a.partials, ring, tile_max);
   }
 }
 
@@ -552,14 +552,16 @@ hipError_t launch_f32(const HeadArgs& a) {
   const int m_tiles = (a.nrows + MR - 1) / MR, n_tiles = a.nT;
   const long tiles = (n_tiles < kF32FewTiles ? n_tiles : 8L * ((n_tiles + 7) / 8)) * m_tiles;
   const dim3 grid((unsigned)(tiles < (1L << 20) ? tiles : 1L << 20)), block(256);
-  const bool stream = streams_w(a.V, a.d, 4, m_tiles, false);
   if (a.d > 1 << 24) {
-    FEF_LAUNCH_HEAD((head_f32_kernel<MR, 1, false, MR == 16>), grid, block, a, a, m_tiles, n_tiles, tiles);
-  } else if (a.d % 4 == 0) {
-    if (stream) FEF_LAUNCH_HEAD((head_f32_kernel<MR, 4, true>), grid, block, a, a, m_tiles, n_tiles, tiles);
-    else FEF_LAUNCH_HEAD((head_f32_kernel<MR, 4, false>), grid, block, a, a, m_tiles, n_tiles, tiles);
+    FEF_LAUNCH_HEAD((head_f32_kernel<MR, 1, 32, false, MR == 16>), grid, block, a, a, m_tiles, n_tiles, tiles);
+  } else if (a.d % 4 != 0) {
+    FEF_LAUNCH_HEAD((head_f32_kernel<MR, 1, 32, false>), grid, block, a, a, m_tiles, n_tiles, tiles);
+  } else if (MR == 32 && a.d % 32 != 0 && a.d >= 896) {
+    FEF_LAUNCH_HEAD((head_f32_kernel<MR, 4, MR == 32 ? 64 : 32, false>), grid, block, a, a, m_tiles, n_tiles, tiles);
+  } else if (streams_w(a.V, a.d, 4, m_tiles, false)) {
+    FEF_LAUNCH_HEAD((head_f32_kernel<MR, 4, 32, true>), grid, block, a, a, m_tiles, n_tiles, tiles);
   } else {
-    FEF_LAUNCH_HEAD((head_f32_kernel<MR, 1, false>), grid, block, a, a, m_tiles, n_tiles, tiles);
+    FEF_LAUNCH_HEAD((head_f32_kernel<MR, 4, 32, false>), grid, block, a, a, m_tiles, n_tiles, tiles);
   }
   return hipGetLastError();
 }

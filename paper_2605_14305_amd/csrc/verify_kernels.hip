@@ -937,7 +937,7 @@ constexpr int kToyWaves = 16, kToyTokens = 16 * kToyWaves;
 
 template <int VEC>
 __global__ __launch_bounds__(kToyWaves * kWave) void toy_round_kernel(HeadArgs h, VerifyArgs a) {
-  __shared__ __attribute__((aligned(16))) float ring[f32_ring_floats<kToyWaves, 16, VEC>()];
+  __shared__ __attribute__((aligned(16))) float ring[f32_ring_floats<kToyWaves, 16, VEC, 32>()];
   __shared__ __attribute__((aligned(16))) float logits[16][kToyTokens];
   __shared__ float tile_max[16][kToyWaves];
   __shared__ float2 partials[16 * (kToyTokens / kTiledTn)];
@@ -949,7 +949,7 @@ __global__ __launch_bounds__(kToyWaves * kWave) void toy_round_kernel(HeadArgs h
   const float* hd = (const float*)h.h_draft + slot * h.d;
   const float* ht = (const float*)h.h_target + slot * h.d - (size_t)K * h.d;
   const auto h_of = [=](int m) { return (m < K ? hd : ht) + (size_t)m * h.d; };
-  f32_tile<kToyWaves, 16, VEC, false, false>(h, 0, 0, 2 * K, h_of, &logits[0][0], kToyTokens, partials, ring, tile_max);
+  f32_tile<kToyWaves, 16, VEC, 32, false, false>(h, 0, 0, 2 * K, h_of, &logits[0][0], kToyTokens, partials, ring, tile_max);
 
   float* diag_lse = a.diag_lse;
   const int BK = a.B * K;

@@ -75,6 +75,12 @@ def test_f32_steps_of_many_rows_in_single_pieces(d):
         _check_rows(M, d, 16321)
 
 
+@pytest.mark.parametrize("d", [892, 896, 900, 1024, 1028, 1052, 1056, 1060, 1084, 1092, 1116, 1148, 2004])  # steps of 64 columns where lines are shared
+def test_f32_steps_of_64_columns(d):
+    for M in (16, 18, 32, 34):
+        _check_rows(M, d, 16321)
+
+
 @pytest.mark.parametrize("d,V", [(1024, 20480), (1024, 20481), (1023, 20500), (1023, 20501)])  # 80 MiB of W and more
 def test_f32_to_either_side_of_the_line_for_non_temporal_loads(d, V):
     for M in (16, 32, 48, 64):
