@@ -781,7 +781,7 @@ __global__ __launch_bounds__(NT) void accept_resid_kernel(VerifyArgs a) {
 
 // ---------------------------------------------------------------------------------------------
 // Kernel 2 of a call that wants the masses of every slot: residual and overlap mass per chunk.
-// grid = (B*K, ceil(nRC / (NW * kMassPer))); a wavefront takes kMassPer neighbouring chunks and asks
+// grid = (B*K, ceil(nRC / (NW * kMassPer))), both capped; a wavefront takes kMassPer neighbouring chunks and asks
 // for all of them before it uses the first.  Bound: the two passes' worth of exponentials and one read of all logits
 // (1.04 GB at 64 x 16 slots, V = 126464).  Which slot was rejected does not matter here, so nothing waits for the
 // accept tests (the final kernel does them); with them repeated in front of every chunk this took 260 us, without them 191, and
@@ -793,11 +793,8 @@ __global__ __launch_bounds__(NT) void accept_resid_kernel(VerifyArgs a) {
 // ---------------------------------------------------------------------------------------------
 constexpr int kMassPer = 2;
 template <bool COPY>
-__global__ __launch_bounds__(NT) void slot_mass_kernel(VerifyArgs a) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int s = blockIdx.x, BK = a.B * a.K;
-  const int c0 = (blockIdx.y * NW + wave) * kMassPer;
-  if (c0 >= a.nRC) return;
+__device__ __forceinline__ void slot_masses(const VerifyArgs& a, int s, int c0) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, BK = a.B * a.K;
   const float* Lq = a.logits + (size_t)s * a.ldl;
   const float* Lp = a.logits + (size_t)(BK + s) * a.ldl;
   const int window = a.window[s / a.K];
@@ -848,6 +845,28 @@ __global__ __launch_bounds__(NT) void slot_mass_kernel(VerifyArgs a) {
       a.amass[(size_t)s * a.nRC + c0 + j] = as;
     }
   }
+}
+
+// MANY: slots that would be 2^32 threads, of which a launch runs only a part, or more groups of chunks than a grid is high.  (The loops cost
+// the ordinary call 2 us of 167.)
+constexpr int kMassSlots = 1 << 23, kMassGroups = 65535;
+template <bool COPY, bool MANY>
+__global__ __launch_bounds__(NT) void slot_mass_kernel(VerifyArgs a) {
+  const int c = (blockIdx.y * NW + (threadIdx.x >> 6)) * kMassPer;
+  if constexpr (MANY) {
+    for (int s = blockIdx.x; s < a.B * a.K; s += kMassSlots)
+      for (int c0 = c; c0 < a.nRC; c0 += kMassGroups * NW * kMassPer) slot_masses<COPY>(a, s, c0);
+  } else if (c < a.nRC) {
+    slot_masses<COPY>(a, blockIdx.x, c);
+  }
+}
+
+template <bool COPY>
+void launch_slot_masses(const VerifyArgs& a) {
+  const int slots = a.B * a.K, groups = (a.nRC + NW * kMassPer - 1) / (NW * kMassPer);
+  const dim3 grid(slots < kMassSlots ? slots : kMassSlots, groups < kMassGroups ? groups : kMassGroups);
+  if (slots > kMassSlots || groups > kMassGroups) hipLaunchKernelGGL((slot_mass_kernel<COPY, true>), grid, dim3(NT), 0, a.stream, a);
+  else hipLaunchKernelGGL((slot_mass_kernel<COPY, false>), grid, dim3(NT), 0, a.stream, a);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1081,9 +1100,8 @@ hipError_t launch_verify(const VerifyArgs& a) {
     hipLaunchKernelGGL(topn_kernel, dim3(a.B), dim3(kWave), 0, a.stream, a);
   } else if (a.phase != 1) {  // everything after the draft sample needs the target laws
     if (a.all_slots) {
-      const dim3 grid(a.B * a.K, (a.nRC + NW * kMassPer - 1) / (NW * kMassPer));
-      if (a.diag_logits) hipLaunchKernelGGL(slot_mass_kernel<true>, grid, dim3(NT), 0, a.stream, a);
-      else hipLaunchKernelGGL(slot_mass_kernel<false>, grid, dim3(NT), 0, a.stream, a);
+      if (a.diag_logits) launch_slot_masses<true>(a);
+      else launch_slot_masses<false>(a);
       hipLaunchKernelGGL(finalize_kernel<kSlots>, dim3(a.B), dim3(NT), 0, a.stream, a);
     } else if (a.nRC <= kAloneChunks || a.greedy) {
       hipLaunchKernelGGL(finalize_kernel<kAlone>, dim3(a.B), dim3(NT), 0, a.stream, a);
