@@ -81,19 +81,22 @@ def test_f32_steps_of_64_columns(d):
         _check_rows(M, d, 16321)
 
 
-@pytest.mark.parametrize("d,V", [(1024, 20480), (1024, 20481), (1023, 20500), (1023, 20501)])  # 80 MiB of W and more
+@pytest.mark.parametrize("d,V", [(1024, 65536), (1024, 65537), (1056, 63551), (1023, 65700), (1028, 65600)])  # 256 MiB of W and more
 def test_f32_to_either_side_of_the_line_for_non_temporal_loads(d, V):
     for M in (16, 32, 48, 64):
         _check_rows(M, d, V)
 
 
+@pytest.mark.parametrize("V", [5, 65])  # the 64th row of a tile starts just under 4 GiB behind the first, and past it from 2^24 + 1 on
 @pytest.mark.parametrize("d", [(1 << 24) - 1, 1 << 24, (1 << 24) + 1])
-def test_f32_rows_of_two_to_the_24(d):
+def test_f32_rows_of_two_to_the_24(d, V):
     at = torch.tensor([0, 5, d // 2, d - 2, d - 1], device="cuda")  # few terms, so that the bound means something
-    W = torch.zeros(5, d, device="cuda").normal_()
+    W = torch.zeros(V, d, device="cuda").normal_()
     h = torch.zeros(4, d, device="cuda")
     h[:, at] = torch.randn(4, 5, device="cuda")
-    vs = fb.VerifyStep(2, 1, 4, d, 5, dtype="f32", diag=True, diag_logits=True)
+    vs = fb.VerifyStep(2, 1, 4, d, V, dtype="f32", diag=True, diag_logits=True)
     vs(h[:2].view(2, 1, d), h[2:].clone().view(2, 1, d), W, 5)
     terms = h[:, None, at].double() * W[None][:, :, at].double()
-    assert bool(((vs.diag["logits"].view(4, 5) - terms.sum(2)).abs() <= 7 * 2.0 ** -24 * terms.abs().sum(2)).all())
+    assert bool(((vs.diag["logits"].view(4, V) - terms.sum(2)).abs() <= 7 * 2.0 ** -24 * terms.abs().sum(2)).all())
+    del W, h, vs
+    torch.cuda.empty_cache()

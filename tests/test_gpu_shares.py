@@ -34,6 +34,18 @@ def _check_round(variant, M, d, V):
     assert bool(((vs.diag["lse"].view(-1) - torch.logsumexp(want, 1)).abs() <= bound.max(1).values + 2e-5).all())
 
 
+def _check_loss(R, d, V):
+    g = torch.Generator(device="cuda").manual_seed(R + V)
+    W = (torch.randn(V, d, generator=g, device="cuda") * 0.1).bfloat16()
+    h = torch.randn(R, d, generator=g, device="cuda").bfloat16()
+    labels = torch.randint(0, V, (R,), generator=g, device="cuda", dtype=torch.int32)
+    ce, _ = fb.HeadCrossEntropy(R, d, V)(h, W, labels)
+    L = h.double() @ W.double().t().contiguous()
+    want = torch.logsumexp(L, 1) - L.gather(1, labels.long()[:, None])[:, 0]
+    bound = 2 * _bound(h.double(), W.double(), d, 1.0).max(1).values + 2e-5
+    assert bool(((ce - want).abs() <= bound).all())
+
+
 @pytest.mark.parametrize("V", VOCABULARIES)
 @pytest.mark.parametrize("variant,d", [(fb.FEF_GEMM_STREAM, 64), (fb.FEF_GEMM_STREAM, 192), (fb.FEF_GEMM_ROWSTREAM, 512)])
 def test_runs(variant, d, V):
@@ -76,37 +88,29 @@ def test_more_row_tiles_where_the_vocabulary_is_short(variant, d, rows, V):
 @pytest.mark.parametrize("R", [200, 257, 300, 512, 513, 1000])
 @pytest.mark.parametrize("d", [128, 1024, 1088])  # eight and four wavefronts
 def test_row_tiles_of_a_cross_entropy_call(V, R, d):
-    g = torch.Generator(device="cuda").manual_seed(R + V)
-    W = (torch.randn(V, d, generator=g, device="cuda") * 0.1).bfloat16()
-    h = torch.randn(R, d, generator=g, device="cuda").bfloat16()
-    labels = torch.randint(0, V, (R,), generator=g, device="cuda", dtype=torch.int32)
-    ce, _ = fb.HeadCrossEntropy(R, d, V)(h, W, labels)
-    L = h.double() @ W.double().t().contiguous()
-    want = torch.logsumexp(L, 1) - L.gather(1, labels.long()[:, None])[:, 0]
-    bound = 2 * _bound(h.double(), W.double(), d, 1.0).max(1).values + 2e-5
-    assert bool(((ce - want).abs() <= bound).all())
+    _check_loss(R, d, V)
 
 
-@pytest.mark.parametrize("variant,M", [(fb.FEF_GEMM_STREAM, 34), (fb.FEF_GEMM_STREAM, 128), (fb.FEF_GEMM_ROWSTREAM, 50),
-                                       (fb.FEF_GEMM_ROWSTREAM, 96), (fb.FEF_GEMM_TILED256, 32), (fb.FEF_GEMM_TILED256, 160),
-                                       (fb.FEF_GEMM_TILED256, 256)])
-@pytest.mark.parametrize("V", [10240, 10241])  # 80 MiB of W and a row more: ordinary and non-temporal loads
-def test_w_to_either_side_of_the_line_for_non_temporal_loads(variant, M, V):
-    _check_round(variant, M, 4096, V)
+# 256 MiB of W and a row, or 64 columns, more: ordinary and non-temporal loads.  One row tile at every height that a form has (one or two in a
+# cross-entropy call of more than 256 rows); that these calls take the forms they are meant for is checked in test_head_rules.py.
+LINE_OF_A_ROUND = [(65536, 2048), (65537, 2048)]
+ROUNDS_AT_THE_LINE = [(fb.FEF_GEMM_STREAM, (2, 34, 66, 128)), (fb.FEF_GEMM_ROWSTREAM, (2, 34, 66, 128)),
+                      (fb.FEF_GEMM_TILED256, (32, 64, 96, 128, 160, 192, 224, 256))]
+LINES_OF_A_LOSS = [(126464, (1024, 1088), (30, 60, 90, 120, 150, 190, 220, 250, 300, 380, 440, 512)),  # whole tiles
+                   (65537, (1984, 2048), (30, 120, 250))]                                              # shares
 
 
-@pytest.mark.parametrize("R", [30, 120, 250])
-@pytest.mark.parametrize("V", [10240, 10241])
-def test_cross_entropy_to_either_side_of_that_line(R, V):
-    g = torch.Generator(device="cuda").manual_seed(R + V)
-    W = (torch.randn(V, 4096, generator=g, device="cuda") * 0.1).bfloat16()
-    h = torch.randn(R, 4096, generator=g, device="cuda").bfloat16()
-    labels = torch.randint(0, V, (R,), generator=g, device="cuda", dtype=torch.int32)
-    ce, _ = fb.HeadCrossEntropy(R, 4096, V)(h, W, labels)
-    L = h.double() @ W.double().t().contiguous()
-    want = torch.logsumexp(L, 1) - L.gather(1, labels.long()[:, None])[:, 0]
-    bound = 2 * _bound(h.double(), W.double(), 4096, 1.0).max(1).values + 2e-5
-    assert bool(((ce - want).abs() <= bound).all())
+@pytest.mark.parametrize("variant,rows", ROUNDS_AT_THE_LINE)
+@pytest.mark.parametrize("V,d", LINE_OF_A_ROUND)
+def test_w_to_either_side_of_the_line_for_non_temporal_loads(variant, rows, V, d):
+    for M in rows:
+        _check_round(variant, M, d, V)
+
+
+@pytest.mark.parametrize("V,d,rows", [(V, d, rows) for V, ds, rows in LINES_OF_A_LOSS for d in ds])
+def test_cross_entropy_to_either_side_of_that_line(V, d, rows):
+    for R in rows:
+        _check_loss(R, d, V)
 
 
 @pytest.mark.parametrize("variant,M", [(fb.FEF_GEMM_TILED256, 40), (fb.FEF_GEMM_STREAM, 40), (fb.FEF_GEMM_ROWSTREAM, 40),

@@ -4,6 +4,10 @@ import subprocess
 
 import pytest
 
+from paper_2605_14305_amd import binding as fb
+import test_gpu_f32_head as f32_head
+import test_gpu_shares as shares
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
@@ -85,3 +89,35 @@ def test_fp32_row_tiles_only_where_the_busiest_cu_gains(ask):
     # rows and token tiles of calls that more row tiles made slower, and of some that they made faster
     assert ask([("f32_row_tiles", *s) for s in [(113, 117), (347, 33), (162, 65), (100, 92)]]) == [2, 6, 3, 2]
     assert ask([("f32_row_tiles", *s) for s in [(32, 79), (64, 125), (48, 284), (16, 500), (32, 500)]]) == [2, 2, 1, 1, 1]
+
+
+def test_what_the_gpu_tests_at_the_line_for_non_temporal_loads_run(ask):
+    (V0, d0), (V1, d1) = shares.LINE_OF_A_ROUND
+    assert ask([("streams_w", V0, d0, 2, 1, 0), ("streams_w", V1, d1, 2, 1, 0)]) == [0, 1]
+    for variant, rows in shares.ROUNDS_AT_THE_LINE:
+        unit, per = {fb.FEF_GEMM_STREAM: (64, 4), fb.FEF_GEMM_ROWSTREAM: (16, 8)}.get(variant, (256, 1))
+        most = 256 if variant == fb.FEF_GEMM_TILED256 else 128
+        for V in (V0, V1):
+            tiles = -(-V // unit) if per == 1 else min(256, -(-(-(-V // unit)) // per))
+            assert ask([("row_tiles", M, tiles, d0, 64, most) for M in rows]) == [1] * len(rows)
+        assert {_height(M, 1) for M in rows} == set(range(32, most + 1, 32))
+    for V, (below, above), rows in shares.LINES_OF_A_LOSS:
+        whole = -(-V // 256) % 256 > 200  # else shares of the vocabulary, one row tile
+        tiles = [ask([("row_tiles", R, -(-V // 256), d, 64 if R <= 256 else 96, 256) for R in rows]) if whole else [1] * len(rows)
+                 for d in (below, above)]
+        assert tiles == [[-(-R // 256) for R in rows]] * 2
+        for t in set(tiles[0]):
+            assert ask([("streams_w", V, d, 2, t, 1) for d in (below, above)]) == [0, 1]
+        if whole:
+            assert {(t, _height(R, t)) for R, t in zip(rows, tiles[0])} == {(1, h) for h in range(32, 257, 32)} | {(2, h) for h in (160, 192, 224, 256)}
+
+
+def test_what_the_gpu_tests_of_the_fp32_head_run(ask):
+    def line(test, name):
+        return next(m.args[1] for m in test.pytestmark if m.name == "parametrize" and m.args[0] == name)
+    sizes = line(f32_head.test_f32_to_either_side_of_the_line_for_non_temporal_loads, "d,V")
+    assert ask([("streams_w", V, d, 4, 1, 0) for d, V in sizes]) == [0, 1, 1, 0, 0]
+    assert all(ask([("f32_row_tiles", M, -(-V // 64)) for M in (16, 32, 48, 64)]) == [1] * 4 for _, V in sizes)
+    # rows per tile of the tests of steps: 48 and 64, and 16, 32 and 48
+    assert {_height(M, m, 16) for M, m in zip((34, 48, 50, 64, 98, 130), ask([("f32_row_tiles", M, 256) for M in (34, 48, 50, 64, 98, 130)]))} == {48, 64}
+    assert {_height(M, m, 16) for M, m in zip((16, 18, 32, 34), ask([("f32_row_tiles", M, 256) for M in (16, 18, 32, 34)]))} == {16, 32, 48}
