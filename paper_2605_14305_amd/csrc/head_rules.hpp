@@ -14,7 +14,7 @@ namespace fef {
 // d = 2560, V = 40000 60 against 77), and so is the second half of a split round (8 rows of d = 5056, V = 10577 111 against 129 us
 // per round); where the cache is swept in between, non-temporal ones are 0 to 4 % ahead.  Some of a W a little longer than the cache
 // stays too: at 258 MiB ordinary loads are up to 1.25 times as fast (16 fp32 rows of d = 2048), at 285 level, from 300 on behind by
-// 4 to 10 %, and at 250 rows from 320 on.  Hence the line.
+// 4 to 10 % (37 rows of a cross-entropy call of d = 1024, V = 151936, 297 MiB, 65 against 59 us).  Hence the line.
 // Rows of W that are not whole 128-byte lines (fp32, d not a multiple of 32): the two k-steps that share a line then fetch it twice, at
 // any size of W (16 fp32 rows of d = 1046, V = 150369 164 -> 191 us with non-temporal loads, 30 of d = 2548, V = 47390 129 -> 152).
 // Two row tiles share W through L2 as far as they keep in step, and non-temporal loads cost a round that (144 rows of d = 7168, V = 22000
@@ -22,7 +22,7 @@ namespace fef {
 // and level, 256 of d = 5120 to 8192 level to 4 % ahead); a cross-entropy call, which writes no logits, loses up to 2 % (300 rows of
 // d = 2048, V = 81920) and gains up to 5 (300 rows of d = 4096, V = 126464 315 -> 303 us, of d = 4096, V = 50257 149 -> 142).
 inline bool streams_w(size_t V, size_t d, size_t element_bytes, int row_tiles, bool loss) {
-  return row_tiles <= (loss ? 2 : 1) && d * element_bytes % 128 == 0 && V * d * element_bytes > (size_t)320 << 20;
+  return row_tiles <= (loss ? 2 : 1) && d * element_bytes % 128 == 0 && V * d * element_bytes > (size_t)288 << 20;
 }
 
 constexpr int kXcds = 8, kCusPerXcd = 32;

@@ -81,7 +81,7 @@ def test_f32_steps_of_64_columns(d):
         _check_rows(M, d, 16321)
 
 
-@pytest.mark.parametrize("d,V", [(1024, 81920), (1024, 81921), (1056, 79439), (1023, 82100), (1028, 81700)])  # 320 MiB of W and more
+@pytest.mark.parametrize("d,V", [(1024, 73728), (1024, 73729), (1056, 71494), (1023, 73900), (1028, 73500)])  # 288 MiB of W and more
 def test_f32_to_either_side_of_the_line_for_non_temporal_loads(d, V):
     for M in (16, 32, 48, 64):
         _check_rows(M, d, V)

@@ -91,13 +91,13 @@ def test_row_tiles_of_a_cross_entropy_call(V, R, d):
     _check_loss(R, d, V)
 
 
-# 320 MiB of W and a row, or 64 columns, more: ordinary and non-temporal loads.  One row tile at every height that a form has (one or two in a
+# 288 MiB of W and a row, or 64 columns, more: ordinary and non-temporal loads.  One row tile at every height that a form has (one or two in a
 # cross-entropy call of more than 256 rows); that these calls take the forms they are meant for is checked in test_head_rules.py.
-LINE_OF_A_ROUND = [(81920, 2048), (81921, 2048)]
+LINE_OF_A_ROUND = [(73728, 2048), (73729, 2048)]
 ROUNDS_AT_THE_LINE = [(fb.FEF_GEMM_STREAM, (2, 34, 66, 128)), (fb.FEF_GEMM_ROWSTREAM, (2, 34, 66, 128)),
                       (fb.FEF_GEMM_TILED256, (32, 64, 96, 128, 160, 192, 224, 256))]
-LINES_OF_A_LOSS = [(126464, (1280, 1344), (30, 60, 90, 120, 150, 190, 220, 250, 300, 380, 440, 512)),  # whole tiles
-                   (65537, (2496, 2560), (30, 120, 250))]                                              # shares
+LINES_OF_A_LOSS = [(126464, (1152, 1216), (30, 60, 90, 120, 150, 190, 220, 250, 300, 380, 440, 512)),  # whole tiles
+                   (65537, (2240, 2304), (30, 120, 250))]                                              # shares
 
 
 @pytest.mark.parametrize("variant,rows", ROUNDS_AT_THE_LINE)

@@ -25,8 +25,8 @@ def ask(tmp_path_factory):
 
 def test_w_of_which_the_infinity_cache_keeps_some_is_read_by_ordinary_loads(ask):
     short = [(17354, 4864, 2), (10577, 5056, 2), (40000, 2560, 2), (32000, 1536, 2), (50257, 2048, 2), (32000, 1024, 4),
-             (32768, 4096, 2), (65536, 1024, 4), (40960, 4096, 2), (81920, 1024, 4)]
-    longer = [(40961, 4096, 2), (81921, 1024, 4), (126464, 4096, 2), (151936, 3584, 2), (2**31 - 1, 2**31 - 64, 2)]
+             (32768, 4096, 2), (65536, 1024, 4), (36864, 4096, 2), (73728, 1024, 4)]
+    longer = [(36865, 4096, 2), (73729, 1024, 4), (126464, 4096, 2), (151936, 3584, 2), (2**31 - 1, 2**31 - 64, 2)]
     assert ask([("streams_w", *s, 1, 0) for s in short + longer]) == [0] * len(short) + [1] * len(longer)
 
 
