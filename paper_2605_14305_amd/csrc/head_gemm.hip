@@ -556,7 +556,7 @@ hipError_t launch_f32(const HeadArgs& a) {
     FEF_LAUNCH_HEAD((head_f32_kernel<MR, 1, 32, false, MR == 16>), grid, block, a, a, m_tiles, n_tiles, tiles);
   } else if (a.d % 4 != 0) {
     FEF_LAUNCH_HEAD((head_f32_kernel<MR, 1, 32, false>), grid, block, a, a, m_tiles, n_tiles, tiles);
-  } else if (MR == 32 && a.d % 32 != 0 && a.d >= 896) {
+  } else if (MR == 32 && a.d % 32 != 0 && a.d >= 768) {
     FEF_LAUNCH_HEAD((head_f32_kernel<MR, 4, MR == 32 ? 64 : 32, false>), grid, block, a, a, m_tiles, n_tiles, tiles);
   } else if (streams_w(a.V, a.d, 4, m_tiles, false)) {
     FEF_LAUNCH_HEAD((head_f32_kernel<MR, 4, 32, true>), grid, block, a, a, m_tiles, n_tiles, tiles);

@@ -75,7 +75,7 @@ def test_f32_steps_of_many_rows_in_single_pieces(d):
         _check_rows(M, d, 16321)
 
 
-@pytest.mark.parametrize("d", [892, 896, 900, 1024, 1028, 1052, 1056, 1060, 1084, 1092, 1116, 1148, 2004])  # steps of 64 columns where lines are shared
+@pytest.mark.parametrize("d", [764, 768, 772, 1024, 1028, 1052, 1056, 1060, 1084, 1092, 1116, 1148, 2004])  # steps of 64 columns where lines are shared
 def test_f32_steps_of_64_columns(d):
     for M in (16, 18, 32, 34):
         _check_rows(M, d, 16321)
