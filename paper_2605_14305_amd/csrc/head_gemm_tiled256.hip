@@ -815,12 +815,9 @@ int tiled256_tiles(int V, int M) {
   return 256 * rounds < units ? 256 * rounds : units;
 }
 
-// Up to 256 rows: eight wavefronts (two per SIMD: the kernel is short of memory parallelism there, not of LDS rate).  More: four; but for
-// the cross-entropy eight where prologue and epilogue, which two wavefronts per SIMD overlap better, are much of what a tile costs: up to
-// d = 1024 (126 -> 121 us at 500 rows of V = 126464, 47.5 -> 46.0 at 1000 rows of V = 20000), and two row tiles of any d (300 rows of V = 50257:
-// 84 -> 77 us at d = 2048, 150 -> 142 at d = 4096; 313 -> 302 at d = 4096, V = 126464; level at 700 rows of d = 2048, and at 2048 rows of
-// d = 4096 4 % behind).  In a verify step a partial there spans 128 tokens, which only four wavefronts hold in one: eight would save
-// 7 % at 512 rows of d = 512.
+// Up to 256 rows: eight wavefronts (two per SIMD: the kernel is short of memory parallelism there, not of LDS rate).  More: four, or eight in a
+// cross-entropy call where they are ahead (loss_takes_eight_wavefronts).  In a verify step a partial there spans 128 tokens, which only four wavefronts hold in
+// one: eight would save 7 % at 512 rows of d = 512.
 hipError_t launch_head_tiled256(const HeadArgs& a) {
   const int m_tiles = (a.nrows + 255) / 256;
   // A launch of 2^32 threads or more runs only in part, without an error.  A cross-entropy call, whose logits need no
@@ -852,7 +849,7 @@ hipError_t launch_head_tiled256(const HeadArgs& a) {
   }
   const int m = row_tiles(a.nrows, a.nT, a.d, 96, 256);
   if (!a.labels) return launch_rows<2, kTiles>(a, m);
-  return a.d <= 1024 || m == 2 ? launch_rows<4, kLossTiles>(a, m) : launch_rows<2, kLossTiles>(a, m);
+  return loss_takes_eight_wavefronts(a.nrows, m, a.d) ? launch_rows<4, kLossTiles>(a, m) : launch_rows<2, kLossTiles>(a, m);
 }
 
 // Workgroups of a launch of runs = partials per row: one per CU, fewer where the vocabulary is short.  The first stages of a

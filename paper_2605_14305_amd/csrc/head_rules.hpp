@@ -60,6 +60,16 @@ inline int row_tiles(int M, int n_tiles, int d, int least, int most) {
   return best;
 }
 
+// Cross-entropy of more than 256 rows in row_tiles row tiles: eight wavefronts, or four as a verify step.  Two wavefronts per SIMD overlap
+// prologue and epilogue better, one asks LDS for fewer fragments.  Up to d = 1024 eight are ahead by 3 to 5 % (500 rows of
+// V = 126464 126 -> 121 us), but for 1 us behind in low tiles of a short vocabulary; beyond, in two row tiles, by up to 10 % (300 rows of V = 50257 84 -> 79 at
+// d = 2048, 147 -> 139 at d = 4096) as long as the tile is low or the walk over k short: 512 rows of d = 3072 2 to 5 % ahead or level, of d = 3584 up
+// to 3 behind, of d = 4352 10 (V = 151936 522 -> 572); 384 rows of d = 4096 4 % ahead, of d = 5120 level.  In more row tiles 1 to 8 % behind.
+inline bool loss_takes_eight_wavefronts(int M, int row_tiles, int d) {
+  const int height = ((M + row_tiles - 1) / row_tiles + 31) / 32 * 32;
+  return d <= 1024 || (row_tiles == 2 && d <= (height <= 192 ? 4096 : 3072));
+}
+
 // Token tiles of an fp32 launch below which they are dealt out one by one instead of by XCD: 2048 sequences x 16 rows of V = 256 80 -> 53 us
 // per call.
 constexpr int kF32FewTiles = 64;

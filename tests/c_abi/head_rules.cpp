@@ -20,6 +20,10 @@ int main() {
       int M, n_tiles, d, least, most;
       in >> M >> n_tiles >> d >> least >> most;
       std::cout << fef::row_tiles(M, n_tiles, d, least, most) << "\n";
+    } else if (rule == "loss_takes_eight_wavefronts") {
+      int M, row_tiles, d;
+      in >> M >> row_tiles >> d;
+      std::cout << fef::loss_takes_eight_wavefronts(M, row_tiles, d) << "\n";
     } else if (rule == "f32_row_tiles") {
       int M, n_tiles;
       in >> M >> n_tiles;

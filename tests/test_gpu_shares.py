@@ -91,6 +91,11 @@ def test_row_tiles_of_a_cross_entropy_call(V, R, d):
     _check_loss(R, d, V)
 
 
+@pytest.mark.parametrize("R,d", [(300, 4096), (300, 4160), (384, 4096), (385, 3072), (385, 3136), (512, 3072), (512, 3584)])  # eight or four
+def test_two_row_tiles_of_a_cross_entropy_call(R, d):
+    _check_loss(R, d, 50257)
+
+
 # 288 MiB of W and a row, or 64 columns, more: ordinary and non-temporal loads.  One row tile at every height that a form has (one or two in a
 # cross-entropy call of more than 256 rows); that these calls take the forms they are meant for is checked in test_head_rules.py.
 LINE_OF_A_ROUND = [(73728, 2048), (73729, 2048)]

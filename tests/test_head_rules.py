@@ -77,6 +77,12 @@ def test_row_tiles_of_calls_that_were_measured(ask):
     assert ask([("row_tiles", 300, 197, 2048, 96, 256), ("row_tiles", 2048, 494, 4096, 96, 256)]) == [2, 8]
 
 
+def test_cross_entropy_in_eight_wavefronts_where_they_are_ahead(ask):
+    calls = {(300, 2, 2048): 1, (300, 2, 4096): 1, (384, 2, 4096): 1, (440, 2, 3072): 1, (512, 2, 3072): 1, (700, 3, 1024): 1, (2048, 8, 512): 1,
+             (385, 2, 3136): 0, (512, 2, 3584): 0, (450, 2, 4352): 0, (300, 2, 4160): 0, (700, 3, 1088): 0, (2048, 8, 4096): 0, (300, 3, 2048): 0}
+    assert ask([("loss_takes_eight_wavefronts", *c) for c in calls]) == list(calls.values())
+
+
 def test_fp32_row_tiles_only_where_the_busiest_cu_gains(ask):
     def work(M, n, m):
         workgroups = -(-n * m // 256) if n < 64 else _rounds(n, m)
