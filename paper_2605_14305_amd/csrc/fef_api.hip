@@ -387,7 +387,8 @@ fef_status run_step(const fef_params* prm, int phase, int n_transfer, const void
   v.stream = stream;
   v.n_transfer = n_transfer;
   // (events mark the head kernel alone; the masses of every slot and the logits come from kernels of their own)
-  if (L.variant == FEF_GEMM_F32 && phase == FEF_PHASE_FUSED && !h.ev_begin && !v.all_slots && !v.diag_logits && fef::toy_round_serves(v.B, K, h.d, h.V)) {
+  if (L.variant == FEF_GEMM_F32 && phase == FEF_PHASE_FUSED && !h.ev_begin && !v.all_slots && !v.diag_logits &&
+      fef::toy_round_serves(v.B, K, h.d, h.V)) {
     const hipError_t e = fef::launch_toy_round(h, v);
     if (e != hipSuccess) return fail(FEF_ERR_HIP, "round kernel launch: %s", hipGetErrorString(e));
     return FEF_OK;

@@ -18,9 +18,9 @@ namespace {
 // W and H go straight from memory to LDS, two steps ahead in a ring of three stages: rows of 128 contiguous bytes, every W element
 // once per MR rows, one barrier per step, and 31 to 51 KB per workgroup, so that three to five share a CU.  The fragments of
 // a step are read while the step before is multiplied.  What it measured, per call with diagnostics and logits, against the form before
-// (one step ahead through registers, 32 or 64 rows): 16 rows of d = 1024, V = 32000 50 -> 42 us, 32 rows 55 -> 52; 48 rows of d = 599,
-// V = 18136 58 -> 48; 4 rows of d = 475, V = 17778 36 -> 31; 16 rows of V = 151936 (round) 165 -> 136.  Four or six stages, steps of 64
-// columns and eight wavefronts: equal or slower.
+// (one step ahead through registers, 32 or 64 rows), with W still in the Infinity Cache and not: 16 rows of d = 1024, V = 32000 50 -> 40 and
+// 53 -> 51 us, 32 rows 52 -> 48 and 55 -> 55; 48 rows of d = 599, V = 18136 60 -> 45 and 61 -> 46; 4 rows of d = 475, V = 17778 36 -> 28 and
+// 37 -> 30; 16 rows of V = 151936 (a round) 165 -> 135.  Four or six stages and eight wavefronts: equal or slower.
 //
 // Operand layout of the 16x16x4 multiply (lane l, i = l % 16, g = l / 16): A[i][g], B[g][i], one
 // float each.  The sums run over k in ascending order, one rounding per product like a chain of FMAs: multiply c of a step takes

@@ -499,7 +499,8 @@ __global__ __launch_bounds__(256) void head_f32_kernel(HeadArgs a, int m_tiles, 
       const int r = a.row0 + m;
       return r < a.BK ? (const float*)a.h_draft + (size_t)r * a.d : (const float*)a.h_target + (size_t)(r - a.BK) * a.d;
     };
-    f32_tile<4, MR, VEC, TK, STREAM_W, WIDE>(a, (long)nt * kTiledTn, mt * MR, min(MR, a.nrows - mt * MR), h_of, a.logits, a.ldl, a.partials, ring, tile_max);
+    f32_tile<4, MR, VEC, TK, STREAM_W, WIDE>(a, (long)nt * kTiledTn, mt * MR, min(MR, a.nrows - mt * MR), h_of, a.logits, a.ldl,
+                                             a.partials, ring, tile_max);
   }
 }
 

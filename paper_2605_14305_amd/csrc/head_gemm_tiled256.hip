@@ -38,10 +38,10 @@
 // two tiles of 160, not 256 + 44), more of them where the vocabulary is short (row_tiles), one instantiation per height.
 //
 // Measured (head kernel by HIP events, unless marked t: by trace; before: W in ordinary loads, as few row tiles as the rows take):
-// d = 4096, V = 126464: 48 rows 182 -> 163 us, 64 rows 188 -> 165 (6.5 TB/s), 96 rows 187 -> 168, 128 rows 197 -> 171, 256 rows 240 -> 237
-// (t, one machine: 223 -> 215), 512 rows 426 -> 423, 2048 rows 1590 -> 1600 (two machines); 128 rows of d = 3584, V = 151936 222 -> 203;
-// 110 rows of d = 2560, V = 100003 116 -> 105 t.  Cross-entropy, 2048 rows 1470 to 1480 (1.43 PFLOP/s, matrix units busy 0.75 of the
-// cycles at 1.77 GHz).
+// d = 4096, V = 126464: 48 rows 182 -> 163 us, 64 rows 188 -> 166 (6.4 TB/s), 96 rows 187 -> 168, 128 rows 197 -> 171, 256 rows 240 -> 237
+// to 238 (t, on one other machine: 223 -> 215), 512 rows 426 -> 423 to 432, 2048 rows 1590 -> 1600 to 1620 (other machines); 128 rows of
+// d = 3584, V = 151936 222 -> 203; 110 rows of d = 2560, V = 100003 116 -> 105 t.  Cross-entropy, 2048 rows 1470 to 1517 (1.40 to 1.43
+// PFLOP/s, matrix units busy 0.75 of the cycles at 1.77 GHz).
 //
 // Operand slabs go HBM/L2 -> LDS directly (global_load_lds_dwordx4: lane l of a wavefront deposits its 16 bytes at
 // LDS base + 16 l): no register staging and no ds_write in the main loop.  A row of a stage is 128 bytes, so one load
@@ -815,9 +815,9 @@ int tiled256_tiles(int V, int M) {
   return 256 * rounds < units ? 256 * rounds : units;
 }
 
-// Up to 256 rows: eight wavefronts (two per SIMD: the kernel is short of memory parallelism there, not of LDS rate).  More: four, or eight in a
-// cross-entropy call where they are ahead (loss_takes_eight_wavefronts).  In a verify step a partial there spans 128 tokens, which only four wavefronts hold in
-// one: eight would save 7 % at 512 rows of d = 512.
+// Up to 256 rows: eight wavefronts (two per SIMD: the kernel is short of memory parallelism there, not of LDS rate).  More: four, or
+// eight in a cross-entropy call where they are ahead (loss_takes_eight_wavefronts).  In a verify step a partial there spans 128
+// tokens, which only four wavefronts hold in one: eight would save 7 % at 512 rows of d = 512.
 hipError_t launch_head_tiled256(const HeadArgs& a) {
   const int m_tiles = (a.nrows + 255) / 256;
   // A launch of 2^32 threads or more runs only in part, without an error.  A cross-entropy call, whose logits need no

@@ -6,8 +6,10 @@
 namespace fef {
 
 // W past the caches: non-temporal loads.  A W longer than the Infinity Cache (256 MB) comes from HBM in every call, and as
-// ordinary loads it pushes what else is in use, H above all, out of the caches: per round of 64 rows of d = 4096, V = 126464
-// 203 -> 179 us, of 256 rows 264 -> 254, of 48 rows of d = 4096, V = 40960 79 -> 69; 16 fp32 rows of d = 2048, V = 40960 90 -> 83.
+// ordinary loads it pushes what else is in use, H above all, out of the caches: of the requests to L2 that are not for W 72 % hit at 64
+// rows of d = 4096, V = 126464 and 87 % with non-temporal loads, 69 and 87 % at 256 rows (reads from memory 8.6 -> 8.2 and 10.2 -> 8.3
+// million lines, W being 8.1).  Per round of 64 rows 203 -> 179 us, of 256 rows 259 -> 252, of 48 rows of d = 4096, V = 40960
+// 79 -> 69; 16 fp32 rows of d = 2048, V = 40960 90 -> 83.  At 64 rows that is more than the lines saved account for.
 // A shorter W is another matter.  Whether it still lies in the Infinity Cache depends on what the program does between two
 // calls, and non-temporal loads neither find it there nor leave it there.  45 bf16 and 20 fp32 calls of 80 to 256 MiB: where nothing
 // runs between the calls ordinary loads are up to 1.5 times as fast (16 rows of d = 4864, V = 17354 44.5 against 62.6 us, 190 rows of
@@ -27,9 +29,9 @@ inline bool streams_w(size_t V, size_t d, size_t element_bytes, int row_tiles, b
 
 constexpr int kXcds = 8, kCusPerXcd = 32;
 
-// Rounds of one workgroup per CU that a launch of row_tiles x n_tiles workgroups takes.  Workgroups go to the XCDs in turn and the row tiles of a
-// token tile stay on one XCD, so the XCD with the most token tiles decides: 18 token tiles x 14 row tiles are 252 workgroups, but
-// 42 on two XCDs and 28 on the others.
+// Rounds of one workgroup per CU that a launch of row_tiles x n_tiles workgroups takes.  Workgroups go to the XCDs in turn and the row
+// tiles of a token tile stay on one XCD, so the XCD with the most token tiles decides: 18 token tiles x 14 row tiles are 252
+// workgroups, but 42 on two XCDs and 28 on the others.
 inline long tile_rounds(long n_tiles, long row_tiles) {
   return ((n_tiles + kXcds - 1) / kXcds * row_tiles + kCusPerXcd - 1) / kCusPerXcd;
 }
@@ -43,8 +45,9 @@ inline long tile_rounds(long n_tiles, long row_tiles) {
 // Fitted to the times of 640 calls in every number of row tiles that they allow, with W still in the Infinity Cache and with that cache
 // swept: against ceil(M / most) 0.84 and 0.87 of the time in the mean, none slower but for one (4 % with the cache swept, 4 % faster
 // without).  Rounds counted over the whole chip instead: 32 of the 640 slower by more than 3 %, up to 1.45 times (2310 rows of d = 4608,
-// V = 4491 113 us in 10 row tiles, 152 in 14).  Without the 10 %: 384 rows of d = 3584, V = 44081 142 us in two, 166 in four; with it also at
-// short rows: 450 of d = 896, V = 71400 18 % slower.  Without the 0.6: 144 rows of d = 3968, V = 29869 64 us in one tile of 160, 83 in two of 96.
+// V = 4491 113 us in 10 row tiles, 152 in 14).  Without the 10 %: 384 rows of d = 3584, V = 44081 142 us in two, 166 in four; with it
+// also at short rows: 450 of d = 896, V = 71400 18 % slower.  Without the 0.6: 144 rows of d = 3968, V = 29869 64 us in one tile of 160,
+// 83 in two of 96.
 inline int row_tiles(int M, int n_tiles, int d, int least, int most) {
   const int fewest = (M + most - 1) / most;
   if ((long)n_tiles * fewest > 8 * 256) return fewest;  // many rounds: the last one matters little
@@ -53,7 +56,9 @@ inline int row_tiles(int M, int n_tiles, int d, int least, int most) {
   const bool runs = most == 128;
   const long enough = cost_of(fewest) * (runs || d <= 1024 ? 100 : 90);
   int best = fewest;
-  for (int m = fewest + 1; (long)n_tiles * m <= 16 * 256 && height_of(m) >= least; ++m) {
+  for (int height = height_of(fewest) - 32; height >= least; height -= 32) {  // the fewest tiles of each height
+    const int m = (M + height - 1) / height;
+    if ((long)n_tiles * m > 16 * 256 || height_of(m) < least) break;
     if (!runs && fewest == 1 && 5 * height_of(m) >= 3 * height_of(1)) continue;
     if (100 * cost_of(m) < enough && cost_of(m) < cost_of(best)) best = m;
   }
@@ -62,9 +67,11 @@ inline int row_tiles(int M, int n_tiles, int d, int least, int most) {
 
 // Cross-entropy of more than 256 rows in row_tiles row tiles: eight wavefronts, or four as a verify step.  Two wavefronts per SIMD overlap
 // prologue and epilogue better, one asks LDS for fewer fragments.  Up to d = 1024 eight are ahead by 3 to 5 % (500 rows of
-// V = 126464 126 -> 121 us), but for 1 us behind in low tiles of a short vocabulary; beyond, in two row tiles, by up to 10 % (300 rows of V = 50257 84 -> 79 at
-// d = 2048, 147 -> 139 at d = 4096) as long as the tile is low or the walk over k short: 512 rows of d = 3072 2 to 5 % ahead or level, of d = 3584 up
-// to 3 behind, of d = 4352 10 (V = 151936 522 -> 572); 384 rows of d = 4096 4 % ahead, of d = 5120 level.  In more row tiles 1 to 8 % behind.
+// V = 126464 126 -> 121 us), but for 1 us behind in low tiles of a short vocabulary; beyond, in two row tiles, by up to 10 % (300 rows
+// of V = 50257 84 -> 79 at d = 2048, 147 -> 139 at d = 4096) as long as the tile is low or the walk over k short: 512 rows of d = 3072 2
+// to 5 % ahead or level, of d = 3584 up to 3 behind, of d = 4352 10 (V = 151936 522 -> 572); 384 rows of d = 4096 4 % ahead, of
+// d = 5120 level.  In more row tiles 1 to 8 % behind.  Their error against 64 bits is the same (nine sizes of 257 to 1000 rows, six
+// seeds each: 1.8e-7 to 3.7e-7 with four and 1.8e-7 to 3.4e-7 with eight, now one ahead and now the other).
 inline bool loss_takes_eight_wavefronts(int M, int row_tiles, int d) {
   const int height = ((M + row_tiles - 1) / row_tiles + 31) / 32 * 32;
   return d <= 1024 || (row_tiles == 2 && d <= (height <= 192 ? 4096 : 3072));
@@ -84,13 +91,15 @@ inline int f32_row_tiles(int M, int n_tiles) {
   const int fewest = (M + 63) / 64;
   const auto cost_of = [=](int m) -> long {
     const long height = ((M + m - 1) / m + 15) / 16 * 16;
-    const long busiest = n_tiles < kF32FewTiles ? ((long)n_tiles * m + kXcds * kCusPerXcd - 1) / (kXcds * kCusPerXcd) : tile_rounds(n_tiles, m);
+    const long cus = kXcds * kCusPerXcd, busiest = n_tiles < kF32FewTiles ? ((long)n_tiles * m + cus - 1) / cus : tile_rounds(n_tiles, m);
     return busiest * (height + 16);
   };
   int best = fewest;
   if (cost_of(fewest) > 8L * (64 + 16)) return best;  // many workgroups per CU: the last ones matter little
-  for (int m = fewest + 1; 16 * (m - 1) < M; ++m)
-    if (100 * cost_of(m) < 97 * cost_of(best)) best = m;
+  for (int height = 48; height >= 16; height -= 16) {  // the fewest tiles of each height
+    const int m = (M + height - 1) / height;
+    if (m > fewest && 100 * cost_of(m) < 97 * cost_of(best)) best = m;
+  }
   return best;
 }
 

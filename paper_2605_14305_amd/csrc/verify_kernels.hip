@@ -787,9 +787,9 @@ __global__ __launch_bounds__(NT) void accept_resid_kernel(VerifyArgs a) {
 // accept tests (the final kernel does them); with them repeated in front of every chunk this took 260 us, without them 191, and
 // 167 (6.2 TB/s) with non-temporal loads: the logits are read once (per call 411 -> 393 us at 540 slots of V = 151936, 148 -> 134 at 512 of
 // V = 50257).  Two chunks per wavefront; four leave a small call short of wavefronts (50.4 -> 49.1 us at 32 slots of V = 100003), one
-// or two per mille behind at the large ones.  COPY: a call that wants the logits too gets them from here, where they are in registers: 122 -> 112 us per
-// call of 128 rows of d = 1024, V = 126464 against a kernel that reads them once more, 106 -> 101 at V = 100003, and a launch less
-// (51.2 -> 50.0 at 32 fp32 rows of V = 32000).
+// or two per mille behind at the large ones.  COPY: a call that wants the logits too gets them from here, where they are in
+// registers: 122 -> 112 us per call of 128 rows of d = 1024, V = 126464 against a kernel that reads them once more, 106 -> 101 at
+// V = 100003, and a launch less (51.2 -> 50.0 at 32 fp32 rows of V = 32000).
 // ---------------------------------------------------------------------------------------------
 constexpr int kMassPer = 2;
 template <bool COPY>
@@ -948,9 +948,10 @@ __global__ __launch_bounds__(NT) void finalize_kernel(VerifyArgs a) {
 // A whole round of a toy model in one launch: one workgroup per sequence takes its 2 K <= 16 rows through the fp32 head, a wavefront
 // per row, and the final phase.  Bound: start-up, code that arrives from a cold instruction cache, and trips to memory that wait for one
 // another; with three kernels each has its own, and what they hand on goes through memory.  Here logits, partials, log-sum-exps and
-// draft tokens stay in LDS: the sequence is a batch of one whose workspace is this workgroup's LDS.  4 tokens of a toy model (d = 64,
-// V = 32) 16.0 -> 10.8 us per call, 8 tokens of d = 128, V = 256 16.0 -> 12.7, 64 sequences of d = 64, V = 256 16.7 -> 13.3.  Four or eight
-// wavefronts are slower (12.4, 12.8 at V = 32, still through memory), and so is handing on through memory (11.7).
+// draft tokens stay in LDS: the sequence is a batch of one whose workspace is this workgroup's LDS.  Per call, calls queued one
+// behind another, three machines: 4 tokens of a toy model (d = 64, V = 32) 13.4 to 16.0 -> 9.7 to 11.3 us (the host's 8 are next),
+// 8 tokens of d = 128, V = 256 16.0 -> 12.7 to 14.5, 64 sequences of d = 64, V = 256 17.6 -> 12.6 to 13.3.  Four or eight wavefronts are
+// slower (12.4, 12.8 at V = 32, still through memory, against 10.8), and so is handing on through memory (11.7).
 // ---------------------------------------------------------------------------------------------
 constexpr int kToyWaves = 16, kToyTokens = 16 * kToyWaves;
 
@@ -1047,9 +1048,10 @@ __global__ __launch_bounds__(kWave) void topn_kernel(VerifyArgs a) {
   }
 }
 
-// Logits without the padding of the workspace rows, for calls without slot_mass_kernel.  grid = (rows, pieces of kCopyPer tokens), the rows capped (a launch
-// has less than 2^32 threads, a call up to 2^25 rows); a thread asks for all of its eight elements before it stores the first.  (One flat index divided by V per element before: 131 -> 122 us
-// per call of 128 rows of V = 126464, d = 1024, that keeps its logits.)
+// Logits without the padding of the workspace rows, for calls without slot_mass_kernel.  grid = (rows, pieces of kCopyPer tokens),
+// the rows capped (a launch has less than 2^32 threads, a call up to 2^25 rows); a thread asks for all of its eight elements before
+// it stores the first.  (One flat index divided by V per element before: 131 -> 122 us per call of 128 rows of V = 126464, d = 1024,
+// that keeps its logits.)
 constexpr int kCopyPer = 8 * NT;
 __global__ __launch_bounds__(NT) void copy_logits_kernel(const float* __restrict__ src, long ldl, float* __restrict__ dst, int V, int rows) {
   for (int r = blockIdx.x; r < rows; r += gridDim.x) {

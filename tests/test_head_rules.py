@@ -57,7 +57,8 @@ def _height(M, m, unit=32):
 @pytest.mark.parametrize("d", [512, 1024, 1088, 4096])
 def test_more_row_tiles_only_where_the_busiest_xcd_gains(ask, d):
     for first, last, least, most in LAUNCHES:
-        sizes = [(M, n) for M in range(first, last + 1, 1 if last <= 256 else 37) for n in [*range(1, 70, 3), 97, 128, 187, 250, 256, 301, 391]]
+        tiles = [*range(1, 70, 3), 97, 128, 187, 250, 256, 301, 391]
+        sizes = [(M, n) for M in range(first, last + 1, 1 if last <= 256 else 37) for n in tiles]
         picked = ask([("row_tiles", M, n, d, least, most) for M, n in sizes])
         for (M, n), m in zip(sizes, picked):
             fewest = -(-M // most)
@@ -115,7 +116,8 @@ def test_what_the_gpu_tests_at_the_line_for_non_temporal_loads_run(ask):
         for t in set(tiles[0]):
             assert ask([("streams_w", V, d, 2, t, 1) for d in (below, above)]) == [0, 1]
         if whole:
-            assert {(t, _height(R, t)) for R, t in zip(rows, tiles[0])} == {(1, h) for h in range(32, 257, 32)} | {(2, h) for h in (160, 192, 224, 256)}
+            every = {(1, h) for h in range(32, 257, 32)} | {(2, h) for h in range(160, 257, 32)}
+            assert {(t, _height(R, t)) for R, t in zip(rows, tiles[0])} == every
 
 
 def test_what_the_gpu_tests_of_the_fp32_head_run(ask):
@@ -124,6 +126,6 @@ def test_what_the_gpu_tests_of_the_fp32_head_run(ask):
     sizes = line(f32_head.test_f32_to_either_side_of_the_line_for_non_temporal_loads, "d,V")
     assert ask([("streams_w", V, d, 4, 1, 0) for d, V in sizes]) == [0, 1, 1, 0, 0]
     assert all(ask([("f32_row_tiles", M, -(-V // 64)) for M in (16, 32, 48, 64)]) == [1] * 4 for _, V in sizes)
-    # rows per tile of the tests of steps: 48 and 64, and 16, 32 and 48
-    assert {_height(M, m, 16) for M, m in zip((34, 48, 50, 64, 98, 130), ask([("f32_row_tiles", M, 256) for M in (34, 48, 50, 64, 98, 130)]))} == {48, 64}
-    assert {_height(M, m, 16) for M, m in zip((16, 18, 32, 34), ask([("f32_row_tiles", M, 256) for M in (16, 18, 32, 34)]))} == {16, 32, 48}
+    def heights(rows):
+        return {_height(M, m, 16) for M, m in zip(rows, ask([("f32_row_tiles", M, 256) for M in rows]))}
+    assert heights((34, 48, 50, 64, 98, 130)) == {48, 64} and heights((16, 18, 32, 34)) == {16, 32, 48}  # the tests of steps
