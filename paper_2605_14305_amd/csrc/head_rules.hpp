@@ -83,16 +83,17 @@ constexpr int kF32FewTiles = 64;
 
 // Row tiles of an fp32 launch: equal heights of 16 to 64 rows.  As few as possible, for every one reads W again, but more where that leaves
 // CUs idle or gives some of them more than others: the number that makes (workgroups of the busiest CU) x (height + 16) smallest,
-// more of them only for 3 % of it.  (Several workgroups share a CU, so a CU's work counts and not its rounds.)  Fitted to 160 calls
-// in every number of row tiles that they allow: 0.89 of the time in as few as possible, 1.1 % behind the best, none slower than 1 %.
-// "More of them up to 240 workgroups", whatever their height, was slower than as few as possible for one call in twenty: 113 rows of
-// d = 3976, V = 7478 109 us in two, 134 in three; 347 rows of d = 484, V = 2058 24.2 in six, 27.4 in eight.
+// more of them only for 3 % of it.  (Several workgroups share a CU, so a CU's work counts and not its rounds.)  A workgroup of 48 or 64 rows
+// that has its CU to itself counts 24 more: one wavefront per SIMD overlaps with nothing (60 rows of d = 1848, V = 9284 60.4 us in one
+// tile, 55.9 in two).  Fitted to 160 calls in every number of row tiles that they allow: 0.89 of the time in as few as possible, 0.9 %
+// behind the best, none slower than 1 %.  "More of them up to 240 workgroups", whatever their height, was slower than as few as possible for
+// one call in twenty: 113 rows of d = 3976, V = 7478 109 us in two, 134 in three (101 in four, as now).
 inline int f32_row_tiles(int M, int n_tiles) {
   const int fewest = (M + 63) / 64;
   const auto cost_of = [=](int m) -> long {
     const long height = ((M + m - 1) / m + 15) / 16 * 16;
     const long cus = kXcds * kCusPerXcd, busiest = n_tiles < kF32FewTiles ? ((long)n_tiles * m + cus - 1) / cus : tile_rounds(n_tiles, m);
-    return busiest * (height + 16);
+    return busiest * (height + 16) + (busiest == 1 && height >= 48 ? 24 : 0);
   };
   int best = fewest;
   if (cost_of(fewest) > 8L * (64 + 16)) return best;  // many workgroups per CU: the last ones matter little

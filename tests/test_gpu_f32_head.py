@@ -63,7 +63,7 @@ def test_f32_edges_of_steps(d):
         _check_rows(M, d, 257)
 
 
-@pytest.mark.parametrize("V", [15297, 15360, 15361])  # up to 64 rows per workgroup from 240 token tiles on
+@pytest.mark.parametrize("V", [15297, 15360, 15361])  # 240 token tiles and one more
 def test_f32_row_tiles(V):
     for M in (14, 16, 18, 32, 34, 48, 50, 64, 66, 96, 130):
         _check_rows(M, 37, V)
@@ -72,13 +72,13 @@ def test_f32_row_tiles(V):
 @pytest.mark.parametrize("d", [1, 2, 31, 33, 63, 65, 95, 97, 127, 129, 1027])  # 4-byte pieces, 48 and 64 rows: two stages, one to 33 steps
 def test_f32_steps_of_many_rows_in_single_pieces(d):
     for M in (34, 48, 50, 64, 98, 130):
-        _check_rows(M, d, 16321)
+        _check_rows(M, d, 32705)
 
 
 @pytest.mark.parametrize("d", [764, 768, 772, 1024, 1028, 1052, 1056, 1060, 1084, 1092, 1116, 1148, 2004])  # steps of 64 columns where lines are shared
 def test_f32_steps_of_64_columns(d):
     for M in (16, 18, 32, 34):
-        _check_rows(M, d, 16321)
+        _check_rows(M, d, 32705)
 
 
 @pytest.mark.parametrize("d,V", [(1024, 73728), (1024, 73729), (1056, 71494), (1023, 73900), (1028, 73500)])  # 288 MiB of W and more

@@ -87,14 +87,14 @@ def test_cross_entropy_in_eight_wavefronts_where_they_are_ahead(ask):
 def test_fp32_row_tiles_only_where_the_busiest_cu_gains(ask):
     def work(M, n, m):
         workgroups = -(-n * m // 256) if n < 64 else _rounds(n, m)
-        return workgroups * (_height(M, m, 16) + 16)
+        return workgroups * (_height(M, m, 16) + 16) + 24 * (workgroups == 1 and _height(M, m, 16) >= 48)
     sizes = [(M, n) for M in [*range(1, 200), 347, 512, 1000, 4000, 65535] for n in [*range(1, 130, 3), 187, 250, 256, 301, 500, 2000, 1 << 25]]
     for (M, n), m in zip(sizes, ask([("f32_row_tiles", *s) for s in sizes])):
         fewest = -(-M // 64)
         assert fewest <= m <= -(-M // 16)
         assert m == fewest or work(M, n, m) < work(M, n, fewest)
-    # rows and token tiles of calls that more row tiles made slower, and of some that they made faster
-    assert ask([("f32_row_tiles", *s) for s in [(113, 117), (347, 33), (162, 65), (100, 92)]]) == [2, 6, 3, 2]
+    # rows and token tiles of calls that were slower in 3, 8, 4 and 3 row tiles, and of one that was slower in one than in two
+    assert ask([("f32_row_tiles", *s) for s in [(113, 117), (347, 33), (162, 65), (100, 92), (60, 146)]]) == [4, 11, 6, 4, 2]
     assert ask([("f32_row_tiles", *s) for s in [(32, 79), (64, 125), (48, 284), (16, 500), (32, 500)]]) == [2, 2, 1, 1, 1]
 
 
@@ -127,5 +127,5 @@ def test_what_the_gpu_tests_of_the_fp32_head_run(ask):
     assert ask([("streams_w", V, d, 4, 1, 0) for d, V in sizes]) == [0, 1, 1, 0, 0]
     assert all(ask([("f32_row_tiles", M, -(-V // 64)) for M in (16, 32, 48, 64)]) == [1] * 4 for _, V in sizes)
     def heights(rows):
-        return {_height(M, m, 16) for M, m in zip(rows, ask([("f32_row_tiles", M, 256) for M in rows]))}
+        return {_height(M, m, 16) for M, m in zip(rows, ask([("f32_row_tiles", M, 512) for M in rows]))}
     assert heights((34, 48, 50, 64, 98, 130)) == {48, 64} and heights((16, 18, 32, 34)) == {16, 32, 48}  # the tests of steps
