@@ -40,9 +40,9 @@ inline long tile_rounds(long n_tiles, long row_tiles) {
 // than that takes only of `least` rows or more.  ceil(M / most) of them multiply the fewest rows that do not exist and read W the fewest
 // times; but a short vocabulary leaves CUs idle then (V = 8437: 33 tiles), or fills a last round badly (V = 20000: 79 tiles x 4
 // row tiles).  So the number is taken that makes rounds x (height + 64) smallest; 64 stands for what a k-step and a tile cost whatever
-// their height.  More of them read W more often, so where a row is long the gain has to be more than 10 % of that unless one round takes
-// them all (1596 rows of d = 1984, V = 7989: 67 us in seven, 63 in eight), and up to 256 rows (one row tile, whose W comes at the rate of the
-// caches) the height has to fall below 0.6 of that of one.
+// their height.  More of them read W more often, so where a row is long the gain has to be more than 10 % of that unless they take no
+// more rounds (1596 rows of d = 1984, V = 7989 67 us in seven, 63 in eight; 1422 of d = 1088, V = 17824 72 us in six, 67 in seven), and up
+// to 256 rows (one row tile, whose W comes at the rate of the caches) the height has to fall below 0.6 of that of one.
 // Fitted to the times of 640 calls in every number of row tiles that they allow, with W still in the Infinity Cache and with that cache
 // swept: against ceil(M / most) 0.84 and 0.87 of the time in the mean, none slower but for one (4 % with the cache swept, 4 % faster
 // without).  Rounds counted over the whole chip instead: 32 of the 640 slower by more than 3 %, up to 1.45 times (2310 rows of d = 4608,
@@ -60,7 +60,7 @@ inline int row_tiles(int M, int n_tiles, int d, int least, int most) {
     const int m = (M + height - 1) / height;
     if ((long)n_tiles * m > 16 * 256 || height_of(m) < least) break;
     if (!runs && fewest == 1 && 5 * height_of(m) >= 3 * height_of(1)) continue;
-    const int enough = runs || d <= 1024 || tile_rounds(n_tiles, m) == 1 ? 100 : 90;
+    const int enough = runs || d <= 1024 || tile_rounds(n_tiles, m) == tile_rounds(n_tiles, fewest) ? 100 : 90;
     if (100 * cost_of(m) < enough * cost_of(fewest) && cost_of(m) < cost_of(best)) best = m;
   }
   return best;

@@ -71,10 +71,11 @@ def test_more_row_tiles_only_where_the_busiest_xcd_gains(ask, d):
 def test_row_tiles_of_calls_that_were_measured(ask):
     # rows, token tiles, d, least, most; what more row tiles (10 -> 14 and so on) made slower
     slower = [(2310, 18, 4608, 96, 256), (432, 50, 6016, 96, 256), (7676, 2, 576, 96, 256), (484, 187, 3712, 96, 256),
-              (144, 117, 3968, 64, 256), (384, 173, 3584, 96, 256)]
-    assert ask([("row_tiles", *r) for r in slower]) == [10, 4, 30, 2, 1, 2]
-    faster = [(1596, 32, 1984, 96, 256), (256, 33, 1024, 64, 256), (528, 63, 3072, 96, 256), (256, 63, 1024, 64, 256), (128, 125, 4096, 64, 128)]
-    assert ask([("row_tiles", *r) for r in faster]) == [8, 4, 4, 4, 2]
+              (144, 117, 3968, 64, 256), (384, 173, 3584, 96, 256), (256, 310, 5312, 64, 256)]
+    assert ask([("row_tiles", *r) for r in slower]) == [10, 4, 30, 2, 1, 2, 1]
+    faster = [(1596, 32, 1984, 96, 256), (1422, 70, 1088, 96, 256), (2214, 69, 3392, 96, 256), (2870, 95, 1472, 96, 256),
+              (256, 33, 1024, 64, 256), (528, 63, 3072, 96, 256), (256, 63, 1024, 64, 256), (128, 125, 4096, 64, 128)]
+    assert ask([("row_tiles", *r) for r in faster]) == [8, 7, 10, 13, 4, 4, 4, 2]
     assert ask([("row_tiles", 300, 197, 2048, 96, 256), ("row_tiles", 2048, 494, 4096, 96, 256)]) == [2, 8]
 
 
