@@ -74,6 +74,7 @@ constexpr int kTiled256Unit = 32;    // ... and the unit of a cross-entropy call
 
 bool skinny_supports(int M, int d);
 hipError_t launch_head_skinny(const HeadArgs& a);
+hipError_t launch_head_slices(const HeadArgs& a);  // the same order of sums, for long vocabularies
 hipError_t launch_head_tiled(const HeadArgs& a);
 int tiled256_tiles(int V, int M);  // cross-entropy: token tiles = partial slots per row of a call over M rows
 hipError_t launch_head_tiled256(const HeadArgs& a);

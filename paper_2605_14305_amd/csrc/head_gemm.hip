@@ -11,7 +11,8 @@
 //                       the MFMA B operand for the whole kernel, streams its 1 KB slice of
 //                       sixteen W rows straight into the MFMA A operand registers one tile
 //                       ahead, and the eight partial 16x16 tiles are summed through LDS.
-//                       One (max, sum exp) partial per (row, workgroup).
+//                       One (max, sum exp) partial per (row, workgroup).  Long vocabularies go to
+//                       head_slices_kernel (head_slices.hip), which gives the same bits.
 //   head_tiled_kernel   any M.  128x128x64 LDS-tiled MFMA GEMM, XCD-aware tile order so the
 //                       workgroups that share a W tile run on the same L2.
 //   head_f32_kernel     fp32 inputs on the fp32 matrix instructions.
@@ -538,7 +539,9 @@ hipError_t launch_head_skinny_nb(const HeadArgs& a) {
   return hipGetLastError();
 }
 
-hipError_t launch_head_skinny(const HeadArgs& a) { return launch_head_skinny_nb<4>(a); }
+hipError_t launch_head_skinny(const HeadArgs& a) {
+  return slices_serve(a.V, a.d) ? launch_head_slices(a) : launch_head_skinny_nb<4>(a);
+}
 
 hipError_t launch_head_tiled(const HeadArgs& a) {
   const int M = a.nrows;

@@ -78,6 +78,15 @@ inline bool loss_takes_eight_wavefronts(int M, int row_tiles, int d) {
   return d <= 1024 || (row_tiles == 2 && d <= (height <= 192 ? 4096 : 3072));
 }
 
+// Up to 32 rows, H in registers or in LDS beside W (head_slices.hip): the latter where a workgroup's run, of one in 256, is longer than 128
+// tokens.  Head alone, 322 calls of 2 to 32 rows in the seven hidden sizes and 23 vocabularies of 12000 to 151936, three Ws in turn: above the
+// line 0.94 of the time in the mean, at V = 32000 1.00, at 28700 1.02, at 16400 1.24, at 12000 1.48 (short runs leave the CUs too little of W
+// on its way).  d = 1024 is ahead up to V = 65536 and again where W is read past the caches, and 3 to 8 % behind in between (16 rows of
+// V = 80000 33.7 -> 35.9 us, of V = 126464 49.9 -> 52.6).
+inline bool slices_serve(int V, int d) {
+  return V > 256 * 128 && (d != 1024 || V <= 65536 || streams_w((size_t)V, (size_t)d, 2, 1, false));
+}
+
 // Token tiles of an fp32 launch below which they are dealt out one by one instead of by XCD: 2048 sequences x 16 rows of V = 256 80 -> 53 us
 // per call.
 constexpr int kF32FewTiles = 64;

@@ -28,6 +28,10 @@ int main() {
       int M, n_tiles;
       in >> M >> n_tiles;
       std::cout << fef::f32_row_tiles(M, n_tiles) << "\n";
+    } else if (rule == "slices_serve") {
+      int V, d;
+      in >> V >> d;
+      std::cout << fef::slices_serve(V, d) << "\n";
     } else {
       return 1;
     }

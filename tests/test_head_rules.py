@@ -130,3 +130,9 @@ def test_what_the_gpu_tests_of_the_fp32_head_run(ask):
     def heights(rows):
         return {_height(M, m, 16) for M, m in zip(rows, ask([("f32_row_tiles", M, 512) for M in rows]))}
     assert heights((34, 48, 50, 64, 98, 130)) == {48, 64} and heights((16, 18, 32, 34)) == {16, 32, 48}  # the tests of steps
+
+
+def test_which_of_the_two_kernels_up_to_32_rows(ask):
+    sizes = {(32768, 4096): 0, (32769, 4096): 1, (32769, 1024): 1, (65536, 1024): 1, (65537, 1024): 0, (147456, 1024): 0, (147457, 1024): 1,
+             (1, 512): 0, (2**31 - 1, 512): 1, (100003, 512): 1, (100003, 2048): 1}
+    assert ask([("slices_serve", *s) for s in sizes]) == list(sizes.values())
