@@ -80,6 +80,8 @@ int tiled256_tiles(int V, int M);  // cross-entropy: token tiles = partial slots
 hipError_t launch_head_tiled256(const HeadArgs& a);
 int runs_grid(int V, int unit);    // STREAM (unit 64), ROWSTREAM (16): workgroups = partial slots per row
 hipError_t launch_head_runs(const HeadArgs& a, int unit);
+hipError_t launch_head_short_runs(const HeadArgs& a, int row_tiles);
+hipError_t launch_head_double_runs(const HeadArgs& a, int unit, int row_tiles);
 hipError_t launch_head_f32(const HeadArgs& a);
 
 // ---------------------------------------------------------------------------------------------

@@ -87,6 +87,23 @@ inline bool slices_serve(int V, int d) {
   return V > 256 * 128 && (d != 1024 || V <= 65536 || streams_w((size_t)V, (size_t)d, 2, 1, false));
 }
 
+// Runs (STREAM, ROWSTREAM: units of 64 and 16 tokens) whose longest has that many tokens: by head_runs_kernel, which walks k once over all of
+// them, or by head_tiled256_kernel, one tile of up to 256 tokens after another.  Head alone in us, three Ws in turn.
+// Runs of up to 128 tokens (V <= 32768) fill half a tile of 256, and half its stages: 48 rows of d = 4096, V = 8000 38.9 -> 33.5, V = 24000
+// 49.0 -> 42.8, 96 rows of d = 2560, V = 32000 46.6 -> 43.9, 80 calls 0.94 of the time in the mean.  At d = 512 eight steps are too few
+// for it to matter and longer runs fall 3 % behind.
+inline bool short_runs_serve(int unit, long longest, int d) { return unit == 16 && longest <= 128 && (d > 512 || longest <= 96); }
+// Runs of 257 to 512 tokens are a tile of 256 and a narrow one, whose k-steps cost the load latency however few tokens it has: 110 rows of
+// d = 2560, V = 100003 111.9 -> 101.4, 64 rows of d = 2048, V = 66000 71.7 -> 59.9, 128 rows of d = 512, V = 126464 43.9 -> 38.4.  Two full
+// tiles do better one after the other (40 rows of d = 4096, V = 115000 149 -> 162 on one machine, level on another), and with more than
+// 96 rows and long rows so do shorter ones (128 rows of d = 3584, V = 75000 122 -> 134).  240 calls of 40 to 128 rows: where this says
+// yes 0.91 of the time in the mean.
+inline bool double_runs_serve(int rows, long longest, int d) {
+  if (longest <= 256) return false;
+  if (d <= 1024) return longest <= (rows <= 48 ? 384 : 512);
+  return rows > 96 ? d <= 2560 && longest <= 448 : longest <= 320;
+}
+
 // Token tiles of an fp32 launch below which they are dealt out one by one instead of by XCD: 2048 sequences x 16 rows of V = 256 80 -> 53 us
 // per call.
 constexpr int kF32FewTiles = 64;

@@ -32,6 +32,16 @@ int main() {
       int V, d;
       in >> V >> d;
       std::cout << fef::slices_serve(V, d) << "\n";
+    } else if (rule == "short_runs_serve") {
+      int unit, d;
+      long longest;
+      in >> unit >> longest >> d;
+      std::cout << fef::short_runs_serve(unit, longest, d) << "\n";
+    } else if (rule == "double_runs_serve") {
+      int rows, d;
+      long longest;
+      in >> rows >> longest >> d;
+      std::cout << fef::double_runs_serve(rows, longest, d) << "\n";
     } else {
       return 1;
     }

@@ -1,0 +1,36 @@
+"""Runs of STREAM and ROWSTREAM in one walk over k (csrc/head_runs.hip) against the tiles they took before: whole rounds against checksums
+recorded then (tests/golden/runs_bits.txt), and logits against a float64 product around the lines of its rules."""
+import os
+
+import pytest
+
+from paper_2605_14305_amd import binding as fb
+import test_gpu_order as order
+import test_gpu_shares as shares
+
+pytestmark = pytest.mark.gpu
+
+GOLDEN = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "runs_bits.txt")
+AUTO, STREAM, ROWSTREAM = fb.FEF_GEMM_AUTO, fb.FEF_GEMM_STREAM, fb.FEF_GEMM_ROWSTREAM
+# kind, variant, B, K, d, V: every tile height, short runs of 16 to 128 tokens, double ones of 257 to 512, starts in the middle of a k-step
+CASES = [
+    ("fused", AUTO, 3, 8, 1024, 32768), ("greedy", AUTO, 3, 7, 1536, 31001), ("fused", ROWSTREAM, 4, 8, 1536, 16001), ("fused", AUTO, 6, 8, 2048, 8191),
+    ("fused", ROWSTREAM, 8, 8, 512, 12289), ("fused", ROWSTREAM, 1, 9, 1536, 129), ("topn", AUTO, 3, 29, 1024, 20011), ("split", AUTO, 9, 4, 1536, 28003),
+    ("fused", AUTO, 3, 8, 2048, 81920), ("fused", AUTO, 5, 8, 1024, 70001), ("fused", AUTO, 6, 8, 512, 126464), ("fused", ROWSTREAM, 1, 16, 1024, 66001),
+    ("fused", AUTO, 4, 8, 1024, 65537), ("fused", AUTO, 8, 8, 2560, 106496), ("fused", AUTO, 5, 10, 576, 90001), ("fused", AUTO, 1, 17, 1088, 73000),
+    ("split", AUTO, 10, 12, 704, 131072), ("topn", AUTO, 4, 16, 64, 100003), ("greedy", AUTO, 4, 12, 512, 69999), ("fused", STREAM, 1, 7, 128, 67001),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
+def test_rounds_to_the_last_bit(case):
+    with open(GOLDEN) as f:
+        golden = {tuple(r[:6]): r[6:] for r in (line.split() for line in f if not line.startswith("#"))}
+    assert dict(zip(order.COLUMNS, order.checksums(fb, *case))) == dict(zip(order.COLUMNS, golden[tuple(map(str, case))]))
+
+
+@pytest.mark.parametrize("variant,d,V", [(ROWSTREAM, 512, 24576), (ROWSTREAM, 512, 24577), (ROWSTREAM, 1024, 32768), (ROWSTREAM, 1024, 17), (ROWSTREAM, 512, 65537),
+                                         (STREAM, 64, 65537), (STREAM, 192, 98305), (STREAM, 1088, 81920), (ROWSTREAM, 512, 131072)])
+def test_against_a_float64_product(variant, d, V):
+    for M in (2, 16, 32, 34, 64, 66, 96, 98, 128):
+        shares._check_round(variant, M, d, V)

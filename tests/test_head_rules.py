@@ -136,3 +136,13 @@ def test_which_of_the_two_kernels_up_to_32_rows(ask):
     sizes = {(32768, 4096): 0, (32769, 4096): 1, (32769, 1024): 1, (65536, 1024): 1, (65537, 1024): 0, (147456, 1024): 0, (147457, 1024): 1,
              (1, 512): 0, (2**31 - 1, 512): 1, (100003, 512): 1, (100003, 2048): 1}
     assert ask([("slices_serve", *s) for s in sizes]) == list(sizes.values())
+
+
+def test_which_runs_are_walked_in_one(ask):
+    short = {(16, 128, 1024): 1, (16, 129, 1024): 0, (64, 128, 1024): 0, (16, 96, 512): 1, (16, 112, 512): 0}
+    assert ask([("short_runs_serve", *s) for s in short]) == list(short.values())
+    # rows of a tile, longest run, d; the last row: calls that were slower in one walk
+    double = {(64, 256, 512): 0, (64, 257, 512): 1, (128, 512, 1024): 1, (40, 384, 1024): 1, (40, 448, 1024): 0, (64, 320, 4096): 1, (64, 384, 4096): 0,
+              (110, 448, 2560): 1, (110, 449, 2560): 0,
+              (128, 320, 3584): 0, (40, 512, 4096): 0, (110, 512, 2048): 0}
+    assert ask([("double_runs_serve", *s) for s in double]) == list(double.values())
