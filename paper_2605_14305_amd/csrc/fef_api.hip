@@ -8,6 +8,7 @@
 
 #include "../../include/fef.h"
 #include "fef_device.hpp"
+#include "head_rules.hpp"
 
 // Scratch of fef_verify_step_static: one copy per GPU the library runs on, held until the process
 // ends.  In host code this name is only a handle for hipGetSymbolAddress; the device address it
@@ -394,13 +395,20 @@ fef_status run_step(const fef_params* prm, int phase, int n_transfer, const void
     return FEF_OK;
   }
   hipError_t e;
-  switch (L.variant) {
-    case FEF_GEMM_SKINNY: e = fef::launch_head_skinny(h); break;
-    case FEF_GEMM_TILED: e = fef::launch_head_tiled(h); break;
-    case FEF_GEMM_TILED256: e = fef::launch_head_tiled256(h); break;
-    case FEF_GEMM_STREAM:
-    case FEF_GEMM_ROWSTREAM: e = fef::launch_head_runs(h, run_unit(L.variant)); break;
-    default: e = fef::launch_head_f32(h); break;
+  const int unit = L.variant == FEF_GEMM_TILED256 ? fef::kTiled256Tn : run_unit(L.variant);  // of a partial's tokens; 0: other kernels
+  const fef::PieceShape pieces = unit ? fef::piece_shape(h.nrows, h.V, h.d, h.nT, unit) : fef::PieceShape{0, 0, 0, 0};
+  if (pieces.pieces) {
+    v.row_sums = unit == 16 ? 16 : 64;
+    e = fef::launch_head_pieces(h, unit, pieces);
+  } else {
+    switch (L.variant) {
+      case FEF_GEMM_SKINNY: e = fef::launch_head_skinny(h); break;
+      case FEF_GEMM_TILED: e = fef::launch_head_tiled(h); break;
+      case FEF_GEMM_TILED256: e = fef::launch_head_tiled256(h); break;
+      case FEF_GEMM_STREAM:
+      case FEF_GEMM_ROWSTREAM: e = fef::launch_head_runs(h, run_unit(L.variant)); break;
+      default: e = fef::launch_head_f32(h); break;
+    }
   }
   if (e != hipSuccess) return fail(FEF_ERR_HIP, "head kernel launch: %s", hipGetErrorString(e));
   e = fef::launch_verify(v);

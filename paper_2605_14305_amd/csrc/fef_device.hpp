@@ -82,6 +82,8 @@ int runs_grid(int V, int unit);    // STREAM (unit 64), ROWSTREAM (16): workgrou
 hipError_t launch_head_runs(const HeadArgs& a, int unit);
 hipError_t launch_head_short_runs(const HeadArgs& a, int row_tiles);
 hipError_t launch_head_double_runs(const HeadArgs& a, int unit, int row_tiles);
+struct PieceShape;
+hipError_t launch_head_pieces(const HeadArgs& a, int unit, const PieceShape& shape);  // unit 256: whole tiles
 hipError_t launch_head_f32(const HeadArgs& a);
 
 // ---------------------------------------------------------------------------------------------
@@ -105,6 +107,7 @@ struct VerifyArgs {
   const float* logits;      // [2*B*K, ldl]
   const float2* partials;   // [2*B*K, nT]
   int nT;                   // partial tiles per row
+  int row_sums;             // 64 or 16: the head left no partials; they are made from the logits, in blocks of as many tokens (0: it did)
   int tile_unit, tile_T, tile_G;  // tile i covers tokens [unit*floor(i*T/G), unit*floor((i+1)*T/G))
   uint64_t seed;
   uint32_t step, seq_base, pos_base;

@@ -1,6 +1,8 @@
 // Vocabulary-head kernel for up to 128 rows whose workgroups walk k once over all their tokens.  It gives bit for bit what the runs of
 // head_tiled256_kernel give, one tile of up to 256 tokens after another, and takes their place where those leave the CUs too little of W
 // on its way: runs of up to 128 tokens, and many of 257 to 512 (short_runs_serve, double_runs_serve, with both sides measured).
+// And where the runs, or up to 256 rows' tiles of 256 tokens, are too few for the CUs: a piece of one per workgroup, without partials
+// (pieces_pay, piece_shape).
 //
 // What bounds it: the pass over W, at 4.8 to 5.3 TB/s with 110 rows of V = 100003 (4.5 to 4.8 in tiles), and for short vocabularies what
 // a CU can have on its way at once: 63 workgroups of 128 tokens (V = 8000, d = 4096) get 33 KB of W each per us whether four,
@@ -19,9 +21,9 @@ constexpr int BK = 64, kThreads = 512;  // columns of a k-step: 128 bytes, one l
 constexpr int kLds = 160 * 1024;
 constexpr float kLog2e = 1.4426950408889634f;
 
-// Order of the sums, as in head_gemm_tiled256.hip: STREAM, ROWSTREAM.
-enum Form { kRuns64, kRuns16 };
-constexpr int form_unit(Form f) { return f == kRuns64 ? 64 : 16; }
+// Order of the sums, as in head_gemm_tiled256.hip: STREAM, ROWSTREAM, TILED256 (a run is a tile of 256 tokens).
+enum Form { kRuns64, kRuns16, kTiles };
+constexpr int form_unit(Form f) { return f == kRuns16 ? 16 : 64; }
 
 template <class F, int... I>
 __device__ __forceinline__ void for_each(std::integer_sequence<int, I...>, F f) {
@@ -73,10 +75,12 @@ constexpr Rings rings(int rows, int tok, int pieces) {
 
 // A workgroup's tokens in NS pieces of up to TOK, walked side by side: at every k-step one piece after another.  Eight wavefronts, WM x 8 / WM,
 // each 16 NR rows x 16 NT tokens of a piece.
-template <int WM, int NR, int TOK, int NS, Form F, bool STREAM_W>
-__global__ __launch_bounds__(kThreads) void head_runs_kernel(HeadArgs a, int m_tiles) {
+// PIECES: the run is cut into `pieces` parts, a workgroup each, and partials are left to the next kernel (row_sums_draft_kernel).
+template <int WM, int NR, int TOK, int NS, Form F, bool PIECES, bool STREAM_W>
+__global__ __launch_bounds__(kThreads) void head_runs_kernel(HeadArgs a, int m_tiles, int pieces) {
+  static_assert(PIECES ? NS == 1 : F != kTiles, "");
   constexpr int WN = 8 / WM, NT = TOK / (16 * WN), BM = 16 * NR * WM, WROWS = 16 * NR;
-  static_assert(NT >= 2 && (F != kRuns64 || NT == 4), "a partial in one wavefront");
+  static_assert(NT >= 2 && (PIECES || F != kRuns64 || NT == 4), "a partial in one wavefront");
   constexpr int LW = TOK / 64, LH = (2 * NR * WM + 7) / 8;  // loads per wavefront and stage, of eight rows each
   constexpr Rings R = rings(BM, TOK, NS);
   constexpr int RW = R.rw, RH = R.rh;
@@ -93,16 +97,24 @@ __global__ __launch_bounds__(kThreads) void head_runs_kernel(HeadArgs a, int m_t
 
   // row tiles of one run follow one another on one XCD, which shares W through its L2
   const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
-  const int nt = xcd + 8 * (seq / m_tiles), m0 = seq % m_tiles * BM;
+  const int per_run = PIECES ? m_tiles * pieces : m_tiles;
+  const int nt = xcd + 8 * (seq / per_run), m0 = seq % m_tiles * BM;
   if (nt >= a.nT) return;
   constexpr int UNIT = form_unit(F);
   const int n_units = (a.V + UNIT - 1) / UNIT;
-  const int unit0 = (int)((long)nt * n_units / a.nT), units = (int)((long)(nt + 1) * n_units / a.nT) - unit0;
+  int unit0 = F == kTiles ? 4 * nt : (int)((long)nt * n_units / a.nT);
+  int units = F == kTiles ? min(4, n_units - unit0) : (int)((long)(nt + 1) * n_units / a.nT) - unit0;
+  if constexpr (PIECES) {
+    const int p = seq % per_run / m_tiles, begin = units * p / pieces;
+    units = units * (p + 1) / pieces - begin;
+    unit0 += begin;
+    if (units == 0) return;
+  }
   const int run0 = unit0 * UNIT, run1 = min(a.V, (unit0 + units) * UNIT);
   auto piece_at = [&](int s) { return min(run1, run0 + (int)(units * s / NS) * UNIT); };
 
   // every run starts its walk over k elsewhere; of a start in the middle of a k-step, the step's first half comes last of all
-  constexpr int kStart = F == kRuns64 ? 32 : 128;
+  constexpr int kStart = F == kRuns64 ? 32 : F == kRuns16 ? 128 : BK;
   const int start = (int)((unsigned)(nt * 37) % (unsigned)(a.d / kStart)) * kStart;
   const bool half = F == kRuns64 && start % BK != 0;
   const int k0 = start / BK, nsteps = nk + (half ? 1 : 0), total = nsteps * NS;
@@ -276,6 +288,7 @@ __global__ __launch_bounds__(kThreads) void head_runs_kernel(HeadArgs a, int m_t
               }
             }
           }
+          if constexpr (PIECES) continue;
           if constexpr (EDGE)
 #pragma unroll
             for (int t = 0; t < NT; ++t)
@@ -307,7 +320,7 @@ __global__ __launch_bounds__(kThreads) void head_runs_kernel(HeadArgs a, int m_t
               swap_halves(e, o);
               if (g == 0) part[(slot + t) * BM + rl] = make_float2(m, e + o);
             }
-          } else {
+          } else if constexpr (F == kRuns64) {
             float mx = kLowest;
 #pragma unroll
             for (int t = 0; t < 4; ++t) mx = max_of(mx, t);
@@ -331,6 +344,7 @@ __global__ __launch_bounds__(kThreads) void head_runs_kernel(HeadArgs a, int m_t
       else rows(std::true_type{});
     }
   });
+  if constexpr (PIECES) return;
   lds_barrier();
   // One (max, sum exp) partial per (row, run), merged in a fixed order by the thread that owns the row.
   if (tid < BM && m0 + tid < M) {
@@ -379,13 +393,13 @@ __global__ __launch_bounds__(kThreads) void head_runs_kernel(HeadArgs a, int m_t
   }
 }
 
-template <int WM, int NR, int TOK, int NS, Form F>
-hipError_t launch_form(const HeadArgs& a, int m_tiles) {
-  const dim3 grid((unsigned)(8L * ((a.nT + 7) / 8) * m_tiles)), block(kThreads);
-  if (streams_w(a.V, a.d, 2, m_tiles, false)) {
-    FEF_LAUNCH_HEAD((head_runs_kernel<WM, NR, TOK, NS, F, true>), grid, block, a, a, m_tiles);
+template <int WM, int NR, int TOK, int NS, Form F, bool PIECES = false>
+hipError_t launch_form(const HeadArgs& a, int m_tiles, int pieces = 1) {
+  const dim3 grid((unsigned)(8L * ((a.nT + 7) / 8) * m_tiles * pieces)), block(kThreads);
+  if (!PIECES && streams_w(a.V, a.d, 2, m_tiles, false)) {
+    FEF_LAUNCH_HEAD((head_runs_kernel<WM, NR, TOK, NS, F, PIECES, !PIECES>), grid, block, a, a, m_tiles, pieces);
   } else {
-    FEF_LAUNCH_HEAD((head_runs_kernel<WM, NR, TOK, NS, F, false>), grid, block, a, a, m_tiles);
+    FEF_LAUNCH_HEAD((head_runs_kernel<WM, NR, TOK, NS, F, PIECES, false>), grid, block, a, a, m_tiles, pieces);
   }
   return hipGetLastError();
 }
@@ -403,12 +417,22 @@ hipError_t launch_double(const HeadArgs& a, int m) {
   return nr == 1 ? launch_form<2, 1, 256, 2, F>(a, m) : nr == 2 ? launch_form<2, 2, 256, 2, F>(a, m)
        : nr == 3 ? launch_form<2, 3, 256, 2, F>(a, m) : launch_form<2, 4, 256, 2, F>(a, m);
 }
+// Pieces of up to 64 or 128 tokens, row tiles of 64 or 128 rows.
+template <Form F>
+hipError_t launch_pieces(const HeadArgs& a, const PieceShape& p) {
+  if (p.tokens == 64)
+    return p.rows == 64 ? launch_form<4, 1, 64, 1, F, true>(a, p.row_tiles, p.pieces) : launch_form<4, 2, 64, 1, F, true>(a, p.row_tiles, p.pieces);
+  return p.rows == 64 ? launch_form<4, 1, 128, 1, F, true>(a, p.row_tiles, p.pieces) : launch_form<4, 2, 128, 1, F, true>(a, p.row_tiles, p.pieces);
+}
 
 }  // namespace
 
 hipError_t launch_head_short_runs(const HeadArgs& a, int row_tiles) { return launch_short<kRuns16>(a, row_tiles); }
 hipError_t launch_head_double_runs(const HeadArgs& a, int unit, int row_tiles) {
   return unit == 64 ? launch_double<kRuns64>(a, row_tiles) : launch_double<kRuns16>(a, row_tiles);
+}
+hipError_t launch_head_pieces(const HeadArgs& a, int unit, const PieceShape& p) {
+  return unit == 64 ? launch_pieces<kRuns64>(a, p) : unit == 16 ? launch_pieces<kRuns16>(a, p) : launch_pieces<kTiles>(a, p);
 }
 
 }  // namespace fef

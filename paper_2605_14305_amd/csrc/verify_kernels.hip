@@ -271,15 +271,14 @@ constexpr int kTilePer = 10;  // tokens per lane inside one partial tile: up to 
 // ---------------------------------------------------------------------------------------------
 constexpr int exchange_floats(int per) { return per > 10 ? kWave * (per + 1) : 0; }
 
-// One row by one wavefront; ex: its slice of LDS for the tokens of a tile, exchange: for the partials (PER > 10).
+// One row by one wavefront from its partials P; ex: its slice of LDS for the tokens of a tile, exchange: for the partials (PER > 10).
 template <int PER>
-__device__ __forceinline__ void row_lse_draft(const VerifyArgs& a, int r, float* ex, float* exchange) {
+__device__ __forceinline__ void row_lse_draft(const VerifyArgs& a, int r, const float2* P, float* ex, float* exchange) {
   const int lane = threadIdx.x & 63;
   const int BK = a.B * a.K;
   const bool is_draft = r < BK;
   const int s = is_draft ? r : r - BK;
   const int b = s / a.K, m = s % a.K;
-  const float2* P = a.partials + (size_t)r * a.nT;
 
   // log-sum-exp of the row from the head kernel's per-tile partials; the window slot and a given draft token are asked
   // for in the same breath (each trip to memory that waits for another costs about 1 us)
@@ -438,7 +437,91 @@ __global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
   __shared__ float exchange[NW][exchange_floats(PER) + 1];
   const int wave = threadIdx.x >> 6;
   const int r = a.row0 + blockIdx.x * NW + wave;
-  if (r < a.row0 + a.nrows) row_lse_draft<PER>(a, r, tile_mass[wave], exchange[wave]);
+  if (r < a.row0 + a.nrows) row_lse_draft<PER>(a, r, a.partials + (size_t)r * a.nT, tile_mass[wave], exchange[wave]);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Kernel 1 of a call whose head left no partials (pieces of runs, head_rules.hpp: piece_shape): one workgroup per row makes them from the
+// logits, with the sums of the head kernels to the bit (head_gemm_tiled256.hip, "The order of the sums"), and one of its wavefronts goes on
+// as above.  BLOCK = 64: (max, sum exp) of 64 tokens, merged per run of up to four; 16: of 16 tokens, up to eight.
+// ---------------------------------------------------------------------------------------------
+constexpr int kSumThreads = 1024, kSumTokens = 32768;
+
+// (max, sum exp) of BLOCK tokens that this thread holds.
+template <int BLOCK>
+__device__ __forceinline__ float2 block_partial(float (&l)[BLOCK]) {
+  constexpr float kLog2e = 1.4426950408889634f;
+  float mx = kLowest;
+#pragma unroll
+  for (int j = 0; j < BLOCK; j += 2) mx = vmax3(mx, l[j], l[j + 1]);
+  const float mb = mx * -kLog2e;
+#pragma unroll
+  for (int j = 0; j < BLOCK; ++j) l[j] = __builtin_amdgcn_exp2f(fmaf(l[j], kLog2e, mb));
+  if constexpr (BLOCK == 64) {
+    // tokens j and j + 32, then bits 3, 2, 1, 0 of j, then bit 4
+#pragma unroll
+    for (int j = 0; j < 32; ++j) l[j] += l[j + 32];
+#pragma unroll
+    for (int bit = 8; bit >= 1; bit /= 2)
+#pragma unroll
+      for (int j = 0; j < bit; ++j) {
+        l[j] += l[j + bit];
+        l[j + 16] += l[j + 16 + bit];
+      }
+    return make_float2(mx, l[0] + l[16]);
+  } else {
+    // four neighbours in order, then the groups of four pairwise
+#pragma unroll
+    for (int j = 0; j < 16; j += 4) l[j] = ((l[j] + l[j + 1]) + l[j + 2]) + l[j + 3];
+    return make_float2(mx, (l[0] + l[4]) + (l[8] + l[12]));
+  }
+}
+
+template <int BLOCK>
+__global__ __launch_bounds__(kSumThreads) void row_sums_draft_kernel(VerifyArgs a) {
+  constexpr float kLog2e = 1.4426950408889634f;
+  constexpr int kStride = BLOCK + 1;  // odd: a block per thread, all banks
+  __shared__ float row[kSumTokens / BLOCK * kStride];
+  __shared__ float2 blocks[kSumTokens / BLOCK];
+  __shared__ float2 runs[256];
+  __shared__ __attribute__((aligned(16))) float tile_mass[4 * kWave];
+  const int tid = threadIdx.x;
+  const int r = a.row0 + blockIdx.x;
+  const float* L = a.logits + (size_t)r * a.ldl;  // rows are padded to 64 tokens
+  const int n_blocks = (a.V + BLOCK - 1) / BLOCK;
+  for (int v0 = 4 * tid; v0 < a.V; v0 += 4 * 4 * kSumThreads) {  // four loads on their way
+    floatx4 x[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int v = v0 + 4 * j * kSumThreads;
+      if (v < a.V) x[j] = *reinterpret_cast<const floatx4*>(L + v);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int v = v0 + 4 * j * kSumThreads;
+      if (v < a.V)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) row[v / BLOCK * kStride + v % BLOCK + c] = v + c < a.V ? x[j][c] : -INFINITY;
+    }
+  }
+  __syncthreads();
+  for (int b = tid; b < n_blocks; b += kSumThreads) {
+    float l[BLOCK];
+    const int n = a.V - b * BLOCK;
+#pragma unroll
+    for (int j = 0; j < BLOCK; ++j) l[j] = j < n ? row[b * kStride + j] : -INFINITY;
+    blocks[b] = block_partial<BLOCK>(l);
+  }
+  __syncthreads();
+  if (tid < a.nT) {
+    const int b0 = tile_start(a, tid) / BLOCK, b1 = (min(tile_start(a, tid + 1), a.V) + BLOCK - 1) / BLOCK;
+    float mx = kLowest, sum = 0.f;
+    for (int b = b0; b < b1; ++b) mx = fmaxf(mx, blocks[b].x);
+    for (int b = b0; b < b1; ++b) sum += blocks[b].y * exp2f((blocks[b].x - mx) * kLog2e);
+    runs[tid] = make_float2(mx, sum);
+  }
+  __syncthreads();
+  if (tid < kWave) row_lse_draft<4>(a, r, runs, tile_mass, nullptr);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -999,7 +1082,7 @@ __global__ __launch_bounds__(kToyWaves * kWave) void toy_round_kernel(HeadArgs h
   move(a.seq_pass, b);
   move(a.seq_rounds, b);
   if (wave < 2 * K) {
-    row_lse_draft<4>(a, wave, ring + wave * (4 * kWave), nullptr);
+    row_lse_draft<4>(a, wave, partials + wave * a.nT, ring + wave * (4 * kWave), nullptr);
     if (diag_lse && (threadIdx.x & 63) == 0) diag_lse[wave < K ? slot + wave : BK + slot + wave - K] = lse[wave];
   }
   __syncthreads();
@@ -1093,7 +1176,9 @@ hipError_t launch_toy_round(const HeadArgs& h, const VerifyArgs& a) {
 
 hipError_t launch_verify(const VerifyArgs& a) {
   const dim3 g1((a.nrows + NW - 1) / NW);
-  if (a.nT <= 64 * 4) hipLaunchKernelGGL(row_lse_draft_kernel<4>, g1, dim3(NT), 0, a.stream, a);
+  if (a.row_sums == 64) hipLaunchKernelGGL(row_sums_draft_kernel<64>, dim3(a.nrows), dim3(kSumThreads), 0, a.stream, a);
+  else if (a.row_sums) hipLaunchKernelGGL(row_sums_draft_kernel<16>, dim3(a.nrows), dim3(kSumThreads), 0, a.stream, a);
+  else if (a.nT <= 64 * 4) hipLaunchKernelGGL(row_lse_draft_kernel<4>, g1, dim3(NT), 0, a.stream, a);
   else if (a.nT <= 64 * 8) hipLaunchKernelGGL(row_lse_draft_kernel<8>, g1, dim3(NT), 0, a.stream, a);
   else if (a.nT <= 64 * 10) hipLaunchKernelGGL(row_lse_draft_kernel<10>, g1, dim3(NT), 0, a.stream, a);  // V = 151936: 594 tiles
   else if (a.nT <= 64 * 40) hipLaunchKernelGGL(row_lse_draft_kernel<40>, g1, dim3(NT), 0, a.stream, a);

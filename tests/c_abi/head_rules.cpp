@@ -42,6 +42,11 @@ int main() {
       long longest;
       in >> rows >> longest >> d;
       std::cout << fef::double_runs_serve(rows, longest, d) << "\n";
+    } else if (rule == "piece_shape") {
+      int M, V, d, n_runs, unit;
+      in >> M >> V >> d >> n_runs >> unit;
+      const fef::PieceShape s = fef::piece_shape(M, V, d, n_runs, unit);
+      std::cout << s.pieces << " " << s.tokens << " " << s.rows << " " << s.row_tiles << "\n";
     } else {
       return 1;
     }
