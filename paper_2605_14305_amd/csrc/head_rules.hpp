@@ -106,27 +106,30 @@ inline bool double_runs_serve(int rows, long longest, int d) {
 
 // Verify steps of a short vocabulary: the runs (or tiles) that carry a partial each are too few for 256 CUs, and a CU takes in no more than some
 // 48 KB per us of W and H however many stages it asks for.  So a run is cut into pieces, a workgroup each (head_runs.hip), and the partials are
-// made from the logits by the kernel that merges them (row_sums_draft_kernel), which costs 1 to 4 us more than reading them.
+// made from the logits by the kernel that merges them (row_sums_draft_kernel), which costs 1 to 2 us more than reading them.
 struct PieceShape {
   int pieces, tokens, rows, row_tiles;  // per run, of up to `tokens` tokens (64 or 128), in row tiles of `rows` rows (64 or 128); pieces 0: none
 };
-// Where that pays.  Per call in us, three Ws in turn: 64 rows of d = 4096, V = 8000 63.9 -> 44.8, V = 32000 82.5 -> 72.5; 256 rows of d = 4096, V = 8000
-// 73.4 -> 50.0, V = 16384 77.3 -> 66.3; 128 rows of d = 2048, V = 12000 41.8 -> 36.1; 16 rows of d = 3200, V = 12000 52.4 -> 37.0; 96 rows of d = 1280,
-// V = 3000 28.9 -> 25.8.  360 calls of 4 to 256 rows, d = 512 to 4096, V = 2000 to 32000: where this says yes 0.88 of the time in the mean,
-// 4 % behind at most.  Beyond V = 16384 up to 64 rows of the runs of 256 tokens gain (64 rows of d = 2560, V = 26000 61.3 -> 55.5), more rows
-// fill a second round badly (192 rows of d = 4096, V = 20000 79.6 -> 84.3); below d = 1536 a walk is short and the sums cost more than it gains (256 rows
-// of d = 1024, V = 12000 29.4 -> 32.0).
-inline bool pieces_pay(int M, int V, int d, int unit) {
-  if (M > 256 || V > 32768 || streams_w((size_t)V, (size_t)d, 2, 1, false)) return false;
-  if (V <= 5120) return d >= 512 && M > 8 && (d >= 1024 || M <= 128);
-  if (V <= 16384) return d >= 1792 || (d >= 1536 && (M <= 128 || V <= 8192));
-  return unit != 16 && M <= 64 && d >= 1792;
+// Where that pays, per call in us, three Ws in turn and with W still in the Infinity Cache: 64 rows of d = 4096, V = 8000 64.1 -> 42.3 and 45.5 -> 39.7;
+// 256 rows of d = 4096, V = 8000 74.2 -> 48.1 and 56.8 -> 43.8, V = 16384 78.0 -> 64.5 and 61.0 -> 59.3; 128 rows of d = 2560, V = 12000 52.9 -> 41.4 and
+// 38.1 -> 35.7; 96 rows of d = 1024, V = 3000 25.5 -> 21.8 and 26.1 -> 22.4.  780 calls of 12 to 256 rows, d = 512 to 4096, V = 3000 to 16384, half of them
+// either way: where this says yes 0.87 of the time in the mean, none more than 5 % behind both ways.  Where it says no: a walk is short and the sums
+// cost what it gains (256 rows of d = 512, V = 13000 1.22 and 1.25 of the time), a second row tile is half empty (192 rows of d = 4096, V = 16384
+// 0.80 and 1.13), and beyond V = 16384 up to 64 rows gain 9 to 19 % one way and lose 8 to 15 the other.
+constexpr int kPieceTokens = 16384;  // the longest vocabulary: a thread of that kernel takes 16 tokens
+inline bool pieces_pay(int M, int V, int d) {
+  if (M > 256 || d < 512 || V > kPieceTokens || streams_w((size_t)V, (size_t)d, 2, 1, false)) return false;
+  if (V <= 5120) return M > 8;
+  if (M <= 16 && d < 1280) return false;
+  if (M <= 128) return V <= (d >= 1280 ? kPieceTokens : M <= 64 ? 12288 : 8192);
+  if (V <= 8192) return d >= 1280;
+  return d >= 1792 && V <= (d >= 2560 ? M > 192 ? kPieceTokens : 12288 : M > 192 ? 12288 : 10240);
 }
 // Equal pieces of 64 or 128 tokens and row tiles of 64 or 128 rows: the shape that makes (rounds of the busiest XCD) x (rows + tokens + 64)
 // smallest, for the bytes of a k-step are those of its rows and its tokens.
 inline PieceShape piece_shape(int M, int V, int d, int n_runs, int unit) {
   PieceShape best{0, 0, 0, 0};
-  if (!pieces_pay(M, V, d, unit)) return best;
+  if (!pieces_pay(M, V, d)) return best;
   const int run = unit == 16 ? 128 : 256;
   long least = 0;
   for (int tokens = 64; tokens <= 128; tokens *= 2)

@@ -22,6 +22,8 @@
 #include <limits.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include "fef_device.hpp"
 #include "head_f32.hpp"
 #include "wave_ops.hpp"
@@ -441,76 +443,74 @@ __global__ __launch_bounds__(NT) void row_lse_draft_kernel(VerifyArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Kernel 1 of a call whose head left no partials (pieces of runs, head_rules.hpp: piece_shape): one workgroup per row makes them from the
-// logits, with the sums of the head kernels to the bit (head_gemm_tiled256.hip, "The order of the sums"), and one of its wavefronts goes on
-// as above.  BLOCK = 64: (max, sum exp) of 64 tokens, merged per run of up to four; 16: of 16 tokens, up to eight.
+// Kernel 1 of a call whose head left no partials (head_rules.hpp: pieces_pay): one workgroup per row makes them from the logits, with the
+// sums of the head kernels to the bit (head_gemm_tiled256.hip, "The order of the sums"), and one of its wavefronts goes on as above.
+// BLOCK = 64: (max, sum exp) of 64 tokens, merged per run of up to four; 16: of 16 tokens, up to eight.
+// Four threads per 64 tokens, 16 tokens each straight from memory: bound by the chain load, exponentials, two hand-overs through LDS (1 to
+// 2 us on top of kernel 1).  A token per lane and reductions over the wavefront instead: +12 us at V = 32000; a block of 64 per thread
+// through LDS: +4, with 20 KB of code that arrive from a cold instruction cache.
 // ---------------------------------------------------------------------------------------------
-constexpr int kSumThreads = 1024, kSumTokens = 32768;
-
-// (max, sum exp) of BLOCK tokens that this thread holds.
-template <int BLOCK>
-__device__ __forceinline__ float2 block_partial(float (&l)[BLOCK]) {
-  constexpr float kLog2e = 1.4426950408889634f;
-  float mx = kLowest;
-#pragma unroll
-  for (int j = 0; j < BLOCK; j += 2) mx = vmax3(mx, l[j], l[j + 1]);
-  const float mb = mx * -kLog2e;
-#pragma unroll
-  for (int j = 0; j < BLOCK; ++j) l[j] = __builtin_amdgcn_exp2f(fmaf(l[j], kLog2e, mb));
-  if constexpr (BLOCK == 64) {
-    // tokens j and j + 32, then bits 3, 2, 1, 0 of j, then bit 4
-#pragma unroll
-    for (int j = 0; j < 32; ++j) l[j] += l[j + 32];
-#pragma unroll
-    for (int bit = 8; bit >= 1; bit /= 2)
-#pragma unroll
-      for (int j = 0; j < bit; ++j) {
-        l[j] += l[j + bit];
-        l[j + 16] += l[j + 16 + bit];
-      }
-    return make_float2(mx, l[0] + l[16]);
-  } else {
-    // four neighbours in order, then the groups of four pairwise
-#pragma unroll
-    for (int j = 0; j < 16; j += 4) l[j] = ((l[j] + l[j + 1]) + l[j + 2]) + l[j + 3];
-    return make_float2(mx, (l[0] + l[4]) + (l[8] + l[12]));
-  }
-}
+constexpr int kSumThreads = kPieceTokens / 16;
 
 template <int BLOCK>
 __global__ __launch_bounds__(kSumThreads) void row_sums_draft_kernel(VerifyArgs a) {
   constexpr float kLog2e = 1.4426950408889634f;
-  constexpr int kStride = BLOCK + 1;  // odd: a block per thread, all banks
-  __shared__ float row[kSumTokens / BLOCK * kStride];
-  __shared__ float2 blocks[kSumTokens / BLOCK];
+  __shared__ float2 blocks[kPieceTokens / BLOCK];
   __shared__ float2 runs[256];
   __shared__ __attribute__((aligned(16))) float tile_mass[4 * kWave];
   const int tid = threadIdx.x;
   const int r = a.row0 + blockIdx.x;
-  const float* L = a.logits + (size_t)r * a.ldl;  // rows are padded to 64 tokens
-  const int n_blocks = (a.V + BLOCK - 1) / BLOCK;
-  for (int v0 = 4 * tid; v0 < a.V; v0 += 4 * 4 * kSumThreads) {  // four loads on their way
-    floatx4 x[4];
+  // This thread's tokens.  BLOCK = 64: v .. v + 7 and v + 32 .. v + 39, v's bits 4 and 3 from the thread; 16: v .. v + 15.
+  const int v = BLOCK == 64 ? tid / 4 * 64 + tid % 4 * 8 : tid * 16;
+  constexpr int kFar = BLOCK == 64 ? 32 : 8;
+  auto token = [&](int j) { return v + (j < 8 ? j : j - 8 + kFar); };
+  if (tid / 4 * 64 < a.V) {  // (the four threads of 64 tokens together: they trade)
+    const float* L = a.logits + (size_t)r * a.ldl + v;  // rows are padded to 64 tokens
+    float l[16];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int v = v0 + 4 * j * kSumThreads;
-      if (v < a.V) x[j] = *reinterpret_cast<const floatx4*>(L + v);
+    for (int j = 0; j < 16; j += 4) {
+      const floatx4 x = *reinterpret_cast<const floatx4*>(L + (j < 8 ? j : j - 8 + kFar));
+#pragma unroll
+      for (int c = 0; c < 4; ++c) l[j + c] = x[c];
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int v = v0 + 4 * j * kSumThreads;
-      if (v < a.V)
+    for (int j = 0; j < 16; ++j)
+      if (token(j) >= a.V) l[j] = -INFINITY;
+    auto other = [](float x, auto ctrl) {  // the value of another thread of the four
+      return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true));
+    };
+    using Bit0 = std::integral_constant<int, 0xB1>;  // quad_perm [1, 0, 3, 2]
+    using Bit1 = std::integral_constant<int, 0x4E>;  // quad_perm [2, 3, 0, 1]
+    float mx = kLowest;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) row[v / BLOCK * kStride + v % BLOCK + c] = v + c < a.V ? x[j][c] : -INFINITY;
+    for (int j = 0; j < 16; j += 2) mx = vmax3(mx, l[j], l[j + 1]);
+    if constexpr (BLOCK == 64) {
+      mx = vmax(mx, other(mx, Bit0{}));
+      mx = vmax(mx, other(mx, Bit1{}));
     }
-  }
-  __syncthreads();
-  for (int b = tid; b < n_blocks; b += kSumThreads) {
-    float l[BLOCK];
-    const int n = a.V - b * BLOCK;
+    const float mb = mx * -kLog2e;
 #pragma unroll
-    for (int j = 0; j < BLOCK; ++j) l[j] = j < n ? row[b * kStride + j] : -INFINITY;
-    blocks[b] = block_partial<BLOCK>(l);
+    for (int j = 0; j < 16; ++j) l[j] = __builtin_amdgcn_exp2f(fmaf(l[j], kLog2e, mb));
+    float e;
+    if constexpr (BLOCK == 64) {
+      // tokens j and j + 32, then bits 3 (the neighbouring thread), 2, 1, 0 of j, then bit 4
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        l[j] += l[j + 8];
+        l[j] += other(l[j], Bit0{});
+      }
+#pragma unroll
+      for (int bit = 4; bit >= 1; bit /= 2)
+#pragma unroll
+        for (int j = 0; j < bit; ++j) l[j] += l[j + bit];
+      e = l[0] + other(l[0], Bit1{});
+    } else {
+      // four neighbours in order, then the groups of four pairwise
+#pragma unroll
+      for (int j = 0; j < 16; j += 4) l[j] = ((l[j] + l[j + 1]) + l[j + 2]) + l[j + 3];
+      e = (l[0] + l[4]) + (l[8] + l[12]);
+    }
+    if (BLOCK == 16 || tid % 4 == 0) blocks[v / BLOCK] = make_float2(mx, e);
   }
   __syncthreads();
   if (tid < a.nT) {

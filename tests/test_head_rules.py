@@ -152,13 +152,15 @@ def test_pieces_of_short_vocabularies(ask):
     def shape(M, V, d, unit):
         runs = -(-V // 256) if unit == 256 else min(256, -(-(-(-V // unit)) // (4 if unit == 64 else 8)))
         return ask([("piece_shape", M, V, d, runs, unit)])
-    for M, V, d, unit in [(64, 32769, 4096, 64), (257, 8000, 4096, 256), (96, 16385, 4096, 16), (65, 20000, 4096, 64), (256, 12000, 1536, 256),
-                          (128, 12000, 1024, 64), (8, 4000, 2112, 64), (256, 4000, 512, 256), (64, 16384, 1 << 14, 64)]:
+    for M, V, d, unit in [(64, 16385, 4096, 64), (257, 8000, 4096, 256), (8, 4000, 2112, 64), (16, 6000, 1024, 64), (65, 8193, 1024, 64), (64, 12289, 1024, 64),
+                          (129, 6000, 1216, 256), (192, 12289, 4096, 256), (193, 12289, 2048, 256), (192, 10241, 2048, 256), (256, 9000, 1536, 256), (64, 4000, 448, 64)]:
         assert shape(M, V, d, unit) == [0, 0, 0, 0], (M, V, d)
     for unit in (16, 64, 256):
         for M in (9, 33, 64, 65, 128, 129, 256) if unit == 256 else (9, 33, 64, 65, 128):
-            for V in (1, 15, 64, 65, 777, 5000, 8437, 16384):
+            for V in (1, 15, 64, 65, 777, 5000, 8437, 12288) + ((16384,) if M != 129 else ()):
                 pieces, tokens, rows, tiles = shape(M, V, 4096, unit)
                 assert tokens in (64, 128) and rows in (64, 128) and tiles == -(-M // rows)      # the instantiations
                 assert pieces * tokens == (128 if unit == 16 else 256)                           # longest run: no token is left out
-    assert shape(64, 32768, 1792, 64)[0] and shape(256, 8192, 1536, 256)[0] and shape(128, 5120, 512, 64)[0]
+    for call in [(128, 16384, 1280, 64), (64, 12288, 512, 64), (128, 8192, 512, 64), (256, 8192, 1280, 256), (256, 16384, 2560, 256), (192, 12288, 2560, 256),
+                 (9, 5120, 512, 64)]:
+        assert shape(*call)[0], call
