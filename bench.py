@@ -57,6 +57,8 @@ def ce_tiles(V, R):
     shares over full rounds of the 256 CUs in units of 32 tokens."""
     whole = -(-V // 256)
     rounds = -(-whole // 256)
+    if 256 < R <= 320 and 256 * 176 < V <= 256 * (224 if R <= 304 else 192):
+        return 256  # all rows in one row tile
     return whole if R > 256 or whole - 256 * (rounds - 1) > 200 else min(256 * rounds, -(-V // 32))
 
 

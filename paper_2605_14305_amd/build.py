@@ -12,7 +12,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfef.so")
-SOURCES = ["fef_api.hip", "head_gemm.hip", "head_gemm_tiled256.hip", "head_slices.hip", "head_runs.hip", "verify_kernels.hip", "ce_kernels.hip"]
+SOURCES = ["fef_api.hip", "head_gemm.hip", "head_gemm_tiled256.hip", "head_slices.hip", "head_runs.hip", "head_loss.hip", "verify_kernels.hip", "ce_kernels.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function"]

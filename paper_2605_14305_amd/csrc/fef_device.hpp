@@ -78,6 +78,7 @@ hipError_t launch_head_slices(const HeadArgs& a);  // the same order of sums, fo
 hipError_t launch_head_tiled(const HeadArgs& a);
 int tiled256_tiles(int V, int M);  // cross-entropy: token tiles = partial slots per row of a call over M rows
 hipError_t launch_head_tiled256(const HeadArgs& a);
+hipError_t launch_head_loss_wide(const HeadArgs& a);  // a cross-entropy call that loss_wide_serves
 int runs_grid(int V, int unit);    // STREAM (unit 64), ROWSTREAM (16): workgroups = partial slots per row
 hipError_t launch_head_runs(const HeadArgs& a, int unit);
 hipError_t launch_head_short_runs(const HeadArgs& a, int row_tiles);

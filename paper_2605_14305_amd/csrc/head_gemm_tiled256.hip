@@ -770,9 +770,11 @@ hipError_t launch_rows(const HeadArgs& a, int m_tiles) {
 // out evenly over full rounds instead, in units of 32: per call 121 -> 109 us at 110 rows (d = 2560, V = 100003), 233 -> 205
 // at 128 rows (d = 3584, V = 151936), 50.5 -> 46.3 at 64 rows (d = 4096, V = 32000), level at 256 rows.  Where the last round
 // is nearly full (V = 126464: 494 tiles, 238 in the last round) whole tiles are 2 % ahead; hence the line at 200 of 256.
+// (Some more than 256 rows: loss_wide_serves.)
 // With several row tiles the multiplies are what it costs, and those of a partly filled tile are not saved.  (A verify
 // step's tiles and runs are fixed by the order of its sums.)
 int tiled256_tiles(int V, int M) {
+  if (loss_wide_serves(M, V)) return 256;
   const int whole = (V + BN - 1) / BN;
   const int rounds = (whole + 255) / 256, last = whole - 256 * (rounds - 1);
   if (M > BN || last > 200) return whole;
@@ -784,6 +786,7 @@ int tiled256_tiles(int V, int M) {
 // eight in a cross-entropy call where they are ahead (loss_takes_eight_wavefronts).  In a verify step a partial there spans 128
 // tokens, which only four wavefronts hold in one: eight would save 7 % at 512 rows of d = 512.
 hipError_t launch_head_tiled256(const HeadArgs& a) {
+  if (a.labels && loss_wide_serves(a.nrows, a.V)) return launch_head_loss_wide(a);
   const int m_tiles = (a.nrows + 255) / 256;
   // A launch of 2^32 threads or more runs only in part, without an error.  A cross-entropy call, whose logits need no
   // memory, gets there within its documented rows (2^22 rows of V = 131072): several launches then.

@@ -144,6 +144,13 @@ inline PieceShape piece_shape(int M, int V, int d, int n_runs, int unit) {
   return best;
 }
 
+// Cross-entropy of a little more than 256 rows whose vocabulary is one round of shares of 177 to 224 tokens (320 rows: 192): all rows in one row tile
+// (head_loss.hip).  Two row tiles of whole token tiles are one round and a half there, and read W twice.  Head alone in us, 300 rows, three Ws in turn
+// and one W: d = 512, V = 50257 28.8 -> 25.6 and 26.4 -> 23.3, d = 2048 77.8 -> 68.4 and 67.4 -> 59.8, d = 4096 137.5 -> 123.6 and 137.1 -> 126.7;
+// d = 3072, V = 47000 111.7 -> 90.7 and 103.5 -> 78.4.  Narrower shares gain 8 to 17 % one way (d = 2048, V = 40000 68.8 -> 58.4) and lose up to 10 the
+// other (260 rows of d = 3072, V = 40000 67.7 -> 74.5): the second round of the two tiles is short then.
+inline bool loss_wide_serves(int M, int V) { return M > 256 && M <= 320 && V > 256 * 176 && V <= 256 * (M <= 304 ? 224 : 192); }
+
 // Token tiles of an fp32 launch below which they are dealt out one by one instead of by XCD: 2048 sequences x 16 rows of V = 256 80 -> 53 us
 // per call.
 constexpr int kF32FewTiles = 64;

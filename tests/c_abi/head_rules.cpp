@@ -47,6 +47,10 @@ int main() {
       in >> M >> V >> d >> n_runs >> unit;
       const fef::PieceShape s = fef::piece_shape(M, V, d, n_runs, unit);
       std::cout << s.pieces << " " << s.tokens << " " << s.rows << " " << s.row_tiles << "\n";
+    } else if (rule == "loss_wide_serves") {
+      int M, V;
+      in >> M >> V;
+      std::cout << fef::loss_wide_serves(M, V) << "\n";
     } else {
       return 1;
     }

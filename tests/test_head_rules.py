@@ -164,3 +164,8 @@ def test_pieces_of_short_vocabularies(ask):
     for call in [(128, 16384, 1280, 64), (64, 12288, 512, 64), (128, 8192, 512, 64), (256, 8192, 1280, 256), (256, 16384, 2560, 256), (192, 12288, 2560, 256),
                  (9, 5120, 512, 64)]:
         assert shape(*call)[0], call
+
+
+def test_losses_with_all_rows_in_one_row_tile(ask):
+    calls = {(256, 50257): 0, (257, 50257): 1, (304, 57344): 1, (304, 57345): 0, (305, 49152): 1, (305, 49153): 0, (320, 45057): 1, (320, 45056): 0, (321, 46000): 0}
+    assert ask([("loss_wide_serves", *c) for c in calls]) == list(calls.values())
