@@ -418,6 +418,11 @@ fef_status run_step(const fef_params* prm, int phase, int n_transfer, const void
 }  // namespace
 
 namespace {
+// workspace of a cross-entropy call: partials, label logits
+size_t ce_bytes(int32_t R, int nT) {
+  return align_up((size_t)R * (size_t)nT * sizeof(float2), 256) + align_up((size_t)R * sizeof(float), 256);
+}
+
 // sizes and kernel choice of a cross-entropy call; *variant receives the head kernel
 fef_status ce_check(const fef_params* p, int32_t R, int* variant, int* nT, size_t* total) {
   if (!p) return fail(FEF_ERR_INVALID_ARG, "params is NULL");
@@ -451,7 +456,7 @@ fef_status ce_check(const fef_params* p, int32_t R, int* variant, int* nT, size_
   }
   *variant = v;
   *nT = v == FEF_GEMM_F32 ? (p->V + fef::kTiledTn - 1) / fef::kTiledTn : fef::tiled256_tiles(p->V, R);
-  *total = align_up((size_t)R * (size_t)*nT * sizeof(float2), 256) + align_up((size_t)R * sizeof(float), 256);
+  *total = ce_bytes(R, *nT);
   return FEF_OK;
 }
 }  // namespace
@@ -468,6 +473,11 @@ fef_status fef_head_cross_entropy(const fef_params* prm, const void* h, const vo
   size_t total;
   fef_status s = ce_check(prm, R, &variant, &nT, &total);
   if (s != FEF_OK) return s;
+  if (variant == FEF_GEMM_TILED256 && prm->workspace_bytes < total && fef::loss_wide_serves(R, prm->V)) {
+    // a workspace that was sized for another call: two row tiles leave fewer partials
+    nT = (prm->V + fef::kTiled256Tn - 1) / fef::kTiled256Tn;
+    total = ce_bytes(R, nT);
+  }
   if (!h || !W_vocab || !labels || !out_ce)
     return fail(FEF_ERR_INVALID_ARG, "h, W_vocab, labels and out_ce must not be NULL");
   if (((uintptr_t)h | (uintptr_t)W_vocab) & 15)

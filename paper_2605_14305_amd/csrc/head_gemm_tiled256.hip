@@ -786,7 +786,7 @@ int tiled256_tiles(int V, int M) {
 // eight in a cross-entropy call where they are ahead (loss_takes_eight_wavefronts).  In a verify step a partial there spans 128
 // tokens, which only four wavefronts hold in one: eight would save 7 % at 512 rows of d = 512.
 hipError_t launch_head_tiled256(const HeadArgs& a) {
-  if (a.labels && loss_wide_serves(a.nrows, a.V)) return launch_head_loss_wide(a);
+  if (a.labels && a.nT == 256 && loss_wide_serves(a.nrows, a.V)) return launch_head_loss_wide(a);
   const int m_tiles = (a.nrows + 255) / 256;
   // A launch of 2^32 threads or more runs only in part, without an error.  A cross-entropy call, whose logits need no
   // memory, gets there within its documented rows (2^22 rows of V = 131072): several launches then.
