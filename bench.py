@@ -62,6 +62,11 @@ def ce_tiles(V, R):
     return whole if R > 256 or whole - 256 * (rounds - 1) > 200 else min(256 * rounds, -(-V // 32))
 
 
+def slices_serve(V, d):
+    """Which of the two kernels of the SKINNY variant a call takes (slices_serve in the library)."""
+    return V > 256 * 128 and (d != 1024 or V <= 65536 or V * d * 2 > 288 << 20)
+
+
 def head_partials(V, variant):
     """Partials per row that a head kernel leaves: one per workgroup for the kernels whose workgroups take a run of tokens."""
     return {"skinny": min(-(-V // 16), 256), "rowstream": min(-(-V // 128), 256), "stream": min(-(-V // 256), 256),
@@ -404,7 +409,8 @@ def time_verify(args, wl, Wd, dev, steps, warmup):
         ach = flops / head_avg_s / 1e12
         roof = {"bound": "mfma", "achieved": ach, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": ach / MFMA_BF16_PEAK_TFLOPS, "traffic": None}
-    roof.update({"kernel": {fb.FEF_GEMM_SKINNY: "head_skinny_kernel" if M <= 16 else "head_skinny32_kernel",
+    roof.update({"kernel": {fb.FEF_GEMM_SKINNY: "head_slices_kernel" if slices_serve(wl.V, wl.d) else
+                            "head_skinny_kernel" if M <= 16 else "head_skinny32_kernel",
                             fb.FEF_GEMM_TILED: "head_tiled_kernel",
                             fb.FEF_GEMM_TILED256: "head_tiled256_kernel", fb.FEF_GEMM_STREAM: "head_tiled256_kernel",
                             fb.FEF_GEMM_ROWSTREAM: "head_tiled256_kernel",
