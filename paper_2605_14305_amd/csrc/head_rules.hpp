@@ -89,8 +89,8 @@ inline bool slices_serve(int V, int d) {
 
 // Runs (STREAM, ROWSTREAM: units of 64 and 16 tokens) whose longest has that many tokens: by head_runs_kernel, which walks k once over all of
 // them, or by head_tiled256_kernel, one tile of up to 256 tokens after another.  Head alone in us, three Ws in turn.
-// Runs of up to 128 tokens (V <= 32768) fill half a tile of 256, and half its stages: 48 rows of d = 4096, V = 8000 38.9 -> 33.5, V = 24000
-// 49.0 -> 42.8, 96 rows of d = 2560, V = 32000 46.6 -> 43.9, 80 calls 0.94 of the time in the mean.  At d = 512 eight steps are too few
+// Runs of up to 128 tokens (V <= 32768; up to 16384 mostly in pieces, see pieces_pay) fill half a tile of 256, and half its stages: 48 rows of
+// d = 4096, V = 24000 49.0 -> 42.8, 96 rows of d = 2560, V = 32000 46.6 -> 43.9, 80 calls 0.94 of the time in the mean.  At d = 512 eight steps are too few
 // for it to matter and longer runs fall 3 % behind.
 inline bool short_runs_serve(int unit, long longest, int d) { return unit == 16 && longest <= 128 && (d > 512 || longest <= 96); }
 // Runs of 257 to 512 tokens are a tile of 256 and a narrow one, whose k-steps cost the load latency however few tokens it has: 110 rows of
