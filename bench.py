@@ -63,8 +63,10 @@ def ce_tiles(V, R):
 
 
 def slices_serve(V, d):
-    """Which of the two kernels of the SKINNY variant a call takes (slices_serve in the library)."""
-    return V > 256 * 128 and (d != 1024 or V <= 65536 or V * d * 2 > 288 << 20)
+    """Which of the two kernels of the SKINNY variant a call takes (slices_serve and not slices_lag in the library)."""
+    streams = V * d * 2 > 288 << 20
+    lag = d == 512 and 65536 < V <= 81920 or d == 1024 and V > 65152 and not streams or d == 2048 and V > 65536 and not streams
+    return V > 256 * 128 and not lag
 
 
 def head_partials(V, variant):

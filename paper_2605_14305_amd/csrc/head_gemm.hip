@@ -540,7 +540,7 @@ hipError_t launch_head_skinny_nb(const HeadArgs& a) {
 }
 
 hipError_t launch_head_skinny(const HeadArgs& a) {
-  return slices_serve(a.V, a.d) ? launch_head_slices(a) : launch_head_skinny_nb<4>(a);
+  return slices_serve(a.V, a.d) && !slices_lag(a.V, a.d) ? launch_head_slices(a) : launch_head_skinny_nb<4>(a);
 }
 
 hipError_t launch_head_tiled(const HeadArgs& a) {

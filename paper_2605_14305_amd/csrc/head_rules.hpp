@@ -86,6 +86,17 @@ inline bool loss_takes_eight_wavefronts(int M, int row_tiles, int d) {
 inline bool slices_serve(int V, int d) {
   return V > 256 * 128 && (d != 1024 || V <= 65536 || streams_w((size_t)V, (size_t)d, 2, 1, false));
 }
+// ... but for calls of short rows where the kernel with H in LDS falls behind nevertheless: its runs have just become two tiles of half the
+// length (V > 65536), which leaves the CUs less W on its way, and non-temporal loads do not make up for it yet.  Per call, with H in registers ->
+// in LDS, three Ws in turn and one W: 2, 16 and 32 rows of d = 512, V = 65600 1.05, 1.03 and 1.04 times either way, from V = 82000 on level or ahead;
+// of d = 2048, V = 67000 1.05, 1.04 and 1.09 and 1.08, 1.04 and 1.10, V = 72000 1.02, 1.00 and 1.05 and 1.06, 1.00 and 1.06, V = 73000 1.00, 1.01 and
+// 1.04 and 1.04, 1.03 and 1.07, from the line of streams_w on 0.91 to 0.99 with three Ws.  d = 1024, V = 65300 to 65536: (almost) all runs start a multiple of
+// 512 KB apart, 16 rows 39.7 -> 44 us with three Ws (V = 65100, where H in registers meets the same: 45 -> 41) and level with one.
+inline bool slices_lag(int V, int d) {
+  if (d == 512) return V > 256 * 256 && V <= 256 * 320;
+  if (d == 1024) return V > 16 * 4072 && V <= 256 * 256;
+  return d == 2048 && V > 256 * 256 && !streams_w((size_t)V, (size_t)d, 2, 1, false);
+}
 
 // Runs (STREAM, ROWSTREAM: units of 64 and 16 tokens) whose longest has that many tokens: by head_runs_kernel, which walks k once over all of
 // them, or by head_tiled256_kernel, one tile of up to 256 tokens after another.  Head alone in us, three Ws in turn.

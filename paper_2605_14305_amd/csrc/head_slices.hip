@@ -1,5 +1,5 @@
 // Vocabulary-head kernel for up to 32 rows and a long vocabulary.  It gives bit for bit what head_skinny_kernel gives (the SKINNY
-// variant's order of sums) and takes its place where a workgroup's run of tokens is longer than 128 (slices_serve).
+// variant's order of sums) and takes its place where a workgroup's run of tokens is longer than 128 (slices_serve; slices_lag: exceptions).
 //
 // The order of the sums.  A logit is eight sums over d / 8 columns each (the slices), each ascending from zero, added in the
 // order of the slices; a workgroup's tokens are a contiguous run of 16-token tiles; a tile's (max, sum exp) adds four

@@ -32,6 +32,10 @@ int main() {
       int V, d;
       in >> V >> d;
       std::cout << fef::slices_serve(V, d) << "\n";
+    } else if (rule == "slices_lag") {
+      int V, d;
+      in >> V >> d;
+      std::cout << fef::slices_lag(V, d) << "\n";
     } else if (rule == "short_runs_serve") {
       int unit, d;
       long longest;

@@ -21,6 +21,9 @@ CASES = [
     ("topn", AUTO, 1, 32, 1024, 65536), ("fused", SKINNY, 1, 16, 1024, 150001), ("fused", SKINNY, 1, 8, 2048, 100003), ("fused", SKINNY, 1, 13, 2048, 33000),
     ("split", AUTO, 1, 20, 2560, 50257), ("fused", SKINNY, 1, 7, 2560, 131073), ("fused", SKINNY, 1, 9, 3072, 48001), ("fused", SKINNY, 1, 8, 3584, 151936),
     ("topn", AUTO, 1, 17, 3584, 36007), ("fused", SKINNY, 2, 8, 4096, 32784), ("fused", SKINNY, 1, 8, 4096, 126464), ("split", AUTO, 2, 8, 4096, 37777),
+    # to either side of the lines of slices_lag
+    ("fused", SKINNY, 1, 16, 512, 81920), ("fused", SKINNY, 1, 7, 512, 81921), ("topn", AUTO, 1, 32, 1024, 65152), ("fused", SKINNY, 1, 16, 2048, 65536),
+    ("fused", SKINNY, 1, 8, 2048, 65537), ("fused", SKINNY, 1, 16, 2048, 73729),
 ]
 
 

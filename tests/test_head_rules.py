@@ -138,6 +138,14 @@ def test_which_of_the_two_kernels_up_to_32_rows(ask):
     assert ask([("slices_serve", *s) for s in sizes]) == list(sizes.values())
 
 
+def test_where_h_in_lds_falls_behind(ask):
+    """Calls that the kernel with H in LDS made slower, and the nearest ones that it does not."""
+    behind = [(65537, 512), (81920, 512), (65153, 1024), (65536, 1024), (65537, 2048), (73728, 2048)]
+    others = [(65536, 512), (81921, 512), (131072, 512), (65152, 1024), (65536, 2048), (73729, 2048), (70000, 2560), (70000, 4096)]
+    assert ask([("slices_lag", *s) for s in behind + others]) == [1] * len(behind) + [0] * len(others)
+    assert ask([("slices_serve", *s) for s in others]) == [1] * len(others)
+
+
 def test_which_runs_are_walked_in_one(ask):
     short = {(16, 128, 1024): 1, (16, 129, 1024): 0, (64, 128, 1024): 0, (16, 96, 512): 1, (16, 112, 512): 0}
     assert ask([("short_runs_serve", *s) for s in short]) == list(short.values())
