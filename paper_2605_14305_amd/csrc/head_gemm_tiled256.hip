@@ -830,7 +830,7 @@ int runs_grid(int V, int unit) {
 hipError_t launch_head_runs(const HeadArgs& a, int unit) {
   const int m = row_tiles(a.nrows, a.nT, a.d, 64, 128);
   const long units = (a.V + unit - 1) / unit, longest = (units + a.nT - 1) / a.nT * unit;
-  if (short_runs_serve(unit, longest, a.d)) return launch_head_short_runs(a, m);
+  if (short_runs_serve(unit, longest, a.d) && !short_runs_lag(a.nrows, a.nT, a.d)) return launch_head_short_runs(a, m);
   if (double_runs_serve((a.nrows + m - 1) / m, longest, a.d)) return launch_head_double_runs(a, unit, m);
   return unit == 64 ? launch_rows<4, kRuns64>(a, m) : launch_rows<4, kRuns16>(a, m);
 }

@@ -104,6 +104,10 @@ inline bool slices_lag(int V, int d) {
 // d = 4096, V = 24000 49.0 -> 42.8, 96 rows of d = 2560, V = 32000 46.6 -> 43.9, 80 calls 0.94 of the time in the mean.  At d = 512 eight steps are too few
 // for it to matter and longer runs fall 3 % behind.
 inline bool short_runs_serve(int unit, long longest, int d) { return unit == 16 && longest <= 128 && (d > 512 || longest <= 96); }
+// ... but sixteen steps are too few up to 64 rows once most CUs have a run: 16 rows of d = 1024, V = 21504 (168 runs) 23.5 -> 24.2 us per call, 32 of
+// V = 27000 26.0 -> 26.9, 64 of V = 24000 and 32768 1.02 times, with three Ws and with one; 2 to 64 rows of V = 18000 0.95 to 1.01, of V = 19000 to 20352 (159
+// runs) 0.95 to 1.04, 66 rows 0.93 to 1.01, 128 0.90 to 0.97.
+inline bool short_runs_lag(int rows, long n_runs, int d) { return d == 1024 && rows <= 64 && n_runs >= 160; }
 // Runs of 257 to 512 tokens are a tile of 256 and a narrow one, whose k-steps cost the load latency however few tokens it has: 110 rows of
 // d = 2560, V = 100003 111.9 -> 101.4, 64 rows of d = 2048, V = 66000 71.7 -> 59.9, 128 rows of d = 512, V = 126464 43.9 -> 38.4.  Two full
 // tiles do better one after the other (40 rows of d = 4096, V = 115000 149 -> 162 on one machine, level on another), and with more than

@@ -41,6 +41,11 @@ int main() {
       long longest;
       in >> unit >> longest >> d;
       std::cout << fef::short_runs_serve(unit, longest, d) << "\n";
+    } else if (rule == "short_runs_lag") {
+      int rows, d;
+      long n_runs;
+      in >> rows >> n_runs >> d;
+      std::cout << fef::short_runs_lag(rows, n_runs, d) << "\n";
     } else if (rule == "double_runs_serve") {
       int rows, d;
       long longest;

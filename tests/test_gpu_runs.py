@@ -19,6 +19,9 @@ CASES = [
     ("fused", AUTO, 3, 8, 2048, 81920), ("fused", AUTO, 5, 8, 1024, 70001), ("fused", AUTO, 6, 8, 512, 126464), ("fused", ROWSTREAM, 1, 16, 1024, 66001),
     ("fused", AUTO, 4, 8, 1024, 65537), ("fused", AUTO, 8, 8, 2560, 106496), ("fused", AUTO, 5, 10, 576, 90001), ("fused", AUTO, 1, 17, 1088, 73000),
     ("split", AUTO, 10, 12, 704, 131072), ("topn", AUTO, 4, 16, 64, 100003), ("greedy", AUTO, 4, 12, 512, 69999), ("fused", STREAM, 1, 7, 128, 67001),
+    # to either side of the line of short_runs_lag
+    ("fused", AUTO, 3, 8, 1024, 20352), ("fused", AUTO, 5, 4, 1024, 20353), ("fused", ROWSTREAM, 1, 8, 1024, 30000), ("fused", ROWSTREAM, 4, 8, 1024, 22000),
+    ("fused", AUTO, 11, 3, 1024, 22000),
     # pieces of runs and tiles, partials from the logits
     ("fused", AUTO, 4, 8, 2048, 16001), ("fused", AUTO, 8, 8, 2560, 12289), ("fused", AUTO, 16, 8, 4096, 8437), ("fused", AUTO, 11, 8, 2048, 16384),
     ("fused", TILED256, 2, 8, 2048, 5003), ("fused", STREAM, 1, 9, 2112, 4001), ("fused", AUTO, 4, 8, 3072, 32700), ("split", AUTO, 12, 8, 2048, 9001),

@@ -149,6 +149,8 @@ def test_where_h_in_lds_falls_behind(ask):
 def test_which_runs_are_walked_in_one(ask):
     short = {(16, 128, 1024): 1, (16, 129, 1024): 0, (64, 128, 1024): 0, (16, 96, 512): 1, (16, 112, 512): 0}
     assert ask([("short_runs_serve", *s) for s in short]) == list(short.values())
+    lag = {(2, 160, 1024): 1, (64, 256, 1024): 1, (64, 159, 1024): 0, (65, 256, 1024): 0, (64, 256, 1536): 0}  # rows, runs, d
+    assert ask([("short_runs_lag", *s) for s in lag]) == list(lag.values())
     # rows of a tile, longest run, d; the last row: calls that were slower in one walk
     double = {(64, 256, 512): 0, (64, 257, 512): 1, (128, 512, 1024): 1, (40, 384, 1024): 1, (40, 448, 1024): 0, (64, 320, 4096): 1, (64, 384, 4096): 0,
               (110, 448, 2560): 1, (110, 449, 2560): 0,
