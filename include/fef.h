@@ -242,7 +242,15 @@ int32_t fef_select_gemm(const fef_params* prm, int32_t K);
  * Fields of prm that are read: struct_size, d, V, dtype, temperature, gemm_variant (AUTO,
  * STREAM for R <= 128, TILED256, or F32 for f32 inputs), workspace, workspace_bytes (at least
  * fef_cross_entropy_workspace_bytes), stream, ev_head_begin / ev_head_end.  Same conventions and
- * error behaviour as fef_verify_step. */
+ * error behaviour as fef_verify_step.
+ * The size is that of one R and may be smaller for a larger one: a workspace for calls of several
+ * sizes is the largest of theirs.  One range of calls also takes less, and says so in its bits:
+ * bf16, 257 <= R <= 304 and 45057 <= V <= 57344, or 305 <= R <= 320 and 45057 <= V <= 49152.  With
+ * fef_cross_entropy_workspace_bytes or more these run all rows in one row tile.  With less, as long as
+ * ceil(V / 256) partials per row fit (R * ceil(V / 256) * 8 bytes rounded up to 256, and R * 4 more),
+ * they run in two row tiles as calls of more rows do, slower and with sums in another order: out_ce
+ * and out_loss then differ from those of the larger workspace by rounding.  Each is the same in every
+ * call; a program that compares losses to the bit gives both calls the size that the function names. */
 size_t fef_cross_entropy_workspace_bytes(const fef_params* prm, int32_t R);
 fef_status fef_head_cross_entropy(const fef_params* prm, const void* h, const void* W_vocab,
                                   const int32_t* labels, int32_t R, float* out_ce, float* out_loss);

@@ -474,7 +474,7 @@ fef_status fef_head_cross_entropy(const fef_params* prm, const void* h, const vo
   fef_status s = ce_check(prm, R, &variant, &nT, &total);
   if (s != FEF_OK) return s;
   if (variant == FEF_GEMM_TILED256 && prm->workspace_bytes < total && fef::loss_wide_serves(R, prm->V)) {
-    // a workspace that was sized for another call: two row tiles leave fewer partials
+    // a workspace of what such a call needs in two row tiles, which leave fewer partials: accepted, with the sums in their order (see fef.h)
     nT = (prm->V + fef::kTiled256Tn - 1) / fef::kTiled256Tn;
     total = ce_bytes(R, nT);
   }

@@ -15,6 +15,33 @@ def test_against_a_float64_product(d, V):
         shares._check_loss(R, d, V)
 
 
+def _inputs(R, d, V, seed=1):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    W = (torch.randn(V, d, generator=g, device="cuda") * 0.1).bfloat16()
+    h = torch.randn(R, d, generator=g, device="cuda").bfloat16()
+    return W, h, torch.randint(0, V, (R,), generator=g, device="cuda", dtype=torch.int32)
+
+
+@pytest.mark.parametrize("d,V", [(64, 45057), (1024, 49152)])
+def test_which_sums_a_workspace_gives(d, V):
+    """With the size that the library names, those of one row tile; with room for whole tiles only, to the bit those of the two row tiles that
+    a call of one more row takes (321: eight wavefronts too), and nothing is written past it."""
+    W, h, labels = _inputs(321, d, V)
+
+    def ce(R, nbytes=None):
+        op = fb.HeadCrossEntropy(R, d, V)
+        named = op.workspace.numel()
+        room = torch.full((named + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        op.workspace = room[:named if nbytes is None else nbytes]
+        out = op(h[:R], W, labels[:R])[0].clone()
+        assert bool((room[op.workspace.numel():] == 0xA5).all())
+        return out
+    whole = -(-(320 * -(-V // 256) * 8) // 256) * 256 + 320 * 4
+    one, two = ce(320), ce(320, whole)
+    assert torch.equal(two, ce(321)[:320]) and torch.equal(ce(320, whole + 256), two)
+    assert torch.equal(one[:257], ce(257)) and not torch.equal(one, two)
+
+
 def test_a_workspace_with_room_for_whole_tiles_only():
     """What two row tiles leave fits: the call takes them, as before there was another way."""
     R, d, V = 300, 128, 50257
