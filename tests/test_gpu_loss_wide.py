@@ -42,6 +42,39 @@ def test_which_sums_a_workspace_gives(d, V):
     assert torch.equal(one[:257], ce(257)) and not torch.equal(one, two)
 
 
+@pytest.mark.parametrize("R,V", [(257, 57344), (300, 50257), (320, 45057)])
+def test_rows_that_do_not_count_labels_past_the_vocabulary_and_a_temperature(R, V):
+    d, tau = 192, 0.7
+    W, h, labels = _inputs(R, d, V, seed=R)
+    labels[::7] = -100
+    labels[3::50] = V - 1
+    labels[5], labels[R - 1], labels[1] = V, 2**31 - 1, -2**31
+    ce, loss = fb.HeadCrossEntropy(R, d, V)(h, W, labels, temperature=tau)
+    scale = float(torch.tensor(1.0) / torch.tensor(tau))
+    L = h.double() @ W.double().t().contiguous() * scale
+    good = (labels >= 0) & (labels < V)
+    want = torch.logsumexp(L, 1) - L.gather(1, labels.long().clamp(0, V - 1)[:, None])[:, 0]
+    bound = 2 * shares._bound(h.double(), W.double(), d, scale).max(1).values + 2e-5
+    assert bool(((ce - want).abs() <= bound)[good].all())
+    assert bool((ce[labels < 0] == 0).all()) and bool(ce[labels >= V].isnan().all()) and bool(loss.isnan().all())
+
+
+@pytest.mark.parametrize("first,last", [(640, 704), (16, 32), (1000, 3000), (50000, 50257)])
+def test_tokens_of_logit_minus_infinity(first, last):
+    """Tokens banned by an overflowing column of W, up to whole shares of them: no mass, no NaN, their neighbours keep theirs."""
+    R, d, V = 300, 128, 50257
+    W, h, labels = _inputs(R, d, V, seed=first)
+    W[first:last, 0], h[:, 0] = -3e38, 8.0
+    keep = torch.ones(V, dtype=torch.bool, device="cuda")
+    keep[first:last] = False
+    labels = torch.where((labels >= first) & (labels < last), torch.full_like(labels, first - 1), labels)
+    ce, _ = fb.HeadCrossEntropy(R, d, V)(h, W, labels)
+    L = h.double() @ W.double().t().contiguous()
+    want = torch.logsumexp(L[:, keep], 1) - L.gather(1, labels.long()[:, None])[:, 0]
+    bound = 2 * shares._bound(h.double(), W.double()[keep], d, 1.0).max(1).values + 2e-5
+    assert bool(((ce - want).abs() <= bound).all())
+
+
 def test_a_workspace_with_room_for_whole_tiles_only():
     """What two row tiles leave fits: the call takes them, as before there was another way."""
     R, d, V = 300, 128, 50257

@@ -43,6 +43,18 @@ def test_against_a_float64_product(variant, d, V):
         shares._check_round(variant, M, d, V)
 
 
+# Every shape of a piece (test_head_rules.py: which): tokens and rows of 64 and 128, both row tiles partly filled.  variant, d, V, rows
+PIECES = [(STREAM, 2112, 12289, (34, 64, 66, 128)), (ROWSTREAM, 2048, 12289, (34, 64, 66, 128)), (STREAM, 2112, 16384, (66, 98, 128)), (ROWSTREAM, 2048, 16383, (66, 98, 128)),
+          (TILED256, 2560, 12288, (130, 192)), (TILED256, 4096, 16384, (194, 256)), (TILED256, 2048, 10240, (130, 192)), (TILED256, 2048, 8437, (66, 128, 130, 256)),
+          (TILED256, 2112, 4001, (130, 192, 256)), (STREAM, 576, 5119, (10, 64)), (ROWSTREAM, 512, 5120, (10, 128))]
+
+
+@pytest.mark.parametrize("variant,d,V,rows", PIECES)
+def test_every_shape_of_a_piece_against_a_float64_product(variant, d, V, rows):
+    for M in rows:
+        shares._check_round(variant, M, d, V)
+
+
 @pytest.mark.parametrize("variant,d,V", [(STREAM, 2112, 16384), (STREAM, 2112, 32768), (STREAM, 2048, 129), (ROWSTREAM, 2048, 16383), (ROWSTREAM, 2048, 31), (TILED256, 2048, 16384),
                                          (TILED256, 2112, 257)])
 def test_pieces_against_a_float64_product(variant, d, V):

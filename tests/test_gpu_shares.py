@@ -112,6 +112,17 @@ def test_w_to_either_side_of_the_line_for_non_temporal_loads(variant, rows, V, d
         _check_round(variant, M, d, V)
 
 
+# (runs of 257 to 320 tokens, as those are, take head_runs_kernel; these stay in the tile kernel)
+TILES_AT_THE_LINE = [(fb.FEF_GEMM_STREAM, (2, 34, 66, 128)), (fb.FEF_GEMM_ROWSTREAM, (2, 34, 66, 128))]
+
+
+@pytest.mark.parametrize("variant,rows", TILES_AT_THE_LINE)
+@pytest.mark.parametrize("V", [36864, 36865])
+def test_runs_of_one_tile_to_either_side_of_that_line(variant, rows, V):
+    for M in rows:
+        _check_round(variant, M, 4096, V)
+
+
 @pytest.mark.parametrize("V,d,rows", [(V, d, rows) for V, ds, rows in LINES_OF_A_LOSS for d in ds])
 def test_cross_entropy_to_either_side_of_that_line(V, d, rows):
     for R in rows:
@@ -124,7 +135,26 @@ def test_cross_entropy_to_either_side_of_that_line(V, d, rows):
 def test_tokens_of_logit_minus_infinity(variant, M, first, last):
     """Tokens banned by an overflowing column of W: a piece of a tile, or all of it, that holds nothing else brings no mass
     and no NaN, and its neighbours keep theirs."""
-    d, V = 512, 9001
+    _check_banned(variant, M, 512, 9001, first, last)
+
+
+# The same where a call takes another kernel or form than those of 9001 tokens do (test_head_rules.py: which): variant, M, d, V
+BANNED = {"tiles, runs of 64": (fb.FEF_GEMM_STREAM, 40, 512, 33001), "tiles, runs of 16": (fb.FEF_GEMM_ROWSTREAM, 40, 512, 33001),
+          "short runs": (fb.FEF_GEMM_ROWSTREAM, 72, 1024, 20011),
+          "double runs of 64": (fb.FEF_GEMM_STREAM, 40, 512, 66000), "double runs of 16": (fb.FEF_GEMM_ROWSTREAM, 40, 512, 70001),
+          "pieces of 128": (fb.FEF_GEMM_TILED256, 256, 4096, 16384),
+          "H in registers": (fb.FEF_GEMM_SKINNY, 16, 512, 9001), "H in registers, 32 rows": (fb.FEF_GEMM_SKINNY, 32, 512, 9001),
+          "H in LDS": (fb.FEF_GEMM_SKINNY, 16, 512, 33001), "H in LDS, 32 rows": (fb.FEF_GEMM_SKINNY, 32, 512, 33001),
+          "H in LDS, from any slice": (fb.FEF_GEMM_SKINNY, 16, 2048, 33001), "H in LDS, two tiles": (fb.FEF_GEMM_SKINNY, 32, 512, 100003)}
+
+
+@pytest.mark.parametrize("first,last", [(640, 704), (512, 768), (16, 32), (1000, 3000)])
+@pytest.mark.parametrize("call", list(BANNED))
+def test_tokens_of_logit_minus_infinity_in_the_other_kernels(call, first, last):
+    _check_banned(*BANNED[call], first, last)
+
+
+def _check_banned(variant, M, d, V, first, last):
     g = torch.Generator(device="cuda").manual_seed(first)
     W = torch.randn(V, d, generator=g, device="cuda") * 0.1
     W[first:last, 0] = -3e38

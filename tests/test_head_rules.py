@@ -6,6 +6,7 @@ import pytest
 
 from paper_2605_14305_amd import binding as fb
 import test_gpu_f32_head as f32_head
+import test_gpu_runs as gpu_runs
 import test_gpu_shares as shares
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -174,6 +175,46 @@ def test_pieces_of_short_vocabularies(ask):
     for call in [(128, 16384, 1280, 64), (64, 12288, 512, 64), (128, 8192, 512, 64), (256, 8192, 1280, 256), (256, 16384, 2560, 256), (192, 12288, 2560, 256),
                  (9, 5120, 512, 64)]:
         assert shape(*call)[0], call
+
+
+UNITS = {fb.FEF_GEMM_STREAM: 64, fb.FEF_GEMM_ROWSTREAM: 16, fb.FEF_GEMM_TILED256: 256}
+
+
+def _runs(V, unit):
+    return -(-V // 256) if unit == 256 else min(256, -(-(-(-V // unit)) // (4 if unit == 64 else 8)))
+
+
+def _kernel(ask, variant, M, d, V):
+    """Which kernel or form of the tile kernel a round over M rows takes."""
+    if variant == fb.FEF_GEMM_SKINNY:
+        return "lds" if ask([("slices_serve", V, d)]) == [1] and ask([("slices_lag", V, d)]) == [0] else "registers"
+    unit = UNITS[variant]
+    n = _runs(V, unit)
+    pieces, tokens, rows, _ = ask([("piece_shape", M, V, d, n, unit)])
+    if pieces:
+        return ("pieces", unit, tokens, rows)
+    if unit == 256:
+        return ("tiles", unit)
+    longest, m = -(-(-(-V // unit)) // n) * unit, ask([("row_tiles", M, n, d, 64, 128)])[0]
+    if ask([("short_runs_serve", unit, longest, d)]) == [1] and ask([("short_runs_lag", M, n, d)]) == [0]:
+        return ("short", unit)
+    return ("double" if ask([("double_runs_serve", -(-M // m), longest, d)]) == [1] else "tiles", unit)
+
+
+def test_what_the_gpu_tests_of_runs_and_pieces_run(ask):
+    shapes = {_kernel(ask, variant, M, d, V) for variant, d, V, rows in gpu_runs.PIECES for M in rows}
+    assert shapes == {("pieces", unit, 64, rows) for unit in (16, 64, 256) for rows in (64, 128)} | {("pieces", 256, 128, 64), ("pieces", 256, 128, 128)}
+    # no other shape exists: that is all that head_runs.hip instantiates
+    grid = [(M, V, d, _runs(V, unit), unit) for unit in (16, 64, 256) for M in range(1, 257 if unit == 256 else 129, 5) for V in range(1, 16385, 241)
+            for d in (512, 1280, 2560, 4096)]
+    answers = ask([("piece_shape", *q) for q in grid])
+    assert {("pieces", q[4], answers[4 * i + 1], answers[4 * i + 2]) for i, q in enumerate(grid) if answers[4 * i]} <= shapes
+    assert {_kernel(ask, v, M, 4096, V) for v, rows in shares.TILES_AT_THE_LINE for M in rows for V in (36864, 36865)} == {("tiles", 64), ("tiles", 16)}
+    forms = {name: _kernel(ask, *call) for name, call in shares.BANNED.items()}
+    assert forms == {"tiles, runs of 64": ("tiles", 64), "tiles, runs of 16": ("tiles", 16), "short runs": ("short", 16),
+                     "double runs of 64": ("double", 64), "double runs of 16": ("double", 16), "pieces of 128": ("pieces", 256, 128, 128),
+                     "H in registers": "registers", "H in registers, 32 rows": "registers", "H in LDS": "lds", "H in LDS, 32 rows": "lds",
+                     "H in LDS, from any slice": "lds", "H in LDS, two tiles": "lds"}
 
 
 def test_losses_with_all_rows_in_one_row_tile(ask):
