@@ -59,6 +59,37 @@ __device__ inline void load_to_lds_16(const void* gptr, uint32_t lds_off) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
                :: "v"(gptr), "s"(lds_off) : "memory");
 }
+// One to four of these behind one write of M0: load q fills the 1024 bytes at lds_off + 1024 q.  (The instruction offset moves the
+// LDS address and the memory address alike, so pointer q is kept q KB low.)  NT: non-temporal.
+template <bool NT, int L>
+__device__ __forceinline__ void load_group_to_lds(const __bf16* const (&p)[L], uint32_t lds_off) {
+  static_assert(L >= 1 && L <= 4 && (!NT || L == 2 || L == 4), "");
+  if constexpr (L == 4 && NT)
+    asm volatile("s_mov_b32 m0, %4\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %0, off nt\n\tglobal_load_lds_dwordx4 %1, off offset:1024 nt\n\t"
+                 "global_load_lds_dwordx4 %2, off offset:2048 nt\n\tglobal_load_lds_dwordx4 %3, off offset:3072 nt"
+                 :: "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "s"(lds_off) : "memory");
+  else if constexpr (L == 4)
+    asm volatile("s_mov_b32 m0, %4\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %0, off\n\tglobal_load_lds_dwordx4 %1, off offset:1024\n\t"
+                 "global_load_lds_dwordx4 %2, off offset:2048\n\tglobal_load_lds_dwordx4 %3, off offset:3072"
+                 :: "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "s"(lds_off) : "memory");
+  else if constexpr (L == 3)
+    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %0, off\n\tglobal_load_lds_dwordx4 %1, off offset:1024\n\t"
+                 "global_load_lds_dwordx4 %2, off offset:2048"
+                 :: "v"(p[0]), "v"(p[1]), "v"(p[2]), "s"(lds_off) : "memory");
+  else if constexpr (L == 2 && NT)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %0, off nt\n\tglobal_load_lds_dwordx4 %1, off offset:1024 nt"
+                 :: "v"(p[0]), "v"(p[1]), "s"(lds_off) : "memory");
+  else if constexpr (L == 2)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %0, off\n\tglobal_load_lds_dwordx4 %1, off offset:1024"
+                 :: "v"(p[0]), "v"(p[1]), "s"(lds_off) : "memory");
+  else
+    load_to_lds_16(p[0], lds_off);
+}
 // Wait until at most N of this wavefront's vector-memory operations are outstanding.
 template <int N>
 __device__ inline void wait_newer() {

@@ -50,7 +50,7 @@ __device__ inline void store_logit(float* p, float v) {
 }
 
 constexpr int kSkinnyWaves = 8;
-constexpr int kSkinnyOutTiles = 40;  // tiles of logits staged in LDS before a flush
+constexpr int kSkinnyOutTiles = 36;  // tiles of a workgroup, at most (d = 1024, V = 147456): their logits wait in LDS
 constexpr int kSkinnyThreads = kSkinnyWaves * kWave;
 
 // NB = tiles accumulated in registers between two cross-wavefront reductions (even).
@@ -82,6 +82,7 @@ __global__ __launch_bounds__(kSkinnyThreads) void head_skinny_kernel(HeadArgs a,
 
   const int t0 = (int)((long)blockIdx.x * tiles_total / gridDim.x);
   const int t1 = (int)((long)(blockIdx.x + 1) * tiles_total / gridDim.x);
+  const int nv = min(16 * t1, a.V) - 16 * t0;  // tokens of this workgroup
   const __bf16* Wl = (const __bf16*)a.W + kofs;
 
   auto load_tile = [&](int t, bf16x8(&buf)[KS]) {
@@ -138,7 +139,6 @@ __global__ __launch_bounds__(kSkinnyThreads) void head_skinny_kernel(HeadArgs a,
   using Half1 = std::integral_constant<int, 1>;
   floatx4 acc[NB];
   int par = 0;
-  int tflush = t0;  // first tile whose logits are still staged in LDS
   if (t0 < t1) {
     if constexpr (kHalves) {
       load_half(t0, Half0{}, buf0);
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(kSkinnyThreads) void head_skinny_kernel(HeadArgs a,
       for (int w = 1; w < kSkinnyWaves; ++w) sum += red[par][jt_o][w][src];
       sum *= a.inv_tau;
       const int v = (t + jt_o) * 16 + 4 * quad;
-      *reinterpret_cast<floatx4*>(&out[m][(t + jt_o - tflush) * 16 + 4 * quad]) = sum;
+      *reinterpret_cast<floatx4*>(&out[m][(t + jt_o - t0) * 16 + 4 * quad]) = sum;
       float mx = -INFINITY;
 #pragma unroll
       for (int c = 0; c < 4; ++c)
@@ -198,21 +198,13 @@ __global__ __launch_bounds__(kSkinnyThreads) void head_skinny_kernel(HeadArgs a,
       else if (mx > -INFINITY) run_s += e * __expf(mx - run_m);
     }
     par ^= 1;
-    if (t + NB - tflush + NB > kSkinnyOutTiles || t + NB >= t1) {
-      // flush rows [tflush*16, min(t+NB, t1)*16) of the staged logits
-      const int tend = min(t + NB, t1);
-      const int v0 = tflush * 16, nv = min(tend * 16, a.V) - v0;
-      __syncthreads();
-      for (int r = wave; r < M; r += kSkinnyWaves)
-        for (int i = lane; i < nv; i += kWave) store_logit(&a.logits[(size_t)r * a.ldl + v0 + i], out[r][i]);
-      __syncthreads();
-      tflush = tend;
-    }
   }
 
   // merge the NB items that share a row and write the workgroup's partial
   if (quad == 0 && jt_o < NB) run_merge[jt_o][m] = make_float2(run_m, run_s);
   __syncthreads();
+  for (int r = wave; r < M; r += kSkinnyWaves)
+    for (int i = lane; i < nv; i += kWave) store_logit(&a.logits[(size_t)r * a.ldl + 16 * t0 + i], out[r][i]);
   if (tid < 16 && tid < M) {
     float mx = -INFINITY;
 #pragma unroll
@@ -263,6 +255,7 @@ __global__ __launch_bounds__(kSkinnyThreads) void head_skinny32_kernel(HeadArgs 
 
   const int t0 = (int)((long)blockIdx.x * tiles_total / gridDim.x);
   const int t1 = (int)((long)(blockIdx.x + 1) * tiles_total / gridDim.x);
+  const int nv = min(16 * t1, a.V) - 16 * t0;  // tokens of this workgroup
   const __bf16* Wl = (const __bf16*)a.W + kofs;
 
   // One W buffer of KS registers, refilled in two halves (tiles of 10 or more k-steps): a half is
@@ -293,7 +286,6 @@ __global__ __launch_bounds__(kSkinnyThreads) void head_skinny32_kernel(HeadArgs 
   float run_m = -INFINITY, run_s = 0.f;
 
   floatx4 acc[NB][2];
-  int tflush = t0;
   if (t0 < t1) load_part(t0, 0, KS);
   for (int t = t0; t < t1; t += NB) {
 #pragma unroll
@@ -333,7 +325,7 @@ __global__ __launch_bounds__(kSkinnyThreads) void head_skinny32_kernel(HeadArgs 
       for (int w = 1; w < kSkinnyWaves; ++w) sum += red[jt_o][mt_o][w][src];
       sum *= a.inv_tau;
       const int v = (t + jt_o) * 16 + 4 * quad;
-      *reinterpret_cast<floatx4*>(&out[row][(t + jt_o - tflush) * 16 + 4 * quad]) = sum;
+      *reinterpret_cast<floatx4*>(&out[row][(t + jt_o - t0) * 16 + 4 * quad]) = sum;
       float mx = -INFINITY;
 #pragma unroll
       for (int c = 0; c < 4; ++c)
@@ -349,19 +341,12 @@ __global__ __launch_bounds__(kSkinnyThreads) void head_skinny32_kernel(HeadArgs 
       if (mx > run_m) { run_s = run_s * __expf(run_m - mx) + e; run_m = mx; }
       else if (mx > -INFINITY) run_s += e * __expf(mx - run_m);
     }
-    if (t + NB - tflush + NB > kSkinnyOutTiles || t + NB >= t1) {
-      const int tend = min(t + NB, t1);
-      const int v0 = tflush * 16, nv = min(tend * 16, a.V) - v0;
-      __syncthreads();
-      for (int r = wave; r < M; r += kSkinnyWaves)
-        for (int i = lane; i < nv; i += kWave) store_logit(&a.logits[(size_t)r * a.ldl + v0 + i], out[r][i]);
-      __syncthreads();
-      tflush = tend;
-    }
   }
   // merge the NB items that share a row and write the workgroup's partial
   if (quad == 0) run_merge[jt_o][row] = make_float2(run_m, run_s);
   __syncthreads();
+  for (int r = wave; r < M; r += kSkinnyWaves)
+    for (int i = lane; i < nv; i += kWave) store_logit(&a.logits[(size_t)r * a.ldl + 16 * t0 + i], out[r][i]);
   if (tid < 32 && tid < M) {
     float mx = -INFINITY;
 #pragma unroll
@@ -540,7 +525,8 @@ hipError_t launch_head_skinny_nb(const HeadArgs& a) {
 }
 
 hipError_t launch_head_skinny(const HeadArgs& a) {
-  return slices_serve(a.V, a.d) && !slices_lag(a.V, a.d) ? launch_head_slices(a) : launch_head_skinny_nb<4>(a);
+  const bool registers = (!slices_serve(a.V, a.d) || slices_lag(a.V, a.d)) && (a.V + kSkinnyUnit - 1L) / kSkinnyUnit <= (long)kSkinnyOutTiles * a.nT;
+  return registers ? launch_head_skinny_nb<4>(a) : launch_head_slices(a);
 }
 
 hipError_t launch_head_tiled(const HeadArgs& a) {

@@ -245,28 +245,7 @@ __global__ __launch_bounds__(128 * WN) void head_tiled256_kernel(HeadArgs a, int
   auto group = [&](auto& p, uint32_t base, int& left, auto stream) __attribute__((always_inline)) {
     constexpr int L = sizeof(p) / sizeof(p[0]);
     static_assert(!decltype(stream)::value || L == 4, "W is streamed in groups of four");
-    base = scalar(base);
-    if constexpr (decltype(stream)::value)
-      asm volatile("s_mov_b32 m0, %4\n\ts_nop 0\n\t"
-                   "global_load_lds_dwordx4 %0, off nt\n\tglobal_load_lds_dwordx4 %1, off offset:1024 nt\n\t"
-                   "global_load_lds_dwordx4 %2, off offset:2048 nt\n\tglobal_load_lds_dwordx4 %3, off offset:3072 nt"
-                   :: "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "s"(base) : "memory");
-    else if constexpr (L == 4)
-      asm volatile("s_mov_b32 m0, %4\n\ts_nop 0\n\t"
-                   "global_load_lds_dwordx4 %0, off\n\tglobal_load_lds_dwordx4 %1, off offset:1024\n\t"
-                   "global_load_lds_dwordx4 %2, off offset:2048\n\tglobal_load_lds_dwordx4 %3, off offset:3072"
-                   :: "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "s"(base) : "memory");
-    else if constexpr (L == 3)
-      asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\t"
-                   "global_load_lds_dwordx4 %0, off\n\tglobal_load_lds_dwordx4 %1, off offset:1024\n\t"
-                   "global_load_lds_dwordx4 %2, off offset:2048"
-                   :: "v"(p[0]), "v"(p[1]), "v"(p[2]), "s"(base) : "memory");
-    else if constexpr (L == 2)
-      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\t"
-                   "global_load_lds_dwordx4 %0, off\n\tglobal_load_lds_dwordx4 %1, off offset:1024"
-                   :: "v"(p[0]), "v"(p[1]), "s"(base) : "memory");
-    else
-      load_to_lds_16(p[0], base);
+    load_group_to_lds<decltype(stream)::value>(p, scalar(base));
     const long move = advance(left);
 #pragma unroll
     for (int q = 0; q < L; ++q) p[q] += move;

@@ -21,16 +21,6 @@ constexpr int BK = 64, kThreads = 512, WM = 4, WN = 2, NR = 5, BM = 16 * NR * WM
 constexpr int kUnit = 16;  // tokens; shares are equal to a unit
 constexpr float kLog2e = 1.4426950408889634f;
 
-// Four direct-to-LDS loads behind one write of M0 (the instruction offset moves the LDS address and the memory address alike, so
-// pointer q is kept q KB low).
-__device__ __forceinline__ void load_four(const __bf16* p0, const __bf16* p1, const __bf16* p2, const __bf16* p3, uint32_t base) {
-  base = __builtin_amdgcn_readfirstlane(base);
-  asm volatile("s_mov_b32 m0, %4\n\ts_nop 0\n\t"
-               "global_load_lds_dwordx4 %0, off\n\tglobal_load_lds_dwordx4 %1, off offset:1024\n\t"
-               "global_load_lds_dwordx4 %2, off offset:2048\n\tglobal_load_lds_dwordx4 %3, off offset:3072"
-               :: "v"(p0), "v"(p1), "v"(p2), "v"(p3), "s"(base) : "memory");
-}
-
 // ROWS: rows of H in LDS.
 template <int NT, int ROWS>
 __global__ __launch_bounds__(kThreads) void head_loss_wide_kernel(HeadArgs a) {
@@ -73,14 +63,15 @@ __global__ __launch_bounds__(kThreads) void head_loss_wide_kernel(HeadArgs a) {
   const uint32_t slotH = lds_offset(ringH + hi0 * 64), slotW = lds_offset(ringW + wi0 * 64);
   auto advance = [&](int& left) __attribute__((always_inline)) -> long { return --left == 0 ? (long)BK - a.d : (long)BK; };
   auto load_h = [&](int stage) __attribute__((always_inline)) {
-    load_four(gh[0], gh[1], gh[2], gh[3], slotH + stage * kStageH * 16);
+    const __bf16* const four[4] = {gh[0], gh[1], gh[2], gh[3]};
+    load_group_to_lds<false>(four, __builtin_amdgcn_readfirstlane(slotH + stage * kStageH * 16));
     load_to_lds_16(gh[4], __builtin_amdgcn_readfirstlane(slotH + stage * kStageH * 16 + 4096));
     const long move = advance(h_left);
 #pragma unroll
     for (int q = 0; q < LH; ++q) gh[q] += move;
   };
   auto load_w = [&](int stage) __attribute__((always_inline)) {
-    load_four(gw[0], gw[1], gw[2], gw[3], slotW + stage * kStageW * 16);
+    load_group_to_lds<false>(gw, __builtin_amdgcn_readfirstlane(slotW + stage * kStageW * 16));
     const long move = advance(w_left);
 #pragma unroll
     for (int q = 0; q < LW; ++q) gw[q] += move;

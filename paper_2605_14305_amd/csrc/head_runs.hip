@@ -30,34 +30,6 @@ __device__ __forceinline__ void for_each(std::integer_sequence<int, I...>, F f) 
   (f(std::integral_constant<int, I>{}), ...);
 }
 
-// L direct-to-LDS loads behind one write of M0 (the instruction offset moves the LDS address and the memory address alike, so
-// pointer q is kept q KB low).
-template <int L, bool STREAM>
-__device__ __forceinline__ void load_group(const __bf16* const (&p)[L], uint32_t base) {
-  static_assert(L == 1 || L == 2 || L == 4, "");
-  base = __builtin_amdgcn_readfirstlane(base);
-  if constexpr (L == 4 && STREAM)
-    asm volatile("s_mov_b32 m0, %4\n\ts_nop 0\n\t"
-                 "global_load_lds_dwordx4 %0, off nt\n\tglobal_load_lds_dwordx4 %1, off offset:1024 nt\n\t"
-                 "global_load_lds_dwordx4 %2, off offset:2048 nt\n\tglobal_load_lds_dwordx4 %3, off offset:3072 nt"
-                 :: "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "s"(base) : "memory");
-  else if constexpr (L == 4)
-    asm volatile("s_mov_b32 m0, %4\n\ts_nop 0\n\t"
-                 "global_load_lds_dwordx4 %0, off\n\tglobal_load_lds_dwordx4 %1, off offset:1024\n\t"
-                 "global_load_lds_dwordx4 %2, off offset:2048\n\tglobal_load_lds_dwordx4 %3, off offset:3072"
-                 :: "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "s"(base) : "memory");
-  else if constexpr (L == 2 && STREAM)
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\t"
-                 "global_load_lds_dwordx4 %0, off nt\n\tglobal_load_lds_dwordx4 %1, off offset:1024 nt"
-                 :: "v"(p[0]), "v"(p[1]), "s"(base) : "memory");
-  else if constexpr (L == 2)
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\t"
-                 "global_load_lds_dwordx4 %0, off\n\tglobal_load_lds_dwordx4 %1, off offset:1024"
-                 :: "v"(p[0]), "v"(p[1]), "s"(base) : "memory");
-  else
-    load_to_lds_16(p[0], base);
-}
-
 // Stages of W (one per k-step and piece of TOK tokens) and of H (one per k-step): W is requested rw - 1 steps ahead, H rh - 1 k-steps,
 // which has to be as early as the W that its step asks for together with it.
 struct Rings {
@@ -144,13 +116,13 @@ __global__ __launch_bounds__(kThreads) void head_runs_kernel(HeadArgs a, int m_t
   constexpr uint32_t kBytesH = kStageH * 16, kBytesW = kStageW * 16;
   auto advance = [&](int& left) __attribute__((always_inline)) -> long { return --left == 0 ? (long)BK - a.d : (long)BK; };
   auto load_h = [&](int stage) __attribute__((always_inline)) {
-    load_group<LH, false>(gh, slotH + stage * kBytesH);
+    load_group_to_lds<false>(gh, __builtin_amdgcn_readfirstlane(slotH + stage * kBytesH));
     const long move = advance(h_left);
 #pragma unroll
     for (int q = 0; q < LH; ++q) gh[q] += move;
   };
   auto load_w = [&](int s, int stage) __attribute__((always_inline)) {
-    load_group<LW, STREAM_W>(gw[s], slotW + stage * kBytesW);
+    load_group_to_lds<STREAM_W>(gw[s], __builtin_amdgcn_readfirstlane(slotW + stage * kBytesW));
     const long move = advance(w_left[s]);
 #pragma unroll
     for (int q = 0; q < LW; ++q) gw[s][q] += move;
@@ -417,12 +389,14 @@ hipError_t launch_double(const HeadArgs& a, int m) {
   return nr == 1 ? launch_form<2, 1, 256, 2, F>(a, m) : nr == 2 ? launch_form<2, 2, 256, 2, F>(a, m)
        : nr == 3 ? launch_form<2, 3, 256, 2, F>(a, m) : launch_form<2, 4, 256, 2, F>(a, m);
 }
-// Pieces of up to 64 or 128 tokens, row tiles of 64 or 128 rows.
+// Pieces of up to 64 tokens, of whole tiles also 128 (up to 128 rows piece_shape gives 64 everywhere), row tiles of 64 or 128 rows.
 template <Form F>
 hipError_t launch_pieces(const HeadArgs& a, const PieceShape& p) {
   if (p.tokens == 64)
     return p.rows == 64 ? launch_form<4, 1, 64, 1, F, true>(a, p.row_tiles, p.pieces) : launch_form<4, 2, 64, 1, F, true>(a, p.row_tiles, p.pieces);
-  return p.rows == 64 ? launch_form<4, 1, 128, 1, F, true>(a, p.row_tiles, p.pieces) : launch_form<4, 2, 128, 1, F, true>(a, p.row_tiles, p.pieces);
+  if constexpr (F == kTiles)
+    return p.rows == 64 ? launch_form<4, 1, 128, 1, F, true>(a, p.row_tiles, p.pieces) : launch_form<4, 2, 128, 1, F, true>(a, p.row_tiles, p.pieces);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace

@@ -35,23 +35,6 @@ namespace {
 constexpr int BK = 64, kTile = 256;  // columns of a k-step: 128 bytes, one line; tokens of a tile, at most
 constexpr int kThreads = 512, kSlices = 8, kChains = 4;
 
-// Four direct-to-LDS loads behind one write of M0 (the instruction offset moves the LDS address and the memory address alike, so
-// pointer q is kept q KB low).
-template <bool STREAM_W>
-__device__ __forceinline__ void load_four(const __bf16* const (&p)[4], uint32_t base) {
-  base = __builtin_amdgcn_readfirstlane(base);
-  if constexpr (STREAM_W)
-    asm volatile("s_mov_b32 m0, %4\n\ts_nop 0\n\t"
-                 "global_load_lds_dwordx4 %0, off nt\n\tglobal_load_lds_dwordx4 %1, off offset:1024 nt\n\t"
-                 "global_load_lds_dwordx4 %2, off offset:2048 nt\n\tglobal_load_lds_dwordx4 %3, off offset:3072 nt"
-                 :: "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "s"(base) : "memory");
-  else
-    asm volatile("s_mov_b32 m0, %4\n\ts_nop 0\n\t"
-                 "global_load_lds_dwordx4 %0, off\n\tglobal_load_lds_dwordx4 %1, off offset:1024\n\t"
-                 "global_load_lds_dwordx4 %2, off offset:2048\n\tglobal_load_lds_dwordx4 %3, off offset:3072"
-                 :: "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "s"(base) : "memory");
-}
-
 // WM: groups of 16 rows.  Eight wavefronts, WM x 8 / WM, each 16 rows x 32 WM tokens.
 template <int WM, bool ROTATE, bool STREAM_W>
 __global__ __launch_bounds__(kThreads) void head_slices_kernel(HeadArgs a, int tiles_total) {
@@ -101,7 +84,7 @@ __global__ __launch_bounds__(kThreads) void head_slices_kernel(HeadArgs a, int t
     gh += advance(h_left);
   };
   auto load_w = [&](int stage) __attribute__((always_inline)) {
-    load_four<STREAM_W>(gw, slotW + stage * kBytesW);
+    load_group_to_lds<STREAM_W>(gw, __builtin_amdgcn_readfirstlane(slotW + stage * kBytesW));
     const long move = advance(w_left);
 #pragma unroll
     for (int q = 0; q < LW; ++q) gw[q] += move;
