@@ -78,13 +78,15 @@ typedef enum {
  * in this call: 2*B*K fused, B*K in a DRAFT or TARGET call. */
 typedef enum {
   FEF_GEMM_AUTO = 0,
+/* A variant of bf16 rounds stands for an order of the sums: it fixes the bits, and which of several kernels
+ * that keep it runs a call follows the sizes. */
   FEF_GEMM_SKINNY = 1, /* bf16, M <= 32, d in {512, 1024, 2048, 2560, 3072, 3584, 4096}: W streamed
-                          once, split-k; other d at M <= 32 go to ROWSTREAM or STREAM
+                          once, k in eight slices; other d at M <= 32 go to ROWSTREAM or STREAM
                           (fef_select_gemm tells)                                             */
   FEF_GEMM_TILED = 2,  /* bf16, any M: plain 128x128 LDS-tiled MFMA GEMM (never picked by AUTO) */
   FEF_GEMM_F32 = 3,    /* f32, any shape: reference-grade kernel, k in ascending order     */
-  FEF_GEMM_TILED256 = 4, /* bf16, any M: LDS-tiled MFMA GEMM, 256 tokens x 32 to 256 rows per workgroup (AUTO: M > 128) */
-  FEF_GEMM_STREAM = 5,   /* bf16, M <= 128: the same tiles, one workgroup per CU over a run of 64-token units (AUTO:
+  FEF_GEMM_TILED256 = 4, /* bf16, any M: LDS-tiled MFMA GEMM, a partial (max, sum exp) per row and 256 tokens (AUTO: M > 128) */
+  FEF_GEMM_STREAM = 5,   /* bf16, M <= 128: a partial per row and run of 64-token units, at most 256 runs (AUTO:
                             48 < M <= 64, 96 < M <= 128, and M <= 128 where neither SKINNY nor ROWSTREAM takes the
                             hidden size)                                                                */
   FEF_GEMM_ROWSTREAM = 6 /* bf16, M <= 128, d a multiple of 512: likewise, runs of 16-token tiles (AUTO: 32 < M <= 48,
@@ -136,7 +138,10 @@ typedef struct {
   size_t workspace_bytes;
   void* stream;                /* hipStream_t; NULL = the null stream                        */
   void* ev_head_begin;         /* optional hipEvent_t pair (both or neither) that receives    */
-  void* ev_head_end;           /* the vocabulary-head kernel's own start / stop timestamps    */
+  void* ev_head_end;           /* the vocabulary-head kernel's own start / stop timestamps.
+                                  In bf16 calls of V <= 16384 that kernel may write logits only:
+                                  the (max, sum exp) partials are then made by the next kernel,
+                                  outside the pair (fef_select_gemm does not tell which)       */
   /* Optional device-side state of Algorithm 2's outer loops, so that a caller can enqueue the
    * rounds of a block back to back without reading anything back (all NULL = not used):       */
   int32_t n_pass;              /* N_step, the number of generation passes; >= 1 with seq_pass */

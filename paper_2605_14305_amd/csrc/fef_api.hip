@@ -83,7 +83,7 @@ fef_status select_variant(const fef_params* p, int32_t K, int* variant) {
     else if (M > 128) v = FEF_GEMM_TILED256;
     else if (!rowstream_supports(M, p->d)) v = FEF_GEMM_STREAM;
     else if (M <= 48 || (M > 64 && M <= 96)) {
-      v = FEF_GEMM_ROWSTREAM;  // the two names run the same kernel (see fef.h); which one AUTO gives is part of the interface
+      v = FEF_GEMM_ROWSTREAM;  // two orders of the sums (see fef.h); which one AUTO gives is part of the interface
     } else {
       v = FEF_GEMM_STREAM;
     }

@@ -1,5 +1,6 @@
-// Vocabulary-head kernel for all row counts and hidden sizes that the kernels with H in registers (head_gemm.hip) do not
-// take, and for the cross-entropy use of the head.
+// Vocabulary-head kernel for all row counts, hidden sizes and vocabularies that the kernels for up to 32 rows (head_gemm.hip,
+// head_slices.hip) and head_runs_kernel (short runs, runs of 257 to 512 tokens, short vocabularies: head_runs.hip) do not take, and for the
+// cross-entropy use of the head but for a few hundred rows in one row tile (head_loss.hip).  Which kernel a call takes: head_rules.hpp.
 //
 // Workgroup tile 32 NR rows of H (NR = 1 to 8) x up to 256 tokens, k-steps of 64, v_mfma_f32_16x16x32_bf16 with the W tile
 // as the A operand and H as the B operand.  Two grids of wavefronts:
@@ -40,7 +41,7 @@
 // Measured (head kernel by HIP events, unless marked t: by trace; before: W in ordinary loads, as few row tiles as the rows take):
 // d = 4096, V = 126464: 48 rows 182 -> 163 us, 64 rows 188 -> 166 (6.4 TB/s), 96 rows 187 -> 168, 128 rows 197 -> 171, 256 rows 240 -> 237
 // to 238 (t, on one other machine: 223 -> 215), 512 rows 426 -> 423 to 432, 2048 rows 1590 -> 1600 to 1620 (other machines); 128 rows of
-// d = 3584, V = 151936 222 -> 203; 110 rows of d = 2560, V = 100003 116 -> 105 t.  Cross-entropy, 2048 rows 1470 to 1517 (1.40 to 1.43
+// d = 3584, V = 151936 222 -> 203.  Cross-entropy, 2048 rows 1470 to 1517 (1.40 to 1.43
 // PFLOP/s, matrix units busy 0.75 of the cycles at 1.77 GHz).
 //
 // Operand slabs go HBM/L2 -> LDS directly (global_load_lds_dwordx4: lane l of a wavefront deposits its 16 bytes at

@@ -7,6 +7,8 @@
 // multiplies.  The fragments of a half step read under the multiplies of the one before: 71 -> 68 us.  Relative error against 64 bits, inputs of the
 // performance cases, twelve seeds each, two row tiles -> one: 300 rows of d = 2048, V = 50257 2.49e-7 -> 2.37e-7, 290 of d = 4096, V = 47000
 // 3.38e-7 -> 3.43e-7, 270 of d = 1024, V = 55000 1.90e-7 -> 1.88e-7; over seven sizes of random labels 5.80e-8 -> 5.80e-8 in the mean.
+// W by ordinary loads at every size: non-temporal ones, which two row tiles want from 288 MiB on, are 1 to 9 % slower here (300 rows of d = 4096,
+// V = 50257 121.7 -> 129.7 us per call, of d = 8192 235.6 -> 254.2, of d = 3072 92.4 -> 96.7; with one W the same).
 //
 // Eight wavefronts, 4 x 2, each 80 rows x 16 NT tokens; k-steps of 64 columns; W is requested two steps ahead, H one (it comes from L2).
 // 304 rows of H and 224 tokens of W fill LDS to the byte; the 16 rows behind them are multiplied as whatever lies there and never used.

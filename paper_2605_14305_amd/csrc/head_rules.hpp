@@ -22,7 +22,7 @@ namespace fef {
 // Two row tiles share W through L2 as far as they keep in step, and non-temporal loads cost a round that (144 rows of d = 7168, V = 22000
 // 124 -> 144 us where nothing runs between the calls and 127 -> 150 where the cache is swept, 160 of d = 4608, V = 30000 95 -> 102
 // and level, 256 of d = 5120 to 8192 level to 4 % ahead); a cross-entropy call, which writes no logits, loses up to 2 % (300 rows of
-// d = 2048, V = 81920) and gains up to 5 (300 rows of d = 4096, V = 126464 315 -> 303 us, of d = 4096, V = 50257 149 -> 142).
+// d = 2048, V = 81920) and gains up to 5 (300 rows of d = 4096, V = 126464 315 -> 303 us).  (Losses that loss_wide_serves: ordinary loads, see head_loss.hip.)
 inline bool streams_w(size_t V, size_t d, size_t element_bytes, int row_tiles, bool loss) {
   return row_tiles <= (loss ? 2 : 1) && d * element_bytes % 128 == 0 && V * d * element_bytes > (size_t)288 << 20;
 }
@@ -69,7 +69,7 @@ inline int row_tiles(int M, int n_tiles, int d, int least, int most) {
 // Cross-entropy of more than 256 rows in row_tiles row tiles: eight wavefronts, or four as a verify step.  Two wavefronts per SIMD overlap
 // prologue and epilogue better, one asks LDS for fewer fragments.  Up to d = 1024 eight are ahead by 3 to 5 % (500 rows of
 // V = 126464 126 -> 121 us), but for 1 us behind in low tiles of a short vocabulary; beyond, in two row tiles, by up to 10 % (300 rows
-// of V = 50257 84 -> 79 at d = 2048, 147 -> 139 at d = 4096) as long as the tile is low or the walk over k short: 512 rows of d = 3072 2
+// of V = 50257, before loss_wide_serves took them, 84 -> 79 at d = 2048, 147 -> 139 at d = 4096) as long as the tile is low or the walk over k short: 512 rows of d = 3072 2
 // to 5 % ahead or level, of d = 3584 up to 3 behind, of d = 4352 10 (V = 151936 522 -> 572); 384 rows of d = 4096 4 % ahead, of
 // d = 5120 level.  In more row tiles 1 to 8 % behind.  Their error against 64 bits is the same (nine sizes of 257 to 1000 rows, six
 // seeds each: 1.8e-7 to 3.7e-7 with four and 1.8e-7 to 3.4e-7 with eight, now one ahead and now the other).
@@ -88,8 +88,8 @@ inline bool slices_serve(int V, int d) {
 }
 // ... but for calls of short rows where the kernel with H in LDS falls behind nevertheless: its runs have just become two tiles of half the
 // length (V > 65536), which leaves the CUs less W on its way, and non-temporal loads do not make up for it yet.  Per call, with H in registers ->
-// in LDS, three Ws in turn and one W: 2, 16 and 32 rows of d = 512, V = 65600 1.05, 1.03 and 1.04 times either way, from V = 82000 on level or ahead;
-// of d = 2048, V = 67000 1.05, 1.04 and 1.09 and 1.08, 1.04 and 1.10, V = 72000 1.02, 1.00 and 1.05 and 1.06, 1.00 and 1.06, V = 73000 1.00, 1.01 and
+// in LDS, three Ws in turn and one W: 8, 16 and 32 rows of d = 512, V = 65600 1.05, 1.03 and 1.04 times either way, from V = 82000 on level or ahead;
+// of d = 2048, V = 67000 1.06, 1.04 and 1.09 and 1.07, 1.04 and 1.10, V = 72000 1.01, 1.00 and 1.05 and 1.01, 1.00 and 1.06, V = 73000 1.02, 1.01 and
 // 1.04 and 1.04, 1.03 and 1.07, from the line of streams_w on 0.91 to 0.99 with three Ws.  d = 1024, V = 65300 to 65536: (almost) all runs start a multiple of
 // 512 KB apart, 16 rows 39.7 -> 44 us with three Ws (V = 65100, where H in registers meets the same: 45 -> 41) and level with one.
 inline bool slices_lag(int V, int d) {
@@ -112,7 +112,9 @@ inline bool short_runs_lag(int rows, long n_runs, int d) { return d == 1024 && r
 // d = 2560, V = 100003 111.9 -> 101.4, 64 rows of d = 2048, V = 66000 71.7 -> 59.9, 128 rows of d = 512, V = 126464 43.9 -> 38.4.  Two full
 // tiles do better one after the other (40 rows of d = 4096, V = 115000 149 -> 162 on one machine, level on another), and with more than
 // 96 rows and long rows so do shorter ones (128 rows of d = 3584, V = 75000 122 -> 134).  240 calls of 40 to 128 rows: where this says
-// yes 0.91 of the time in the mean.
+// yes 0.91 of the time in the mean; 312 of 2 to 32 rows 0.90, and 0.91 with one W, 3 and 5 % behind at most.  Between d = 2560 and 3584 with more than
+// 96 rows the line is drawn on the careful side: 120 calls of 98 to 128 rows of d = 2688 to 3584, V = 66000 to 106496 take 0.90 to 1.02 of the
+// time in one walk, 0.93 to 1.05 with one W.
 inline bool double_runs_serve(int rows, long longest, int d) {
   if (longest <= 256) return false;
   if (d <= 1024) return longest <= (rows <= 48 ? 384 : 512);
@@ -128,7 +130,8 @@ struct PieceShape {
 // Where that pays, per call in us, three Ws in turn and with W still in the Infinity Cache: 64 rows of d = 4096, V = 8000 64.1 -> 42.3 and 45.5 -> 39.7;
 // 256 rows of d = 4096, V = 8000 74.2 -> 48.1 and 56.8 -> 43.8, V = 16384 78.0 -> 64.5 and 61.0 -> 59.3; 128 rows of d = 2560, V = 12000 52.9 -> 41.4 and
 // 38.1 -> 35.7; 96 rows of d = 1024, V = 3000 25.5 -> 21.8 and 26.1 -> 22.4.  780 calls of 12 to 256 rows, d = 512 to 4096, V = 3000 to 16384, half of them
-// either way: where this says yes 0.87 of the time in the mean, none more than 5 % behind both ways.  Where it says no: a walk is short and the sums
+// either way: where this says yes 0.87 of the time in the mean, none more than 5 % behind both ways; 297 of 2 to 10
+// rows 0.82 and 0.89, none behind by more than 2 % either way.  Where it says no: a walk is short and the sums
 // cost what it gains (256 rows of d = 512, V = 13000 1.22 and 1.25 of the time), a second row tile is half empty (192 rows of d = 4096, V = 16384
 // 0.80 and 1.13), and beyond V = 16384 up to 64 rows gain 9 to 19 % one way and lose 8 to 15 the other.
 constexpr int kPieceTokens = 16384;  // the longest vocabulary: a thread of that kernel takes 16 tokens

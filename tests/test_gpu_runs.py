@@ -22,7 +22,7 @@ CASES = [
     # to either side of the line of short_runs_lag
     ("fused", AUTO, 3, 8, 1024, 20352), ("fused", AUTO, 5, 4, 1024, 20353), ("fused", ROWSTREAM, 1, 8, 1024, 30000), ("fused", ROWSTREAM, 4, 8, 1024, 22000),
     ("fused", AUTO, 11, 3, 1024, 22000),
-    # pieces of runs and tiles, partials from the logits
+    # pieces of runs and tiles, partials from the logits (but two calls past the lines of pieces_pay: 176 rows, and V = 32700)
     ("fused", AUTO, 4, 8, 2048, 16001), ("fused", AUTO, 8, 8, 2560, 12289), ("fused", AUTO, 16, 8, 4096, 8437), ("fused", AUTO, 11, 8, 2048, 16384),
     ("fused", TILED256, 2, 8, 2048, 5003), ("fused", STREAM, 1, 9, 2112, 4001), ("fused", AUTO, 4, 8, 3072, 32700), ("split", AUTO, 12, 8, 2048, 9001),
     ("topn", AUTO, 5, 20, 2048, 15001), ("greedy", AUTO, 9, 8, 2048, 777), ("fused", AUTO, 3, 7, 2048, 15), ("fused", AUTO, 6, 8, 3584, 14001),
