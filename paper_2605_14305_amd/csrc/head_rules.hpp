@@ -131,16 +131,20 @@ struct PieceShape {
 // 256 rows of d = 4096, V = 8000 74.2 -> 48.1 and 56.8 -> 43.8, V = 16384 78.0 -> 64.5 and 61.0 -> 59.3; 128 rows of d = 2560, V = 12000 52.9 -> 41.4 and
 // 38.1 -> 35.7; 96 rows of d = 1024, V = 3000 25.5 -> 21.8 and 26.1 -> 22.4.  780 calls of 12 to 256 rows, d = 512 to 4096, V = 3000 to 16384, half of them
 // either way: where this says yes 0.87 of the time in the mean, none more than 5 % behind both ways; 297 of 2 to 10
-// rows 0.82 and 0.89, none behind by more than 2 % either way.  Where it says no: a walk is short and the sums
+// rows 0.82 and 0.89, none behind by more than 2 % either way; 1030 of 34 to 256 rows 0.83 and 0.85, 1 % of them behind by 2 to 4 % (200 to 224 rows of
+// d = 2560, V = 10000 by 3 to 5).  Where it says no: the second row tile of 128 multiplies rows that one of 224 does not have (194 to 224 rows of d = 1792 to 2304,
+// V = 8193 to 12288 1.05 to 1.08 of the time both ways, 226 to 256 0.98 to 1.01), steps are few (256 rows of d = 512, V = 4608 1.03, V = 5120 1.05, but V = 4000
+// 0.96), a walk is short and the sums
 // cost what it gains (256 rows of d = 512, V = 13000 1.22 and 1.25 of the time), a second row tile is half empty (192 rows of d = 4096, V = 16384
 // 0.80 and 1.13), and beyond V = 16384 up to 64 rows gain 9 to 19 % one way and lose 8 to 15 the other.
 constexpr int kPieceTokens = 16384;  // the longest vocabulary: a thread of that kernel takes 16 tokens
 inline bool pieces_pay(int M, int V, int d) {
   if (M > 256 || d < 512 || V > kPieceTokens || streams_w((size_t)V, (size_t)d, 2, 1, false)) return false;
-  if (V <= 5120) return M > 8;
+  if (V <= 5120) return M > 8 && (M <= 192 || d >= 1024 || V <= 4096);
   if (M <= 16 && d < 1280) return false;
   if (M <= 128) return V <= (d >= 1280 ? kPieceTokens : M <= 64 ? 12288 : 8192);
   if (V <= 8192) return d >= 1280;
+  if (M > 192 && M <= 224 && d < 2560) return false;
   return d >= 1792 && V <= (d >= 2560 ? M > 192 ? kPieceTokens : 12288 : M > 192 ? 12288 : 10240);
 }
 // Equal pieces of 64 or 128 tokens and row tiles of 64 or 128 rows: the shape that makes (rounds of the busiest XCD) x (rows + tokens + 64)

@@ -26,6 +26,8 @@ CASES = [
     ("fused", AUTO, 4, 8, 2048, 16001), ("fused", AUTO, 8, 8, 2560, 12289), ("fused", AUTO, 16, 8, 4096, 8437), ("fused", AUTO, 11, 8, 2048, 16384),
     ("fused", TILED256, 2, 8, 2048, 5003), ("fused", STREAM, 1, 9, 2112, 4001), ("fused", AUTO, 4, 8, 3072, 32700), ("split", AUTO, 12, 8, 2048, 9001),
     ("topn", AUTO, 5, 20, 2048, 15001), ("greedy", AUTO, 9, 8, 2048, 777), ("fused", AUTO, 3, 7, 2048, 15), ("fused", AUTO, 6, 8, 3584, 14001),
+    # to either side of the lines of whole tiles in pieces
+    ("fused", AUTO, 14, 8, 2048, 9000), ("fused", AUTO, 15, 8, 2048, 9000), ("fused", AUTO, 16, 8, 512, 4097), ("fused", AUTO, 16, 8, 512, 4096),
 ]
 
 

@@ -175,6 +175,10 @@ def test_pieces_of_short_vocabularies(ask):
     for call in [(128, 16384, 1280, 64), (64, 12288, 512, 64), (128, 8192, 512, 64), (256, 8192, 1280, 256), (256, 16384, 2560, 256), (192, 12288, 2560, 256),
                  (9, 5120, 512, 64)]:
         assert shape(*call)[0], call
+    # calls that pieces made slower, and their nearest neighbours that they do not
+    for M, V, d, pays in [(193, 8193, 1792, 0), (224, 12288, 2496, 0), (192, 8193, 1792, 1), (225, 12288, 2496, 1), (224, 8192, 1792, 1), (224, 8193, 2560, 1),
+                          (193, 4097, 960, 0), (256, 5120, 512, 0), (256, 4096, 512, 1), (192, 5120, 512, 1), (256, 5120, 1024, 1)]:
+        assert bool(shape(M, V, d, 256)[0]) == bool(pays), (M, V, d)
 
 
 UNITS = {fb.FEF_GEMM_STREAM: 64, fb.FEF_GEMM_ROWSTREAM: 16, fb.FEF_GEMM_TILED256: 256}
